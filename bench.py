@@ -47,11 +47,11 @@ def lu_traffic_valid():
 
 
 def blu_step_flops(N: int, b: int = 64) -> float:
-    """Algorithmic LU flops of the k_blu_step launches of one factorisation: step k
+    """Algorithmic LU flops of the k_gj_step launches of one factorisation: step k
     forms the m = nb - k - 1 left factors L_ik = A_ik D_k (2 b^3 each) and updates the
     m^2 trailing tiles (2 b^3 each), i.e. 2 b^3 (m^2 + m); summed over the steps this is
-    2/3 N^3 up to the diagonal-block inversions.  The accumulation of the block-triangular
-    inverses that the same launches carry is not counted."""
+    2/3 N^3 up to the diagonal-block inversions.  The elimination of the blocks above and left of the pivot, by which the
+    same launches leave the explicit inverse, is not counted."""
     nb = N // b
     return sum(2.0 * b ** 3 * (m * m + m) for m in range(1, nb))
 
@@ -121,7 +121,7 @@ def run(w, nsteps, T, mixed, steps, warmup, profile, tuned=True):
         ctx.shoot_eval(params, T, nsteps)
         prof_ms = 1e3 * (time.perf_counter() - ta)
         lu_ms, lu_n = ctx.profile_stats(0)
-        try:   # HIP events around every k_blu_step launched outside a graph
+        try:   # HIP events around every k_gj_step launched outside a graph
             step_ms, step_n = ctx.profile_stats(4)
         except ww.WWError:
             step_ms, step_n = None, 0
@@ -599,15 +599,16 @@ def main():
     n3 = float(w.N) ** 3
     roofline = None
     if phases:
-        # dominant kernel: k_blu_step (15 launches per LU sequence; each launch carries
-        # the tasks of the G stages of a group).  Achieved = algorithmic LU flops per
-        # launch (the sequence's step flops / launches) over the mean launch duration
-        # from HIP events on the launching stream.
+        # dominant kernel: k_gj_step (16 launches per sequence, 15 of them with a diagonal
+        # inverse; each launch carries the tasks of the G stages of a group).  Achieved =
+        # algorithmic LU flops per timed launch (the sequence's step flops / 15) over the
+        # mean duration of the launches with a diagonal inverse, from HIP events on the
+        # launching stream.
         G = phases["lu_stages_per_sequence"]
         nb = w.N // 64
         seq_flops = G * blu_step_flops(w.N)
         valid = lu_traffic_valid() and w.N == 1024 and timing["tuning"]["lu_group"] == LU_TRAFFIC_GROUP
-        seq = {"kernels": "k_blu_init, 15 x k_blu_step, k_blu_final, k_minv",
+        seq = {"kernels": "k_gj_init, 16 x k_gj_step",
                "stages": G, "ms": phases["block_lu_ms"],
                "achieved": G * (2.0 / 3.0) * n3 / (phases["block_lu_ms"] * 1e-3) / 1e12,
                "traffic": LU_SEQ_TRAFFIC_BYTES if valid else None}
@@ -616,7 +617,7 @@ def main():
             ach = seq_flops / (nb - 1) / step_s / 1e12
             roofline = {"bound": "mfma", "achieved": ach, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                         "frac": ach / FP64_PEAK_TFLOPS, "traffic": BLU_STEP_TRAFFIC_BYTES if valid else None,
-                        "kernel": f"k_blu_step<double>, one launch per block step of a group of {G:g} stages",
+                        "kernel": f"k_gj_step<double>, one launch per block step of a group of {G:g} stages",
                         "flops_per_launch": seq_flops / (nb - 1),
                         "launch_us": phases["blu_step_ms"] * 1e3,
                         "launches_timed": phases["blu_step_launches"],

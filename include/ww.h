@@ -70,13 +70,14 @@ typedef struct ww_ctx ww_ctx;
                               with LU factors (WW_FB_DIRECT) */
 
 /*
- * Fallbacks.  The block LU of A runs without row interchanges (A = I/2 + K/N is
- * diagonally dominant for graph surfaces; Sec. 3.3 does not discuss pivoting) behind a
- * guard on its pivots: every pivot must be at least 1e-8 in magnitude (environment
+ * Fallbacks.  The factorisation of A is a block Gauss-Jordan elimination that leaves the
+ * explicit inverse (called LU below, after the method's one factorisation per stage).  It
+ * runs without row interchanges (A = I/2 + K/N is diagonally dominant for graph surfaces;
+ * Sec. 3.3 does not discuss pivoting) behind a guard on its pivots: every pivot must be at least 1e-8 in magnitude (environment
  * WW_PIVOT_GUARD, read by ww_create, replaces that bound for the unpivoted LU only; a
  * test hook for the fallback path).  When a pivot falls below the guard, the call is
  * redone with partial pivoting: Gaussian elimination with row interchanges (largest
- * magnitude in the column) fixes a row order P on the GPU, the block LU factors P A in
+ * magnitude in the column) fixes a row order P on the GPU, the elimination inverts P A in
  * FP64, and every solve gathers its right-hand side by P (the adjoint scatters its
  * transposed solve by P^T).  A march is redone whole, without a step graph, on one
  * stream.  If a pivot of the pivoted factorisation is also below 1e-8 the call fails
@@ -361,7 +362,7 @@ int shoot_eval_batch(int n_inst, ww_ctx *const *ctx, const double *const *params
  * Gm, -d/dx, -H), with the base state recomputed from checkpoints taken every
  * `ckpt_every` steps.  The factors are FP64 also in a WW_MIXED context.  Device
  * workspace for the checkpoints and for the factors of one segment (ckpt_every x stages
- * x 3 Np^2 doubles) is allocated on the first call and kept until ww_destroy.
+ * x 2 Np^2 doubles) is allocated on the first call and kept until ww_destroy.
  * grad: device M.  dfdT (host or NULL): df/dT = r . drdT.  f (host or NULL).
  * Synchronises.  A pivot below the guard redoes the call with partial pivoting.
  * Errors: WW_ENOSETUP, WW_EINVAL, WW_EPIVOT, WW_ENONFINITE, WW_EHIP.
@@ -373,13 +374,12 @@ int shoot_adjoint(ww_ctx *ctx, const double *params, double T, int nsteps, int c
  * Measurement hooks (not part of the method): ww_profile(ctx, 1) adds timestamp nodes
  * (a one-thread kernel reading the GPU's constant-rate wall clock) around three phases
  * of every stage of the step graph -- 0: the block LU of A (a launch sequence, which in
- * a lagged-factor march factors a group of stages, with the block-triangular inverses
- * and the explicit inverse), 1: the whole base chain (spectral prep, assembly, base
+ * a lagged-factor march inverts the matrices of a group of stages), 1: the whole base chain (spectral prep, assembly, base
  * solve, base DtN, base right-hand side), 2: the column chain (the M variational
  * columns) -- and clears the accumulated sums (stream-ordered); phase 3 is the host
  * time spent enqueueing one step (graph launches and event operations).  With 2 added
- * to `enable` (enable = 3), every block-LU step kernel (k_blu_step) that a march step
- * launches directly (not from a graph) also carries a pair of HIP events attached to its
+ * to `enable` (enable = 3), every elimination step kernel (k_gj_step) that carries a
+ * diagonal inverse and that a march step launches directly (not from a graph) also carries a pair of HIP events attached to its
  * dispatch on its stream (hipExtLaunchKernel), which take the kernel's own start and end
  * times; phase 4 reads their mean elapsed time (the kernel's average launch duration,
  * over at most the first 16384 launches of the interval).
@@ -520,8 +520,10 @@ unsigned ww_next_fallback(unsigned flags, unsigned fb, int status);
  *   graph_parts  march parts replayed from HIP graphs, one bit each: 1 prep and
  *                assembly, 2 LU, 4 base chain, 8 column chain (the rest launched
  *                directly), 0..15
- *   minv_wgs     workgroup cap of the explicit-inverse launch, >= 1
- *   blu_strip    64-tiles per task of a block-LU step, 1..16
+ *   minv_wgs     >= 1; kept for callers that set it, without effect (the elimination leaves
+ *                the explicit inverse in place, which once took a launch of its own)
+ *   blu_strip    64-tiles per task of a block elimination step, 1..16: a step takes the
+ *                fewest that leave every task a compute unit, at most twice this number
  *   dtn_rows     rows per workgroup of the base DtN launch, 4..32, a multiple of 4
  *   gemm_split   wave groups splitting the inner dimension of a column product, 2 or 4
  *   gemm_rows    rows of a column product's output tile, 16 or 32 (16: twice the
@@ -531,7 +533,7 @@ unsigned ww_next_fallback(unsigned flags, unsigned fb, int status);
  *                copy of the lagged inverse, written by the same launch as the FP64 one;
  *                the residuals stay FP64 and the solve still ends with the 2^-43 test, so
  *                only the contraction per sweep changes (half the bytes per product)
- *   asm_cw       columns per assembly workgroup, 16 or 32
+ *   asm_cw       rows per assembly workgroup, 16 or 32
  *   lag_sweeps   refinement sweeps of a lagged-factor base solve, 1..8 (default 2, or
  *                WW_NREF_LAG); each sweep multiplies the error by about
  *                ||A_old^-1 A - I||, so marches whose matrix moves faster per step need

@@ -39,7 +39,7 @@ SPACE = {
     "lag": [8, 6, 10],
     "lag_sweeps": [2, 3, 4],
     "blu_strip": [4, 2, 3, 6, 8],
-    "minv_wgs": [1 << 20, 256, 128],
+    "minv_wgs": [1 << 20],   # (without effect)
     "dtn_rows": [8, 4, 16],
     "gemm_split": [4, 2],
     "asm_cw": [16, 32],

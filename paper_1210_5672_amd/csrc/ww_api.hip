@@ -13,6 +13,7 @@
 
 #include "ww.h"
 #include "ww_kernels.hpp"
+#include "ww_inv.hpp"
 #include "ww_mesh.hpp"
 #include "ww_dd.hpp"
 #include "ww_sdc.hpp"
@@ -55,11 +56,14 @@ static int fail(int code, const std::string& msg) {
       return fail(WW_EHIP, std::string("kernel launch: ") + hipGetErrorString(e_));     \
   } while (0)
 
-// One stage's factor set of the lagged-factor pipeline (all Np x Np unless noted)
-struct RingSet {
-  double *A = nullptr, *Gm = nullptr, *X = nullptr, *Z = nullptr, *V = nullptr, *Dinv = nullptr;
-  double *Mi = nullptr, *Gmr = nullptr, *Ar = nullptr, *aux = nullptr;
-  float *A32 = nullptr, *X32 = nullptr, *Z32 = nullptr, *V32 = nullptr, *Dinv32 = nullptr;
+// One stage's factor set (all Np x Np row-major unless noted): A (kept: residuals multiply
+// by it), the two scratch buffers of the elimination, the diagonal inverses (nb x 4096),
+// the explicit inverse, Gm and the per-point arrays; with the mixed form, their FP32
+// counterparts
+struct FacSet {
+  double *Ar = nullptr, *W0 = nullptr, *W1 = nullptr, *Dinv = nullptr;
+  double *Mi = nullptr, *Gmr = nullptr, *aux = nullptr;
+  float *A32 = nullptr, *V0 = nullptr, *V1 = nullptr, *Dinv32 = nullptr;
   float* Mi32 = nullptr;
 };
 #define PIPE_MAXLAG 11
@@ -85,28 +89,16 @@ struct ww_ctx {
   // tableau
   int nst = 0;
   double ta[16 * 16], tb[16];
-  // device buffers
-  double *A = nullptr, *Gm = nullptr, *Xi = nullptr, *Zi = nullptr, *Vi = nullptr, *Dinv = nullptr;
-  // second factor set and per-point arrays: stages alternate between the two sets so
-  // that the column chain of stage s overlaps the base chain of stage s + 1
-  double *A_1 = nullptr, *Gm_1 = nullptr, *Xi_1 = nullptr, *Zi_1 = nullptr, *Vi_1 = nullptr, *Dinv_1 = nullptr;
-  float *A32_1 = nullptr, *X32_1 = nullptr, *Z32_1 = nullptr, *V32_1 = nullptr, *Dinv32_1 = nullptr;
-  double* aux_1 = nullptr;
-  // row-major explicit inverses A^{-1} (per parity; FP32 in the mixed form) and
-  // row-major Gm, read by the one-vector products of the base chain and (the inverse)
-  // by the column solves
-  double *Mi = nullptr, *Gmr = nullptr, *Mi_1 = nullptr, *Gmr_1 = nullptr;
-  float *Mi32 = nullptr, *Mi32_1 = nullptr;
-  double *Ar = nullptr, *Ar_1 = nullptr;   // mixed mode: FP64 A for the residuals
+  // device buffers: two factor sets; stages alternate between them so that the column
+  // chain of stage s overlaps the base chain of stage s + 1
+  FacSet set[2];
   hipStream_t side = nullptr;  // column-chain stream
   hipEvent_t evB[16] = {}, evC[16] = {};
-  float *A32 = nullptr, *X32 = nullptr, *Z32 = nullptr, *V32 = nullptr, *Dinv32 = nullptr;
   double *Rr = nullptr, *rr0 = nullptr;   // residuals of the refinement sweeps
   int nref = 2;                            // refinement sweeps per solve (mixed mode)
   int nref_lag = -1;                       // sweeps of a lagged-factor solve (-1: nref)
   double *cosT = nullptr, *sinT = nullptr, *c0T = nullptr, *sig = nullptr;
   cplx* tw = nullptr;
-  double* aux = nullptr;
   double *rhs0 = nullptr, *y0t = nullptr, *mu0 = nullptr, *gam0 = nullptr, *hg0 = nullptr, *gphi0 = nullptr;
   double *Psi = nullptr, *Ytmp = nullptr, *Mu = nullptr, *Gam = nullptr, *HG = nullptr, *Gpsi = nullptr;
   double *y = nullptr, *Ys = nullptr, *K = nullptr, *Kx = nullptr, *ydtn = nullptr;
@@ -171,7 +163,7 @@ struct ww_ctx {
   size_t ckpt_cap = 0;
   double* seg = nullptr;
   size_t seg_cap = 0;
-  double* adj = nullptr;   // lam, mu, ups[16], gt, hd, e1, q, g2, zeta, y1, y2, rv, dv
+  double* adj = nullptr;   // lam, mu, ups[16], gt, hd, e1, q, g2, zeta, y2, rv, dv
   // optional HIP events around phases of every stage of the captured step
   // (0: block LU, 1: whole base chain, 2: column chain); the values of the last
   // replayed step are read back by ww_profile_read
@@ -213,7 +205,7 @@ struct ww_ctx {
   // stage s runs on one of `lag` streams; the column chain of stage s waits for it
   int lag = 8;   // environment WW_PIPE_LAG, 0..PIPE_MAXLAG (0: every solve uses its own factors)
   // stages factored together by one LU launch sequence (environment WW_LU_GROUP,
-  // 1..BLU_GMAX; at most the lag)
+  // 1..GJ_GMAX; at most the lag)
   int lu_group = 2;
   int minv_wgs = 1 << 20;                  // workgroup cap of the explicit-inverse launch
   int graph_parts = 10;                    // parts of a march stage replayed from graphs (bit per part)
@@ -232,7 +224,7 @@ struct ww_ctx {
   // of on the column stream (environment WW_COLS_ON_LU=0 turns it off)
   bool cols_on_lu = true;
   int ring_n = 0;          // factor sets allocated (one per stage)
-  RingSet ring[16];
+  FacSet ring[16];
   hipStream_t lus[PIPE_MAXLUS] = {};
   hipEvent_t evA[16] = {}, evL[16] = {};
   // one graph per branch and stage of the lagged-factor march (prep, LU, base, columns)
@@ -273,6 +265,22 @@ static int dalloc(ww_ctx* c, void** p, size_t bytes) {
   if (e != hipSuccess) return fail(WW_EHIP, std::string("hipMalloc: ") + hipGetErrorString(e));
   c->allocs.push_back(*p);
   return 0;
+}
+
+// one factor set for n_max
+static int alloc_set(ww_ctx* c, FacSet& f) {
+  int rc;
+  const size_t np = c->np_max, nn = np * np, nd = np / WW_TB * 4096;
+  double** d[] = {&f.Ar, &f.W0, &f.W1, &f.Mi, &f.Gmr};
+  for (double** q : d)
+    if ((rc = dalloc(c, (void**)q, nn * 8))) return rc;
+  if ((rc = dalloc(c, (void**)&f.Dinv, nd * 8))) return rc;
+  if ((rc = dalloc(c, (void**)&f.aux, (size_t)AUX_COUNT * c->n_max * 8))) return rc;
+  if (!(c->flags & WW_MIXED)) return 0;
+  float** e[] = {&f.A32, &f.V0, &f.V1, &f.Mi32};
+  for (float** q : e)
+    if ((rc = dalloc(c, (void**)q, nn * 4))) return rc;
+  return dalloc(c, (void**)&f.Dinv32, nd * 4);
 }
 
 // circulant and spectral tables for grid size N (host-computed in double)
@@ -376,51 +384,18 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
   c->r_max = r_max;
   c->np_max = (n_max + WW_TB - 1) / WW_TB * WW_TB;
   const size_t np = c->np_max, nm = n_max, R = r_max;
-  const int nbm = (int)(np / WW_TB);
   int rc = 0;
 #define AL(ptr, bytes) \
   if ((rc = dalloc(c, (void**)&(ptr), (bytes))) != 0) { ww_destroy(c); return rc; }
-  AL(c->A, np * np * 8);
-  AL(c->Gm, np * np * 8);
-  AL(c->Xi, np * np * 8);
-  AL(c->Zi, np * np * 8);
-  AL(c->Vi, np * np * 8);
-  AL(c->Dinv, (size_t)nbm * 4096 * 8);
-  AL(c->A_1, np * np * 8);
-  AL(c->Gm_1, np * np * 8);
-  AL(c->Xi_1, np * np * 8);
-  AL(c->Zi_1, np * np * 8);
-  AL(c->Vi_1, np * np * 8);
-  AL(c->Dinv_1, (size_t)nbm * 4096 * 8);
-  AL(c->Mi, np * np * 8);
-  AL(c->Gmr, np * np * 8);
-  AL(c->Mi_1, np * np * 8);
-  AL(c->Gmr_1, np * np * 8);
-  if (flags & WW_MIXED) {
-    AL(c->Mi32, np * np * 4);
-    AL(c->Mi32_1, np * np * 4);
-    AL(c->Ar, np * np * 8);
-    AL(c->Ar_1, np * np * 8);
-    AL(c->A32, np * np * 4);
-    AL(c->X32, np * np * 4);
-    AL(c->Z32, np * np * 4);
-    AL(c->V32, np * np * 4);
-    AL(c->Dinv32, (size_t)nbm * 4096 * 4);
-    AL(c->A32_1, np * np * 4);
-    AL(c->X32_1, np * np * 4);
-    AL(c->Z32_1, np * np * 4);
-    AL(c->V32_1, np * np * 4);
-    AL(c->Dinv32_1, (size_t)nbm * 4096 * 4);
-    AL(c->Rr, np * R * 8);
-  }
+  for (FacSet& f : c->set)
+    if ((rc = alloc_set(c, f))) { ww_destroy(c); return rc; }
+  if (flags & WW_MIXED) AL(c->Rr, np * R * 8);
   AL(c->rr0, np * 8);   // residual of the one-vector solves (mixed form, lagged factors)
   AL(c->cosT, nm * 8);
   AL(c->sinT, nm * 8);
   AL(c->c0T, nm * 8);
   AL(c->sig, nm * 8);
   AL(c->tw, nm * sizeof(cplx));
-  AL(c->aux, (size_t)AUX_COUNT * nm * 8);
-  AL(c->aux_1, (size_t)AUX_COUNT * nm * 8);
   AL(c->rhs0, np * 8);
   AL(c->y0t, np * 8);
   AL(c->mu0, np * 8);
@@ -475,7 +450,7 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
     const char* ns = std::getenv("WW_LU_STREAMS");
     if (ns) c->nlus = std::max(1, std::min(PIPE_MAXLUS, std::atoi(ns)));
     const char* lg = std::getenv("WW_LU_GROUP");
-    if (lg) c->lu_group = std::max(1, std::min(BLU_GMAX, std::atoi(lg)));
+    if (lg) c->lu_group = std::max(1, std::min(GJ_GMAX, std::atoi(lg)));
     const char* gp = std::getenv("WW_GRAPH_PARTS");
     if (gp) c->graph_parts = std::atoi(gp) & 15;
     const char* mw = std::getenv("WW_MINV_WGS");
@@ -499,14 +474,8 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
   }
   // kernels whose dynamic LDS can exceed the default 64 KiB
   const int big = 160 * 1024;
-  CCHK(hipFuncSetAttribute((const void*)k_blu_init<double>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_blu_step<double>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_blu_final<double>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_minv<double>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_minv<float>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_blu_init<float>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_blu_step<float>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_blu_final<float>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
+  CCHK(hipFuncSetAttribute((const void*)k_gj_step<double>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
+  CCHK(hipFuncSetAttribute((const void*)k_gj_step<float>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_base_prep, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   {
     // k_gamma holds static LDS too (the folded refinement test): dynamic + static <= big
@@ -599,11 +568,11 @@ int ww_get_tuning(ww_ctx* c, ww_tuning* t) {
 int ww_set_tuning(ww_ctx* c, const ww_tuning* t) {
   if (!c || !t) return fail(WW_EINVAL, "null argument");
   if (t->lag < 0 || t->lag > PIPE_MAXLAG) return fail(WW_EINVAL, "tuning: lag out of range");
-  if (t->lu_group < 1 || t->lu_group > BLU_GMAX) return fail(WW_EINVAL, "tuning: lu_group out of range");
+  if (t->lu_group < 1 || t->lu_group > GJ_GMAX) return fail(WW_EINVAL, "tuning: lu_group out of range");
   if (t->lu_streams < 1 || t->lu_streams > PIPE_MAXLUS) return fail(WW_EINVAL, "tuning: lu_streams out of range");
   if (t->graph_parts < 0 || t->graph_parts > 15) return fail(WW_EINVAL, "tuning: graph_parts out of range");
   if (t->minv_wgs < 1) return fail(WW_EINVAL, "tuning: minv_wgs out of range");
-  if (t->blu_strip < 1 || t->blu_strip > BLU_STRIP_MAX) return fail(WW_EINVAL, "tuning: blu_strip out of range");
+  if (t->blu_strip < 1 || t->blu_strip > GJ_STRIP_MAX) return fail(WW_EINVAL, "tuning: blu_strip out of range");
   if (t->dtn_rows < 4 || t->dtn_rows > 32 || t->dtn_rows % 4) return fail(WW_EINVAL, "tuning: dtn_rows out of range");
   if (t->gemm_split != 2 && t->gemm_split != 4) return fail(WW_EINVAL, "tuning: gemm_split must be 2 or 4");
   if (t->asm_cw != 16 && t->asm_cw != 32) return fail(WW_EINVAL, "tuning: asm_cw must be 16 or 32");
@@ -656,24 +625,6 @@ int ww_set_tableau(ww_ctx* c, int s, const double* a, const double* b, const dou
 // kernel sequences
 // ------------------------------------------------------------------------------------
 static size_t fft_lds_bytes(int N, int nbuf) { return (size_t)nbuf * N * sizeof(cplx); }
-static const size_t TILE_BYTES = (size_t)TILE_DBL * 8;
-
-template <typename T>
-static BluBufs<T> blu_bufs(ww_ctx* c, T* A, T* X, T* Z, T* V, T* D, double guard) {
-  BluBufs<T> b;
-  b.A = A;
-  b.X = X;
-  b.Z = Z;
-  b.V = V;
-  b.Dinv = D;
-  b.Xr = nullptr;   // the solves use the explicit inverse (k_minv), not row-major factors
-  b.Zr = nullptr;
-  b.status = c->status;
-  b.Np = c->Np;
-  b.pivguard = guard;
-  return b;
-}
-
 // measurement hook: a pair of HIP events attached to one kernel dispatch on the current
 // stream (hipExtLaunchKernel: the events take the dispatch's own start and end times),
 // only inside a march step, where the phase marks are taken too, outside stream capture,
@@ -701,31 +652,30 @@ static int kev_pair(ww_ctx* c, hipEvent_t* a, hipEvent_t* b) {
   return 0;
 }
 
+// the elimination of a group (see ww_inv.hpp)
 template <typename T>
-static int enqueue_blu(ww_ctx* c, const BluGroup<T>& g) {
+static int enqueue_gj(ww_ctx* c, const GjGroup<T>& g) {
   const int nb = c->Np / WW_TB;
-  const size_t es = sizeof(T);
   int rc;
-  hipLaunchKernelGGL(k_blu_init<T>, dim3(g.count), dim3(WW_NT), (TILE_DBL + GJ_SCR) * es, c->stream, g);
+  hipLaunchKernelGGL(k_gj_init<T>, dim3(g.count), dim3(WW_NT), 0, c->stream, g);
   LAUNCHCHK();
-  for (int k = 0; k + 1 < nb; ++k) {
-    const int nblk = blu_step_tasks(nb, k, g.strip);
-    hipEvent_t ea, eb;
-    if ((rc = kev_pair(c, &ea, &eb))) return rc;
+  if (nb == 1) return 0;
+  const size_t lds = 2 * GJ_TILE * sizeof(T);
+  for (int k = 0; k < nb; ++k) {
+    const int nblk = gj_step_tasks(nb, k, g.strip) * g.count;
+    hipEvent_t ea = nullptr, eb = nullptr;
+    // (the steps that carry a diagonal inverse; the last one only writes the result)
+    if (k + 1 < nb && (rc = kev_pair(c, &ea, &eb))) return rc;
     if (ea) {
-      BluGroup<T> ga = g;
+      GjGroup<T> ga = g;
       int ka = k;
       void* args[] = {&ga, &ka};
-      HIPCHK(hipExtLaunchKernel(reinterpret_cast<const void*>(&k_blu_step<T>), dim3(nblk * g.count), dim3(WW_NT),
-                                args, 2 * TILE_DBL * es, c->stream, ea, eb, 0));
+      HIPCHK(hipExtLaunchKernel(reinterpret_cast<const void*>(&k_gj_step<T>), dim3(nblk), dim3(WW_NT), args, lds,
+                                c->stream, ea, eb, 0));
       ++c->kev_n;
     } else {
-      hipLaunchKernelGGL(k_blu_step<T>, dim3(nblk * g.count), dim3(WW_NT), 2 * TILE_DBL * es, c->stream, g, k);
+      hipLaunchKernelGGL(k_gj_step<T>, dim3(nblk), dim3(WW_NT), lds, c->stream, g, k);
     }
-    LAUNCHCHK();
-  }
-  if (nb > 1) {
-    hipLaunchKernelGGL(k_blu_final<T>, dim3((nb - 1) * g.count), dim3(WW_NT), 2 * TILE_DBL * es, c->stream, g);
     LAUNCHCHK();
   }
   return 0;
@@ -748,35 +698,22 @@ static bool pivoted(const ww_ctx* c) { return (c->fb & WW_FB_PIVOTED) != 0; }
 // pivot bound of the pivoted factorisation (near singularity)
 static const double PIVOTED_GUARD = 1e-8;
 
-// The FP64 factor set of one stage: A (overwritten by the Schur complements), Gm, the
-// block-triangular inverses X, Z, and the scratch V, Dinv.  The adjoint keeps one set
-// per stage of a segment; everything else uses the context's set.
-struct Fac {
-  double *A, *Gm, *X, *Z, *V, *Dinv;
-  bool use32;   // mixed precision: factor the FP32 copy and refine the solves
-  float *A32, *X32, *Z32, *V32, *Dinv32;
-  double* aux;    // per-point base arrays of the stage
-  // row-major arrays: Mi = A^{-1} from the FP64 factors, Mi32 from the FP32 factors
-  // (every solve is one product with it), Gm, and the FP64 A of the residuals
-  double *Mi, *Gmr, *Ar;
-  float* Mi32;
-  int* perm;   // partial-pivoting row order of this set, or null (no interchanges)
-  bool lag32 = false;   // FP64 factors whose lagged solves read the FP32 copy Mi32 of Mi
+// A factor set as the kernel sequences use it: the buffers, the precision of its
+// elimination and of its lagged solves, and its row order
+struct Fac : FacSet {
+  bool use32 = false;     // mixed precision: invert the FP32 copy and refine the solves
+  int* perm = nullptr;    // partial-pivoting row order of this set, or null (no interchanges)
+  bool lag32 = false;     // FP64 elimination whose lagged solves read the FP32 copy Mi32 of Mi
 };
-// factor set of parity `p`; `cols` selects the column chain's GEMM partials
-static Fac fac_set(ww_ctx* c, int p, bool cols) {
+static Fac fac_of(const ww_ctx* c, const FacSet& f) {
   Fac F;
-  if (p == 0) {
-    F = Fac{c->A, c->Gm, c->Xi, c->Zi, c->Vi, c->Dinv, use32(c), c->A32, c->X32, c->Z32, c->V32, c->Dinv32, c->aux,
-            nullptr};
-  } else {
-    F = Fac{c->A_1, c->Gm_1, c->Xi_1, c->Zi_1, c->Vi_1, c->Dinv_1, use32(c), c->A32_1, c->X32_1, c->Z32_1, c->V32_1,
-            c->Dinv32_1, c->aux_1, nullptr};
-  }
-  F.Mi = p ? c->Mi_1 : c->Mi;
-  F.Gmr = p ? c->Gmr_1 : c->Gmr;
-  F.Ar = p ? c->Ar_1 : c->Ar;
-  F.Mi32 = p ? c->Mi32_1 : c->Mi32;
+  static_cast<FacSet&>(F) = f;
+  F.use32 = use32(c);
+  return F;
+}
+// factor set of parity `p`
+static Fac fac_set(ww_ctx* c, int p) {
+  Fac F = fac_of(c, c->set[p]);
   F.perm = pivoted(c) ? c->perm : nullptr;
   return F;
 }
@@ -791,13 +728,12 @@ static int ensure_pivot_buffers(ww_ctx* c) {
   return dalloc(c, (void**)&c->pb, np * (size_t)c->r_max * 8);
 }
 
-// Row order of partial pivoting for the assembled A of F (column-major, ld Np), then
-// A := P A.  Elimination runs on a copy in the workspace; the padding rows keep their
-// place (the padding of A is the identity).
+// Row order of partial pivoting for the assembled A of F, then P A (row-major) into the
+// scratch buffer W1, where the elimination starts.  The search runs on a column-major copy
+// in the workspace; the padding rows keep their place (the padding of A is the identity).
 static int enqueue_pivot_order(ww_ctx* c, const Fac& F) {
   const int N = c->N, Np = c->Np;
-  const int cblk = (int)std::min<size_t>(((size_t)Np * Np + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_pad_copy, dim3(cblk), dim3(256), 0, c->stream, F.A, Np, c->pw, Np, Np, Np, Np);
+  hipLaunchKernelGGL(k_plu_copy, dim3(Np / 32, Np / 32), dim3(256), 0, c->stream, F.Ar, c->pw, Np);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_iota, dim3((Np + 255) / 256), dim3(256), 0, c->stream, F.perm, Np);
   LAUNCHCHK();
@@ -811,20 +747,17 @@ static int enqueue_pivot_order(ww_ctx* c, const Fac& F) {
       LAUNCHCHK();
     }
   }
-  hipLaunchKernelGGL(k_permute_rows, dim3(cblk), dim3(256), 0, c->stream, F.A, c->pw, F.perm, Np, Np, 0);
-  LAUNCHCHK();
-  hipLaunchKernelGGL(k_pad_copy, dim3(cblk), dim3(256), 0, c->stream, c->pw, Np, F.A, Np, Np, Np, Np);
+  hipLaunchKernelGGL(k_gather_rows, dim3(Np), dim3(256), 0, c->stream, F.Ar, F.W1, F.perm, Np);
   LAUNCHCHK();
   return 0;
 }
-static Fac fac_default(ww_ctx* c) { return fac_set(c, 0, false); }
+static Fac fac_default(ww_ctx* c) { return fac_set(c, 0); }
 
-// assembly of A, Gm (and the row-major FP64 copy Ar when the solves refine: mixed
-// mode, or lagged factors)
+// assembly of A and Gm (row-major; in the mixed form also A's FP32 copy)
 // The lagged inverse Fo (optional): the same launch forms x0 = Fo.Mi psi (the first
 // solve of a lagged-factor base chain) in 16 more rows of workgroups.
-static int enqueue_assemble(ww_ctx* c, const Fac& F, bool want_ar, const Fac* Fo = nullptr,
-                            const double* psi = nullptr, double* x0 = nullptr) {
+static int enqueue_assemble(ww_ctx* c, const Fac& F, const Fac* Fo = nullptr, const double* psi = nullptr,
+                            double* x0 = nullptr) {
   const int nb = c->Np / WW_TB;
   const bool f32 = Fo && (Fo->use32 || Fo->lag32);
   const double* mx64 = (Fo && !f32) ? Fo->Mi : nullptr;
@@ -832,74 +765,82 @@ static int enqueue_assemble(ww_ctx* c, const Fac& F, bool want_ar, const Fac* Fo
   if (Fo && !(mx64 || mx32)) return fail(WW_EHIP, "internal: lagged first solve without its inverse");
   if (c->mapped) {
     hipLaunchKernelGGL(k_assemble_map, dim3(nb, c->Np / 16 + (Fo ? 16 : 0)), dim3(WW_NT), 0, c->stream, F.aux,
-                       c->mesh, c->n_max, c->c0T, F.A, F.Gm, F.use32 ? F.A32 : nullptr, F.Gmr,
-                       (F.use32 || want_ar) ? F.Ar : nullptr, c->N, c->Np, c->finite, mx64, mx32, psi, x0);
+                       c->mesh, c->n_max, c->c0T, F.Ar, F.use32 ? F.A32 : nullptr, F.Gmr, c->N, c->Np, c->finite,
+                       mx64, mx32, psi, x0);
     LAUNCHCHK();
     return 0;
   }
   const int cw = c->asm_cw == 32 ? 32 : 16;
   const int gy = c->Np / cw + (Fo ? 16 : 0);
   hipLaunchKernelGGL(cw == 32 ? k_assemble<32> : k_assemble<16>, dim3(nb, gy), dim3(WW_NT), 0, c->stream, F.aux,
-                     c->n_max, c->cosT, c->sinT, c->c0T, F.A, F.Gm, F.use32 ? F.A32 : nullptr, F.Gmr,
-                     (F.use32 || want_ar) ? F.Ar : nullptr, c->N, c->Np, c->finite, mx64, mx32, psi, x0);
+                     c->n_max, c->cosT, c->sinT, c->c0T, F.Ar, F.use32 ? F.A32 : nullptr, F.Gmr, c->N, c->Np,
+                     c->finite, mx64, mx32, psi, x0);
   LAUNCHCHK();
   return 0;
 }
 
-// block LU of A (FP64, or of the FP32 copy in mixed mode) with the block-triangular
-// inverses and the explicit inverse Mi = Z (I + X); with a row order, first the
-// partial-pivoting order and A := P A.  A group (count > 1: consecutive stages of a
-// lagged-factor march, never pivoted) shares every launch of the sequence.
-static int minv_grid(const ww_ctx* c, int ntask) { return std::max(1, std::min(ntask, c->minv_wgs)); }
+// Tiles per strip task: the fewest with which a step's tasks still find a CU each (256, the
+// critical task of every matrix among them: with one more workgroup than CUs the critical
+// one shares its matrix units and the step gets longer), at most blu_strip.  One tile a
+// task repeats the row's left factor for every tile; four leave most CUs idle below
+// N = 1024.
+static int gj_strip(const ww_ctx* c, int count) {
+  const int nb = c->Np / WW_TB;
+  int s = 1;
+  while (s < 2 * c->blu_strip && gj_step_tasks(nb, 0, s) * count > 256) ++s;
+  return s;
+}
 
+// the explicit inverse Mi of A (FP64, or of the FP32 copy in mixed mode); with a row
+// order, first the partial-pivoting order, and the inverse is that of P A.  A group
+// (count > 1: consecutive stages of a lagged-factor march, never pivoted) shares every
+// launch of the sequence.
 static int enqueue_lu_group(ww_ctx* c, const Fac* F, int count) {
   int rc;
-  if (count < 1 || count > BLU_GMAX) return fail(WW_EHIP, "internal: LU group size");
+  if (count < 1 || count > GJ_GMAX) return fail(WW_EHIP, "internal: LU group size");
   if ((rc = prof_mark(c, 0, 0))) return rc;
   if (count == 1 && F[0].perm && (rc = enqueue_pivot_order(c, F[0]))) return rc;
-  const int nb = c->Np / WW_TB;
+  auto common = [&](auto& g) {
+    g.status = c->status;
+    g.pivguard = F[0].perm ? PIVOTED_GUARD : c->guard;
+    g.Np = c->Np;
+    g.count = count;
+    g.strip = gj_strip(c, count);
+  };
   if (F[0].use32) {
-    BluGroup<float> g{};
-    MinvGroup<float> mg{};
+    GjGroup<float> g{};
     for (int q = 0; q < count; ++q) {
-      if (!F[q].Mi32) return fail(WW_EHIP, "internal: LU without its inverse buffer");
-      g.m[q] = blu_bufs<float>(c, F[q].A32, F[q].X32, F[q].Z32, F[q].V32, F[q].Dinv32, c->guard);
-      mg.Z[q] = F[q].Z32;
-      mg.X[q] = F[q].X32;
-      mg.Mr[q] = F[q].Mi32;
+      if (!F[q].Mi32 || !F[q].A32) return fail(WW_EHIP, "internal: LU without its buffers");
+      g.S0[q] = F[q].A32;
+      g.W0[q] = F[q].V0;
+      g.W1[q] = F[q].V1;
+      g.Mr[q] = F[q].Mi32;
+      g.Dinv[q] = F[q].Dinv32;
     }
-    g.count = count;
-    g.strip = c->blu_strip;
-    if ((rc = enqueue_blu<float>(c, g))) return rc;
-    mg.count = count;
-    hipLaunchKernelGGL(k_minv<float>, dim3(minv_grid(c, nb * nb * count)), dim3(WW_NT), 2 * TILE_DBL * sizeof(float),
-                       c->stream, mg, c->Np);
+    common(g);
+    rc = enqueue_gj<float>(c, g);
   } else {
-    BluGroup<double> g{};
-    MinvGroup<double> mg{};
+    GjGroup<double> g{};
     for (int q = 0; q < count; ++q) {
-      if (!F[q].Mi) return fail(WW_EHIP, "internal: LU without its inverse buffer");
-      g.m[q] = blu_bufs<double>(c, F[q].A, F[q].X, F[q].Z, F[q].V, F[q].Dinv, F[q].perm ? PIVOTED_GUARD : c->guard);
-      mg.Z[q] = F[q].Z;
-      mg.X[q] = F[q].X;
-      mg.Mr[q] = F[q].Mi;
-      mg.Mr32[q] = F[q].lag32 ? F[q].Mi32 : nullptr;
+      if (!F[q].Mi || !F[q].Ar) return fail(WW_EHIP, "internal: LU without its buffers");
+      g.S0[q] = F[q].perm ? F[q].W1 : F[q].Ar;
+      g.W0[q] = F[q].W0;
+      g.W1[q] = F[q].W1;
+      g.Mr[q] = F[q].Mi;
+      g.Dinv[q] = F[q].Dinv;
+      g.Mr32[q] = F[q].lag32 ? F[q].Mi32 : nullptr;
     }
-    g.count = count;
-    g.strip = c->blu_strip;
-    if ((rc = enqueue_blu<double>(c, g))) return rc;
-    mg.count = count;
-    hipLaunchKernelGGL(k_minv<double>, dim3(minv_grid(c, nb * nb * count)), dim3(WW_NT), 2 * TILE_DBL * sizeof(double),
-                       c->stream, mg, c->Np);
+    common(g);
+    rc = enqueue_gj<double>(c, g);
   }
-  LAUNCHCHK();
+  if (rc) return rc;
   return prof_mark(c, 0, 1);
 }
 static int enqueue_lu(ww_ctx* c, const Fac& F) { return enqueue_lu_group(c, &F, 1); }
 
 static int enqueue_assemble_lu(ww_ctx* c, const Fac& F) {
   int rc;
-  if ((rc = enqueue_assemble(c, F, false))) return rc;
+  if ((rc = enqueue_assemble(c, F))) return rc;
   return enqueue_lu(c, F);
 }
 
@@ -947,7 +888,7 @@ static const double REFINE_TOL = 1.1368683772161603e-13;
 static int enqueue_solve(ww_ctx* c, const Fac& F, double* B, double* Y, double* X, double* Rs, int R) {
   (void)Y;
   int rc;
-  if (F.perm) {   // P A = Lt Ut: solve with P B
+  if (F.perm) {   // the inverse is that of P A: solve with P B
     const size_t n = (size_t)c->Np * R;
     const int blocks = (int)std::min<size_t>((n + 255) / 256, 4096);
     hipLaunchKernelGGL(k_permute_rows, dim3(blocks), dim3(256), 0, c->stream, B, c->pb, F.perm, c->Np, R, 0);
@@ -988,9 +929,6 @@ static size_t kstride(const ww_ctx* c) { return (size_t)2 * c->N * (c->M + 1); }
 static int ensure_gmres(ww_ctx* c) {
   int rc;
   const size_t np = c->np_max, m = GM_MAXM;
-  // the row-major FP64 A that GMRES multiplies by (allocated with the mixed form only)
-  if (!c->Ar && (rc = dalloc(c, (void**)&c->Ar, np * np * 8))) return rc;
-  if (!c->Ar_1 && (rc = dalloc(c, (void**)&c->Ar_1, np * np * 8))) return rc;
   if (c->gmV) return 0;
   if ((rc = dalloc(c, (void**)&c->gmV, np * (m + 1) * 8))) return rc;
   if ((rc = dalloc(c, (void**)&c->gmw, np * 8))) return rc;
@@ -1053,7 +991,7 @@ static int gmres_calibrate(ww_ctx* c) {
                      0, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
   LAUNCHCHK();
   int rc;
-  if ((rc = enqueue_assemble(c, F, true))) return rc;
+  if ((rc = enqueue_assemble(c, F))) return rc;
   // a rough right-hand side (the initial potential is often zero, which GMRES solves in
   // no step)
   hipLaunchKernelGGL(k_gm_probe_rhs, dim3((c->Np + 255) / 256), dim3(256), 0, c->stream, c->y0t, c->N, c->Np);
@@ -1078,7 +1016,7 @@ static int enqueue_base_chain(ww_ctx* c, const double* ysrc, int s, double* kout
                      s, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
   LAUNCHCHK();
   if (c->gm_active) {
-    if ((rc = enqueue_assemble(c, F, true))) return rc;
+    if ((rc = enqueue_assemble(c, F))) return rc;
     if ((rc = enqueue_gmres(c, F, c->rhs0, c->mu0, c->rr0))) return rc;
     hipLaunchKernelGGL(k_gamma, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->mu0, c->Np, 1, c->gam0,
                        c->hg0, c->tw, c->N, nullptr, nullptr, 0.0, nullptr, 0);
@@ -1147,22 +1085,11 @@ static hipStream_t lu_stream(const ww_ctx* c, int s) { return c->lus[(s / lu_gro
 // the first n factor sets of the ring (each for n_max)
 static int ensure_ring(ww_ctx* c, int n) {
   int rc;
-  const size_t np = c->np_max, nn = np * np;
-  const size_t nbm = np / WW_TB;
   while (c->ring_n < n) {
-    RingSet& r = c->ring[c->ring_n];
-    double** d[] = {&r.A, &r.Gm, &r.X, &r.Z, &r.V, &r.Mi, &r.Gmr, &r.Ar};
-    for (double** q : d)
-      if ((rc = dalloc(c, (void**)q, nn * 8))) return rc;
-    if ((rc = dalloc(c, (void**)&r.Dinv, nbm * 4096 * 8))) return rc;
-    if ((rc = dalloc(c, (void**)&r.aux, (size_t)AUX_COUNT * c->n_max * 8))) return rc;
-    if ((rc = dalloc(c, (void**)&r.Mi32, nn * 4))) return rc;   // also the FP64 form's FP32 copy
-    if (mixed(c)) {
-      float** f[] = {&r.A32, &r.X32, &r.Z32, &r.V32};
-      for (float** q : f)
-        if ((rc = dalloc(c, (void**)q, nn * 4))) return rc;
-      if ((rc = dalloc(c, (void**)&r.Dinv32, nbm * 4096 * 4))) return rc;
-    }
+    FacSet& r = c->ring[c->ring_n];
+    if ((rc = alloc_set(c, r))) return rc;
+    // the FP64 form's FP32 copy of the inverse (lag_fp32)
+    if (!r.Mi32 && (rc = dalloc(c, (void**)&r.Mi32, (size_t)c->np_max * c->np_max * 4))) return rc;
     ++c->ring_n;
   }
   return 0;
@@ -1179,15 +1106,9 @@ static int ensure_pipe(ww_ctx* c) {
   return ensure_ring(c, c->nst);
 }
 
-static Fac pipe_set(ww_ctx* c, int s, bool cols) {
-  const RingSet& r = c->ring[s];
-  Fac F = Fac{r.A, r.Gm, r.X, r.Z, r.V, r.Dinv, use32(c), r.A32, r.X32, r.Z32, r.V32, r.Dinv32, r.aux, nullptr};
-  F.Mi = r.Mi;
-  F.Gmr = r.Gmr;
-  F.Ar = r.Ar;
-  F.Mi32 = r.Mi32;
-  F.perm = nullptr;
-  F.lag32 = c->lag32 && !F.use32 && r.Mi32;
+static Fac pipe_set(ww_ctx* c, int s) {
+  Fac F = fac_of(c, c->ring[s]);
+  F.lag32 = c->lag32 && !F.use32 && F.Mi32;
   return F;
 }
 
@@ -1196,15 +1117,15 @@ static Fac pipe_set(ww_ctx* c, int s, bool cols) {
 static int pipe_prologue(ww_ctx* c) {
   int rc;
   const int nst = c->nst, L = c->lag;
-  const Fac P0 = pipe_set(c, nst - L, false);
+  const Fac P0 = pipe_set(c, nst - L);
   hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->y, c->K, c->Ys, c->coef,
                      0, kstride(c), P0.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
   LAUNCHCHK();
-  if ((rc = enqueue_assemble(c, P0, true))) return rc;
+  if ((rc = enqueue_assemble(c, P0))) return rc;
   if ((rc = enqueue_lu(c, P0))) return rc;
   const size_t nn = (size_t)c->Np * c->Np;
   for (int q = nst - L + 1; q < nst; ++q) {
-    const RingSet &a = c->ring[nst - L], &b = c->ring[q];
+    const FacSet &a = c->ring[nst - L], &b = c->ring[q];
     if (use32(c) || P0.lag32)
       HIPCHK(hipMemcpyAsync(b.Mi32, a.Mi32, nn * 4, hipMemcpyDeviceToDevice, c->stream));
     if (!use32(c))
@@ -1227,9 +1148,9 @@ enum { PP_PREP = 0, PP_LU = 1, PP_BASE = 2, PP_COL = 3 };
 
 static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
   const int nst = c->nst, L = c->lag;
-  const Fac F = pipe_set(c, s, false);
+  const Fac F = pipe_set(c, s);
   int rc = 0;
-  const Fac Fo = pipe_set(c, (s - L + nst) % nst, false);   // the lagged factor set
+  const Fac Fo = pipe_set(c, (s - L + nst) % nst);   // the lagged factor set
   if (part == PP_PREP) {
     // spectral prep; assembly, and in the same launch the first lagged solve
     // x0 = Mi_old psi, which does not need this stage's matrix
@@ -1239,17 +1160,14 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
                          c->coef, s, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
       LAUNCHCHK();
     }
-    // the march reads Gm only row-major (base and column chains): no column-major copy
-    Fac Fa = F;
-    Fa.Gm = nullptr;
-    return enqueue_assemble(c, Fa, true, &Fo, c->rhs0, c->mu0);
+    return enqueue_assemble(c, F, &Fo, c->rhs0, c->mu0);
   }
   if (part == PP_LU) {
     // the group that ends at this stage (stages of a group are never pivoted)
     if (s != grp_last(c, s)) return 0;
     const int f = grp_first(c, s);
-    Fac Fs[BLU_GMAX];
-    for (int q = f; q <= s; ++q) Fs[q - f] = pipe_set(c, q, false);
+    Fac Fs[GJ_GMAX];
+    for (int q = f; q <= s; ++q) Fs[q - f] = pipe_set(c, q);
     return enqueue_lu_group(c, Fs, s - f + 1);
   }
   if (part == PP_BASE) {
@@ -1269,7 +1187,7 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
                        c->mu0, c->rhs0, F.Gmr, F.Ar, c->Np, c->tw, c->N, c->gphi0, chk, c->dtn_rows);
     LAUNCHCHK();
     if (s + 1 < nst && c->mapped) {
-      const Fac Fn = pipe_set(c, s + 1, false);
+      const Fac Fn = pipe_set(c, s + 1);
       hipLaunchKernelGGL(k_base_rhs_prep_map, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->gphi0,
                          F.aux, c->K + (size_t)s * kstride(c), chk, REFINE_TOL, c->sig, c->g, c->tau, c->y, c->K,
                          c->Ys, c->coef, s + 1, kstride(c), Fn.aux, c->rhs0, c->Np, c->hsurf, c->n_max, c->tw, c->N,
@@ -1280,7 +1198,7 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
                          c->sig, c->N, c->g, c->tau);
     } else if (s + 1 < nst) {
       // this stage's right-hand side and the next stage's prep in one launch
-      const Fac Fn = pipe_set(c, s + 1, false);
+      const Fac Fn = pipe_set(c, s + 1);
       hipLaunchKernelGGL(k_base_rhs_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->gphi0, F.aux,
                          c->K + (size_t)s * kstride(c), chk, REFINE_TOL, c->sig, c->g, c->tau, c->y, c->K, c->Ys,
                          c->coef, s + 1, kstride(c), Fn.aux, c->rhs0, c->Np, c->hsurf, c->n_max, c->tw, c->N,
@@ -1293,7 +1211,7 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
     LAUNCHCHK();
     return prof_mark(c, 1, 1);
   }
-  return enqueue_col_chain(c, s, pipe_set(c, s, true));
+  return enqueue_col_chain(c, s, pipe_set(c, s));
 }
 
 // the step end of the base column (cols false; it counts the step) or of the Jacobian
@@ -1475,17 +1393,17 @@ static int enqueue_step(ww_ctx* c, bool cols, bool two_streams) {
     c->prof_stage = s;
     // the factor set of this parity was last read by the column chain of stage s - 2
     if (two && s >= 2) HIPCHK(hipStreamWaitEvent(s0, c->evC[s - 2], 0));
-    rc = enqueue_base_chain(c, c->y, s, c->K + (size_t)s * kstride(c), fac_set(c, par, false));
+    rc = enqueue_base_chain(c, c->y, s, c->K + (size_t)s * kstride(c), fac_set(c, par));
     if (!rc && two) {
       // column chain of stage s on the side stream, overlapping the next base chain
       HIPCHK(hipEventRecord(c->evB[s], s0));
       HIPCHK(hipStreamWaitEvent(c->side, c->evB[s], 0));
       c->stream = c->side;
-      rc = enqueue_col_chain(c, s, fac_set(c, par, true));
+      rc = enqueue_col_chain(c, s, fac_set(c, par));
       c->stream = s0;
       if (!rc) HIPCHK(hipEventRecord(c->evC[s], c->side));
     } else if (!rc && cols && c->M > 0) {
-      rc = enqueue_col_chain(c, s, fac_set(c, par, true));   // one stream: after the base chain
+      rc = enqueue_col_chain(c, s, fac_set(c, par));   // one stream: after the base chain
     }
     c->prof_stage = -1;
     if (rc) return rc;
@@ -1597,7 +1515,7 @@ int dtn_setup(ww_ctx* c, const double* surface, double h, double tau, int N) {
   hipLaunchKernelGGL(k_status_reset, dim3(1), dim3(64), 0, c->stream, c->status);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(N, 4), c->stream, c->ydtn, c->K, c->Ys,
-                     c->coef, 0, (size_t)0, c->aux, c->n_max, c->rhs0, c->Np, c->tw, N, c->hsurf, c->status);
+                     c->coef, 0, (size_t)0, c->set[0].aux, c->n_max, c->rhs0, c->Np, c->tw, N, c->hsurf, c->status);
   LAUNCHCHK();
   if ((rc = dtn_factor(c))) return rc;
   c->dtn_ready = true;
@@ -1789,7 +1707,7 @@ static int dd_tables(ww_ctx* c, int N) {
 static size_t dd_lds_bytes(int N) { return (size_t)(3 * N + N / 2) * sizeof(cdd); }
 
 // The buffers of one double-double DtN: per-point quantities, A and Gm (hi and lo
-// planes), and the FP64 factor set whose A receives A's leading part and whose Mi the
+// planes), and the FP64 factor set whose Ar receives A's leading part and whose Mi the
 // explicit inverse.  The context's own (dd_lane) serves dtn_setup_dd / dtn_solve_multi_dd
 // and the double-double march's predictor; the nodes of its correction sweeps take one
 // lane each (with the ring's factor sets).
@@ -1803,7 +1721,6 @@ static Fac dd_fac(const ww_ctx* c, Fac F) {
   F.use32 = mixed(c);
   F.lag32 = false;
   F.perm = nullptr;
-  F.Gm = nullptr;
   return F;
 }
 static DdLane dd_lane(ww_ctx* c) {
@@ -1819,12 +1736,12 @@ static int dd_prep_assemble(ww_ctx* c, const DdLane& L, const double* sh, const 
                      c->n_max, L.pt_hi, L.pt_lo, c->finite ? domain : nullptr);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_dd_assemble, dim3(Np / WW_TB, Np / 16), dim3(WW_NT), 0, c->stream, L.pt_hi, L.pt_lo, c->n_max,
-                     c->dd_tab_hi, c->dd_tab_lo, N, Np, c->finite, L.Ah, L.Al, L.Gh, L.Gl, L.F.A);
+                     c->dd_tab_hi, c->dd_tab_lo, N, Np, c->finite, L.Ah, L.Al, L.Gh, L.Gl, L.F.Ar);
   LAUNCHCHK();
   if (L.F.use32) {
     if (!L.F.A32) return fail(WW_EHIP, "internal: FP32 factors without their buffer");
     const size_t nn = (size_t)Np * Np;
-    hipLaunchKernelGGL(k_dd_a32, dim3((int)std::min<size_t>((nn + 255) / 256, 4096)), dim3(256), 0, c->stream, L.F.A,
+    hipLaunchKernelGGL(k_dd_a32, dim3((int)std::min<size_t>((nn + 255) / 256, 4096)), dim3(256), 0, c->stream, L.F.Ar,
                        L.F.A32, nn);
     LAUNCHCHK();
   }
@@ -2291,14 +2208,14 @@ static int seg_run(ww_ctx* c, const double* params, double T, int nseg, const ww
       if ((rc = pipe_join(c))) return rc;   // the lagged march's LU and column streams
       const int No = c->N, Nn = sg[l].N;
       const int ncols = 2 * (cols ? c->M + 1 : 1);
-      // interpolation weights (row-major Nn x No, in the A buffer of the default factor
+      // interpolation weights (row-major Nn x No, in the A buffer of the first factor
       // set, free between segments), then the old state to the stage buffer
-      hipLaunchKernelGGL(k_regrid_w, dim3(Nn), dim3(WW_NT), 0, c->stream, c->A, Nn, No, Al, sg[l].refine_at,
+      hipLaunchKernelGGL(k_regrid_w, dim3(Nn), dim3(WW_NT), 0, c->stream, c->set[0].Ar, Nn, No, Al, sg[l].refine_at,
                          mesh_coef(sg[l - 1].rho), sg[l - 1].refine_at);
       LAUNCHCHK();
       HIPCHK(hipMemcpyAsync(c->Ys, c->y, (size_t)ncols * No * 8, hipMemcpyDeviceToDevice, c->stream));
       if ((rc = set_grid(c, Nn, c->shootH))) return rc;
-      hipLaunchKernelGGL(k_regrid_apply, dim3((Nn + 63) / 64, (ncols + 63) / 64), dim3(WW_NT), 0, c->stream, c->A,
+      hipLaunchKernelGGL(k_regrid_apply, dim3((Nn + 63) / 64, (ncols + 63) / 64), dim3(WW_NT), 0, c->stream, c->set[0].Ar,
                          c->Ys, c->y, Nn, No, ncols);
       LAUNCHCHK();
       if (sdc) {
@@ -2573,9 +2490,8 @@ struct SdcStep {
 
   SdcStep(ww_ctx* cc, bool cl, double d) : c(cc), cols(cl), dt(d), ks(kstride(cc)) {
     for (int m = 0; m < SDC_NODES; ++m) {
-      F[m] = pipe_set(c, m, false);
+      F[m] = pipe_set(c, m);
       F[m].lag32 = false;
-      F[m].Gm = nullptr;   // the chains read Gm row-major only
     }
     lag = c->sdc_lag && !(c->fb & WW_FB_DIRECT);
     bm = Bs{c->y0t, c->mu0, c->gam0, c->hg0, c->gphi0, c->rr0};
@@ -2597,16 +2513,15 @@ struct SdcStep {
     LAUNCHCHK();
     return 0;
   }
-  // main stream: the lane is free, the stage state's base column, prep, assembly (with
-  // the row-major FP64 A of the lagged solves' residuals when want_ar)
-  int front(int s, int q, bool want_ar = false) {
+  // main stream: the lane is free, the stage state's base column, prep, assembly
+  int front(int s, int q) {
     int rc;
     HIPCHK(hipStreamWaitEvent(c->stream, c->sdc_evC[q], 0));
     if ((rc = combine(s, q, false))) return rc;
     hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, yn(q), c->K, ysn(q),
                        c->coef, 0, ks, F[q].aux, c->n_max, rhsn(q), c->Np, c->tw, c->N, c->hsurf, c->status);
     LAUNCHCHK();
-    return enqueue_assemble(c, F[q], want_ar);
+    return enqueue_assemble(c, F[q]);
   }
   // A predictor stage on lagged factors (lane q, the factors of lane qb): its own LU on
   // the LU stream, read only by its column chain (so none without columns: the lane's
@@ -2617,7 +2532,7 @@ struct SdcStep {
   // then gamma, G phi and the right-hand side as in the direct chain
   int lagged(int s, int q, int qb) {
     int rc;
-    if ((rc = front(s, q, true))) return rc;
+    if ((rc = front(s, q))) return rc;
     const hipStream_t main = c->stream, ls = c->lus[0];
     if (cols) {
       HIPCHK(hipEventRecord(c->sdc_ev, main));
@@ -2698,9 +2613,9 @@ struct SdcStep {
     return sdc_col_rhs(c, ysn(q), F[q].aux, kout);
   }
   int sweep(int s0) {
-    static_assert(SDC_NODES == 2 * BLU_GMAX, "a sweep is factored in two groups");
+    static_assert(SDC_NODES == 2 * GJ_GMAX, "a sweep is factored in two groups");
     int rc;
-    const int G = BLU_GMAX;
+    const int G = GJ_GMAX;
     const hipStream_t main = c->stream, ls = c->lus[0];
     // the second group first, so that its LU runs beside the first group's work
     // Without columns, the sweeps after the first solve each node on the factors the
@@ -2708,7 +2623,7 @@ struct SdcStep {
     // Picard corrections), refined to the 2^-43 test; no LU
     if (!cols && lag && s0 > SDC_FIRST_SWEEP) {
       for (int m = G; m < SDC_NODES; ++m)
-        if ((rc = front(s0 + m, m, true))) return rc;
+        if ((rc = front(s0 + m, m))) return rc;
       HIPCHK(hipEventRecord(c->sdc_ev, main));
       HIPCHK(hipStreamWaitEvent(ls, c->sdc_ev, 0));
       c->stream = ls;
@@ -2717,7 +2632,7 @@ struct SdcStep {
       if (rc) return rc;
       HIPCHK(hipEventRecord(c->sdc_ev, ls));
       for (int m = 0; m < G; ++m) {
-        if ((rc = front(s0 + m, m, true))) return rc;
+        if ((rc = front(s0 + m, m))) return rc;
         if ((rc = lagged_base(s0 + m, m, m, bm))) return rc;
       }
       HIPCHK(hipStreamWaitEvent(main, c->sdc_ev, 0));
@@ -3075,10 +2990,10 @@ static DdLane dd_sweep_lane(ww_ctx* c, int m, double** yh, double** yl) {
   double* b = c->sdd_lane + (size_t)m * (4 * nn + 12 * nm);
   *yh = b + 4 * nn + 8 * nm;
   *yl = *yh + 2 * nm;
-  const bool second = m >= BLU_GMAX;   // the second group's workspace
+  const bool second = m >= GJ_GMAX;   // the second group's workspace
   return DdLane{b + 4 * nn, b + 4 * nn + 4 * nm,   b,
                 b + nn,     b + 2 * nn,            b + 3 * nn,
-                dd_fac(c, pipe_set(c, m, false)), second ? c->sdd_w2 : c->dd_w, second ? c->sdd_part2 : c->dd_part};
+                dd_fac(c, pipe_set(c, m)), second ? c->sdd_w2 : c->dd_w, second ? c->sdd_part2 : c->dd_part};
 }
 
 // The nodes of one correction sweep (stages s0 .. s0 + SDC_NODES - 1) read only slopes of
@@ -3089,9 +3004,9 @@ static DdLane dd_sweep_lane(ww_ctx* c, int m, double** yh, double** yl) {
 // The kernels per lane are those of the stage-by-stage form: the same bits.
 static int dd_sweep(ww_ctx* c, int s0, double tau, double g,
                     const std::function<int(int, double*, double*)>& combine) {
-  static_assert(SDC_NODES == 2 * BLU_GMAX, "a sweep is factored in two groups");
+  static_assert(SDC_NODES == 2 * GJ_GMAX, "a sweep is factored in two groups");
   int rc;
-  const int G = BLU_GMAX;
+  const int G = GJ_GMAX;
   const size_t n2 = (size_t)2 * c->N;
   DdLane L[SDC_NODES];
   double *yh[SDC_NODES], *yl[SDC_NODES];
@@ -3102,7 +3017,7 @@ static int dd_sweep(ww_ctx* c, int s0, double tau, double g,
     return dd_prep_assemble(c, L[m], yh[m], yl[m], c->status);
   };
   auto lu = [&](int m0) -> int {
-    Fac F[BLU_GMAX];
+    Fac F[GJ_GMAX];
     for (int q = 0; q < G; ++q) F[q] = L[m0 + q].F;
     return enqueue_lu_group(c, F, G);
   };
@@ -3373,7 +3288,7 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
   const int nseg = (nsteps + C - 1) / C;
   // buffers: checkpoints, per-stage factor sets of one segment, adjoint work vectors
   const size_t n2 = (size_t)2 * N;
-  const size_t slot = (size_t)3 * Np * Np + (size_t)3 * N;   // X, Z, Gm, saux
+  const size_t slot = (size_t)2 * Np * Np + (size_t)3 * N;   // inverse, Gm, saux
   const size_t nslot = (size_t)C * nst;
   if (c->ckpt_cap < (size_t)(nseg + 1) * n2) {
     if (c->ckpt) HIPCHK(hipFree(c->ckpt));
@@ -3399,7 +3314,7 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
       c->seg_perm_cap = nslot * c->np_max;
     }
   }
-  if (!c->adj) HIPCHK(hipMalloc(&c->adj, (size_t)(20 * 2 * c->n_max + 9 * c->np_max) * 8));
+  if (!c->adj) HIPCHK(hipMalloc(&c->adj, (size_t)(20 * 2 * c->n_max + 8 * c->np_max) * 8));
   double* lam = c->adj;
   double* mu = lam + 2 * c->n_max;
   double* ups = mu + 2 * c->n_max;                 // 16 x 2N
@@ -3410,22 +3325,20 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
   double* qv = e1 + c->np_max;
   double* g2 = qv + c->np_max;
   double* zeta = g2 + c->np_max;
-  double* y1 = zeta + c->np_max;
-  double* y2 = y1 + c->np_max;
+  double* y2 = zeta + c->np_max;
   double* rv = y2 + c->np_max;       // r (N)
   double* dv = rv + c->n_max;        // drdT (N)
   double* y2p = dv + c->n_max;       // P^T y2 (Np), pivoted factors
   auto slot_fac = [&](size_t k) {
     double* b = c->seg + k * slot;
-    Fac F = fac_set(c, 0, false);
-    F.Gm = b + 2 * (size_t)Np * Np;
-    F.X = b;
-    F.Z = b + (size_t)Np * Np;
+    Fac F = fac_set(c, 0);
+    F.Mi = b;
+    F.Gmr = b + (size_t)Np * Np;
     F.use32 = false;
     F.perm = pivoted(c) ? c->seg_perm + k * c->np_max : nullptr;
     return F;
   };
-  auto slot_aux = [&](size_t k) { return c->seg + k * slot + (size_t)3 * Np * Np; };
+  auto slot_aux = [&](size_t k) { return c->seg + k * slot + (size_t)2 * Np * Np; };
   // step coefficients
   double coef[COEF_SIZE];
   std::memset(coef, 0, sizeof(coef));
@@ -3445,7 +3358,7 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
     LAUNCHCHK();
   }
   // 1. forward base march with checkpoints (FP64 factors)
-  Fac F0 = fac_set(c, 0, false);
+  Fac F0 = fac_set(c, 0);
   F0.use32 = false;
   auto base_step = [&](const Fac* per_stage_base, size_t slot0) -> int {
     for (int s = 0; s < nst; ++s) {
@@ -3498,16 +3411,13 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
         hipLaunchKernelGGL(k_adj_pre, dim3(1), dim3(WW_NT), fft_lds_bytes(N, 4), c->stream, mu, ups, ustride, c->coef,
                            s, nst, sa, c->tw, c->sig, N, Np, g, tau, gt, hd, e1, qv);
         LAUNCHCHK();
-        const int gblk = (Np * 64 + WW_NT - 1) / WW_NT;
-        hipLaunchKernelGGL(k_gemv_t, dim3(gblk), dim3(WW_NT), 0, c->stream, F.Gm, Np, 0, gt, nullptr, g2);
+        hipLaunchKernelGGL(k_gemv_tr, dim3(Np / 16), dim3(GTV_NT), 0, c->stream, F.Gmr, Np, gt, g2);
         LAUNCHCHK();
         hipLaunchKernelGGL(k_adj_mid, dim3(1), dim3(WW_NT), fft_lds_bytes(N, 3), c->stream, g2, hd, c->tw, N, Np, zeta);
         LAUNCHCHK();
-        hipLaunchKernelGGL(k_gemv_t, dim3(gblk), dim3(WW_NT), 0, c->stream, F.Z, Np, 2, zeta, nullptr, y1);
+        hipLaunchKernelGGL(k_gemv_tr, dim3(Np / 16), dim3(GTV_NT), 0, c->stream, F.Mi, Np, zeta, y2);
         LAUNCHCHK();
-        hipLaunchKernelGGL(k_gemv_t, dim3(gblk), dim3(WW_NT), 0, c->stream, F.X, Np, 1, y1, y1, y2);
-        LAUNCHCHK();
-        const double* yt = y2;   // A^{-T} zeta; with P A = Lt Ut it is P^T (Lt Ut)^{-T} zeta
+        const double* yt = y2;   // A^{-T} zeta; with the inverse of P A it is P^T (P A)^{-T} zeta
         if (F.perm) {
           hipLaunchKernelGGL(k_permute_rows, dim3((Np + 255) / 256), dim3(256), 0, c->stream, y2, y2p, F.perm, Np, 1,
                              1);

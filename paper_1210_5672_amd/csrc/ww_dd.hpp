@@ -221,7 +221,7 @@ __global__ __launch_bounds__(WW_NT) void k_dd_prep(const double* __restrict__ eh
 // -------------------------------------------------------------------------------------
 // Assembly in double-double (eq. (K1K2), the same formulas as k_assemble): A = I/2 +
 // K/N and Gm = G/N, column-major Np x Np, hi and lo planes; Af receives the leading
-// part of A for the FP64 factorisation.  cos, sin (of 2 pi d/N) and cot(pi d/N)/2 come
+// part of A, row-major, for the FP64 elimination.  cos, sin (of 2 pi d/N) and cot(pi d/N)/2 come
 // from double-double circulant tables (d = (i - j) mod N).  N is a power of two, so the
 // scaling by 1/N is exact.  One strip of 64 rows x 16 columns per workgroup.
 // -------------------------------------------------------------------------------------
@@ -233,6 +233,7 @@ __global__ __launch_bounds__(WW_NT) void k_dd_assemble(const double* __restrict_
                                                        double* __restrict__ G_hi, double* __restrict__ G_lo,
                                                        double* __restrict__ Af) {
   constexpr int CW = 16;
+  __shared__ double rt[WW_TB][CW + 1];   // the strip of A for the row-major copy
   const int i0 = blockIdx.x * WW_TB, j0 = blockIdx.y * CW;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int i = i0 + tx;
@@ -293,7 +294,12 @@ __global__ __launch_bounds__(WW_NT) void k_dd_assemble(const double* __restrict_
     A_lo[o] = a.lo;
     G_hi[o] = gm.hi;
     G_lo[o] = gm.lo;
-    Af[o] = a.hi;
+    rt[tx][jj] = a.hi;
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < WW_TB * CW; idx += WW_NT) {
+    const int r = idx / CW, cc = idx % CW;
+    Af[(size_t)(i0 + r) * Np + j0 + cc] = rt[r][cc];
   }
 }
 

@@ -259,8 +259,8 @@ __device__ __forceinline__ void gemv_row_wave(const T* __restrict__ Mr, int Np, 
 //   D = cot((zeta_i - conj zeta_j)/2), K -= Im{conj(zeta'_j) D}/2, G -= Re{zeta'_i D}/2
 // with zeta' = 1 + i eta_x, zeta'' = i eta_xx.  The image terms enter with a minus
 // sign (the bracket of eq. (Phi) / (plemelj:1)-(plemelj:2)).
-// One strip of 64 rows x 16 columns per workgroup; thread (tx, ty) owns row tx and
-// columns ty + 4m.
+// The matrices are written row-major: thread (tx, ty) owns column tx of the strip and the
+// rows ty + 4 m, so that every store is 64 consecutive doubles of a row.
 // -------------------------------------------------------------------------------------
 __device__ __forceinline__ void cot_half_branch(double cx, double sx, double chy, double shy,
                                                 double& re, double& im) {
@@ -276,20 +276,20 @@ __device__ __forceinline__ void cot_half_branch(double cx, double sx, double chy
   }
 }
 
-// Launch: grid (Np / 64, Np / ASM_CW): one workgroup per strip of 64 rows x ASM_CW
+// Launch: grid (Np / 64, Np / ASM_CW): one workgroup per strip of ASM_CW rows x 64
 // columns, several workgroups per 64-tile, so that enough waves are resident to hide
 // the latency of the dependent FP64 chains (divisions of the cot branch formula).
 // With a lagged inverse (Mx64 or Mx32, row-major), 16 more rows of workgroups follow
 // the assembly grid: they form x0 = Mx psi (the first solve of the lagged-factor base
 // chain, which does not need this stage's matrix), one wave per row.
-// ASM_CW: columns per assembly workgroup (16 or 32)
+// Writes A (row-major FP64: what the FP64 elimination starts from and what residuals
+// multiply by), A32 (its FP32 copy, or null) and Gmr (row-major Gm).
 template <int ASM_CW>
 __global__ __launch_bounds__(WW_NT) void k_assemble(
     const double* __restrict__ aux, int nmax, const double* __restrict__ cosT,
     const double* __restrict__ sinT, const double* __restrict__ c0T, double* __restrict__ A,
-    double* __restrict__ Gm, float* __restrict__ A32, double* __restrict__ Gmr, double* __restrict__ Ar, int N,
-    int Np, int finite, const double* __restrict__ Mx64, const float* __restrict__ Mx32,
-    const double* __restrict__ psi, double* __restrict__ x0) {
+    float* __restrict__ A32, double* __restrict__ Gmr, int N, int Np, int finite, const double* __restrict__ Mx64,
+    const float* __restrict__ Mx32, const double* __restrict__ psi, double* __restrict__ x0) {
   if (blockIdx.y >= (unsigned)(Np / ASM_CW)) {
     // (uniform per workgroup: no barrier below is reached by these blocks)
     const int g = (blockIdx.y - Np / ASM_CW) * gridDim.x + blockIdx.x;
@@ -301,27 +301,26 @@ __global__ __launch_bounds__(WW_NT) void k_assemble(
       gemv_row_wave<double>(Mx64, Np, 0, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
     return;
   }
-  // stage the per-point quantities of the strip's 64 rows and 16 columns and the 79
-  // circulant table entries d = i - j it touches in LDS
-  __shared__ double rt[WW_TB][ASM_CW + 1];   // the strip of Gm (then A) for the row-major copies
-  __shared__ double rq[4][WW_TB];            // eta_x, eta_xx, exp(s), exp(-s) of rows
-  __shared__ double cq[3][ASM_CW];           // eta_x, exp(s), exp(-s) of columns
+  // stage the per-point quantities of the strip's rows and 64 columns and the circulant
+  // table entries d = i - j it touches in LDS
+  __shared__ double rq[4][ASM_CW];           // eta_x, eta_xx, exp(s), exp(-s) of rows
+  __shared__ double cq[3][WW_TB];            // eta_x, exp(s), exp(-s) of columns
   __shared__ double tb[3][WW_TB + ASM_CW];   // cos, sin, cot/2 of 2 pi d / N, d = i - j
-  const int i0 = blockIdx.x * WW_TB, j0 = blockIdx.y * ASM_CW;
+  const int j0 = blockIdx.x * WW_TB, i0 = blockIdx.y * ASM_CW;
   const int t = threadIdx.x;
   {
-    const int q = t >> 6, r = t & 63;   // 4 x 64 row quantities
-    const int ir = i0 + r;
-    rq[q][r] = (ir < N) ? aux[(q == 0 ? AUX_EX : q == 1 ? AUX_EXX : q == 2 ? AUX_EP : AUX_EM) * nmax + ir] : 0.0;
-    if (q < 3 && r < ASM_CW) {
-      const int jc = j0 + r;
-      cq[q][r] = (jc < N) ? aux[(q == 0 ? AUX_EX : q == 1 ? AUX_EP : AUX_EM) * nmax + jc] : 0.0;
+    const int q = t >> 6, r = t & 63;
+    const int jc = j0 + r;
+    if (q < 3) cq[q][r] = (jc < N) ? aux[(q == 0 ? AUX_EX : q == 1 ? AUX_EP : AUX_EM) * nmax + jc] : 0.0;
+    if (r < ASM_CW) {
+      const int ir = i0 + r;
+      rq[q][r] = (ir < N) ? aux[(q == 0 ? AUX_EX : q == 1 ? AUX_EXX : q == 2 ? AUX_EP : AUX_EM) * nmax + ir] : 0.0;
     }
-    // table entries e = 0..78 <-> d = (i0 - j0 - 15 + e) mod N
+    // table entries e <-> d = (i0 - j0 - 63 + e) mod N
     constexpr int NE = WW_TB + ASM_CW - 1;
     for (int e = t; e < 3 * NE; e += WW_NT) {
       const int which = e / NE, ee = e - which * NE;
-      int d = (i0 - j0 - (ASM_CW - 1) + ee) % N;
+      int d = (i0 - j0 - (WW_TB - 1) + ee) % N;
       if (d < 0) d += N;
       tb[which][ee] = which == 0 ? cosT[d] : which == 1 ? sinT[d] : c0T[d];
     }
@@ -329,19 +328,19 @@ __global__ __launch_bounds__(WW_NT) void k_assemble(
   __syncthreads();
   const int tx = t & 63;
   const int ty = t >> 6;
-  const int i = i0 + tx;
+  const int j = j0 + tx;
   const double invN = 1.0 / (double)N;
-  const double exi = rq[0][tx], exxi = rq[1][tx], epi = rq[2][tx], emi = rq[3][tx];
+  const double exj = cq[0][tx], epj = cq[1][tx], emj = cq[2][tx];
 #pragma unroll
-  for (int jj = ty; jj < ASM_CW; jj += 4) {
-    const int j = j0 + jj;
+  for (int ii = ty; ii < ASM_CW; ii += 4) {
+    const int i = i0 + ii;
     double a, gm;
     if (i >= N || j >= N) {
       a = (i == j) ? 1.0 : 0.0;
       gm = 0.0;
     } else {
-      const double exj = cq[0][jj], epj = cq[1][jj], emj = cq[2][jj];
-      const int e = tx - jj + (ASM_CW - 1);
+      const double exi = rq[0][ii], exxi = rq[1][ii], epi = rq[2][ii], emi = rq[3][ii];
+      const int e = ii - tx + (WW_TB - 1);
       const double cx = tb[0][e], sx = tb[1][e];
       double Kv, Gv;
       if (i != j) {
@@ -367,85 +366,17 @@ __global__ __launch_bounds__(WW_NT) void k_assemble(
       a = Kv * invN + (i == j ? 0.5 : 0.0);
       gm = Gv * invN;
     }
-    const size_t o = (size_t)j * Np + i;
+    const size_t o = (size_t)i * Np + j;
     A[o] = a;
-    if (Gm) Gm[o] = gm;
     if (A32) A32[o] = (float)a;
-    rt[tx][jj] = gm;
-  }
-  // row-major copies (Gmr always, Ar when given): 16 contiguous doubles per row
-  __syncthreads();
-  for (int idx = t; idx < WW_TB * ASM_CW; idx += WW_NT) {
-    const int r = idx / ASM_CW, cc = idx % ASM_CW;
-    Gmr[(size_t)(i0 + r) * Np + j0 + cc] = rt[r][cc];
-  }
-  if (!Ar) return;
-  __syncthreads();
-  for (int jj = ty; jj < ASM_CW; jj += 4) rt[tx][jj] = A[(size_t)(j0 + jj) * Np + i];
-  __syncthreads();
-  for (int idx = t; idx < WW_TB * ASM_CW; idx += WW_NT) {
-    const int r = idx / ASM_CW, cc = idx % ASM_CW;
-    Ar[(size_t)(i0 + r) * Np + j0 + cc] = rt[r][cc];
+    Gmr[o] = gm;
   }
 }
 
 // -------------------------------------------------------------------------------------
-// 64 x 64 tile routines, templated on the element type T (double: FP64 path; float:
-// the factorisation of the mixed-precision path).  LDS tiles are row-major with a pad
-// column: T[r * TLD + c].  Every routine is called by all WW_NT = 256 threads.
-// -------------------------------------------------------------------------------------
-#define TLD 65
-#define TILE_DBL (64 * TLD)
-
-// global (column-major, ld, element type S) -> LDS tile of T; ncol valid columns, the
-// rest zero; all 16 loads of a thread are issued before the stores
-template <typename T, typename S>
-__device__ inline void tile_load(T* Ts, const S* __restrict__ G, size_t ld, int ncol = 64) {
-  S v[16];
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    const int c = idx >> 6;
-    v[m] = (c < ncol) ? G[(size_t)c * ld + (idx & 63)] : S(0);
-  }
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    Ts[(idx & 63) * TLD + (idx >> 6)] = (T)v[m];
-  }
-}
-template <typename T>
-__device__ inline void rhs_tile_load(T* Ts, const double* __restrict__ G, size_t ld, int ncol) {
-  tile_load<T, double>(Ts, G, ld, ncol);
-}
-template <typename T, typename S>
-__device__ inline void tile_store(const T* Ts, S* __restrict__ G, size_t ld, int ncol = 64, T scale = T(1)) {
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    const int c = idx >> 6;
-    if (c < ncol) G[(size_t)c * ld + (idx & 63)] = (S)(scale * Ts[(idx & 63) * TLD + c]);
-  }
-}
-
-// LDS tile -> row-major global copy (the row-major matrix pointer already offset to the
-// tile), coalesced along the rows
-template <typename T>
-__device__ inline void tile_store_rm(const T* Ts, T* __restrict__ G, size_t ld, T scale = T(1)) {
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    const int r = idx >> 6, c = idx & 63;
-    G[(size_t)r * ld + c] = scale * Ts[r * TLD + c];
-  }
-}
-
-// -------------------------------------------------------------------------------------
-// MFMA 64 x 64 x 64 product of two LDS tiles: acc = As * Bs (accumulating).
-// Wave w computes the 32 x 32 quadrant (w >> 1, w & 1) as 2 x 2 blocks of 16 x 16 x 4
-// MFMAs (v_mfma_f64_16x16x4f64 / v_mfma_f32_16x16x4f32).  Operand layout (lane l):
-// A[row l%16][k l/16], B[k l/16][col l%16].  Result lane l holds column l%16 and rows
-// 4 i + l/16 (f64) or 4 (l/16) + i (f32), i = 0..3.
+// Matrix instructions v_mfma_f64_16x16x4f64 / v_mfma_f32_16x16x4f32.  Operand layout (lane
+// l): A[row l%16][k l/16], B[k l/16][col l%16].  Result lane l holds column l%16 and rows
+// row(i, l/16), i = 0..3: 4 i + l/16 (f64) or 4 (l/16) + i (f32).
 // -------------------------------------------------------------------------------------
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef float flt4 __attribute__((ext_vector_type(4)));
@@ -456,828 +387,66 @@ template <> struct Mfma<double> {
   static __device__ __forceinline__ V step(double a, double b, V c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ int row(int i, int rq) { return 4 * i + rq; }
+  // row(i, rq) = rowc(i) + rowl(rq): the part common to the wave and the lane's
+  static __device__ __forceinline__ int rowc(int i) { return 4 * i; }
+  static __device__ __forceinline__ int rowl(int rq) { return rq; }
+  static __device__ __forceinline__ int row(int i, int rq) { return rowc(i) + rowl(rq); }
   // element index and lane group (lane >> 4) of the result entries in row p
-  static __device__ __forceinline__ int row_elem(int p) { return p >> 2; }
-  static __device__ __forceinline__ int row_grp(int p) { return p & 3; }
+  static constexpr int row_elem(int p) { return p >> 2; }
+  static constexpr int row_grp(int p) { return p & 3; }
 };
 template <> struct Mfma<float> {
   typedef flt4 V;
   static __device__ __forceinline__ V step(float a, float b, V c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ int row(int i, int rq) { return 4 * rq + i; }
-  static __device__ __forceinline__ int row_elem(int p) { return p & 3; }
-  static __device__ __forceinline__ int row_grp(int p) { return p >> 2; }
+  static __device__ __forceinline__ int rowc(int i) { return i; }
+  static __device__ __forceinline__ int rowl(int rq) { return 4 * rq; }
+  static __device__ __forceinline__ int row(int i, int rq) { return rowc(i) + rowl(rq); }
+  static constexpr int row_elem(int p) { return p & 3; }
+  static constexpr int row_grp(int p) { return p >> 2; }
 };
 
-template <typename T>
-struct Acc64 {
-  typename Mfma<T>::V v[2][2];
-};
-
-template <typename T>
-__device__ inline void acc_zero(Acc64<T>& acc) {
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) acc.v[a][b] = typename Mfma<T>::V{T(0), T(0), T(0), T(0)};
-}
-
-// The operands of a wave are read from LDS a quarter of the inner dimension at a time,
-// all reads of a quarter issued before its MFMAs, so that the MFMAs run back to back
-// instead of each waiting for its own LDS read.
-template <typename T>
-__device__ inline void mfma_tile(const T* As, const T* Bs, Acc64<T>& acc) {
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int r0 = (w >> 1) * 32, c0 = (w & 1) * 32;
-  const int li = lane & 15, lk = lane >> 4;
-#pragma unroll
-  for (int h = 0; h < 64; h += 16) {
-    T a0[4], a1[4], b0[4], b1[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = h + 4 * q;
-      a0[q] = As[(r0 + li) * TLD + k + lk];
-      a1[q] = As[(r0 + 16 + li) * TLD + k + lk];
-      b0[q] = Bs[(k + lk) * TLD + c0 + li];
-      b1[q] = Bs[(k + lk) * TLD + c0 + 16 + li];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc.v[0][0] = Mfma<T>::step(a0[q], b0[q], acc.v[0][0]);
-      acc.v[0][1] = Mfma<T>::step(a0[q], b1[q], acc.v[0][1]);
-      acc.v[1][0] = Mfma<T>::step(a1[q], b0[q], acc.v[1][0]);
-      acc.v[1][1] = Mfma<T>::step(a1[q], b1[q], acc.v[1][1]);
-    }
-  }
-}
-
-// acc into an LDS tile: T = s * acc (mode 0) or T += s * acc (mode 1)
-template <typename T>
-__device__ inline void acc_to_lds(const Acc64<T>& acc, T* Ts, int mode, T s) {
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int r0 = (w >> 1) * 32, c0 = (w & 1) * 32;
-  const int col = lane & 15, rq = lane >> 4;
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rr = r0 + 16 * a + Mfma<T>::row(i, rq);
-        const int cc = c0 + 16 * b + col;
-        if (mode == 0) Ts[rr * TLD + cc] = s * acc.v[a][b][i];
-        else Ts[rr * TLD + cc] += s * acc.v[a][b][i];
-      }
-}
-
-// The same product with the operands' roles swapped (the MFMA computes (A B)^T), which
-// leaves the result in the column layout: lane (cl = lane & 15, rq = lane >> 4) of wave w
-// holds in acc.v[a][b][i] the entry (r0 + 16 a + cl, c0 + 16 b + Mfma<T>::row(i, rq)),
-// r0 = 32 (w >> 1), c0 = 32 (w & 1).  In that layout the 16 lanes of a row group hold 16
-// consecutive rows of one column, so a column-major tile is read and written straight
-// from and to the accumulators, 128-byte segments per row group.
-template <typename T>
-__device__ inline void mfma_tile_t(const T* As, const T* Bs, Acc64<T>& acc) {
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int r0 = (w >> 1) * 32, c0 = (w & 1) * 32;
-  const int li = lane & 15, lk = lane >> 4;
-#pragma unroll
-  for (int h = 0; h < 64; h += 16) {
-    T a0[4], a1[4], b0[4], b1[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = h + 4 * q;
-      a0[q] = As[(r0 + li) * TLD + k + lk];
-      a1[q] = As[(r0 + 16 + li) * TLD + k + lk];
-      b0[q] = Bs[(k + lk) * TLD + c0 + li];
-      b1[q] = Bs[(k + lk) * TLD + c0 + 16 + li];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc.v[0][0] = Mfma<T>::step(b0[q], a0[q], acc.v[0][0]);
-      acc.v[0][1] = Mfma<T>::step(b1[q], a0[q], acc.v[0][1]);
-      acc.v[1][0] = Mfma<T>::step(b0[q], a1[q], acc.v[1][0]);
-      acc.v[1][1] = Mfma<T>::step(b1[q], a1[q], acc.v[1][1]);
-    }
-  }
-}
-
-// column-major 64 x 64 global tile (leading dimension ld) <-> column-layout accumulators
-template <typename T>
-__device__ inline void acc_load_cm(Acc64<T>& acc, const T* __restrict__ G, size_t ld) {
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int r0 = (w >> 1) * 32, c0 = (w & 1) * 32;
-  const int cl = lane & 15, rq = lane >> 4;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        acc.v[a][b][i] = G[(size_t)(c0 + 16 * b + Mfma<T>::row(i, rq)) * ld + r0 + 16 * a + cl];
-}
-template <typename T>
-__device__ inline void acc_store_cm(const Acc64<T>& acc, T* __restrict__ G, size_t ld) {
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int r0 = (w >> 1) * 32, c0 = (w & 1) * 32;
-  const int cl = lane & 15, rq = lane >> 4;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        G[(size_t)(c0 + 16 * b + Mfma<T>::row(i, rq)) * ld + r0 + 16 * a + cl] = acc.v[a][b][i];
-}
-// column-layout accumulators into an LDS tile: T = acc
-template <typename T>
-__device__ inline void acc_t_to_lds(const Acc64<T>& acc, T* Ts) {
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int r0 = (w >> 1) * 32, c0 = (w & 1) * 32;
-  const int cl = lane & 15, rq = lane >> 4;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) Ts[(r0 + 16 * a + cl) * TLD + c0 + 16 * b + Mfma<T>::row(i, rq)] = acc.v[a][b][i];
-}
-
-// -------------------------------------------------------------------------------------
-// In-place Gauss-Jordan inverse of the 64 x 64 LDS tile, without pivoting.  Thread
-// (tr = tid & 15, tc = tid >> 4) keeps the 4 x 4 block of rows 4tr.., columns 4tc.. in
-// registers.  For pivot p every entry follows one rule,  a_rc <- a_rc - kap_r rho_c,
-//   rho_c = a_pc / a_pp (c != p),  rho_p = 1 + 1/a_pp,
-//   kap_r = a_rp (r != p),         kap_p = a_pp - 1,
-// which yields A_QQ - a_Qp a_pQ / a_pp, a_pQ / a_pp, -a_Qp / a_pp and 1/a_pp on the four
-// parts.  The pivot row and column are published in LDS (double-buffered, one barrier
-// per pivot).  1/a_pp: hardware reciprocal refined by Newton steps.  `pub` is LDS
-// scratch of 256 elements.  Returns the smallest |pivot|.
-// -------------------------------------------------------------------------------------
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-__device__ __forceinline__ float recip(float x) {
-  float r = __builtin_amdgcn_rcpf(x);
-  float e = fmaf(-x, r, 1.0f);
-  return fmaf(r, e, r);
-}
-
-template <typename T>
-__device__ inline double lds_gj_inverse(T* Ts, T* pub) {
-  const int tr = threadIdx.x & 15, tc = threadIdx.x >> 4;
-  const int R0 = 4 * tr, C0 = 4 * tc;
-  T v[4][4];
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[i][j] = Ts[(R0 + i) * TLD + C0 + j];
-  T minpiv = T(1e30);
-  for (int pb = 0; pb < 16; ++pb) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int p = 4 * pb + q;
-      T* prow = pub + (q & 1) * 128;
-      T* pcol = prow + 64;
-      if (tr == pb) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) prow[C0 + j] = v[q][j];
-      }
-      if (tc == pb) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pcol[R0 + i] = v[i][q];
-      }
-      __syncthreads();
-      const T piv = prow[p];
-      minpiv = fmin(minpiv, fabs(piv));
-      const T ip = recip(piv);
-      T rho[4], kap[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rho[j] = prow[C0 + j] * ip;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) kap[i] = pcol[R0 + i];
-      if (tc == pb) rho[q] = T(1) + ip;
-      if (tr == pb) kap[q] = piv - T(1);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[i][j] = fma(-kap[i], rho[j], v[i][j]);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) Ts[(R0 + i) * TLD + C0 + j] = v[i][j];
-  __syncthreads();
-  return (double)minpiv;
-}
-
-// -------------------------------------------------------------------------------------
-// In-place inverse of the 64 x 64 LDS tile by Gauss-Jordan over 16 x 16 blocks, without
-// pivoting (the rule above, applied to blocks).  Wave w keeps row band w (rows 16w ..
-// 16w + 15) in registers as four 16 x 16 blocks in the MFMA result layout.  Block step P:
-// wave P inverts its diagonal block in registers (the scalar rule across the wave's
-// lanes: the pivot entry by a lane read, pivot row and column by lane shuffles, no
-// workgroup barrier), replaces its other blocks by D B_PJ (D = B_PP^-1) and publishes
-// the band; after one barrier every other wave updates B_wJ <- B_wJ - B_wP (D B_PJ) and
-// B_wP <- -B_wP D, all 16 x 16 x 16 MFMA products.  The pivots are those of the scalar
-// elimination.  `scr`: LDS scratch of GJ_SCR elements; it may start at Ts (each wave
-// keeps its rows in registers in between).  Returns the smallest |pivot|.
-// -------------------------------------------------------------------------------------
-#define GJ_SLD 65
-#define GJ_BAND (16 * GJ_SLD)
-#define GJ_SCR (6 * GJ_BAND + 8)
-static_assert(GJ_SCR <= 2 * TILE_DBL, "the inverse scratch must fit in two LDS tiles");
-
-__device__ __forceinline__ double lane_read(double x, int lane) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u & 0xffffffffull), lane);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ float lane_read(float x, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
-}
-
-// Broadcast of lane n of each 16-lane row to the whole row (DPP row_newbcast on the
-// 64-bit move of CDNA3/4; a float travels in the low half).  n must fold to a
-// constant (unrolled loops): the switch then reduces to one move.
+// Broadcast of lane n of each 16-lane row to the whole row (DPP row_newbcast).  n must
+// fold to a constant (unrolled loops): the switch then reduces to one move.
 template <int CTRL>
-__device__ __forceinline__ long long dpp64(long long v) {
-  return __builtin_amdgcn_update_dpp(0LL, v, CTRL, 0xf, 0xf, false);
+__device__ __forceinline__ double dpp_bcast(double v) {
+  return __longlong_as_double((long long)__builtin_amdgcn_update_dpp(0LL, __double_as_longlong(v), CTRL, 0xf, 0xf,
+                                                                     true));
 }
-__device__ __forceinline__ long long bits64(double v) { return __double_as_longlong(v); }
-__device__ __forceinline__ long long bits64(float v) { return (long long)(unsigned)__float_as_int(v); }
-__device__ __forceinline__ void from_bits64(long long u, double& v) { v = __longlong_as_double(u); }
-__device__ __forceinline__ void from_bits64(long long u, float& v) { v = __int_as_float((int)(unsigned)u); }
+template <int CTRL>
+__device__ __forceinline__ float dpp_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
 template <typename T>
 __device__ __forceinline__ T row_bcast(T v, int n) {
-  const long long u = bits64(v);
-  long long r;
   switch (n & 15) {
-    case 0: r = dpp64<0x150>(u); break;
-    case 1: r = dpp64<0x151>(u); break;
-    case 2: r = dpp64<0x152>(u); break;
-    case 3: r = dpp64<0x153>(u); break;
-    case 4: r = dpp64<0x154>(u); break;
-    case 5: r = dpp64<0x155>(u); break;
-    case 6: r = dpp64<0x156>(u); break;
-    case 7: r = dpp64<0x157>(u); break;
-    case 8: r = dpp64<0x158>(u); break;
-    case 9: r = dpp64<0x159>(u); break;
-    case 10: r = dpp64<0x15a>(u); break;
-    case 11: r = dpp64<0x15b>(u); break;
-    case 12: r = dpp64<0x15c>(u); break;
-    case 13: r = dpp64<0x15d>(u); break;
-    case 14: r = dpp64<0x15e>(u); break;
-    default: r = dpp64<0x15f>(u); break;
-  }
-  T out;
-  from_bits64(r, out);
-  return out;
-}
-
-// Gauss-Jordan inverse of one 16 x 16 block held by a whole wave in the MFMA result
-// layout (lane: column lane & 15, rows Mfma<T>::row(i, lane >> 4)).  The pivot column
-// entries a lane needs sit in lane p of its own 16-lane row (row broadcasts); the
-// pivot row entry sits in another row (one lane shuffle); the pivot by a lane read.
-template <typename T>
-__device__ __forceinline__ void leaf_gj16(typename Mfma<T>::V& x, T& minpiv) {
-  const int lane = threadIdx.x & 63;
-  const int cl = lane & 15, rq = lane >> 4;
-#pragma unroll
-  for (int p = 0; p < 16; ++p) {
-    const int pe = Mfma<T>::row_elem(p), pg = Mfma<T>::row_grp(p);
-    const T piv = lane_read(x[pe], pg * 16 + p);     // a_pp
-    const T rsrc = __shfl(x[pe], pg * 16 + cl);      // a_p,cl
-    T ksrc[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ksrc[i] = row_bcast(x[i], p);   // a_row(i),p
-    minpiv = fmin(minpiv, fabs(piv));
-    const T ip = recip(piv);
-    const T rho = (cl == p) ? T(1) + ip : rsrc * ip;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const T kap = (Mfma<T>::row(i, rq) == p) ? piv - T(1) : ksrc[i];
-      x[i] = fma(-kap, rho, x[i]);
-    }
-  }
-}
-
-// The step loop stays rolled (one copy of the leaf code); blocks of the band are only
-// addressed with compile-time indices under uniform branches on P (a select on P
-// would be turned into a dynamically indexed private array).
-template <typename T>
-__device__ __forceinline__ double blk_gj_inverse(T* Ts, T* scr) {
-  typedef typename Mfma<T>::V V;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int cl = lane & 15, rq = lane >> 4;
-  T* stg = scr + w * GJ_BAND;       // this wave's staging band
-  T* pubs = scr + 4 * GJ_BAND;      // two published bands (by step parity)
-  T* red = scr + 6 * GJ_BAND;       // smallest pivot of each wave's leaf
-  const V zero = V{T(0), T(0), T(0), T(0)};
-  V v[4];
-  __syncthreads();
-#pragma unroll
-  for (int J = 0; J < 4; ++J)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[J][i] = Ts[(16 * w + Mfma<T>::row(i, rq)) * TLD + 16 * J + cl];
-  __syncthreads();   // the tile is in registers: scr may overlay Ts
-  T minpiv = T(1e30);
-#pragma unroll 1
-  for (int P = 0; P < 4; ++P) {
-    T* pub = pubs + (P & 1) * GJ_BAND;
-    if (w == P) {
-      // stage the band, invert the diagonal block (read back from the staging copy)
-      __syncwarp();
-#pragma unroll
-      for (int J = 0; J < 4; ++J)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) stg[Mfma<T>::row(i, rq) * GJ_SLD + 16 * J + cl] = v[J][i];
-      __syncwarp();
-      V x;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = stg[Mfma<T>::row(i, rq) * GJ_SLD + 16 * P + cl];
-      leaf_gj16<T>(x, minpiv);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) stg[Mfma<T>::row(i, rq) * GJ_SLD + 16 * P + cl] = x[i];
-      __syncwarp();
-#pragma unroll
-      for (int J = 0; J < 4; ++J) {
-        if (J == P) {
-          v[J] = x;
-        } else {
-          V acc = zero;
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-            acc = Mfma<T>::step(stg[cl * GJ_SLD + 16 * P + 4 * kk + rq], stg[(4 * kk + rq) * GJ_SLD + 16 * J + cl], acc);
-          v[J] = acc;
-        }
-      }
-#pragma unroll
-      for (int J = 0; J < 4; ++J)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pub[Mfma<T>::row(i, rq) * GJ_SLD + 16 * J + cl] = v[J][i];
-    }
-    __syncthreads();
-    if (w != P) {
-      __syncwarp();
-#pragma unroll
-      for (int J = 0; J < 4; ++J)
-        if (J == P) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) stg[Mfma<T>::row(i, rq) * GJ_SLD + cl] = v[J][i];   // L = B_wP
-        }
-      __syncwarp();
-      T a[4];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) a[kk] = -stg[cl * GJ_SLD + 4 * kk + rq];
-#pragma unroll
-      for (int J = 0; J < 4; ++J) {
-        V acc = (J == P) ? zero : v[J];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) acc = Mfma<T>::step(a[kk], pub[(4 * kk + rq) * GJ_SLD + 16 * J + cl], acc);
-        v[J] = acc;
-      }
-    }
-  }
-  if (lane == 0) red[w] = minpiv;
-  __syncthreads();   // every wave is done with the bands before Ts is rewritten
-#pragma unroll
-  for (int J = 0; J < 4; ++J)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) Ts[(16 * w + Mfma<T>::row(i, rq)) * TLD + 16 * J + cl] = v[J][i];
-  __syncthreads();
-  const T mp = fmin(fmin(red[0], red[1]), fmin(red[2], red[3]));
-  return (double)mp;
-}
-
-// -------------------------------------------------------------------------------------
-// Block LU factorisation (Sec. 3.3: one factorisation of I/2 + K per stage), 64-blocks,
-// no pivoting (A is diagonally dominant; a pivot guard reports violations):
-//   A = Lt Ut,  Lt unit block-lower, Ut block-upper whose diagonal blocks are the
-//   Schur-complement blocks A_kk^(k); D_k = (A_kk^(k))^{-1} by Gauss-Jordan.
-// Step k:  Lt_ik = A_ik D_k (i > k),  A_ij -= Lt_ik A_kj (i, j > k).
-// The block-triangular inverses X = Lt^{-1} and Z = Ut^{-1} are accumulated in the
-// same launches, so every later solve A^{-1} B = Z (B + X B) is two MFMA GEMMs:
-//   X_ij (i > j) = -sum_{m=j}^{i-1} Lt_im X_mj     (rows of X final after step i-1)
-//   Z_kk = D_k,  Z_ik (i < k) = V_ik D_k,  V_ij = -sum_{m=i}^{j-1} Z_im Ut_mj.
-// Launch per step k (one workgroup per 64-tile task):
-//   role 1 (i, j > k):  L = A_ik D_k;  A_ij -= L A_kj;  (i, j) = (k+1, k+1) then
-//                       inverts its updated tile: D_{k+1}
-//   role 2 (i > k, j <= k): L = A_ik D_k;  X_ik = -L (j = k) or X_ij -= L X_kj
-//   role 3 (i <= k, j > k): Z_ik = D_k (i = k) or V_ik D_k (stored when j = k+1);
-//                       the diagonal Z_kk = D_k is stored here (step k), not by the
-//                       workgroup that inverted the block (k_blu_final stores the last)
-//                       V_kj = -D_k A_kj (i = k) or V_ij -= Z_ik A_kj
-// T = double (FP64 path) or float (mixed path: factor of an FP32 copy of A).
-// -------------------------------------------------------------------------------------
-template <typename T>
-struct BluBufs {
-  T* A;      // Np x Np, overwritten by the Schur complements
-  T* X;      // Lt^{-1}, strictly lower blocks (unit diagonal implicit)
-  T* Z;      // Ut^{-1}, upper blocks incl. diagonal
-  T* V;      // accumulators of Z (upper blocks)
-  T* Dinv;   // nb x 4096, D_k column-major
-  T* Xr;     // row-major copies of X and Z (one-vector solves read rows), or null
-  T* Zr;
-  int* status;
-  int Np;
-  double pivguard;
-};
-
-// Several matrices factored by one launch sequence (the lagged-factor march factors
-// consecutive stages together): block b of a launch works on matrix b % count, task
-// b / count, so the critical tasks (the next diagonal block of every matrix) come first.
-#define BLU_GMAX 4
-template <typename T>
-struct BluGroup {
-  BluBufs<T> m[BLU_GMAX];
-  int count;
-  int strip;   // tiles per strip task of a step (1..BLU_STRIP_MAX)
-};
-// Field by field, each a select among kernel-argument values: selecting whole structs
-// makes the compiler copy the argument block into per-lane scratch memory.
-template <typename T>
-__device__ __forceinline__ BluBufs<T> blu_pick(const BluGroup<T>& g, int m) {
-#define BLU_SEL(f) (m == 0 ? g.m[0].f : m == 1 ? g.m[1].f : m == 2 ? g.m[2].f : g.m[3].f)
-  BluBufs<T> b;
-  b.A = BLU_SEL(A);
-  b.X = BLU_SEL(X);
-  b.Z = BLU_SEL(Z);
-  b.V = BLU_SEL(V);
-  b.Dinv = BLU_SEL(Dinv);
-  b.Xr = BLU_SEL(Xr);
-  b.Zr = BLU_SEL(Zr);
-  b.status = BLU_SEL(status);
-  b.Np = BLU_SEL(Np);
-  b.pivguard = BLU_SEL(pivguard);
-#undef BLU_SEL
-  return b;
-}
-
-template <typename T>
-__device__ inline T* tileptr(T* M, int Np, int i, int j) {
-  return M + (size_t)j * WW_TB * Np + (size_t)i * WW_TB;
-}
-
-template <typename T>
-__device__ inline T* rmptr(T* M, int Np, int i, int j) {
-  return M + (size_t)i * WW_TB * Np + (size_t)j * WW_TB;
-}
-
-template <typename T>
-__device__ inline void store_dinv(const T* Ts, T* D) {
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    D[idx] = Ts[(idx & 63) * TLD + (idx >> 6)];
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(WW_NT) void k_blu_init(BluGroup<T> g) {
-  const BluBufs<T> b = blu_pick(g, blockIdx.x);
-  extern __shared__ double sm_raw[];
-  T* sm = reinterpret_cast<T*>(sm_raw);
-  T* Ts = sm;
-  tile_load<T, T>(Ts, b.A, b.Np);
-  const double mp = blk_gj_inverse<T>(Ts, sm + TILE_DBL);
-  if (threadIdx.x == 0 && !(mp >= b.pivguard)) atomicOr(b.status, 1);
-  store_dinv<T>(Ts, b.Dinv);
-  if (b.Np == WW_TB) {   // one block: no step launch stores Z_00
-    tile_store<T, T>(Ts, b.Z, b.Np);
-    if (b.Zr) tile_store_rm<T>(Ts, b.Zr, b.Np);
-  }
-}
-
-// One 64 x 64 column-major tile into registers (thread t holds entries t + 256 m, m =
-// 0..15, of the column-major order), then into an LDS tile; the same thread owns the
-// same entries in tile_put, tile_store and tile_store_sum, so a tile kept in registers
-// can be combined with an LDS tile without a barrier.
-template <typename T>
-__device__ inline void tile_fetch(T (&v)[16], const T* __restrict__ G, size_t ld) {
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    v[m] = G[(size_t)(idx >> 6) * ld + (idx & 63)];
-  }
-}
-template <typename T>
-__device__ inline void tile_put(T* Ts, const T (&v)[16]) {
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    Ts[(idx & 63) * TLD + (idx >> 6)] = v[m];
-  }
-}
-// Ts += v (each thread its own entries)
-template <typename T>
-__device__ inline void tile_add_own(T* Ts, const T (&v)[16]) {
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    Ts[(idx & 63) * TLD + (idx >> 6)] += v[m];
-  }
-}
-// G = Ts + v
-template <typename T>
-__device__ inline void tile_store_sum(const T* Ts, const T (&v)[16], T* __restrict__ G, size_t ld) {
-#pragma unroll
-  for (int m = 0; m < 16; ++m) {
-    const int idx = threadIdx.x + WW_NT * m;
-    G[(size_t)(idx >> 6) * ld + (idx & 63)] = Ts[(idx & 63) * TLD + (idx >> 6)] + v[m];
-  }
-}
-
-// Tasks of step k (per matrix of a group).  Task 0 updates the next diagonal tile
-// (k+1, k+1) and inverts it (the critical path of the factorisation).  Every other task
-// is a strip of at most `strip` tiles of one row i: it forms the row's left factor
-// once (A_ik D_k for i > k; V_ik D_k for i < k; D_k itself for i = k) and applies it to
-// each tile of its strip, so no product is repeated across the tiles of a row.  Row i
-// > k runs over j = k+1 .. nb-1 (role 1: A_ij -= L A_kj; row k+1 without the diagonal
-// tile) and then j = 0 .. k (role 2: X_ik = -L, X_ij -= L X_kj); row i <= k over
-// j = k+1 .. nb-1 (role 3: V_ij -= L A_kj, V_kj = -D_k A_kj; the strip starting at
-// j = k+1 also stores Z_ik = L).
-#define BLU_STRIP_MAX 16
-__host__ __device__ inline int blu_row_len(int nb, int k, int i) {
-  return i > k ? (i == k + 1 ? nb - 1 : nb) : nb - k - 1;
-}
-__host__ __device__ inline int blu_step_tasks(int nb, int k, int strip) {
-  int n = 1;
-  for (int i = 0; i < nb; ++i) n += (blu_row_len(nb, k, i) + strip - 1) / strip;
-  return n;
-}
-
-// Two LDS tiles per workgroup (two workgroups share a CU): S0 holds the negated left
-// factor -L, S1 the right factor R of the current tile.  The tile C being updated goes
-// from global memory straight into the MFMA accumulators (column layout), which then
-// accumulate -L R and are stored straight back: C - L R summed into C in increasing
-// inner index.  The next tile's R and C are in flight during the current product.
-template <typename T>
-__global__ __launch_bounds__(WW_NT) void k_blu_step(BluGroup<T> g, int k) {
-  extern __shared__ double sm_raw[];
-  T* sm = reinterpret_cast<T*>(sm_raw);
-  T* S0 = sm;
-  T* S1 = sm + TILE_DBL;
-  const BluBufs<T> b = blu_pick(g, (int)(blockIdx.x % g.count));
-  const int Np = b.Np, nb = Np / WW_TB;
-  const int nt = nb - k - 1;
-  const T* Dk = b.Dinv + (size_t)k * 4096;
-  int q = blockIdx.x / g.count;
-  Acc64<T> acc;
-  if (q == 0) {
-    // the next diagonal tile: L = A_{k+1,k} D_k, A_{k+1,k+1} -= L A_{k,k+1}, then its
-    // inverse D_{k+1} (the inverse's scratch overlays both slots)
-    T vl[16], vd[16], vr[16];
-    tile_fetch<T>(vl, tileptr(b.A, Np, k + 1, k), Np);
-    tile_fetch<T>(vd, Dk, 64);
-    tile_fetch<T>(vr, tileptr(b.A, Np, k, k + 1), Np);
-    tile_put<T>(S0, vl);
-    tile_put<T>(S1, vd);
-    __syncthreads();
-    acc_zero(acc);
-    mfma_tile(S0, S1, acc);
-    __syncthreads();
-    acc_to_lds(acc, S0, 0, T(-1));   // S0 = -L
-    tile_put<T>(S1, vr);
-    acc_load_cm<T>(acc, tileptr(b.A, Np, k + 1, k + 1), Np);
-    __syncthreads();
-    mfma_tile_t(S0, S1, acc);
-    __syncthreads();
-    acc_t_to_lds(acc, S0);
-    const double mp = blk_gj_inverse<T>(S0, sm);
-    if (threadIdx.x == 0 && !(mp >= b.pivguard)) atomicOr(b.status, 1);
-    store_dinv<T>(S0, b.Dinv + (size_t)(k + 1) * 4096);   // Z_{k+1,k+1} is stored one step later
-    return;
-  }
-  // the strip: row i, positions p0 .. p0 + len - 1 of the row's tile list
-  q -= 1;
-  int i = -1, p0 = 0, len = 0;
-  for (int r = 0; r < nb; ++r) {
-    const int n = blu_row_len(nb, k, r);
-    const int ch = (n + g.strip - 1) / g.strip;
-    if (q < ch) {
-      i = r;
-      p0 = q * g.strip;
-      len = min(g.strip, n - p0);
-      break;
-    }
-    q -= ch;
-  }
-  if (i < 0 || len <= 0) return;
-  const bool low = i > k;      // roles 1 and 2
-  const bool ldiag = i == k;   // role 3 on row k: the left factor is D_k
-  const bool vfirst = ldiag;   // V_kj = -D_k A_kj: nothing to accumulate into
-  // the tile (i, j) of position p
-  auto col_of = [&](int p) {
-    if (!low) return k + 1 + p;
-    const int nrt = (i == k + 1) ? nt - 1 : nt;   // tiles right of column k in this row
-    const int jr0 = (i == k + 1) ? k + 2 : k + 1;
-    return p < nrt ? jr0 + p : p - nrt;
-  };
-  auto dst_of = [&](int j) {
-    return (low && j <= k) ? tileptr(b.X, Np, i, j) : (low ? tileptr(b.A, Np, i, j) : tileptr(b.V, Np, i, j));
-  };
-  // right factor (registers) and current value (accumulator layout) of the tile at
-  // position p; the X_ik = -L position reads nothing
-  auto fetch = [&](int p, T (&vr)[16], Acc64<T>& cn) {
-    const int j = col_of(p);
-    const bool role2 = low && j <= k;
-    if (role2 && j == k) return;
-    tile_fetch<T>(vr, role2 ? tileptr(b.X, Np, k, j) : tileptr(b.A, Np, k, j), Np);
-    if (vfirst)
-      acc_zero(cn);
-    else
-      acc_load_cm<T>(cn, dst_of(j), Np);
-  };
-  T vr[16];
-  Acc64<T> cn;
-  {
-    T vl[16], vd[16];
-    tile_fetch<T>(vl, ldiag ? Dk : (low ? tileptr(b.A, Np, i, k) : tileptr(b.V, Np, i, k)), ldiag ? 64 : Np);
-    if (!ldiag) tile_fetch<T>(vd, Dk, 64);
-    fetch(p0, vr, cn);
-    if (ldiag) {
-#pragma unroll
-      for (int m = 0; m < 16; ++m) vl[m] = -vl[m];
-    }
-    tile_put<T>(S0, vl);
-    if (!ldiag) tile_put<T>(S1, vd);
-    __syncthreads();
-    if (!ldiag) {
-      acc_zero(acc);
-      mfma_tile(S0, S1, acc);
-      __syncthreads();
-      acc_to_lds(acc, S0, 0, T(-1));   // S0 = -L
-    }
-  }
-  if (!low && p0 == 0) {
-    __syncthreads();
-    tile_store<T, T>(S0, tileptr(b.Z, Np, i, k), Np, 64, T(-1));   // Z_ik = L (Z_kk = D_k)
-  }
-  for (int p = p0; p < p0 + len; ++p) {
-    const int j = col_of(p);
-    if (low && j == k) {   // X_ik = -L (final); the last position of its row
-      __syncthreads();
-      tile_store<T, T>(S0, tileptr(b.X, Np, i, k), Np);
-      continue;
-    }
-    __syncthreads();   // S1 is free (every wave is done with the previous product)
-    tile_put<T>(S1, vr);
-    acc = cn;
-    __syncthreads();
-    if (p + 1 < p0 + len) fetch(p + 1, vr, cn);
-    mfma_tile_t(S0, S1, acc);
-    acc_store_cm<T>(acc, dst_of(j), Np);
-  }
-}
-
-// last column block of Z: Z_i,nb-1 = V_i,nb-1 D_nb-1 (i < nb - 1)
-template <typename T>
-__global__ __launch_bounds__(WW_NT) void k_blu_final(BluGroup<T> g) {
-  extern __shared__ double sm_raw[];
-  T* sm = reinterpret_cast<T*>(sm_raw);
-  T* As = sm;
-  T* Bs = sm + TILE_DBL;
-  const BluBufs<T> b = blu_pick(g, (int)(blockIdx.x % g.count));
-  const int Np = b.Np, nb = Np / WW_TB;
-  const int i = blockIdx.x / g.count, k = nb - 1;
-  tile_load<T, T>(As, tileptr(b.V, Np, i, k), Np);
-  tile_load<T, T>(Bs, b.Dinv + (size_t)k * 4096, 64);
-  __syncthreads();
-  if (i == 0) {   // Z of the last diagonal block = D_{nb-1}
-    tile_store<T, T>(Bs, tileptr(b.Z, Np, k, k), Np);
-    if (b.Zr) tile_store_rm<T>(Bs, rmptr(b.Zr, Np, k, k), Np);
-  }
-  Acc64<T> acc;
-  acc_zero(acc);
-  mfma_tile(As, Bs, acc);
-  __syncthreads();
-  acc_to_lds(acc, As, 0, T(1));
-  __syncthreads();
-  tile_store<T, T>(As, tileptr(b.Z, Np, i, k), Np);
-  if (b.Zr) tile_store_rm<T>(As, rmptr(b.Zr, Np, i, k), Np);
-}
-
-// -------------------------------------------------------------------------------------
-// Explicit inverse from the block LU: A^{-1} = Ut^{-1} Lt^{-1} = Z (I + X), written
-// row-major (the one-vector products read it along rows, the column products read
-// row-major tiles), so that every later solve is one product.  Output tile (i, j):
-//   [i <= j] Z_ij + sum_{m = max(i, j+1)}^{nb-1} Z_im X_mj,
-// one tile per task, the sum in increasing m (fixed order).  The next pair of tiles is in
-// flight in registers during the MFMAs of the current one.
-// -------------------------------------------------------------------------------------
-// Matrices of a group (Z, X, Mr of matrix z).
-template <typename T>
-struct MinvGroup {
-  const T* Z[BLU_GMAX];
-  const T* X[BLU_GMAX];
-  T* Mr[BLU_GMAX];
-  float* Mr32[BLU_GMAX];   // optional FP32 row-major copy of the inverse (null: none)
-  int count;
-};
-
-// Tile of rank r in decreasing order of work: level m = max(i, j + 1) holds the 2m
-// tiles (m, 0..m-1) and (0..m-1, m-1) with nb - m products each (m < nb), level nb the
-// nb tiles (0..nb-1, nb-1) with none; level m starts at rank m (m - 1).
-__host__ __device__ inline void minv_tile(int r, int nb, int& i, int& j) {
-  if (r >= nb * (nb - 1)) {
-    i = r - nb * (nb - 1);
-    j = nb - 1;
-    return;
-  }
-  int m = (int)((1.0 + sqrt(1.0 + 4.0 * (double)r)) * 0.5);
-  while (m > 1 && m * (m - 1) > r) --m;
-  while ((m + 1) * m <= r) ++m;
-  const int idx = r - m * (m - 1);
-  if (idx < m) {
-    i = m;
-    j = idx;
-  } else {
-    i = idx - m;
-    j = m - 1;
-  }
-}
-
-// A fixed grid works through the tiles of every matrix of the group, longest sums
-// first, so that the launch occupies a bounded number of compute units: the inverse is
-// not on the critical path of the march (it is first read `lag` stages later) and the
-// units it leaves free serve the latency-bound base chain.
-template <typename T>
-__global__ __launch_bounds__(WW_NT) void k_minv(MinvGroup<T> gr, int Np) {
-  extern __shared__ double sm_raw[];
-  T* sm = reinterpret_cast<T*>(sm_raw);
-  T* As = sm;
-  T* Bs = sm + TILE_DBL;
-  const int nb = Np / WW_TB;
-  const int ntask = nb * nb * gr.count;
-  for (int task = blockIdx.x; task < ntask; task += gridDim.x) {
-    const int z = task % gr.count;
-    int i, j;
-    minv_tile(task / gr.count, nb, i, j);
-    const T* __restrict__ Z = z == 0 ? gr.Z[0] : z == 1 ? gr.Z[1] : z == 2 ? gr.Z[2] : gr.Z[3];
-    const T* __restrict__ X = z == 0 ? gr.X[0] : z == 1 ? gr.X[1] : z == 2 ? gr.X[2] : gr.X[3];
-    T* __restrict__ Mr = z == 0 ? gr.Mr[0] : z == 1 ? gr.Mr[1] : z == 2 ? gr.Mr[2] : gr.Mr[3];
-    float* __restrict__ Mr32 = z == 0 ? gr.Mr32[0] : z == 1 ? gr.Mr32[1] : z == 2 ? gr.Mr32[2] : gr.Mr32[3];
-    const int m0 = max(i, j + 1);
-    Acc64<T> acc;
-    acc_zero(acc);
-    T za[16], xb[16];
-    if (m0 < nb) {
-      tile_fetch<T>(za, tileptr(Z, Np, i, m0), Np);
-      tile_fetch<T>(xb, tileptr(X, Np, m0, j), Np);
-    }
-    for (int m = m0; m < nb; ++m) {
-      __syncthreads();
-      tile_put<T>(As, za);
-      tile_put<T>(Bs, xb);
-      __syncthreads();
-      if (m + 1 < nb) {
-        tile_fetch<T>(za, tileptr(Z, Np, i, m + 1), Np);
-        tile_fetch<T>(xb, tileptr(X, Np, m + 1, j), Np);
-      }
-      mfma_tile(As, Bs, acc);
-    }
-    __syncthreads();
-    if (i <= j) {
-      tile_load<T, T>(As, tileptr(Z, Np, i, j), Np);
-      __syncthreads();
-      acc_to_lds(acc, As, 1, T(1));
-    } else {
-      acc_to_lds(acc, As, 0, T(1));
-    }
-    __syncthreads();
-    tile_store_rm<T>(As, rmptr(Mr, Np, i, j), Np);
-    if (Mr32) {
-      float* G = rmptr(Mr32, Np, i, j);
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        const int idx = threadIdx.x + WW_NT * m;
-        const int r = idx >> 6, c = idx & 63;
-        G[(size_t)r * Np + c] = (float)As[r * TLD + c];
-      }
-    }
+    case 0: return dpp_bcast<0x150>(v);
+    case 1: return dpp_bcast<0x151>(v);
+    case 2: return dpp_bcast<0x152>(v);
+    case 3: return dpp_bcast<0x153>(v);
+    case 4: return dpp_bcast<0x154>(v);
+    case 5: return dpp_bcast<0x155>(v);
+    case 6: return dpp_bcast<0x156>(v);
+    case 7: return dpp_bcast<0x157>(v);
+    case 8: return dpp_bcast<0x158>(v);
+    case 9: return dpp_bcast<0x159>(v);
+    case 10: return dpp_bcast<0x15a>(v);
+    case 11: return dpp_bcast<0x15b>(v);
+    case 12: return dpp_bcast<0x15c>(v);
+    case 13: return dpp_bcast<0x15d>(v);
+    case 14: return dpp_bcast<0x15e>(v);
+    default: return dpp_bcast<0x15f>(v);
   }
 }
 
 // -------------------------------------------------------------------------------------
 // Pivoting fallback.  The paper factors A without discussing pivoting (Sec. 3.3); A is
-// diagonally dominant for the surfaces it treats, and the block LU above runs without
+// diagonally dominant for the surfaces it treats, and the elimination runs without
 // interchanges behind a pivot guard.  When a pivot falls below the guard, Gaussian
 // elimination with partial pivoting (largest magnitude in the column, first row on
-// ties) fixes a row order P; the block LU then factors P A, whose elimination pivots
-// are the partial-pivoting ones, and every solve gathers its right-hand side by P.
+// ties) fixes a row order P; the elimination then runs on P A, whose pivots are the
+// partial-pivoting ones, and every solve gathers its right-hand side by P.
 // Two launches per column of the leading N x N block of W (column-major, ld Np):
 // k_plu_pivot (one workgroup) picks the pivot, interchanges the two rows over all
 // columns, records the interchange in perm ((P A) row i = A row perm[i]) and forms the
@@ -1360,6 +529,22 @@ __global__ __launch_bounds__(256) void k_plu_update(double* __restrict__ W, int 
 
 __global__ void k_iota(int* __restrict__ p, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = i;
+}
+
+// column-major copy of the row-major Np x Np matrix (the elimination's workspace)
+__global__ void k_plu_copy(const double* __restrict__ A, double* __restrict__ W, int Np) {
+  __shared__ double t[32][33];
+  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int r = ty; r < 32; r += 8) t[r][tx] = A[(size_t)(i0 + r) * Np + j0 + tx];
+  __syncthreads();
+  for (int c = ty; c < 32; c += 8) W[(size_t)(j0 + c) * Np + i0 + tx] = t[tx][c];
+}
+// the rows of the row-major Np x Np matrix by perm: dst row i = src row perm[i] (P A)
+__global__ void k_gather_rows(const double* __restrict__ src, double* __restrict__ dst, const int* __restrict__ perm,
+                              int Np) {
+  const size_t i = blockIdx.x, q = perm[i];
+  for (int j = threadIdx.x; j < Np; j += blockDim.x) dst[i * Np + j] = src[q * Np + j];
 }
 
 // rows of an Np x ncols column-major array (ld Np) by perm: gather dst[i] = src[perm[i]]
@@ -2040,7 +1225,7 @@ __global__ void k_check_finite(const double* __restrict__ y, size_t n, int* __re
 //   a = S_F alpha,  b = P S_F beta,  gt = a + v b,
 //   psit = A^{-T} D (H gt / 2 - Gm^T gt) + D(u b),
 //   etat = u D a + u v D b - g b + tau D(w3^{-1} D b) - v psit,   phit = psit.
-// A^{-T} = (Z (I + X))^T = (I + X^T) Z^T with the stored block-triangular inverses.
+// A^{-T} and Gm^T are products with the stored row-major inverse and Gm, transposed.
 // =====================================================================================
 
 // adjoint stage, part 1 (one workgroup):  kappa = wb * mu + sum_{i > s} wa_i upsilon_i
@@ -2166,25 +1351,33 @@ __global__ __launch_bounds__(WW_NT) void k_adj_mid(const double* __restrict__ g2
   for (int t = threadIdx.x; t < Np; t += WW_NT) zeta[t] = (t < N) ? hd[t] - Z[t].x : 0.0;
 }
 
-// y = add + M^T x for one vector (M column-major, ld Np): y_i = sum_j M[j, i] x_j over
-// j in the block range of the mode: 0 all; 1 blk(j) > blk(i) (transpose of the strictly
-// lower X); 2 blk(j) <= blk(i) (transpose of the upper Z).  One wave per output.
-__global__ __launch_bounds__(WW_NT) void k_gemv_t(const double* __restrict__ M, int Np, int mode,
-                                                  const double* __restrict__ x, const double* __restrict__ add,
-                                                  double* __restrict__ y) {
-  const int wave = (blockIdx.x * WW_NT + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (wave >= Np) return;
-  const int i = wave;
-  const int bi = i / WW_TB;
-  int lo = 0, hi = Np;
-  if (mode == 1) lo = (bi + 1) * WW_TB;
-  if (mode == 2) hi = (bi + 1) * WW_TB;
-  const double* col = M + (size_t)i * Np;
-  double s = 0.0;
-  for (int j = lo + lane; j < hi; j += 64) s = fma(col[j], x[j], s);
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if (lane == 0) y[i] = (add ? add[i] : 0.0) + s;
+// y = M^T x for one vector, M row-major Np x Np: a workgroup forms 16 outputs (128 B of
+// every row), each lane a column and every 32nd row from its own, eight loads in flight; the
+// partial sums are added in a fixed order (lane groups, then waves).  Bound by the reads of
+// M; 16 columns per workgroup keep Np / 16 workgroups on the chip.
+#define GTV_NT 512
+__global__ __launch_bounds__(GTV_NT) void k_gemv_tr(const double* __restrict__ M, int Np, const double* __restrict__ x,
+                                                    double* __restrict__ y) {
+  __shared__ double part[GTV_NT / 64][16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = blockIdx.x * 16 + (lane & 15);
+  const int r0 = w * 4 + (lane >> 4);
+  double s0 = 0.0, s1 = 0.0;
+  // Np is a multiple of 64: an even number of 32-row steps
+  for (int j = r0; j < Np; j += 64) {
+    s0 = fma(M[(size_t)j * Np + i], x[j], s0);
+    s1 = fma(M[(size_t)(j + 32) * Np + i], x[j + 32], s1);
+  }
+  double s = s0 + s1;
+  s += __shfl_xor(s, 16);
+  s += __shfl_xor(s, 32);
+  if (lane < 16) part[w][lane] = s;
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    double t = part[0][threadIdx.x];
+    for (int q = 1; q < GTV_NT / 64; ++q) t += part[q][threadIdx.x];
+    y[i] = t;
+  }
 }
 
 // adjoint stage, part 3: psit = y + q;  upsilon = (e1 - v psit, psit)

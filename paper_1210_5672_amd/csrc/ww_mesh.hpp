@@ -56,16 +56,15 @@ __global__ void k_mesh_tables(double* __restrict__ mesh, int nmax, int N, double
 //   finite depth: D = cot((zeta_i - conj zeta_j)/2), K -= Im{conj(zeta'_j) D}/2,
 //                 G -= Re{zeta'_i D}/2
 // The regularising cot((alpha_i - alpha_j)/2)/2 stays on the uniform alpha grid (the
-// circulant table).  cos x_ij and sin x_ij are evaluated per entry.  One strip of 64
-// rows x 16 columns per workgroup (grid Np/64 x Np/16); writes what k_assemble writes.
+// circulant table).  cos x_ij and sin x_ij are evaluated per entry.  One strip of 16
+// rows x 64 columns per workgroup (grid Np/64 x Np/16); writes what k_assemble writes.
 // With a lagged inverse (Mx64 or Mx32, row-major) 16 more rows of workgroups form
 // x0 = Mx psi, the first solve of the lagged-factor base chain, one wave per row.
 // -------------------------------------------------------------------------------------
 __global__ __launch_bounds__(WW_NT) void k_assemble_map(const double* __restrict__ aux, const double* __restrict__ mesh,
                                                         int nmax, const double* __restrict__ c0T,
-                                                        double* __restrict__ A, double* __restrict__ Gm,
-                                                        float* __restrict__ A32, double* __restrict__ Gmr,
-                                                        double* __restrict__ Ar, int N, int Np, int finite,
+                                                        double* __restrict__ A, float* __restrict__ A32,
+                                                        double* __restrict__ Gmr, int N, int Np, int finite,
                                                         const double* __restrict__ Mx64, const float* __restrict__ Mx32,
                                                         const double* __restrict__ psi, double* __restrict__ x0) {
   constexpr int CW = 16;
@@ -80,14 +79,13 @@ __global__ __launch_bounds__(WW_NT) void k_assemble_map(const double* __restrict
       gemv_row_wave<double>(Mx64, Np, 0, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
     return;
   }
-  __shared__ double rt[WW_TB][CW + 1];
-  __shared__ double rq[7][WW_TB];   // eta', eta'', exp(s), exp(-s), xi, E, E' of the rows
-  __shared__ double cq[5][CW];      // eta', exp(s), exp(-s), xi, E of the columns
+  __shared__ double rq[7][CW];      // eta', eta'', exp(s), exp(-s), xi, E, E' of the rows
+  __shared__ double cq[5][WW_TB];   // eta', exp(s), exp(-s), xi, E of the columns
   __shared__ double c0s[WW_TB + CW];
-  const int i0 = blockIdx.x * WW_TB, j0 = blockIdx.y * CW;
+  const int j0 = blockIdx.x * WW_TB, i0 = blockIdx.y * CW;
   const int t = threadIdx.x;
-  for (int e = t; e < 7 * WW_TB; e += WW_NT) {
-    const int q = e / WW_TB, r = e - q * WW_TB, ir = i0 + r;
+  for (int e = t; e < 7 * CW; e += WW_NT) {
+    const int q = e / CW, r = e - q * CW, ir = i0 + r;
     const double* src = q == 0 ? aux + AUX_EX * nmax
                         : q == 1 ? aux + AUX_EXX * nmax
                         : q == 2 ? aux + AUX_EP * nmax
@@ -97,8 +95,8 @@ __global__ __launch_bounds__(WW_NT) void k_assemble_map(const double* __restrict
                                  : mesh + MESH_EP * nmax;
     rq[q][r] = ir < N ? src[ir] : 0.0;
   }
-  for (int e = t; e < 5 * CW; e += WW_NT) {
-    const int q = e / CW, r = e - q * CW, jc = j0 + r;
+  for (int e = t; e < 5 * WW_TB; e += WW_NT) {
+    const int q = e / WW_TB, r = e - q * WW_TB, jc = j0 + r;
     const double* src = q == 0 ? aux + AUX_EX * nmax
                         : q == 1 ? aux + AUX_EP * nmax
                         : q == 2 ? aux + AUX_EM * nmax
@@ -107,26 +105,26 @@ __global__ __launch_bounds__(WW_NT) void k_assemble_map(const double* __restrict
     cq[q][r] = jc < N ? src[jc] : 0.0;
   }
   for (int e = t; e < WW_TB + CW - 1; e += WW_NT) {
-    int d = (i0 - j0 - (CW - 1) + e) % N;
+    int d = (i0 - j0 - (WW_TB - 1) + e) % N;
     if (d < 0) d += N;
     c0s[e] = c0T[d];
   }
   __syncthreads();
   const int tx = t & 63, ty = t >> 6;
-  const int i = i0 + tx;
+  const int j = j0 + tx;
   const double invN = 1.0 / (double)N;
-  const double exi = rq[0][tx], exxi = rq[1][tx], epi = rq[2][tx], emi = rq[3][tx];
-  const double xii = rq[4][tx], Ei = rq[5][tx], Epi = rq[6][tx];
-  for (int jj = ty; jj < CW; jj += 4) {
-    const int j = j0 + jj;
+  const double exj = cq[0][tx], epj = cq[1][tx], emj = cq[2][tx], Ej = cq[4][tx];
+  for (int ii = ty; ii < CW; ii += 4) {
+    const int i = i0 + ii;
     double a, gm;
     if (i >= N || j >= N) {
       a = (i == j) ? 1.0 : 0.0;
       gm = 0.0;
     } else {
-      const double exj = cq[0][jj], epj = cq[1][jj], emj = cq[2][jj], Ej = cq[4][jj];
+      const double exi = rq[0][ii], exxi = rq[1][ii], epi = rq[2][ii], emi = rq[3][ii];
+      const double Ei = rq[5][ii], Epi = rq[6][ii];
       double sx, cx;
-      sincos(xii - cq[3][jj], &sx, &cx);
+      sincos(rq[4][ii] - cq[3][tx], &sx, &cx);
       double Kv, Gv;
       if (i != j) {
         const double e1 = epi * emj, e2 = emi * epj;
@@ -134,7 +132,7 @@ __global__ __launch_bounds__(WW_NT) void k_assemble_map(const double* __restrict
         double cre, cim;
         cot_half_branch(cx, sx, chy, shy, cre, cim);
         Kv = 0.5 * (Ej * cim + exj * cre);
-        Gv = 0.5 * (Ei * cre - exi * cim) - c0s[tx - jj + (CW - 1)];
+        Gv = 0.5 * (Ei * cre - exi * cim) - c0s[ii - tx + (WW_TB - 1)];
       } else {
         const double den = 1.0 / (Ei * Ei + exi * exi);
         Kv = -0.5 * (exxi * Ei - Epi * exi) * den;
@@ -151,24 +149,10 @@ __global__ __launch_bounds__(WW_NT) void k_assemble_map(const double* __restrict
       a = Kv * invN + (i == j ? 0.5 : 0.0);
       gm = Gv * invN;
     }
-    const size_t o = (size_t)j * Np + i;
+    const size_t o = (size_t)i * Np + j;
     A[o] = a;
-    if (Gm) Gm[o] = gm;
     if (A32) A32[o] = (float)a;
-    rt[tx][jj] = gm;
-  }
-  __syncthreads();
-  for (int idx = t; idx < WW_TB * CW; idx += WW_NT) {
-    const int r = idx / CW, cc = idx % CW;
-    Gmr[(size_t)(i0 + r) * Np + j0 + cc] = rt[r][cc];
-  }
-  if (!Ar) return;
-  __syncthreads();
-  for (int jj = ty; jj < CW; jj += 4) rt[tx][jj] = A[(size_t)(j0 + jj) * Np + i];
-  __syncthreads();
-  for (int idx = t; idx < WW_TB * CW; idx += WW_NT) {
-    const int r = idx / CW, cc = idx % CW;
-    Ar[(size_t)(i0 + r) * Np + j0 + cc] = rt[r][cc];
+    Gmr[o] = gm;
   }
 }
 
