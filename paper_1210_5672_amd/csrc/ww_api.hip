@@ -37,6 +37,51 @@ static double* g_scratch_dev[SCRATCH_MAX_DEV] = {};
 
 static thread_local std::string g_err;
 
+// The library's working streams of a device (LU streams; one of them doubles as the column
+// stream where there is one), shared by its contexts: HIP spreads a process's streams over
+// four hardware queues, in the order of their creation, and a second context with streams
+// of its own would have its LUs queue in front of base chains (measured, N = 1024, 24 steps,
+// one context marching beside two idle ones: 58.8 ms with streams of their own, 47 ms alone).
+// A context holds the pool from ww_create to ww_destroy; the last one to go destroys the
+// streams.  Work of several contexts on one stream is only put in sequence: every
+// dependency is an event recorded before its wait, so no order of enqueues can deadlock.
+// Nothing is ever captured from these streams (captures take streams of their own).
+#define POOL_STREAMS 6
+#define POOL_SIDE 2   // the column stream: not LU stream 0 or 1, which it runs beside
+struct StreamPool {
+  int refs = 0;
+  hipStream_t s[POOL_STREAMS] = {};
+};
+static std::mutex g_pool_mu;
+static StreamPool g_pool[SCRATCH_MAX_DEV];
+
+static void pool_acquire(int dev) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  ++g_pool[dev].refs;
+}
+static void pool_release(int dev) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  StreamPool& p = g_pool[dev];
+  if (--p.refs > 0) return;
+  for (hipStream_t& s : p.s)
+    if (s) {
+      (void)hipStreamDestroy(s);
+      s = nullptr;
+    }
+}
+// streams 0..i of the pool (created in order on first need, with the device current)
+static hipError_t pool_get(int dev, int i, hipStream_t* out) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  StreamPool& p = g_pool[dev];
+  for (int q = 0; q <= i; ++q)
+    if (!p.s[q]) {
+      const hipError_t e = hipStreamCreateWithFlags(&p.s[q], hipStreamNonBlocking);
+      if (e != hipSuccess) return e;
+    }
+  *out = p.s[i];
+  return hipSuccess;
+}
+
 static int fail(int code, const std::string& msg) {
   g_err = msg;
   return code;
@@ -67,7 +112,7 @@ struct FacSet {
   float* Mi32 = nullptr;
 };
 #define PIPE_MAXLAG 11
-#define PIPE_MAXLUS 6
+#define PIPE_MAXLUS POOL_STREAMS
 
 struct ww_ctx {
   int dev = 0;
@@ -92,7 +137,8 @@ struct ww_ctx {
   // device buffers: two factor sets; stages alternate between them so that the column
   // chain of stage s overlaps the base chain of stage s + 1
   FacSet set[2];
-  hipStream_t side = nullptr;  // column-chain stream
+  hipStream_t side = nullptr;  // column-chain stream (of the device's pool)
+  bool pool = false;           // the context holds the device's stream pool
   hipEvent_t evB[16] = {}, evC[16] = {};
   double *Rr = nullptr, *rr0 = nullptr;   // residuals of the refinement sweeps
   int nref = 2;                            // refinement sweeps per solve (mixed mode)
@@ -179,7 +225,7 @@ struct ww_ctx {
   // one RK step captured as a graph, replayed nsteps times
   bool use_graph = true;
   bool overlap = true;   // column chain on the side stream (environment WW_NO_OVERLAP=1: one stream)
-  hipStream_t cap_stream = nullptr;
+  hipStream_t cap_stream = nullptr;   // only while a graph is being captured
   hipGraphExec_t step_exec = nullptr;
   int gN = -1, gM = -1, gcols = -1, gnst = -1, gtwo = -1;
   unsigned gfb = ~0u;
@@ -455,17 +501,13 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
     if (gp) c->graph_parts = std::atoi(gp) & 15;
     const char* mw = std::getenv("WW_MINV_WGS");
     if (mw) c->minv_wgs = std::max(1, std::atoi(mw));
-    // streams: the working ones first, the capture stream (which never executes) last.
-    // HIP shares its few hardware queues among a process's streams, each new stream
-    // taking the least-used queue: created in this order, the caller's stream and the
-    // three LU streams of a march (or the column stream and two LU streams) each get a
-    // queue of their own (with four), and no LU waits in the base chain's in-order queue.
+    // the working streams: created in order, so that the caller's stream and three LU
+    // streams each get a hardware queue of their own (with four)
+    pool_acquire(c->dev);
+    c->pool = true;
     const int nls = c->lag > 0 ? std::min(c->nlus, c->lag) : 0;
-    // the column stream only where it is used (created on first need otherwise: every
-    // stream a context holds shifts the queues of the streams created after it)
-    if (!c->cols_on_lu) CCHK(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-    for (int i = 0; i < nls; ++i) CCHK(hipStreamCreateWithFlags(&c->lus[i], hipStreamNonBlocking));
-    CCHK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
+    for (int i = 0; i < nls; ++i) CCHK(pool_get(c->dev, i, &c->lus[i]));
+    if (!c->cols_on_lu) CCHK(pool_get(c->dev, POOL_SIDE, &c->side));
     const char* pg = std::getenv("WW_PIVOT_GUARD");
     if (pg) {
       const double v = std::atof(pg);
@@ -532,14 +574,11 @@ void ww_destroy(ww_ctx* c) {
   if (c->seg) (void)hipFree(c->seg);
   if (c->adj) (void)hipFree(c->adj);
   if (c->seg_perm) (void)hipFree(c->seg_perm);
-  for (int i = 0; i < PIPE_MAXLUS; ++i)
-    if (c->lus[i]) (void)hipStreamDestroy(c->lus[i]);
   for (int i = 0; i < 16; ++i) {
     if (c->evA[i]) (void)hipEventDestroy(c->evA[i]);
     if (c->evL[i]) (void)hipEventDestroy(c->evL[i]);
   }
-  if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  if (c->side) (void)hipStreamDestroy(c->side);
+  if (c->pool) pool_release(c->dev);
   for (int i = 0; i < 16; ++i) {
     if (c->evB[i]) (void)hipEventDestroy(c->evB[i]);
     if (c->evC[i]) (void)hipEventDestroy(c->evC[i]);
@@ -1097,7 +1136,7 @@ static int ensure_ring(ww_ctx* c, int n) {
 
 static int ensure_pipe(ww_ctx* c) {
   for (int i = 0; i < lu_count(c); ++i)
-    if (!c->lus[i]) HIPCHK(hipStreamCreateWithFlags(&c->lus[i], hipStreamNonBlocking));
+    if (!c->lus[i]) HIPCHK(pool_get(c->dev, i, &c->lus[i]));
   for (int i = 0; i < 16; ++i) {
     if (!c->evA[i]) HIPCHK(hipEventCreateWithFlags(&c->evA[i], hipEventDisableTiming));
     if (!c->evL[i]) HIPCHK(hipEventCreateWithFlags(&c->evL[i], hipEventDisableTiming));
@@ -1134,6 +1173,7 @@ static int pipe_prologue(ww_ctx* c) {
   // the first step of the per-branch graphs waits, at stage s, for the column chain of
   // stage s and the LU of stage s - lag of the step before: here, for this prologue
   for (int q = 0; q < nst; ++q) {
+    if (q != grp_last(c, q)) continue;
     HIPCHK(hipEventRecord(c->evC[q], c->stream));
     HIPCHK(hipEventRecord(c->evL[q], c->stream));
   }
@@ -1211,7 +1251,13 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
     LAUNCHCHK();
     return prof_mark(c, 1, 1);
   }
-  return enqueue_col_chain(c, s, pipe_set(c, s));
+  // the column chains of the group that ends at this stage, in stage order
+  if (s != grp_last(c, s)) return 0;
+  for (int q = grp_first(c, s); q <= s && !rc; ++q) {
+    if (c->prof_stage >= 0) c->prof_stage = q;
+    rc = enqueue_col_chain(c, q, pipe_set(c, q));
+  }
+  return rc;
 }
 
 // the step end of the base column (cols false; it counts the step) or of the Jacobian
@@ -1222,6 +1268,31 @@ static int enqueue_pipe_end(ww_ctx* c, bool cols) {
   LAUNCHCHK();
   return 0;
 }
+
+// A stream to capture on (and, for a step of two streams, one for its branch), for the
+// time of the captures only: a stream that is never replayed on still takes a place in the
+// assignment of streams to hardware queues.
+struct CaptureStreams {
+  ww_ctx* c;
+  hipStream_t branch = nullptr, side = nullptr;
+  bool swapped = false;
+  explicit CaptureStreams(ww_ctx* cc) : c(cc) {}
+  int open(bool with_branch) {
+    HIPCHK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
+    if (!with_branch) return 0;
+    HIPCHK(hipStreamCreateWithFlags(&branch, hipStreamNonBlocking));
+    side = c->side;
+    c->side = branch;
+    swapped = true;
+    return 0;
+  }
+  ~CaptureStreams() {
+    if (swapped) c->side = side;
+    if (branch) (void)hipStreamDestroy(branch);
+    if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+    c->cap_stream = nullptr;
+  }
+};
 
 // capture one part on the capture stream, alone (part -1: the step end of the base
 // column, -2: that of the Jacobian columns)
@@ -1256,6 +1327,8 @@ static int ensure_pipe_graphs(ww_ctx* c) {
   int rc;
   if (c->pkey == pipe_key(c) && c->pgend) {
     if (!c->pcols || c->pgendc) return 0;
+    CaptureStreams cs(c);
+    if ((rc = cs.open(false))) return rc;
     // the column branches (first march with columns on these graphs; an exec left by a
     // capture that failed part-way has never been replayed)
     for (int s = 0; s < c->nst; ++s) {
@@ -1263,6 +1336,7 @@ static int ensure_pipe_graphs(ww_ctx* c) {
         HIPCHK(hipGraphExecDestroy(c->pgx[s][PP_COL]));
         c->pgx[s][PP_COL] = nullptr;
       }
+      if (s != grp_last(c, s)) continue;
       if ((rc = capture_part(c, s, PP_COL, &c->pgx[s][PP_COL]))) return rc;
     }
     return capture_part(c, 0, -2, &c->pgendc);
@@ -1280,10 +1354,13 @@ static int ensure_pipe_graphs(ww_ctx* c) {
       *g = nullptr;
     }
   c->pkey = -1;
+  CaptureStreams cs(c);
+  if ((rc = cs.open(false))) return rc;
   for (int s = 0; s < c->nst; ++s)
     for (int q = 0; q < 4; ++q) {
       if (q == PP_COL && !c->pcols) continue;
-      if (q == PP_LU && s != grp_last(c, s)) continue;   // one LU graph per group
+      // one LU graph and one graph of column chains per group
+      if ((q == PP_LU || q == PP_COL) && s != grp_last(c, s)) continue;
       if ((rc = capture_part(c, s, q, &c->pgx[s][q]))) return rc;
     }
   if ((rc = capture_part(c, 0, -1, &c->pgend))) return rc;
@@ -1324,10 +1401,11 @@ static int pipe_step(ww_ctx* c, bool graphed) {
     hipStream_t ls = lu_stream(c, s);
     const bool last = s == grp_last(c, s);
     // Each wait is a barrier packet that the command processor takes microseconds to
-    // clear even when its event has long completed, and these sit on the critical path:
-    // a group's sets are released together (its column chains run in stage order, and
-    // its LU records the events of all its stages at once), so the first stage of a
-    // group waits for the whole group and the others wait for nothing.
+    // clear even when its event has long completed, and every record and wait costs the
+    // host a few microseconds (it enqueues a stage in about the time the GPU takes for
+    // one at N = 256): everything crosses streams once per group.  A group's sets are
+    // released together by its last column chain, or its LU; its column chains start
+    // after its last base chain, which its LU outlasts, and run back to back.
     const int q = (s - L + nst) % nst;   // the stage whose factors the lagged solve reads
     if (s == grp_first(c, s)) HIPCHK(hipStreamWaitEvent(s0, c->pcols ? c->evC[grp_last(c, s)] : c->evL[grp_last(c, s)], 0));
     // the prep part already applies the lagged inverse (the first solve)
@@ -1338,23 +1416,20 @@ static int pipe_step(ww_ctx* c, bool graphed) {
       HIPCHK(hipEventRecord(c->evA[s], s0));
       HIPCHK(hipStreamWaitEvent(ls, c->evA[s], 0));
       if ((rc = pipe_launch(c, s, PP_LU, ls, graphed))) return rc;
-      for (int q = grp_first(c, s); q <= s; ++q) HIPCHK(hipEventRecord(c->evL[q], ls));
+      HIPCHK(hipEventRecord(c->evL[s], ls));
     }
     if ((rc = pipe_launch(c, s, PP_BASE, s0, graphed))) return rc;
-    if (!c->pcols) continue;
+    if (!c->pcols || !last) continue;
+    // the column chains of the group, after its LU, its base chains and the column chains
+    // of the group before (the first group of a step: the last step's Jacobian step end)
+    const int f = grp_first(c, s);
+    hipStream_t cs = c->cols_on_lu ? ls : c->side;
     HIPCHK(hipEventRecord(c->evB[s], s0));
-    if (!last) continue;
-    // the column chains of the group, after its LU, each after the base chain of its
-    // stage and the column chain before it (stage order; the first of a step waits
-    // for the last step's Jacobian step end)
-    for (int q = grp_first(c, s); q <= s; ++q) {
-      hipStream_t cs = c->cols_on_lu ? ls : c->side;
-      if (!c->cols_on_lu) HIPCHK(hipStreamWaitEvent(cs, c->evL[q], 0));
-      HIPCHK(hipStreamWaitEvent(cs, c->evB[q], 0));
-      HIPCHK(hipStreamWaitEvent(cs, q == 0 ? c->evE : c->evC[q - 1], 0));
-      if ((rc = pipe_launch(c, q, PP_COL, cs, graphed))) return rc;
-      HIPCHK(hipEventRecord(c->evC[q], cs));
-    }
+    if (!c->cols_on_lu) HIPCHK(hipStreamWaitEvent(cs, c->evL[s], 0));
+    HIPCHK(hipStreamWaitEvent(cs, c->evB[s], 0));
+    HIPCHK(hipStreamWaitEvent(cs, f == 0 ? c->evE : c->evC[f - 1], 0));
+    if ((rc = pipe_launch(c, s, PP_COL, cs, graphed))) return rc;
+    HIPCHK(hipEventRecord(c->evC[s], cs));
   }
   if ((rc = pipe_launch(c, 0, -1, s0, graphed))) return rc;
   if (c->pcols) {
@@ -1374,7 +1449,8 @@ static int pipe_join(ww_ctx* c) {
   if (c->pcols) {
     HIPCHK(hipStreamWaitEvent(c->stream, c->evE, 0));
   } else {
-    for (int s = 0; s < c->nst; ++s) HIPCHK(hipStreamWaitEvent(c->stream, c->evL[s], 0));
+    for (int s = 0; s < c->nst; ++s)
+      if (s == grp_last(c, s)) HIPCHK(hipStreamWaitEvent(c->stream, c->evL[s], 0));
   }
   c->pjoin = false;
   return 0;
@@ -1429,9 +1505,11 @@ static int ensure_step_graph(ww_ctx* c, bool cols, bool two_streams) {
     HIPCHK(hipGraphExecDestroy(c->step_exec));
     c->step_exec = nullptr;
   }
+  CaptureStreams cs(c);
+  if (int ro = cs.open(two_streams)) return ro;
+  HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
   hipStream_t user = c->stream;
   c->stream = c->cap_stream;
-  HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
   const int rc = enqueue_step(c, cols, two_streams);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(c->cap_stream, &g);
@@ -1990,7 +2068,7 @@ static int shoot_prepare(ww_ctx* c, const double* params, double T, int nsteps, 
     // do not run on the LU streams
     const bool pipe = pipelined(c, cols, two_streams);
     if (cols && c->M > 0 && two_streams && !(pipe && graphed(c) && c->cols_on_lu) && !c->side)
-      HIPCHK(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+      HIPCHK(pool_get(c->dev, POOL_SIDE, &c->side));
   }
   if (pipelined(c, cols, two_streams)) {
     c->pcols = cols && c->M > 0;
@@ -2447,8 +2525,8 @@ static int sdc_col_rhs(ww_ctx* c, const double* Ys, const double* aux, double* k
 // the factor sets, the LU and column streams and the lane events of the two-stream form
 // (first use)
 static int ensure_sdc_groups(ww_ctx* c) {
-  if (!c->lus[0]) HIPCHK(hipStreamCreateWithFlags(&c->lus[0], hipStreamNonBlocking));
-  if (!c->side) HIPCHK(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+  if (!c->lus[0]) HIPCHK(pool_get(c->dev, 0, &c->lus[0]));
+  if (!c->side) HIPCHK(pool_get(c->dev, POOL_SIDE, &c->side));
   if (!c->sdc_ev) HIPCHK(hipEventCreateWithFlags(&c->sdc_ev, hipEventDisableTiming));
   for (int i = 0; i < SDC_NODES; ++i) {
     if (!c->sdc_evB[i]) HIPCHK(hipEventCreateWithFlags(&c->sdc_evB[i], hipEventDisableTiming));
