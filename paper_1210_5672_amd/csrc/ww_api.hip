@@ -1115,7 +1115,11 @@ static bool pipelined(const ww_ctx* c, bool cols, bool two_streams) {
 static int lu_count(const ww_ctx* c) { return std::min(c->pcols ? c->nlus : std::min(c->nlus, 2), c->lag); }
 // LU groups: consecutive stages g G .. g G + G - 1 (the last group of a step may be
 // shorter) are factored by one launch sequence, on LU stream g mod (LU streams); the
-// group is at most the lag, so that a base solve never waits for its own group
+// group is at most the lag, so that a base solve never waits for its own group.  The
+// lagged solves read the factors of the last stage of a group (a solve waits for the whole
+// group anyway); without columns nothing reads the others, and only that stage is
+// factored (N = 1024, two streams: the LUs of every stage took 141 us a stage, the base
+// chain 100).
 static int lu_group(const ww_ctx* c) { return std::max(1, std::min(c->lu_group, c->lag)); }
 static int grp_first(const ww_ctx* c, int s) { return s / lu_group(c) * lu_group(c); }
 static int grp_last(const ww_ctx* c, int s) { return std::min(c->nst, grp_first(c, s) + lu_group(c)) - 1; }
@@ -1190,7 +1194,8 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
   const int nst = c->nst, L = c->lag;
   const Fac F = pipe_set(c, s);
   int rc = 0;
-  const Fac Fo = pipe_set(c, (s - L + nst) % nst);   // the lagged factor set
+  // the lagged factor set: the newest of the group that the solve waits for
+  const Fac Fo = pipe_set(c, grp_last(c, (s - L + nst) % nst));
   if (part == PP_PREP) {
     // spectral prep; assembly, and in the same launch the first lagged solve
     // x0 = Mi_old psi, which does not need this stage's matrix
@@ -1205,6 +1210,7 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
   if (part == PP_LU) {
     // the group that ends at this stage (stages of a group are never pivoted)
     if (s != grp_last(c, s)) return 0;
+    if (!c->pcols) return enqueue_lu(c, F);
     const int f = grp_first(c, s);
     Fac Fs[GJ_GMAX];
     for (int q = f; q <= s; ++q) Fs[q - f] = pipe_set(c, q);
@@ -1325,22 +1331,7 @@ static long long pipe_key(const ww_ctx* c) {
 
 static int ensure_pipe_graphs(ww_ctx* c) {
   int rc;
-  if (c->pkey == pipe_key(c) && c->pgend) {
-    if (!c->pcols || c->pgendc) return 0;
-    CaptureStreams cs(c);
-    if ((rc = cs.open(false))) return rc;
-    // the column branches (first march with columns on these graphs; an exec left by a
-    // capture that failed part-way has never been replayed)
-    for (int s = 0; s < c->nst; ++s) {
-      if (c->pgx[s][PP_COL]) {
-        HIPCHK(hipGraphExecDestroy(c->pgx[s][PP_COL]));
-        c->pgx[s][PP_COL] = nullptr;
-      }
-      if (s != grp_last(c, s)) continue;
-      if ((rc = capture_part(c, s, PP_COL, &c->pgx[s][PP_COL]))) return rc;
-    }
-    return capture_part(c, 0, -2, &c->pgendc);
-  }
+  if (c->pkey == pipe_key(c) && c->pgend && c->pgendc) return 0;
   HIPCHK(hipDeviceSynchronize());   // no replay of the old graphs may still run
   for (int s = 0; s < 16; ++s)
     for (int q = 0; q < 4; ++q)
@@ -1358,13 +1349,12 @@ static int ensure_pipe_graphs(ww_ctx* c) {
   if ((rc = cs.open(false))) return rc;
   for (int s = 0; s < c->nst; ++s)
     for (int q = 0; q < 4; ++q) {
-      if (q == PP_COL && !c->pcols) continue;
       // one LU graph and one graph of column chains per group
       if ((q == PP_LU || q == PP_COL) && s != grp_last(c, s)) continue;
       if ((rc = capture_part(c, s, q, &c->pgx[s][q]))) return rc;
     }
   if ((rc = capture_part(c, 0, -1, &c->pgend))) return rc;
-  if (c->pcols && (rc = capture_part(c, 0, -2, &c->pgendc))) return rc;
+  if ((rc = capture_part(c, 0, -2, &c->pgendc))) return rc;
   c->pkey = pipe_key(c);
   return 0;
 }
@@ -2026,6 +2016,9 @@ int shoot_setup(ww_ctx* c, int N, double h, double tau, double g, const double* 
 
 // the pivoting fallback launches two kernels per column of A and runs without a graph
 static bool graphed(const ww_ctx* c) { return c->use_graph && !pivoted(c); }
+// the parts of a lagged-factor march are replayed from graphs only with columns: without,
+// they are few launches, and a driver that alternates the two kinds of march keeps its graphs
+static bool pipe_graphed(const ww_ctx* c) { return graphed(c) && c->pcols; }
 
 // step coefficients a_sj dt, b_s dt and dt of nsteps steps over T/4
 static void coef_fill(const ww_ctx* c, double T, int nsteps, double* coef) {
@@ -2074,7 +2067,7 @@ static int shoot_prepare(ww_ctx* c, const double* params, double T, int nsteps, 
     c->pcols = cols && c->M > 0;
     if ((rc = ensure_pipe(c))) return rc;
     if ((rc = pipe_prologue(c))) return rc;
-    if (graphed(c)) return ensure_pipe_graphs(c);
+    if (pipe_graphed(c)) return ensure_pipe_graphs(c);
     return 0;
   }
   if (graphed(c)) return ensure_step_graph(c, cols, two_streams);
@@ -2082,7 +2075,7 @@ static int shoot_prepare(ww_ctx* c, const double* params, double T, int nsteps, 
 }
 
 static int shoot_one_step(ww_ctx* c, bool cols, bool two_streams) {
-  if (graphed(c) && pipelined(c, cols, two_streams)) return pipe_step(c, true);
+  if (graphed(c) && pipelined(c, cols, two_streams)) return pipe_step(c, pipe_graphed(c));
   if (graphed(c)) {
     HIPCHK(hipGraphLaunch(c->step_exec, c->stream));
     return 0;
@@ -2309,7 +2302,7 @@ static int seg_run(ww_ctx* c, const double* params, double T, int nseg, const ww
         // first surface into the sets its first stages read
         if ((rc = ensure_pipe(c))) return rc;
         if ((rc = pipe_prologue(c))) return rc;
-        if (graphed(c) && (rc = ensure_pipe_graphs(c))) return rc;
+        if (pipe_graphed(c) && (rc = ensure_pipe_graphs(c))) return rc;
       } else if (graphed(c) && (rc = ensure_step_graph(c, cols, two))) {
         return rc;
       }
