@@ -274,14 +274,19 @@ struct ww_ctx {
   hipStream_t lus[PIPE_MAXLUS] = {};
   hipEvent_t evA[16] = {}, evL[16] = {};
   // one graph per branch and stage of the lagged-factor march (prep, LU, base, columns)
-  // and the two halves of the step end (base column: main stream; Jacobian columns:
-  // column stream), replayed on their own streams; pkey: what they were captured for.
-  // evE: the column stream's step end; pjoin: the main stream has not yet waited for it
+  // and the step end of the Jacobian columns, replayed on their own streams; pkey: what
+  // they were captured for.  evE: the column stream's step end; pjoin: the main stream has
+  // not yet waited for it
   hipGraphExec_t pgx[16][4] = {};
-  hipGraphExec_t pgend = nullptr, pgendc = nullptr;
+  hipGraphExec_t pgend = nullptr;
   hipEvent_t evE = nullptr;
   bool pjoin = false;
   bool pcols = true;   // the current lagged march has Jacobian columns (column chains)
+  bool plast = false;  // the step being enqueued is the march's (or the segment's) last
+  // the spectrum of the base state of a lagged-factor march (its slopes are spectra too, in
+  // the base column of the stage slots)
+  cplx* yhat = nullptr;
+  double* chk = nullptr;   // the maxima of the lagged solves' test
   long long pkey = -1;
   // thin SVD / Levenberg-Marquardt workspace (first use): W (n_max x r_max), residuals,
   // parameters, V (r_max^2), column norms and dots, convergence flag, column order
@@ -458,6 +463,8 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
   AL(c->Ys, 2 * nm * R * 8);
   AL(c->K, 16 * 2 * nm * R * 8);
   AL(c->Kx, 2 * nm * 8);
+  AL(c->yhat, nm * sizeof(cplx));
+  AL(c->chk, np / 2 * 8);   // two maxima per workgroup of k_base_dtn (at least 4 rows each)
   AL(c->ydtn, 2 * nm * 8);
   AL(c->basis, 2 * nm * (R > 1 ? R - 1 : 1) * 8);
   AL(c->qfix, 2 * nm * 8);
@@ -518,30 +525,35 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
   const int big = 160 * 1024;
   CCHK(hipFuncSetAttribute((const void*)k_gj_step<double>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_gj_step<float>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_base_prep, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  {
-    // k_gamma holds static LDS too (the folded refinement test): dynamic + static <= big
+#define NF_ALL(K) \
+  (const void*)K<256>, (const void*)K<512>, (const void*)K<1024>, (const void*)K<2048>, (const void*)K<-1>, (const void*)K<0>
+#define NF_ALL2(K, M)                                                                                        \
+  (const void*)K<256, M>, (const void*)K<512, M>, (const void*)K<1024, M>, (const void*)K<2048, M>, (const void*)K<-1, M>, \
+      (const void*)K<0, M>
+  // Dynamic LDS of a launch beside the kernel's static LDS must stay within a compute
+  // unit's 160 KB: five work buffers of the largest transform take all of it.
+  static_assert(5 * WW_NMAX * sizeof(cplx) <= 160 * 1024, "five transform buffers must fit");
+  for (const void* fn : {NF_ALL(k_base_prep), NF_ALL(k_base_rhs), NF_ALL(k_col_rhs), NF_ALL(k_gamma)}) {
     hipFuncAttributes fa;
-    CCHK(hipFuncGetAttributes(&fa, (const void*)k_gamma));
-    CCHK(hipFuncSetAttribute((const void*)k_gamma, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             big - (int)fa.sharedSizeBytes));
+    CCHK(hipFuncGetAttributes(&fa, fn));
+    if (5 * WW_NMAX * sizeof(cplx) + fa.sharedSizeBytes > (size_t)big) {
+      ww_destroy(c);
+      return fail(WW_EHIP, "internal: static LDS beside five transform buffers");
+    }
+    CCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   }
-  for (const void* fn : {(const void*)k_base_rhs_map, (const void*)k_col_rhs_map, (const void*)k_base_rhs_prep_map}) {
-    // static LDS (a reduction buffer) besides the dynamic transform buffers
+  for (const void* fn : {NF_ALL(k_base_dtn), NF_ALL(k_step_end), NF_ALL2(k_base_stage, 0), NF_ALL2(k_base_stage, 1),
+                         (const void*)k_base_rhs_map, (const void*)k_col_rhs_map}) {
     hipFuncAttributes fa;
     CCHK(hipFuncGetAttributes(&fa, fn));
     CCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, big - (int)fa.sharedSizeBytes));
   }
-  CCHK(hipFuncSetAttribute((const void*)k_base_rhs, hipFuncAttributeMaxDynamicSharedMemorySize, big));
+#undef NF_ALL
+#undef NF_ALL2
   CCHK(hipFuncSetAttribute((const void*)k_dd_prep, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_dd_gamma, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_dd_base_rhs, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_dd_filter_state, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_base_rhs_prep, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_base_dtn<16>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_base_dtn<WW_NMAX / 64>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_col_rhs, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-  CCHK(hipFuncSetAttribute((const void*)k_step_end, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_adj_pre, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_adj_mid, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_adj_step, hipFuncAttributeMaxDynamicSharedMemorySize, big));
@@ -559,7 +571,6 @@ void ww_destroy(ww_ctx* c) {
     for (int q = 0; q < 4; ++q)
       if (c->pgx[s][q]) (void)hipGraphExecDestroy(c->pgx[s][q]);
   if (c->pgend) (void)hipGraphExecDestroy(c->pgend);
-  if (c->pgendc) (void)hipGraphExecDestroy(c->pgendc);
   if (c->evE) (void)hipEventDestroy(c->evE);
   if (c->sdc_ev) (void)hipEventDestroy(c->sdc_ev);
   for (int i = 0; i < SDC_NODES; ++i) {
@@ -663,6 +674,12 @@ int ww_set_tableau(ww_ctx* c, int s, const double* a, const double* b, const dou
 // ------------------------------------------------------------------------------------
 // kernel sequences
 // ------------------------------------------------------------------------------------
+// the instance of a spectral kernel for the size class of N (FftSz)
+#define NF_SEL(N, K) \
+  ((N) == 256 ? K<256> : (N) == 512 ? K<512> : (N) == 1024 ? K<1024> : (N) == 2048 ? K<2048> : (N) <= 1024 ? K<-1> : K<0>)
+#define NF_SEL2(N, K, M)                                                                              \
+  ((N) == 256 ? K<256, M> : (N) == 512 ? K<512, M> : (N) == 1024 ? K<1024, M> : (N) == 2048 ? K<2048, M> \
+                                                                   : (N) <= 1024 ? K<-1, M> : K<0, M>)
 static size_t fft_lds_bytes(int N, int nbuf) { return (size_t)nbuf * N * sizeof(cplx); }
 // measurement hook: a pair of HIP events attached to one kernel dispatch on the current
 // stream (hipExtLaunchKernel: the events take the dispatch's own start and end times),
@@ -955,7 +972,7 @@ static int enqueue_dtn_cols(ww_ctx* c, const Fac& F, double* B, double* Yt, doub
                             double* out, double* Rs, int R) {
   int rc;
   if ((rc = enqueue_solve(c, F, B, Yt, Mu, Rs, R))) return rc;
-  hipLaunchKernelGGL(k_gamma, dim3((R + 1) / 2), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, Mu, c->Np, R, Gam,
+  hipLaunchKernelGGL(NF_SEL(c->N, k_gamma), dim3((R + 1) / 2), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, Mu, c->Np, R, Gam,
                      HGm, c->tw, c->N, nullptr, nullptr, 0.0, nullptr, 0);
   LAUNCHCHK();
   return enqueue_gemm<double>(c, F.Gmr, 0, Gam, HGm, 1.0, out, R);
@@ -1026,8 +1043,8 @@ static int read_status(ww_ctx* c, int* st, int* where = nullptr);
 // to LU factors).
 static int gmres_calibrate(ww_ctx* c) {
   const Fac F = fac_default(c);
-  hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->y, c->K, c->Ys, c->coef,
-                     0, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
+  hipLaunchKernelGGL(NF_SEL(c->N, k_base_prep), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->y, c->K, c->Ys, c->coef,
+                     0, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status, (cplx*)nullptr);
   LAUNCHCHK();
   int rc;
   if ((rc = enqueue_assemble(c, F))) return rc;
@@ -1051,13 +1068,13 @@ static int gmres_calibrate(ww_ctx* c) {
 static int enqueue_base_chain(ww_ctx* c, const double* ysrc, int s, double* kout, const Fac& F) {
   int rc;
   if ((rc = prof_mark(c, 1, 0))) return rc;
-  hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, ysrc, c->K, c->Ys, c->coef,
-                     s, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
+  hipLaunchKernelGGL(NF_SEL(c->N, k_base_prep), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, ysrc, c->K, c->Ys, c->coef,
+                     s, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status, (cplx*)nullptr);
   LAUNCHCHK();
   if (c->gm_active) {
     if ((rc = enqueue_assemble(c, F))) return rc;
     if ((rc = enqueue_gmres(c, F, c->rhs0, c->mu0, c->rr0))) return rc;
-    hipLaunchKernelGGL(k_gamma, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->mu0, c->Np, 1, c->gam0,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_gamma), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->mu0, c->Np, 1, c->gam0,
                        c->hg0, c->tw, c->N, nullptr, nullptr, 0.0, nullptr, 0);
     LAUNCHCHK();
     if ((rc = enqueue_gemm<double>(c, F.Gmr, 0, c->gam0, c->hg0, 1.0, c->gphi0, 1))) return rc;
@@ -1067,11 +1084,11 @@ static int enqueue_base_chain(ww_ctx* c, const double* ysrc, int s, double* kout
   }
   if (c->mapped)
     hipLaunchKernelGGL(k_base_rhs_map, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys, c->gphi0,
-                       F.aux, c->mesh, c->n_max, kout, (unsigned long long*)nullptr, 0.0, (int*)nullptr, c->tw,
+                       F.aux, c->mesh, c->n_max, kout, c->tw,
                        c->sig, c->N, c->g, c->tau);
   else
-    hipLaunchKernelGGL(k_base_rhs, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys, c->gphi0, F.aux,
-                       c->n_max, kout, (unsigned long long*)nullptr, 0.0, (int*)nullptr, c->tw, c->sig, c->N, c->g,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_base_rhs), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->Ys, c->gphi0, F.aux,
+                       c->n_max, kout, c->tw, c->sig, c->N, c->g,
                        c->tau);
   LAUNCHCHK();
   return prof_mark(c, 1, 1);
@@ -1092,7 +1109,7 @@ static int enqueue_col_chain(ww_ctx* c, int s, const Fac& F) {
                        c->Np, F.aux, c->mesh, c->n_max, c->K + (size_t)s * kstride(c), c->tw, c->sig, c->N, c->g,
                        c->tau);
   else
-    hipLaunchKernelGGL(k_col_rhs, dim3(M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys, c->Gpsi, c->Np,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_col_rhs), dim3(M), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->Ys, c->Gpsi, c->Np,
                        F.aux, c->n_max, c->K + (size_t)s * kstride(c), c->tw, c->sig, c->N, c->g, c->tau);
   LAUNCHCHK();
   return prof_mark(c, 2, 1);
@@ -1161,8 +1178,8 @@ static int pipe_prologue(ww_ctx* c) {
   int rc;
   const int nst = c->nst, L = c->lag;
   const Fac P0 = pipe_set(c, nst - L);
-  hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->y, c->K, c->Ys, c->coef,
-                     0, kstride(c), P0.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
+  hipLaunchKernelGGL(NF_SEL(c->N, k_base_prep), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->y, c->K, c->Ys, c->coef,
+                     0, kstride(c), P0.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status, (cplx*)nullptr);
   LAUNCHCHK();
   if ((rc = enqueue_assemble(c, P0))) return rc;
   if ((rc = enqueue_lu(c, P0))) return rc;
@@ -1174,6 +1191,11 @@ static int pipe_prologue(ww_ctx* c) {
     if (!use32(c))
       HIPCHK(hipMemcpyAsync(b.Mi, a.Mi, nn * 8, hipMemcpyDeviceToDevice, c->stream));
   }
+  // the prep of the first stage, with the spectrum of the initial state
+  hipLaunchKernelGGL(NF_SEL(c->N, k_base_prep), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->y, c->K,
+                     c->Ys, c->coef, 0, kstride(c), pipe_set(c, 0).aux, c->n_max, c->rhs0, c->Np, c->tw, c->N,
+                     c->hsurf, c->status, c->yhat);
+  LAUNCHCHK();
   // the first step of the per-branch graphs waits, at stage s, for the column chain of
   // stage s and the LU of stage s - lag of the step before: here, for this prologue
   for (int q = 0; q < nst; ++q) {
@@ -1185,11 +1207,13 @@ static int pipe_prologue(ww_ctx* c) {
   return 0;
 }
 
-// The parts of stage s of the lagged-factor march, each captured alone: 0 spectral prep
-// and assembly (main stream), 1 the LU of the stage (LU stream s % lag), 2 the lagged
-// base solve to the base right-hand side (main), 3 the column chain (side stream).
+// The parts of stage s of the lagged-factor march, each captured alone: 0 assembly and
+// first lagged solve (main stream), 1 the LU of the group that ends at the stage (an LU
+// stream), 2 the lagged base solve to the base right-hand side and the next stage's prep
+// (main), 3 the column chains of the group.
 enum { PP_PREP = 0, PP_LU = 1, PP_BASE = 2, PP_COL = 3 };
 
+static const size_t STAGE_LDS = 160 * 1024 - 64;   // dynamic LDS of k_base_stage (beside its static reduction)
 static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
   const int nst = c->nst, L = c->lag;
   const Fac F = pipe_set(c, s);
@@ -1197,14 +1221,10 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
   // the lagged factor set: the newest of the group that the solve waits for
   const Fac Fo = pipe_set(c, grp_last(c, (s - L + nst) % nst));
   if (part == PP_PREP) {
-    // spectral prep; assembly, and in the same launch the first lagged solve
-    // x0 = Mi_old psi, which does not need this stage's matrix
+    // assembly, and in the same launch the first lagged solve x0 = Mi_old psi, which does
+    // not need this stage's matrix (the spectral prep is part of the base chain of the
+    // stage before, or of the prologue)
     if ((rc = prof_mark(c, 1, 0))) return rc;
-    if (s == 0) {   // later stages are prepared by the base chain of the stage before
-      hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->y, c->K, c->Ys,
-                         c->coef, s, kstride(c), F.aux, c->n_max, c->rhs0, c->Np, c->tw, c->N, c->hsurf, c->status);
-      LAUNCHCHK();
-    }
     return enqueue_assemble(c, F, &Fo, c->rhs0, c->mu0);
   }
   if (part == PP_LU) {
@@ -1226,34 +1246,46 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
       if (rc) return rc;
     }
     // gamma, (1/2) H gamma, G phi and the residual of the convergence test in one
-    // launch; the test's decision is taken at the start of k_base_rhs
-    unsigned long long* chk = (unsigned long long*)(c->status + 4);
-    hipLaunchKernelGGL(c->N <= 1024 ? k_base_dtn<16> : k_base_dtn<WW_NMAX / 64>,
-                       dim3((c->Np + c->dtn_rows - 1) / c->dtn_rows), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream,
-                       c->mu0, c->rhs0, F.Gmr, F.Ar, c->Np, c->tw, c->N, c->gphi0, chk, c->dtn_rows);
+    // launch; the test's decision is taken at the start of k_base_stage
+    const int nchk = (c->Np + c->dtn_rows - 1) / c->dtn_rows;
+    hipLaunchKernelGGL(NF_SEL(c->N, k_base_dtn), dim3(nchk), dim3(WW_NT),
+                       fft_lds_bytes(c->N, 4), c->stream, c->mu0, c->rhs0, F.Gmr, F.Ar, c->Np, c->tw, c->N, c->gphi0,
+                       c->chk, c->dtn_rows);
     LAUNCHCHK();
-    if (s + 1 < nst && c->mapped) {
-      const Fac Fn = pipe_set(c, s + 1);
-      hipLaunchKernelGGL(k_base_rhs_prep_map, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->gphi0,
-                         F.aux, c->K + (size_t)s * kstride(c), chk, REFINE_TOL, c->sig, c->g, c->tau, c->y, c->K,
-                         c->Ys, c->coef, s + 1, kstride(c), Fn.aux, c->rhs0, c->Np, c->hsurf, c->n_max, c->tw, c->N,
-                         c->status, c->mesh);
-    } else if (c->mapped) {
-      hipLaunchKernelGGL(k_base_rhs_map, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys, c->gphi0,
-                         F.aux, c->mesh, c->n_max, c->K + (size_t)s * kstride(c), chk, REFINE_TOL, c->status, c->tw,
-                         c->sig, c->N, c->g, c->tau);
-    } else if (s + 1 < nst) {
-      // this stage's right-hand side and the next stage's prep in one launch
-      const Fac Fn = pipe_set(c, s + 1);
-      hipLaunchKernelGGL(k_base_rhs_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->gphi0, F.aux,
-                         c->K + (size_t)s * kstride(c), chk, REFINE_TOL, c->sig, c->g, c->tau, c->y, c->K, c->Ys,
-                         c->coef, s + 1, kstride(c), Fn.aux, c->rhs0, c->Np, c->hsurf, c->n_max, c->tw, c->N,
-                         c->status);
-    } else {
-      hipLaunchKernelGGL(k_base_rhs, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys, c->gphi0, F.aux,
-                         c->n_max, c->K + (size_t)s * kstride(c), chk, REFINE_TOL, c->status, c->tw, c->sig, c->N,
-                         c->g, c->tau);
-    }
+    // this stage's right-hand side and the prep of the next stage (of the next step)
+    StageArgs q;
+    q.Gphi = c->gphi0;
+    q.aux_cur = F.aux;
+    q.aux_next = pipe_set(c, (s + 1) % nst).aux;
+    q.Ys = c->Ys;
+    q.y = c->y;
+    q.yhat = c->yhat;
+    q.K = c->K;
+    q.kstride = kstride(c);
+    q.end = s + 1 == nst;
+    q.w = q.end ? c->coef + COEF_B : c->coef + (s + 1) * 16;
+    q.chk = c->chk;
+    q.nchk = nchk;
+    q.status = c->status;
+    q.tw = c->tw;
+    q.sig = c->sig;
+    q.mesh = c->mesh;
+    q.rhs0 = c->rhs0;
+    q.chk_tol = REFINE_TOL;
+    q.g = c->g;
+    q.tau = c->tau;
+    q.hsurf = c->hsurf;
+    q.s = s;
+    q.check = !(q.end && c->plast);   // the state at T/4 has no stage: shoot_finish checks it
+    q.nmax = c->n_max;
+    q.N = c->N;
+    q.Np = c->Np;
+    q.inplace = fft_lds_bytes(c->N, 7) > STAGE_LDS;
+    const size_t lds = fft_lds_bytes(c->N, q.inplace ? 4 : 7);
+    if (c->mapped)
+      hipLaunchKernelGGL(NF_SEL2(c->N, k_base_stage, 1), dim3(1), dim3(STAGE_NT), lds, c->stream, q);
+    else
+      hipLaunchKernelGGL(NF_SEL2(c->N, k_base_stage, 0), dim3(1), dim3(STAGE_NT), lds, c->stream, q);
     LAUNCHCHK();
     return prof_mark(c, 1, 1);
   }
@@ -1266,11 +1298,11 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
   return rc;
 }
 
-// the step end of the base column (cols false; it counts the step) or of the Jacobian
-// columns 1..M (cols true)
-static int enqueue_pipe_end(ww_ctx* c, bool cols) {
-  hipLaunchKernelGGL(k_step_end, dim3(cols ? c->M : 1), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y, c->K,
-                     kstride(c), c->nst, c->coef, c->tw, c->sig, c->N, cols ? 1 : 0, cols ? nullptr : c->status);
+// the step end of the Jacobian columns 1..M (that of the base column is part of its last
+// stage's right-hand side)
+static int enqueue_pipe_end(ww_ctx* c) {
+  hipLaunchKernelGGL(NF_SEL(c->N, k_step_end), dim3(c->M), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y, c->K,
+                     kstride(c), c->nst, c->coef, c->tw, c->sig, c->N, 1, (int*)nullptr);
   LAUNCHCHK();
   return 0;
 }
@@ -1300,15 +1332,15 @@ struct CaptureStreams {
   }
 };
 
-// capture one part on the capture stream, alone (part -1: the step end of the base
-// column, -2: that of the Jacobian columns)
+// capture one part on the capture stream, alone (part -1: the step end of the Jacobian
+// columns)
 static int capture_part(ww_ctx* c, int s, int part, hipGraphExec_t* out) {
   hipStream_t user = c->stream;
   const hipError_t eb = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   if (eb != hipSuccess) return fail(WW_EHIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(eb));
   c->stream = c->cap_stream;
   c->prof_stage = part < 0 ? -1 : s;
-  const int rc = part < 0 ? enqueue_pipe_end(c, part == -2) : enqueue_pipe_part(c, s, part);
+  const int rc = part < 0 ? enqueue_pipe_end(c) : enqueue_pipe_part(c, s, part);
   c->prof_stage = -1;
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(c->cap_stream, &g);
@@ -1331,7 +1363,7 @@ static long long pipe_key(const ww_ctx* c) {
 
 static int ensure_pipe_graphs(ww_ctx* c) {
   int rc;
-  if (c->pkey == pipe_key(c) && c->pgend && c->pgendc) return 0;
+  if (c->pkey == pipe_key(c) && c->pgend) return 0;
   HIPCHK(hipDeviceSynchronize());   // no replay of the old graphs may still run
   for (int s = 0; s < 16; ++s)
     for (int q = 0; q < 4; ++q)
@@ -1339,11 +1371,10 @@ static int ensure_pipe_graphs(ww_ctx* c) {
         HIPCHK(hipGraphExecDestroy(c->pgx[s][q]));
         c->pgx[s][q] = nullptr;
       }
-  for (hipGraphExec_t* g : {&c->pgend, &c->pgendc})
-    if (*g) {
-      HIPCHK(hipGraphExecDestroy(*g));
-      *g = nullptr;
-    }
+  if (c->pgend) {
+    HIPCHK(hipGraphExecDestroy(c->pgend));
+    c->pgend = nullptr;
+  }
   c->pkey = -1;
   CaptureStreams cs(c);
   if ((rc = cs.open(false))) return rc;
@@ -1354,7 +1385,6 @@ static int ensure_pipe_graphs(ww_ctx* c) {
       if ((rc = capture_part(c, s, q, &c->pgx[s][q]))) return rc;
     }
   if ((rc = capture_part(c, 0, -1, &c->pgend))) return rc;
-  if ((rc = capture_part(c, 0, -2, &c->pgendc))) return rc;
   c->pkey = pipe_key(c);
   return 0;
 }
@@ -1370,14 +1400,16 @@ static int ensure_pipe_graphs(ww_ctx* c) {
 // s - lag + nst of the step before.  The main stream joins the other streams
 // (pipe_join) before the march's outputs are read.
 static int pipe_launch(ww_ctx* c, int s, int part, hipStream_t st, bool graphed) {
-  if (graphed && (part < 0 || ((c->graph_parts >> part) & 1))) {
-    HIPCHK(hipGraphLaunch(part < 0 ? (part == -1 ? c->pgend : c->pgendc) : c->pgx[s][part], st));
+  // (the last base chain of a march differs in its check of the state: not from a graph)
+  const bool own = part == PP_BASE && s + 1 == c->nst && c->plast;
+  if (graphed && !own && (part < 0 || ((c->graph_parts >> part) & 1))) {
+    HIPCHK(hipGraphLaunch(part < 0 ? c->pgend : c->pgx[s][part], st));
     return 0;
   }
   hipStream_t user = c->stream;
   c->stream = st;
   c->prof_stage = part < 0 ? -1 : s;
-  const int rc = part < 0 ? enqueue_pipe_end(c, part == -2) : enqueue_pipe_part(c, s, part);
+  const int rc = part < 0 ? enqueue_pipe_end(c) : enqueue_pipe_part(c, s, part);
   c->prof_stage = -1;
   c->stream = user;
   return rc;
@@ -1421,10 +1453,9 @@ static int pipe_step(ww_ctx* c, bool graphed) {
     if ((rc = pipe_launch(c, s, PP_COL, cs, graphed))) return rc;
     HIPCHK(hipEventRecord(c->evC[s], cs));
   }
-  if ((rc = pipe_launch(c, 0, -1, s0, graphed))) return rc;
   if (c->pcols) {
     hipStream_t cs = c->cols_on_lu ? lu_stream(c, nst - 1) : c->side;   // after the last column chain
-    if ((rc = pipe_launch(c, 0, -2, cs, graphed))) return rc;
+    if ((rc = pipe_launch(c, 0, -1, cs, graphed))) return rc;
     HIPCHK(hipEventRecord(c->evE, cs));
   }
   c->pjoin = true;
@@ -1476,7 +1507,7 @@ static int enqueue_step(ww_ctx* c, bool cols, bool two_streams) {
   }
   if (two) HIPCHK(hipStreamWaitEvent(s0, c->evC[c->nst - 1], 0));
   const int ncol = cols ? c->M + 1 : 1;
-  hipLaunchKernelGGL(k_step_end, dim3(ncol), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y, c->K, kstride(c),
+  hipLaunchKernelGGL(NF_SEL(c->N, k_step_end), dim3(ncol), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y, c->K, kstride(c),
                      c->nst, c->coef, c->tw, c->sig, c->N, 0, c->status);
   LAUNCHCHK();
   return 0;
@@ -1582,8 +1613,8 @@ int dtn_setup(ww_ctx* c, const double* surface, double h, double tau, int N) {
   HIPCHK(hipMemsetAsync(c->ydtn + N, 0, N * 8, c->stream));
   hipLaunchKernelGGL(k_status_reset, dim3(1), dim3(64), 0, c->stream, c->status);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(N, 4), c->stream, c->ydtn, c->K, c->Ys,
-                     c->coef, 0, (size_t)0, c->set[0].aux, c->n_max, c->rhs0, c->Np, c->tw, N, c->hsurf, c->status);
+  hipLaunchKernelGGL(NF_SEL(N, k_base_prep), dim3(1), dim3(PREP_NT), fft_lds_bytes(N, 5), c->stream, c->ydtn, c->K, c->Ys,
+                     c->coef, 0, (size_t)0, c->set[0].aux, c->n_max, c->rhs0, c->Np, c->tw, N, c->hsurf, c->status, (cplx*)nullptr);
   LAUNCHCHK();
   if ((rc = dtn_factor(c))) return rc;
   c->dtn_ready = true;
@@ -2074,7 +2105,9 @@ static int shoot_prepare(ww_ctx* c, const double* params, double T, int nsteps, 
   return 0;
 }
 
-static int shoot_one_step(ww_ctx* c, bool cols, bool two_streams) {
+// one step; last: the march's (or, on segments, the segment's) last one
+static int shoot_one_step(ww_ctx* c, bool cols, bool two_streams, bool last) {
+  c->plast = last;
   if (graphed(c) && pipelined(c, cols, two_streams)) return pipe_step(c, pipe_graphed(c));
   if (graphed(c)) {
     HIPCHK(hipGraphLaunch(c->step_exec, c->stream));
@@ -2161,7 +2194,7 @@ static int shoot_run(ww_ctx* c, const double* params, double T, int nsteps, doub
   const bool pipe = pipelined(c, cols, two);   // after the set-up, which decides on GMRES
   for (int n = 0; n < nsteps; ++n) {
     const auto h0 = std::chrono::steady_clock::now();
-    if ((rc = shoot_one_step(c, cols, two))) return rc;
+    if ((rc = shoot_one_step(c, cols, two, n + 1 == nsteps))) return rc;
     if (c->prof) {
       c->host_enq_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - h0).count();
       ++c->host_enq_steps;
@@ -2312,7 +2345,7 @@ static int seg_run(ww_ctx* c, const double* params, double T, int nseg, const ww
       if ((rc = sdc_steps(c, cols, Tl / (4.0 * sg[l].nsteps), sg[l].nsteps, sdc_two))) return rc;
     } else {
       for (int n = 0; n < sg[l].nsteps; ++n)
-        if ((rc = shoot_one_step(c, cols, two))) return rc;
+        if ((rc = shoot_one_step(c, cols, two, n + 1 == sg[l].nsteps))) return rc;
     }
   }
   if ((rc = shoot_finish(c, cols, r, J, drdT, f))) {
@@ -2496,11 +2529,11 @@ static int ensure_sdc(ww_ctx* c) {
 static int sdc_base_rhs(ww_ctx* c, const double* Ys, const double* gphi, double* aux, double* kout) {
   if (c->mapped)
     hipLaunchKernelGGL(k_base_rhs_map, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, Ys, gphi, aux,
-                       c->mesh, c->n_max, kout, (unsigned long long*)nullptr, 0.0, (int*)nullptr, c->tw, c->sig, c->N,
+                       c->mesh, c->n_max, kout, c->tw, c->sig, c->N,
                        c->g, c->tau);
   else
-    hipLaunchKernelGGL(k_base_rhs, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, Ys, gphi, aux, c->n_max,
-                       kout, (unsigned long long*)nullptr, 0.0, (int*)nullptr, c->tw, c->sig, c->N, c->g, c->tau);
+    hipLaunchKernelGGL(NF_SEL(c->N, k_base_rhs), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, Ys, gphi, aux, c->n_max,
+                       kout, c->tw, c->sig, c->N, c->g, c->tau);
   LAUNCHCHK();
   return 0;
 }
@@ -2509,7 +2542,7 @@ static int sdc_col_rhs(ww_ctx* c, const double* Ys, const double* aux, double* k
     hipLaunchKernelGGL(k_col_rhs_map, dim3(c->M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, Ys, c->Gpsi, c->Np,
                        aux, c->mesh, c->n_max, kout, c->tw, c->sig, c->N, c->g, c->tau);
   else
-    hipLaunchKernelGGL(k_col_rhs, dim3(c->M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, Ys, c->Gpsi, c->Np, aux,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_col_rhs), dim3(c->M), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, Ys, c->Gpsi, c->Np, aux,
                        c->n_max, kout, c->tw, c->sig, c->N, c->g, c->tau);
   LAUNCHCHK();
   return 0;
@@ -2589,8 +2622,8 @@ struct SdcStep {
     int rc;
     HIPCHK(hipStreamWaitEvent(c->stream, c->sdc_evC[q], 0));
     if ((rc = combine(s, q, false))) return rc;
-    hipLaunchKernelGGL(k_base_prep, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, yn(q), c->K, ysn(q),
-                       c->coef, 0, ks, F[q].aux, c->n_max, rhsn(q), c->Np, c->tw, c->N, c->hsurf, c->status);
+    hipLaunchKernelGGL(NF_SEL(c->N, k_base_prep), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, yn(q), c->K, ysn(q),
+                       c->coef, 0, ks, F[q].aux, c->n_max, rhsn(q), c->Np, c->tw, c->N, c->hsurf, c->status, (cplx*)nullptr);
     LAUNCHCHK();
     return enqueue_assemble(c, F[q]);
   }
@@ -2646,7 +2679,7 @@ struct SdcStep {
       if ((rc = lag_mul(b.rr0, b.mu0, b.mu0))) return rc;
     }
     if ((rc = enqueue_gemm<double>(c, F[q].Ar, 0, b.mu0, psi, -1.0, b.rr0, 1))) return rc;
-    hipLaunchKernelGGL(k_gamma, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, b.mu0, c->Np, 1, b.gam0,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_gamma), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, b.mu0, c->Np, 1, b.gam0,
                        b.hg0, c->tw, c->N, b.rr0, psi, REFINE_TOL, c->status, 32);
     LAUNCHCHK();
     if ((rc = enqueue_gemm<double>(c, F[q].Gmr, 0, b.gam0, b.hg0, 1.0, b.gphi0, 1))) return rc;
@@ -2759,7 +2792,7 @@ struct SdcStep {
                        c->sdc_j + SDC_STAGES * SDC_MAXNZ, c->sdc_w + SDC_STAGES * SDC_MAXNZ, c->sdc_cnt[SDC_STAGES],
                        dt, c->y, n);
     LAUNCHCHK();
-    hipLaunchKernelGGL(k_step_end, dim3(cols ? c->M + 1 : 1), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_step_end), dim3(cols ? c->M + 1 : 1), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y,
                        c->K, ks, 0, c->coef, c->tw, c->sig, c->N, 0, c->status);
     LAUNCHCHK();
     return 0;
@@ -2799,7 +2832,7 @@ static int enqueue_sdc_step(ww_ctx* c, bool cols, double dt) {
     if (cols && (rc = enqueue_col_chain_at(c, c->sdc_y, kout, F))) return rc;
   }
   // the filter (no stage terms) and the step count
-  hipLaunchKernelGGL(k_step_end, dim3(cols ? c->M + 1 : 1), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y,
+  hipLaunchKernelGGL(NF_SEL(c->N, k_step_end), dim3(cols ? c->M + 1 : 1), dim3(WW_NT), fft_lds_bytes(c->N, 3), c->stream, c->y,
                      c->K, ks, 0, c->coef, c->tw, c->sig, c->N, 0, c->status);
   LAUNCHCHK();
   return 0;
@@ -3321,7 +3354,7 @@ int shoot_eval_batch(int n_inst, ww_ctx* const* ctx, const double* const* params
   for (int n = 0; n < maxsteps; ++n)
     for (int i = 0; i < n_inst; ++i)
       if (n < nsteps[i])
-        if ((rc = shoot_one_step(ctx[i], J && J[i] && ctx[i]->M > 0, two))) return settle(rc);
+        if ((rc = shoot_one_step(ctx[i], J && J[i] && ctx[i]->M > 0, two, n + 1 == nsteps[i]))) return settle(rc);
   for (int i = 0; i < n_inst; ++i) {
     const bool cols = J && J[i] && ctx[i]->M > 0;
     if ((rc = shoot_finish(ctx[i], cols, r[i], J ? J[i] : nullptr, drdT ? drdT[i] : nullptr, f ? &f[i] : nullptr)))
@@ -3442,7 +3475,7 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
         LAUNCHCHK();
       }
     }
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(WW_NT), fft_lds_bytes(N, 3), c->stream, c->y, c->K, kstride(c), nst,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_step_end), dim3(1), dim3(WW_NT), fft_lds_bytes(N, 3), c->stream, c->y, c->K, kstride(c), nst,
                        c->coef, c->tw, c->sig, N, 0, c->status);
     LAUNCHCHK();
     return 0;

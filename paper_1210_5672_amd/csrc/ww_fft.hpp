@@ -108,45 +108,79 @@ __device__ __forceinline__ void fft_load(const cplx* src, const cplx* twp, int n
   }
 }
 
-// One Stockham pass src -> dst; outputs scaled by sc (the last pass of an inverse).
+// A transform is run by a team of 256 threads, thread tid of the team; a workgroup may hold
+// several teams, each on buffers of its own, which run transforms of one size side by side:
+// every barrier is the workgroup's, so all teams make the same calls, a team without a
+// transform with on = false.  b: scratch of N complex, or a itself (every pass in place, at
+// the price of a second barrier per pass: for sizes whose scratch does not fit).
+#define FFT_NT 256
+
+// One Stockham pass src -> dst, general size; outputs scaled by sc.  In place (src == dst):
+// all inputs of the team are read before the barrier.
 template <int R>
 __device__ __forceinline__ void fft_pass(const cplx* src, cplx* dst, const cplx* twp, int N, int Ns, int dir,
-                                         int lgNs, bool rsw, bool wsw, double sc) {
+                                         int lgNs, bool rsw, bool wsw, double sc, int tid, bool on) {
   const int nb = N / R;
-  for (int j = threadIdx.x; j < nb; j += blockDim.x) {
-    const int jq = lgNs >= 0 ? (j >> lgNs) : j / Ns;
-    const int jm = j - jq * Ns;
-    cplx v[R];
-    fft_load<R>(src, twp, nb, j, jm, Ns, dir, rsw, v);
-    fft_bfly<R>(v, dir);
-    const int idxD = jq * Ns * R + jm;
+  if (src != dst) {
+    if (on)
+      for (int j = tid; j < nb; j += FFT_NT) {
+        const int jq = lgNs >= 0 ? (j >> lgNs) : j / Ns;
+        const int jm = j - jq * Ns;
+        cplx v[R];
+        fft_load<R>(src, twp, nb, j, jm, Ns, dir, rsw, v);
+        fft_bfly<R>(v, dir);
+        const int idxD = jq * Ns * R + jm;
 #pragma unroll
-    for (int q = 0; q < R; ++q) dst[fft_swz(idxD + q * Ns, wsw)] = cscale(v[q], sc);
+        for (int q = 0; q < R; ++q) dst[fft_swz(idxD + q * Ns, wsw)] = cscale(v[q], sc);
+      }
+    return;
   }
-}
-
-// The same transform with N a compile-time power of two (the sizes up to WW_NMAX) and
-// 256 threads: the passes are unrolled with their span, radix and layout flags as
-// constants, so that the index arithmetic folds away; the last pass works in place
-// (all of its inputs are read before a barrier, then written), which saves the copy of
-// an odd pass count, and carries the 1/N of the inverse.  Same passes, same butterflies
-// and the same twiddles as fft_lds, hence the same result.
-template <int N, int R, int Ns>
-__device__ __forceinline__ void fft_pass_fixed(const cplx* src, cplx* dst, const cplx* twp, int dir, bool rsw,
-                                               bool wsw, bool inplace, double sc) {
-  constexpr int nb = N / R;
-  constexpr int per = (nb + 255) / 256;   // butterflies per thread
+  constexpr int per = (WW_NMAX / R + FFT_NT - 1) / FFT_NT;
   cplx v[per][R];
 #pragma unroll
   for (int u = 0; u < per; ++u) {
-    const int j = threadIdx.x + 256 * u;
-    if (j < nb) fft_load<R>(src, twp, nb, j, j & (Ns - 1), Ns, dir, rsw, v[u]);
+    const int j = tid + FFT_NT * u;
+    if (on && j < nb) {
+      const int jq = lgNs >= 0 ? (j >> lgNs) : j / Ns;
+      fft_load<R>(src, twp, nb, j, j - jq * Ns, Ns, dir, rsw, v[u]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < per; ++u) {
+    const int j = tid + FFT_NT * u;
+    if (on && j < nb) {
+      fft_bfly<R>(v[u], dir);
+      const int jq = lgNs >= 0 ? (j >> lgNs) : j / Ns;
+      const int idxD = jq * Ns * R + j - jq * Ns;
+#pragma unroll
+      for (int q = 0; q < R; ++q) dst[fft_swz(idxD + q * Ns, wsw)] = cscale(v[u][q], sc);
+    }
+  }
+}
+
+// The same transform with N a compile-time power of two (256 .. WW_NMAX): the passes are
+// unrolled with their span, radix and layout flags as constants, so that the index
+// arithmetic folds away; the last pass works in place (all of its inputs read before a
+// barrier, then written), which saves the copy of an odd pass count, and carries the 1/N of
+// the inverse.  Same passes, same butterflies and the same twiddles as the general form,
+// hence the same result.
+template <int N, int R, int Ns>
+__device__ __forceinline__ void fft_pass_fixed(const cplx* src, cplx* dst, const cplx* twp, int dir, bool rsw,
+                                               bool wsw, bool inplace, double sc, int tid, bool on) {
+  constexpr int nb = N / R;
+  constexpr int per = (nb + FFT_NT - 1) / FFT_NT;   // butterflies per thread
+  cplx v[per][R];
+#pragma unroll
+  for (int u = 0; u < per; ++u) {
+    const int j = tid + FFT_NT * u;
+    if (on && j < nb) fft_load<R>(src, twp, nb, j, j & (Ns - 1), Ns, dir, rsw, v[u]);
   }
   if (inplace) __syncthreads();   // every input of the pass has been read
 #pragma unroll
   for (int u = 0; u < per; ++u) {
-    const int j = threadIdx.x + 256 * u;
-    if (j < nb) {
+    const int j = tid + FFT_NT * u;
+    if (on && j < nb) {
       fft_bfly<R>(v[u], dir);
       const int jm = j & (Ns - 1);
       const int idxD = (j - jm) * R + jm;
@@ -157,7 +191,8 @@ __device__ __forceinline__ void fft_pass_fixed(const cplx* src, cplx* dst, const
 }
 
 template <int N, int Ns>
-__device__ __forceinline__ void fft_fixed_from(cplx* a, cplx* b, const cplx* tw, int dir, bool first) {
+__device__ __forceinline__ void fft_fixed_from(cplx* a, cplx* b, const cplx* tw, int dir, bool first, int tid,
+                                               bool on) {
   if constexpr (Ns < N) {
     constexpr int R = (N / Ns) % 4 == 0 ? 4 : 2;
     constexpr bool last = Ns * R == N;
@@ -165,32 +200,24 @@ __device__ __forceinline__ void fft_fixed_from(cplx* a, cplx* b, const cplx* tw,
     const cplx* twp = tw + (Ns - 1);
     // ping-pong a -> b -> a ...; the last pass lands in a (in place when it reads a)
     constexpr int p = __builtin_ctz(Ns) / 2;   // passes before this one (radix 4 first)
-    const bool from_a = (p & 1) == 0;
+    constexpr bool from_a = (p & 1) == 0;
     cplx* src = from_a ? a : b;
     cplx* dst = last ? a : (from_a ? b : a);
     const double sc = (last && dir > 0) ? 1.0 / (double)N : 1.0;
-    fft_pass_fixed<N, R, Ns>(src, dst, twp, dir, sw && !first, sw && !last, last && from_a, sc);
+    fft_pass_fixed<N, R, Ns>(src, dst, twp, dir, sw && !first, sw && !last, (last && from_a) || a == b, sc, tid, on);
     __syncthreads();
-    fft_fixed_from<N, Ns * R>(a, b, tw, dir, false);
+    fft_fixed_from<N, Ns * R>(a, b, tw, dir, false, tid, on);
   }
 }
 
-template <int N>
-__device__ __forceinline__ void fft_fixed(cplx* a, cplx* b, const cplx* tw, int dir) {
-  __syncthreads();
-  fft_fixed_from<N, 1>(a, b, tw, dir, true);
-}
-
-// Transform `a` (N complex in LDS) in place; `b` is LDS scratch of N complex.
-// tw: twiddle table in LDS (load_twiddles) in pass order: the pass with radix R that
-// starts at span Ns reads the N_s R - N_s entries from offset Ns - 1 (the offsets
-// telescope: the table holds N - 1 entries).
+// Transform `a` (N complex in LDS) in place by the team of 256 threads; `b` is LDS scratch
+// of N complex, or a.  tw: twiddle table in LDS (load_twiddles) in pass order: the pass with
+// radix R that starts at span Ns reads the N_s R - N_s entries from offset Ns - 1 (the
+// offsets telescope: the table holds N - 1 entries).
 // dir = -1 forward, +1 inverse (inverse also scales by 1/N).
 // Must be called by all threads of the workgroup.  Ends with a barrier.
-__device__ inline void fft_lds_general(cplx* a, cplx* b, const cplx* tw, const FftPlan& P, int dir) {
+__device__ inline void fft_team_general(cplx* a, cplx* b, const cplx* tw, const FftPlan& P, int dir, int tid, bool on) {
   const int N = P.n;
-  const int nt = blockDim.x;
-  const int tid = threadIdx.x;
   cplx* src = a;
   cplx* dst = b;
   int Ns = 1;
@@ -201,13 +228,13 @@ __device__ inline void fft_lds_general(cplx* a, cplx* b, const cplx* tw, const F
     const bool rsw = sw && ps > 0, wsw = sw && ps + 1 < npass;
     const cplx* twp = tw + (Ns - 1);
     if (ps < P.n4) {
-      fft_pass<4>(src, dst, twp, N, Ns, dir, 2 * ps, rsw, wsw, 1.0);   // Ns = 4^ps
+      fft_pass<4>(src, dst, twp, N, Ns, dir, 2 * ps, rsw, wsw, 1.0, tid, on);   // Ns = 4^ps
       Ns *= 4;
     } else if (ps < P.n4 + P.n3) {
-      fft_pass<3>(src, dst, twp, N, Ns, dir, -1, rsw, wsw, 1.0);
+      fft_pass<3>(src, dst, twp, N, Ns, dir, -1, rsw, wsw, 1.0, tid, on);
       Ns *= 3;
     } else {
-      fft_pass<2>(src, dst, twp, N, Ns, dir, -1, rsw, wsw, 1.0);
+      fft_pass<2>(src, dst, twp, N, Ns, dir, -1, rsw, wsw, 1.0, tid, on);
       Ns *= 2;
     }
     __syncthreads();
@@ -217,44 +244,59 @@ __device__ inline void fft_lds_general(cplx* a, cplx* b, const cplx* tw, const F
   }
   // result is in src; copy to a if needed and scale for the inverse
   const double sc = dir > 0 ? 1.0 / (double)N : 1.0;
-  if (src != a) {
-    for (int t = tid; t < N; t += nt) a[t] = cscale(src[t], sc);
-  } else if (dir > 0) {
-    for (int t = tid; t < N; t += nt) a[t] = cscale(a[t], sc);
-  }
+  if (on && (src != a || dir > 0))
+    for (int t = tid; t < N; t += FFT_NT) a[t] = cscale(src[t], sc);
   __syncthreads();
 }
 
-// Power-of-two sizes with 256 threads take the unrolled passes, the others the general
-// ones.
-__device__ inline void fft_lds(cplx* a, cplx* b, const cplx* tw, const FftPlan& P, int dir) {
-  if (blockDim.x == 256) {
-    switch (P.n) {
-      case 256: fft_fixed<256>(a, b, tw, dir); return;
-      case 512: fft_fixed<512>(a, b, tw, dir); return;
-      case 1024: fft_fixed<1024>(a, b, tw, dir); return;
-      case 2048: fft_fixed<2048>(a, b, tw, dir); return;
-      default: break;
+// Size classes of the spectral kernels (a template argument, so that a kernel holds the code
+// of one transform and loops of the right length: with every size in every kernel the code of
+// one launch no longer fits the instruction cache of the unit it lands on): N itself for the
+// powers of two from 256, -1 for other sizes up to 1024, 0 for the rest.
+// PT: entries per thread of a team.
+template <int NF>
+struct FftSz {
+  static constexpr int PT = NF > 0 ? NF / FFT_NT : NF < 0 ? 4 : WW_NMAX / FFT_NT;
+  static __device__ __forceinline__ void run(cplx* a, cplx* b, const cplx* tw, const FftPlan& P, int dir, int tid,
+                                             bool on) {
+    if constexpr (NF > 0) {
+      __syncthreads();
+      fft_fixed_from<NF, 1>(a, b, tw, dir, true, tid, on);
+    } else {
+      fft_team_general(a, b, tw, P, dir, tid, on);
     }
   }
-  fft_lds_general(a, b, tw, P, dir);
+};
+// a workgroup of one team, any size
+__device__ inline void fft_lds(cplx* a, cplx* b, const cplx* tw, const FftPlan& P, int dir) {
+  const int tid = threadIdx.x;
+  switch (P.n) {
+    case 256: FftSz<256>::run(a, b, tw, P, dir, tid, true); return;
+    case 512: FftSz<512>::run(a, b, tw, P, dir, tid, true); return;
+    case 1024: FftSz<1024>::run(a, b, tw, P, dir, tid, true); return;
+    case 2048: FftSz<2048>::run(a, b, tw, P, dir, tid, true); return;
+    default: FftSz<0>::run(a, b, tw, P, dir, tid, true);
+  }
 }
 
-// Copy the global twiddle table into LDS (once per kernel, before the first FFT).
+// Copy the global twiddle table into LDS (once per kernel, before the first FFT).  PT:
+// entries per thread of a 256-thread workgroup (ceil(N / 256)); larger workgroups pass a
+// smaller PT.
+template <int PT = WW_NMAX / 256>
 __device__ inline void load_twiddles(cplx* tws, const cplx* __restrict__ twg, int N) {
   // clamped, unconditional loads first (all in flight), then the guarded LDS stores
-  cplx v[WW_NMAX / 256];
+  cplx v[PT];
 #pragma unroll
-  for (int m = 0; m < WW_NMAX / 256; ++m) {
-    const int t = threadIdx.x + 256 * m;
+  for (int m = 0; m < PT; ++m) {
+    const int t = threadIdx.x + blockDim.x * m;
     v[m] = twg[t < N ? t : N - 1];
   }
   // keep the loads here, all in flight, instead of sunk into the guarded stores below
 #pragma unroll
-  for (int m = 0; m < WW_NMAX / 256; ++m) asm volatile("" ::"v"(v[m].x), "v"(v[m].y));
+  for (int m = 0; m < PT; ++m) asm volatile("" ::"v"(v[m].x), "v"(v[m].y));
 #pragma unroll
-  for (int m = 0; m < WW_NMAX / 256; ++m) {
-    const int t = threadIdx.x + 256 * m;
+  for (int m = 0; m < PT; ++m) {
+    const int t = threadIdx.x + blockDim.x * m;
     if (t < N) tws[t] = v[m];
   }
 }

@@ -17,6 +17,10 @@
 #define WW_TB 64          // tile edge of the blocked LU / triangular solves / GEMM
 #define WW_NT 256         // threads per workgroup
 
+// offsets of the mesh tables that the shared kernels read (see ww_mesh.hpp)
+__device__ __forceinline__ size_t mesh_e(int nmax) { return (size_t)nmax; }
+__device__ __forceinline__ size_t mesh_einv(int nmax) { return (size_t)2 * nmax; }
+
 // per-point base quantities, each nmax doubles, at aux + AUX_x * nmax
 enum {
   AUX_EX = 0,   // eta_x
@@ -36,9 +40,9 @@ enum {
 #define COEF_DT 300
 #define COEF_SIZE 320
 
-// Per-thread element sets: thread x owns t = x + 256 m, m < NPT.  Global loads go
-// through clamped, unconditional register loads (all in flight at once); only the
-// stores are guarded by t < N.
+// Per-thread element sets: thread tid of a team of 256 owns t = tid + 256 m, m < PT.
+// Global loads go through clamped, unconditional register loads (all in flight at once);
+// only the stores are guarded by t < N.
 #define NPT (WW_NMAX / WW_NT)
 
 __device__ __forceinline__ int tidx(int m) { return threadIdx.x + WW_NT * m; }
@@ -48,37 +52,40 @@ __device__ __forceinline__ int tclamp(int m, int N) {
 }
 // Pin register values at this point (stops the compiler from sinking their loads into
 // later guarded blocks, which would serialise them).
-__device__ __forceinline__ void pin(const double (&v)[NPT]) {
+template <int PT>
+__device__ __forceinline__ void pin(const double (&v)[PT]) {
 #pragma unroll
-  for (int m = 0; m < NPT; ++m) asm volatile("" ::"v"(v[m]));
+  for (int m = 0; m < PT; ++m) asm volatile("" ::"v"(v[m]));
 }
-__device__ __forceinline__ void gload(double (&v)[NPT], const double* __restrict__ p, int N) {
+template <int PT>
+__device__ __forceinline__ void gload(double (&v)[PT], const double* __restrict__ p, int N, int tid = threadIdx.x) {
 #pragma unroll
-  for (int m = 0; m < NPT; ++m) v[m] = p[tclamp(m, N)];
+  for (int m = 0; m < PT; ++m) {
+    const int t = tid + WW_NT * m;
+    v[m] = p[t < N ? t : N - 1];
+  }
 }
 
 // acc[m] = y[off + t_m] + sum_{j < stage} (a_sj dt) K[j][off + t_m]: stage values of the
 // thread's elements; the loads of two stages for all elements are issued together.
 // crow: the count weights (a_sj dt for a stage, b_s dt for the end of a step).
-__device__ __forceinline__ void stage_combine_vec(double (&acc)[NPT], const double* __restrict__ y,
+template <int PT>
+__device__ __forceinline__ void stage_combine_vec(double (&acc)[PT], const double* __restrict__ y,
                                                   const double* __restrict__ K, size_t kstride, size_t off,
-                                                  const double* __restrict__ crow, int count, int N) {
-#pragma unroll
-  for (int m = 0; m < NPT; ++m) acc[m] = y[off + tclamp(m, N)];
+                                                  const double* __restrict__ crow, int count, int N,
+                                                  int tid = threadIdx.x) {
+  gload(acc, y + off, N, tid);
   for (int j0 = 0; j0 < count; j0 += 2) {
     const int j1 = (j0 + 1 < count) ? j0 + 1 : j0;
     const double a0 = crow[j0];
     const double a1 = (j0 + 1 < count) ? crow[j0 + 1] : 0.0;
-    double k0[NPT], k1[NPT];
-#pragma unroll
-    for (int m = 0; m < NPT; ++m) {
-      k0[m] = K[(size_t)j0 * kstride + off + tclamp(m, N)];
-      k1[m] = K[(size_t)j1 * kstride + off + tclamp(m, N)];
-    }
+    double k0[PT], k1[PT];
+    gload(k0, K + (size_t)j0 * kstride + off, N, tid);
+    gload(k1, K + (size_t)j1 * kstride + off, N, tid);
     pin(k0);
     pin(k1);
 #pragma unroll
-    for (int m = 0; m < NPT; ++m) acc[m] = fma(a1, k1[m], fma(a0, k0[m], acc[m]));
+    for (int m = 0; m < PT; ++m) acc[m] = fma(a1, k1[m], fma(a0, k0[m], acc[m]));
   }
 }
 
@@ -100,14 +107,6 @@ __device__ __forceinline__ double stage_combine(double y0, const double* __restr
   return acc;
 }
 
-// -------------------------------------------------------------------------------------
-// LDS helpers for real-signal pairs
-// -------------------------------------------------------------------------------------
-
-// z[t] = a[t] + i b[t] for t < N
-__device__ __forceinline__ void load_pair(cplx* z, const double* a, const double* b, int N) {
-  for (int t = threadIdx.x; t < N; t += blockDim.x) z[t] = cmk(a ? a[t] : 0.0, b ? b[t] : 0.0);
-}
 
 // -------------------------------------------------------------------------------------
 // state initialisation: q0 = q_fixed + basis @ params (column 0), Qdot(0) = basis
@@ -130,84 +129,90 @@ __global__ void k_init_state(double* __restrict__ y, const double* __restrict__ 
 }
 
 // -------------------------------------------------------------------------------------
-// base stage prep (one workgroup).  Stage value of the base column
+// base stage prep (one workgroup of two teams).  Stage value of the base column
 //   Y_s = y + sum_{j<s} a_sj dt k_j,
 // then eta_x, eta_xx (spectral), varphi', exp(+-surface height) and the Dirichlet
-// data varphi into column 0 of the solve array (rows N..Np-1 zero).
-// Dynamic LDS: 4 N complex (three work buffers and the twiddles).
+// data varphi into column 0 of the solve array (rows N..Np-1 zero).  Team 0 carries eta,
+// team 1 varphi; the two inverse transforms run side by side.
+// yhat (optional): the spectrum of eta + i varphi.  Dynamic LDS: 5 N complex (three work
+// buffers, scratch, twiddles).
 // -------------------------------------------------------------------------------------
-// The prep of one stage on LDS work buffers Z, W, S and the twiddles tws (loaded).
-__device__ inline void base_prep_stage(cplx* Z, cplx* W, cplx* S, const cplx* tws, const FftPlan& P,
-                                       const double* __restrict__ y, const double* __restrict__ K,
-                                       double* __restrict__ Ys, const double* __restrict__ coef, int stage,
-                                       size_t kstride, double* __restrict__ aux, int nmax, double* __restrict__ rhs0,
-                                       int Np, int N, double hsurf, int* __restrict__ status) {
-  const int tid = threadIdx.x;
-  double ev[NPT], pv[NPT];
-  stage_combine_vec(ev, y, K, kstride, 0, coef + stage * 16, stage, N);
-  stage_combine_vec(pv, y, K, kstride, N, coef + stage * 16, stage, N);
-  pin(ev);
-  pin(pv);
-#pragma unroll
-  for (int m = 0; m < NPT; ++m) {
-    const int t = tidx(m);
-    if (t < N) {
-      Ys[t] = ev[m];
-      Ys[N + t] = pv[m];
-      Z[t] = cmk(ev[m], pv[m]);
-    }
-  }
-  fft_lds(Z, S, tws, P, -1);   // spectrum of eta + i varphi
-  for (int t = tid; t < N; t += WW_NT) {
-    cplx E, F;
-    split_pair(Z, t, N, E, F);
-    const int k = wavenum(t, N);
-    cplx ex = sym_deriv(E, k, N);
-    cplx exx = sym_deriv(ex, k, N);
-    W[t] = pack_pair(ex, exx);
-    S[t] = sym_deriv(F, k, N);
-  }
-  fft_lds(W, Z, tws, P, +1);   // eta_x + i eta_xx
-  fft_lds(S, Z, tws, P, +1);   // varphi' (imaginary part zero)
-  bool bad = false, bed = false;
-#pragma unroll
-  for (int m = 0; m < NPT; ++m) {
-    const int i = tidx(m);
-    if (i < N) {
-      aux[AUX_EX * nmax + i] = W[i].x;
-      aux[AUX_EXX * nmax + i] = W[i].y;
-      aux[AUX_PHS * nmax + i] = S[i].x;
-      const double sh = ev[m] + hsurf;
-      aux[AUX_EP * nmax + i] = exp(sh);
-      aux[AUX_EM * nmax + i] = exp(-sh);
-      rhs0[i] = pv[m];
-      bad |= !isfinite(ev[m]) || !isfinite(pv[m]);
-      bed |= hsurf > 0.0 && sh <= 0.0;   // (a NaN height is reported as non-finite)
-    }
-  }
-  for (int i = N + tid; i < Np; i += WW_NT) rhs0[i] = 0.0;
-  // failure detection: non-finite stage state (bit 2) or, at finite depth, a surface
-  // through the bottom (bit 16); status[2] keeps the first 16 step + stage (status[1]
-  // counts the completed steps)
+#define PREP_NT 512
+
+// failure detection: non-finite stage state (bit 2) or, at finite depth, a surface
+// through the bottom (bit 16); status[2] keeps the first 16 step + stage
+__device__ __forceinline__ void flag_state(int* __restrict__ status, bool bad, bool bed, int where) {
   if (status && (bad || bed)) {
     atomicOr(status, (bad ? 2 : 0) | (bed ? 16 : 0));
-    atomicMin(status + 2, status[1] * 16 + stage);
+    atomicMin(status + 2, where);
   }
 }
 
-__global__ __launch_bounds__(WW_NT) void k_base_prep(
+template <int NF>
+__global__ __launch_bounds__(PREP_NT) void k_base_prep(
     const double* __restrict__ y, const double* __restrict__ K, double* __restrict__ Ys,
     const double* __restrict__ coef, int stage, size_t kstride, double* __restrict__ aux, int nmax,
-    double* __restrict__ rhs0, int Np, const cplx* __restrict__ tw, int N, double hsurf, int* __restrict__ status) {
+    double* __restrict__ rhs0, int Np, const cplx* __restrict__ tw, int N, double hsurf, int* __restrict__ status,
+    cplx* __restrict__ yhat) {
+  constexpr int PT = FftSz<NF>::PT;
   extern __shared__ cplx lds[];
   cplx* Z = lds;
   cplx* W = lds + N;
   cplx* S = lds + 2 * N;
-  cplx* tws = lds + 3 * N;
+  cplx* X = lds + 3 * N;
+  cplx* tws = lds + 4 * N;
   const FftPlan P = make_plan(N);
-  const int tid = threadIdx.x;
-  load_twiddles(tws, tw, N);
-  base_prep_stage(Z, W, S, tws, P, y, K, Ys, coef, stage, kstride, aux, nmax, rhs0, Np, N, hsurf, status);
+  const int tid = threadIdx.x & 255, team = threadIdx.x >> 8;
+  load_twiddles<(PT + 1) / 2>(tws, tw, N);
+  double v[PT];   // team 0: eta, team 1: varphi
+  stage_combine_vec(v, y, K, kstride, team ? N : 0, coef + stage * 16, stage, N, tid);
+  pin(v);
+#pragma unroll
+  for (int m = 0; m < PT; ++m) {
+    const int t = tid + WW_NT * m;
+    if (t < N) {
+      Ys[team * N + t] = v[m];
+      if (team) Z[t].y = v[m];
+      else Z[t].x = v[m];
+    }
+  }
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, team == 0);   // spectrum of eta + i varphi
+  for (int t = tid; t < N; t += WW_NT) {
+    cplx E, F;
+    split_pair(Z, t, N, E, F);
+    const int k = wavenum(t, N);
+    if (team) {
+      S[t] = sym_deriv(F, k, N);
+      if (yhat) yhat[t] = Z[t];
+    } else {
+      cplx ex = sym_deriv(E, k, N);
+      W[t] = pack_pair(ex, sym_deriv(ex, k, N));
+    }
+  }
+  // team 0: eta_x + i eta_xx; team 1: varphi' (imaginary part zero)
+  FftSz<NF>::run(team ? S : W, team ? X : Z, tws, P, +1, tid, true);
+  bool bad = false, bed = false;
+#pragma unroll
+  for (int m = 0; m < PT; ++m) {
+    const int i = tid + WW_NT * m;
+    if (i < N) {
+      bad |= !isfinite(v[m]);
+      if (team) {
+        aux[AUX_PHS * nmax + i] = S[i].x;
+        rhs0[i] = v[m];
+      } else {
+        aux[AUX_EX * nmax + i] = W[i].x;
+        aux[AUX_EXX * nmax + i] = W[i].y;
+        const double sh = v[m] + hsurf;
+        aux[AUX_EP * nmax + i] = exp(sh);
+        aux[AUX_EM * nmax + i] = exp(-sh);
+        bed |= hsurf > 0.0 && sh <= 0.0;   // (a NaN height is reported as non-finite)
+      }
+    }
+  }
+  for (int i = N + (int)threadIdx.x; i < Np; i += PREP_NT) rhs0[i] = 0.0;
+  // (status[1] counts the completed steps)
+  if (status && (bad || bed)) flag_state(status, bad, bed, status[1] * 16 + stage);
 }
 
 // -------------------------------------------------------------------------------------
@@ -698,61 +703,69 @@ __global__ __launch_bounds__(8 * TR * GSPLIT) void k_gemm_rm(const T* __restrict
 // -------------------------------------------------------------------------------------
 // gamma = d mu / d alpha and (1/2) H gamma for a pair of columns (eq. (G)):
 // spectrum of mu_a + i mu_b, gamma_hat = i k mu_hat, (H gamma)_hat = |k| mu_hat
-// (both zero at k = 0 and at Nyquist).  Rows N..Np-1 of the outputs are zero.
-// Dynamic LDS: 4 N complex (three work buffers and the twiddles).
+// (both zero at k = 0 and at Nyquist).  Rows N..Np-1 of the outputs are zero.  Two teams:
+// the inverse transforms of the two columns run side by side.
+// Dynamic LDS: 5 N complex (three work buffers, scratch and the twiddles).
 // -------------------------------------------------------------------------------------
+template <int NT>
 __device__ inline void refine_check_col(const double* __restrict__ rc, const double* __restrict__ bc, int N,
-                                        double tol, int* __restrict__ status, int flag);
+                                        double tol, int* __restrict__ status, int flag, double* red);
 
-__global__ __launch_bounds__(WW_NT) void k_gamma(const double* __restrict__ Mu, int Np, int ncols,
-                                                 double* __restrict__ Gam, double* __restrict__ HG,
-                                                 const cplx* __restrict__ tw, int N,
-                                                 const double* __restrict__ chk_r, const double* __restrict__ chk_b,
-                                                 double chk_tol, int* __restrict__ status, int chk_flag) {
+template <int NF>
+__global__ __launch_bounds__(PREP_NT) void k_gamma(const double* __restrict__ Mu, int Np, int ncols,
+                                                   double* __restrict__ Gam, double* __restrict__ HG,
+                                                   const cplx* __restrict__ tw, int N,
+                                                   const double* __restrict__ chk_r, const double* __restrict__ chk_b,
+                                                   double chk_tol, int* __restrict__ status, int chk_flag) {
+  constexpr int PT = FftSz<NF>::PT;
   // the refinement test of the solve that produced Mu's first column, when chk_r is
   // given (the check kernel's work, folded into this launch)
-  if (chk_r && blockIdx.x == 0) refine_check_col(chk_r, chk_b, N, chk_tol, status, chk_flag);
   extern __shared__ cplx lds[];
+  // (in the transform buffers: at N = 2048 they take all of a compute unit's LDS)
+  if (chk_r && blockIdx.x == 0) {
+    refine_check_col<PREP_NT>(chk_r, chk_b, N, chk_tol, status, chk_flag, reinterpret_cast<double*>(lds));
+    __syncthreads();
+  }
   cplx* Z = lds;
   cplx* W = lds + N;
   cplx* S = lds + 2 * N;
-  cplx* tws = lds + 3 * N;
+  cplx* X = lds + 3 * N;
+  cplx* tws = lds + 4 * N;
   const FftPlan P = make_plan(N);
-  load_twiddles(tws, tw, N);
+  const int tid = threadIdx.x & 255, team = threadIdx.x >> 8;
+  load_twiddles<(PT + 1) / 2>(tws, tw, N);
   const int ca = 2 * blockIdx.x, cb = ca + 1;
   const bool hasb = cb < ncols;
-  const int tid = threadIdx.x;
   {
-    double va[NPT], vb[NPT];
-    gload(va, Mu + (size_t)ca * Np, N);
-    gload(vb, Mu + (size_t)(hasb ? cb : ca) * Np, N);
-    pin(va);
-    pin(vb);
+    double v[PT];
+    gload(v, Mu + (size_t)(team && hasb ? cb : ca) * Np, N, tid);
+    pin(v);
 #pragma unroll
-    for (int m = 0; m < NPT; ++m) {
-      const int t = tidx(m);
-      if (t < N) Z[t] = cmk(va[m], hasb ? vb[m] : 0.0);
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      if (t < N) {
+        if (team) Z[t].y = hasb ? v[m] : 0.0;
+        else Z[t].x = v[m];
+      }
     }
   }
-  fft_lds(Z, W, tws, P, -1);
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, team == 0);
   for (int t = tid; t < N; t += WW_NT) {
     cplx A, B;
     split_pair(Z, t, N, A, B);
     const int k = wavenum(t, N);
     const double hk = (k == 0 || 2 * k == N || 2 * k == -N) ? 0.0 : 0.5 * fabs((double)k);
-    W[t] = pack_pair(sym_deriv(A, k, N), cscale(A, hk));
-    S[t] = pack_pair(sym_deriv(B, k, N), cscale(B, hk));
+    if (team) S[t] = pack_pair(sym_deriv(B, k, N), cscale(B, hk));
+    else W[t] = pack_pair(sym_deriv(A, k, N), cscale(A, hk));
   }
-  fft_lds(W, Z, tws, P, +1);
-  if (hasb) fft_lds(S, Z, tws, P, +1);
+  FftSz<NF>::run(team ? S : W, team ? X : Z, tws, P, +1, tid, !team || hasb);
+  if (team && !hasb) return;
+  const cplx* V = team ? S : W;
+  const size_t o = (size_t)(team ? cb : ca) * Np;
   for (int t = tid; t < Np; t += WW_NT) {
     const bool in = t < N;
-    Gam[(size_t)ca * Np + t] = in ? W[t].x : 0.0;
-    HG[(size_t)ca * Np + t] = in ? W[t].y : 0.0;
-    if (hasb) {
-      Gam[(size_t)cb * Np + t] = in ? S[t].x : 0.0;
-      HG[(size_t)cb * Np + t] = in ? S[t].y : 0.0;
-    }
+    Gam[o + t] = in ? V[t].x : 0.0;
+    HG[o + t] = in ? V[t].y : 0.0;
   }
 }
 
@@ -763,21 +776,26 @@ __global__ __launch_bounds__(WW_NT) void k_gamma(const double* __restrict__ Mu, 
 //   G phi_i = (1/2) H gamma_i + sum_j Gm_ij gamma_j          (row-major Gm)
 //   r_i     = psi_i - sum_j A_ij mu_j                          (row-major A)
 // the FP64 residual of the refined solve.  The convergence test of that solve
-// (max |r| <= tol max |psi|) needs both maxima over all rows: each wave folds its own
-// into chk[0] = max |r|, chk[1] = max |psi| with an atomic maximum on the bit patterns
-// (non-negative doubles order like their bits; a NaN residual is larger than any
-// finite one), and the next kernel on the stream (k_base_rhs) takes the decision and
-// clears chk.  Rows N..Np-1 of Gphi are zero.  Dynamic LDS: 4 N complex.  A workgroup
+// (max |r| <= tol max |psi|) needs both maxima over all rows: every workgroup leaves its own
+// in chk[block] (max |r|; a NaN residual counts as infinite) and chk[grid + block] (max
+// |psi|), and the next kernel on the stream (k_base_stage) takes the decision.  (One atomic
+// maximum per wave on two shared words took 10 us of this launch's 23.)
+//  Rows N..Np-1 of Gphi are zero.  Dynamic LDS: 4 N complex.  A workgroup
 // takes `rows` consecutive rows (a multiple of 4; grid ceil(Np / rows)).
 // -------------------------------------------------------------------------------------
-// NR: entries of a row per lane, N <= 64 NR (16 up to N = 1024, 32 above), so that the
-// row prefetch holds no more registers than the grid needs.
-template <int NR>
+// The entries of a wave's rows come from memory once; with two rows a wave (8 per
+// workgroup) and rows of at most 1024 entries both rows are in flight before the
+// transforms, which do not need them.
+// -------------------------------------------------------------------------------------
+template <int NF>
 __global__ __launch_bounds__(WW_NT) void k_base_dtn(const double* __restrict__ mu, const double* __restrict__ psi,
                                                     const double* __restrict__ Gmr, const double* __restrict__ Ar,
                                                     int Np, const cplx* __restrict__ tw, int N,
                                                     double* __restrict__ Gphi,
-                                                    unsigned long long* __restrict__ chk, int rows) {
+                                                    double* __restrict__ chk, int rows) {
+  constexpr int PT = FftSz<NF>::PT;
+  constexpr int NR = 4 * PT;               // entries of a row per lane, N <= 64 NR
+  constexpr int PRE = NR <= 16 ? 2 : 1;    // rows in flight
   extern __shared__ cplx lds[];
   cplx* Z = lds;
   cplx* W = lds + N;
@@ -786,10 +804,8 @@ __global__ __launch_bounds__(WW_NT) void k_base_dtn(const double* __restrict__ m
   double* gs = xs + N;                                   // gamma (N doubles)
   const int tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
-  // a row's entries of Gm and A, all in flight at once (clamped, unconditional loads);
-  // the first row's loads are issued before the transforms, which they do not need
-  double gv[NR], av[NR];
-  auto load_row = [&](int row) {
+  double gv[PRE][NR], av[PRE][NR];
+  auto load_row = [&](int b, int row) {   // clamped, unconditional loads
     const int rr = row < N ? row : N - 1;
     const double* gr = Gmr + (size_t)rr * Np;
     const double* ar = Ar + (size_t)rr * Np;
@@ -797,20 +813,22 @@ __global__ __launch_bounds__(WW_NT) void k_base_dtn(const double* __restrict__ m
     for (int m = 0; m < NR; ++m) {
       const int j = lane + 64 * m;
       const int jj = j < N ? j : N - 1;
-      gv[m] = gr[jj];
-      av[m] = ar[jj];
+      gv[b][m] = gr[jj];
+      av[b][m] = ar[jj];
     }
   };
   const int row0 = blockIdx.x * rows + wv;
-  load_row(row0);
+#pragma unroll
+  for (int b = 0; b < PRE; ++b)
+    if (b == 0 || rows > 4) load_row(b, row0 + 4 * b);
   const FftPlan P = make_plan(N);
-  load_twiddles(tws, tw, N);
+  load_twiddles<PT>(tws, tw, N);
   {
-    double va[NPT];
+    double va[PT];
     gload(va, mu, N);
     pin(va);
 #pragma unroll
-    for (int m = 0; m < NPT; ++m) {
+    for (int m = 0; m < PT; ++m) {
       const int t = tidx(m);
       if (t < N) {
         Z[t] = cmk(va[m], 0.0);
@@ -818,7 +836,7 @@ __global__ __launch_bounds__(WW_NT) void k_base_dtn(const double* __restrict__ m
       }
     }
   }
-  fft_lds(Z, W, tws, P, -1);
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, true);
   for (int t = tid; t < N; t += WW_NT) {
     const int k = wavenum(t, N);
     const double hk = (k == 0 || 2 * k == N || 2 * k == -N) ? 0.0 : 0.5 * fabs((double)k);
@@ -826,60 +844,75 @@ __global__ __launch_bounds__(WW_NT) void k_base_dtn(const double* __restrict__ m
     // = |k| mu_hat / 2; both real signals travel as one complex signal
     W[t] = pack_pair(sym_deriv(Z[t], k, N), cscale(Z[t], hk));
   }
-  fft_lds(W, Z, tws, P, +1);
+  FftSz<NF>::run(W, Z, tws, P, +1, tid, true);
   for (int t = tid; t < N; t += WW_NT) gs[t] = W[t].x;
   __syncthreads();
   double mr = 0.0, mb = 0.0;
-  for (int q = 0; q < rows / 4; ++q) {
-    const int row = blockIdx.x * rows + q * 4 + wv;
-    if (row >= Np) break;
-    if (q > 0) load_row(row);
-    if (row >= N) {
-      if (lane == 0) Gphi[row] = 0.0;
-      continue;
-    }
-    double s0 = 0.0, s1 = 0.0, t0 = 0.0, t1 = 0.0;
+  for (int q0 = 0; q0 < rows / 4; q0 += PRE) {
 #pragma unroll
-    for (int m = 0; m < NR; m += 2) {
-      const int j0 = lane + 64 * m, j1 = j0 + 64;
-      if (j0 < N) {
-        s0 = fma(gv[m], gs[j0], s0);
-        t0 = fma(av[m], xs[j0], t0);
+    for (int b = 0; b < PRE; ++b) {
+      const int q = q0 + b, row = row0 + 4 * q;
+      if (q >= rows / 4 || row >= Np) break;
+      if (q >= PRE) load_row(b, row);
+      if (row >= N) {
+        if (lane == 0) Gphi[row] = 0.0;
+        continue;
       }
-      if (j1 < N) {
-        s1 = fma(gv[m + 1], gs[j1], s1);
-        t1 = fma(av[m + 1], xs[j1], t1);
+      double s0 = 0.0, s1 = 0.0, t0 = 0.0, t1 = 0.0;
+#pragma unroll
+      for (int m = 0; m < NR; m += 2) {
+        const int j0 = lane + 64 * m, j1 = j0 + 64;
+        if (j0 < N) {
+          s0 = fma(gv[b][m], gs[j0], s0);
+          t0 = fma(av[b][m], xs[j0], t0);
+        }
+        if (j1 < N) {
+          s1 = fma(gv[b][m + 1], gs[j1], s1);
+          t1 = fma(av[b][m + 1], xs[j1], t1);
+        }
       }
-    }
-    double s = s0 + s1, t = t0 + t1;
-    for (int off = 32; off > 0; off >>= 1) {
-      s += __shfl_down(s, off, 64);
-      t += __shfl_down(t, off, 64);
-    }
-    if (lane == 0) {
-      Gphi[row] = W[row].y + s;
-      const double r = psi[row] - t;
-      mr = fmax(mr, fabs(r));
-      if (r != r) mr = INFINITY;
-      mb = fmax(mb, fabs(psi[row]));
+      double s = s0 + s1, t = t0 + t1;
+      for (int off = 32; off > 0; off >>= 1) {
+        s += __shfl_down(s, off, 64);
+        t += __shfl_down(t, off, 64);
+      }
+      if (lane == 0) {
+        Gphi[row] = W[row].y + s;
+        const double r = psi[row] - t;
+        mr = fmax(mr, fabs(r));
+        if (r != r) mr = INFINITY;
+        mb = fmax(mb, fabs(psi[row]));
+      }
     }
   }
-  if (lane == 0 && chk) {
-    atomicMax(chk, (unsigned long long)__double_as_longlong(mr));
-    atomicMax(chk + 1, (unsigned long long)__double_as_longlong(mb));
+  __syncthreads();   // the transform buffer is free: the waves' maxima
+  double* red = reinterpret_cast<double*>(Z);
+  if (lane == 0) {
+    red[wv] = mr;
+    red[4 + wv] = mb;
+  }
+  __syncthreads();
+  if (tid < 2) {
+    const double* m = red + 4 * tid;
+    chk[tid * gridDim.x + blockIdx.x] = fmax(fmax(m[0], m[1]), fmax(m[2], m[3]));
   }
 }
 
-// The convergence test of a lagged-factor solve from the maxima left by k_base_dtn
-// (one thread), then the maxima are cleared for the next stage.
-__device__ __forceinline__ void lagged_check(unsigned long long* __restrict__ chk, double tol, int* __restrict__ status,
-                                             int flag) {
-  if (!chk || threadIdx.x != 0) return;
-  const double mr = __longlong_as_double((long long)chk[0]);
-  const double mb = __longlong_as_double((long long)chk[1]);
-  if (!(mr <= tol * mb)) atomicOr(status, flag);
-  chk[0] = 0ull;
-  chk[1] = 0ull;
+// The convergence test of a lagged-factor solve from the n maxima of |r| and of |psi| left by
+// k_base_dtn, by one wave.
+__device__ __forceinline__ void lagged_check(const double* __restrict__ chk, int n, double tol,
+                                             int* __restrict__ status, int flag) {
+  const int lane = threadIdx.x & 63;
+  double mr = 0.0, mb = 0.0;
+  for (int i = lane; i < n; i += 64) {
+    mr = fmax(mr, chk[i]);
+    mb = fmax(mb, chk[n + i]);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    mr = fmax(mr, __shfl_xor(mr, off));
+    mb = fmax(mb, __shfl_xor(mb, off));
+  }
+  if (lane == 0 && !(mr <= tol * mb)) atomicOr(status, flag);
 }
 
 // -------------------------------------------------------------------------------------
@@ -889,25 +922,37 @@ __device__ __forceinline__ void lagged_check(unsigned long long* __restrict__ ch
 //   varphi_t = P[v eta_t - u^2/2 - v^2/2 - g eta + tau d/dx(eta_x/sqrt(1 + eta_x^2))]
 // both filtered; u, v, (1 + eta_x^2)^{3/2} are kept for the variational columns.
 // -------------------------------------------------------------------------------------
-// The right-hand side of one stage on LDS work buffers Z, W, S and the twiddles tws.
-__device__ inline void base_rhs_stage(cplx* Z, cplx* W, cplx* S, const cplx* tws, const FftPlan& P,
-                                      const double* __restrict__ Ys, const double* __restrict__ Gphi,
-                                      double* __restrict__ aux, int nmax, double* __restrict__ Kout,
-                                      const double* __restrict__ sig, int N, double g, double tau) {
-  const int tid = threadIdx.x;
-  {
-    double exv[NPT], psv[NPT], Gv[NPT], etv[NPT];
-    gload(exv, aux + AUX_EX * nmax, N);
-    gload(psv, aux + AUX_PHS * nmax, N);
-    gload(Gv, Gphi, N);
-    gload(etv, Ys, N);
+// One workgroup of two teams: the transforms of (eta_t, undifferentiated terms) and of the
+// tension term run side by side (without tension there is none).  Dynamic LDS: 5 N complex.
+template <int NF>
+__global__ __launch_bounds__(PREP_NT) void k_base_rhs(const double* __restrict__ Ys, const double* __restrict__ Gphi,
+                                                      double* __restrict__ aux, int nmax, double* __restrict__ Kout,
+                                                      const cplx* __restrict__ tw, const double* __restrict__ sig,
+                                                      int N, double g, double tau) {
+  constexpr int PT = FftSz<NF>::PT;
+  extern __shared__ cplx lds[];
+  cplx* Z = lds;
+  cplx* W = lds + N;
+  cplx* S = lds + 2 * N;
+  cplx* X = lds + 3 * N;
+  cplx* tws = lds + 4 * N;
+  const FftPlan P = make_plan(N);
+  const int tid = threadIdx.x & 255, team = threadIdx.x >> 8;
+  load_twiddles<(PT + 1) / 2>(tws, tw, N);
+  double exv[PT];
+  gload(exv, aux + AUX_EX * nmax, N, tid);
+  if (team == 0) {
+    double psv[PT], Gv[PT], etv[PT];
+    gload(psv, aux + AUX_PHS * nmax, N, tid);
+    gload(Gv, Gphi, N, tid);
+    gload(etv, Ys, N, tid);
     pin(exv);
     pin(psv);
     pin(Gv);
     pin(etv);
 #pragma unroll
-    for (int m = 0; m < NPT; ++m) {
-      const int t = tidx(m);
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
       if (t < N) {
         const double ex = exv[m], ps = psv[m], G = Gv[m];
         const double den = 1.0 + ex * ex;
@@ -917,68 +962,274 @@ __device__ inline void base_rhs_stage(cplx* Z, cplx* W, cplx* S, const cplx* tws
         aux[AUX_V * nmax + t] = v;
         aux[AUX_W3 * nmax + t] = den * sqrt(den);
         Z[t] = cmk(G, v * G - 0.5 * u * u - 0.5 * v * v - g * etv[m]);
-        S[t] = cmk(tau * ex / sqrt(den), 0.0);
       }
     }
+  } else {
+#pragma unroll
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      if (t < N) S[t] = cmk(tau * exv[m] / sqrt(1.0 + exv[m] * exv[m]), 0.0);
+    }
   }
-  fft_lds(Z, W, tws, P, -1);
-  fft_lds(S, W, tws, P, -1);
-  for (int t = tid; t < N; t += WW_NT) {
-    cplx A, C, F, dummy;
+  FftSz<NF>::run(team ? S : Z, team ? X : W, tws, P, -1, tid, team == 0 || tau != 0.0);
+  for (int t = threadIdx.x; t < N; t += PREP_NT) {
+    cplx A, C, F = cmk(0.0, 0.0), dummy;
     split_pair(Z, t, N, A, C);
-    split_pair(S, t, N, F, dummy);
+    if (tau != 0.0) split_pair(S, t, N, F, dummy);
     const int k = wavenum(t, N);
     const double sg = sig[t];
     cplx et = cscale(A, sg);
     cplx pt = (k == 0) ? cmk(0.0, 0.0) : cscale(cadd(C, sym_deriv(F, k, N)), sg);
     W[t] = pack_pair(et, pt);
   }
-  fft_lds(W, Z, tws, P, +1);
-  for (int t = tid; t < N; t += WW_NT) {
+  FftSz<NF>::run(W, Z, tws, P, +1, tid, team == 0);
+  for (int t = threadIdx.x; t < N; t += PREP_NT) {
     Kout[t] = W[t].x;
     Kout[N + t] = W[t].y;
   }
 }
 
-__global__ __launch_bounds__(WW_NT) void k_base_rhs(const double* __restrict__ Ys, const double* __restrict__ Gphi,
-                                                    double* __restrict__ aux, int nmax, double* __restrict__ Kout,
-                                                    unsigned long long* __restrict__ chk, double chk_tol,
-                                                    int* __restrict__ status,
-                                                    const cplx* __restrict__ tw, const double* __restrict__ sig,
-                                                    int N, double g, double tau) {
-  extern __shared__ cplx lds[];
-  cplx* Z = lds;
-  cplx* W = lds + N;
-  cplx* S = lds + 2 * N;
-  cplx* tws = lds + 3 * N;
-  const FftPlan P = make_plan(N);
-  const int tid = threadIdx.x;
-  lagged_check(chk, chk_tol, status, 32);
-  load_twiddles(tws, tw, N);
-  base_rhs_stage(Z, W, S, tws, P, Ys, Gphi, aux, nmax, Kout, sig, N, g, tau);
-}
+// -------------------------------------------------------------------------------------
+// The right-hand side of stage s and the prep of the next stage state in one workgroup, on
+// the march's critical path: the base column of a lagged-factor march is kept in spectral
+// form.  The slope's spectrum K_s^ (of eta_t + i varphi_t, filtered) goes to the stage
+// slot, the next stage state's spectrum is
+//   Y^ = y^ + sum_{j <= s} w_j K_j^       (w: a row of the tableau times dt)
+// or, at the end of a step (end = 1, w = b dt), y^ <- S_F Y^ with the filter symbol, and
+// three inverse transforms give eta + i varphi, eta_x + i eta_xx and varphi'.  Bound by
+// latency (one compute unit): three teams run the two forward transforms and then the
+// three inverse ones side by side, and the terms j < s of the combination are summed
+// while the forward transforms run.  One transform after the other, with the combination
+// and the forward transform of the stage state in physical space, the same work took 24.5
+// us at N = 1024 (27.8 us in the march, and 50 us at the end of a step in three
+// launches); so: 11.7 us alone and 13.7 us in the march, at the end of a step too.
+// MAP: on the mapped grid (the right-hand side of eq. (ww) with x-derivatives (1/E)
+// d/dalpha, G phi / E and the E-weighted zero mean).  Dynamic LDS: 7 N complex, or 4 N
+// (transforms in place) where 7 N does not fit.
+// -------------------------------------------------------------------------------------
+#define STAGE_NT 768
+struct StageArgs {
+  const double* Gphi;          // (1/2) H gamma + Gm gamma
+  double* aux_cur;             // per-point quantities of stage s (in) and of the next (out)
+  double* aux_next;
+  double* Ys;                  // base stage state: eta of stage s (in), the next state (out)
+  double* y;                   // base state in physical space (written at the end of a step)
+  cplx* yhat;                  // its spectrum
+  double* K;                   // stage slots (stride kstride doubles): spectra in the base column
+  size_t kstride;
+  const double* w;             // s + 1 weights
+  const double* chk;           // the maxima of the lagged solve's test (nchk workgroups)
+  int* status;
+  const cplx* tw;
+  const double* sig;
+  const double* mesh;          // MAP: mesh tables
+  double* rhs0;
+  double chk_tol, g, tau, hsurf;
+  int nchk, s, end, check, nmax, N, Np, inplace;
+};
 
-// The right-hand side of stage s and, in the same workgroup, the prep of stage s + 1
-// (s + 1 < stages of the step): one launch and one twiddle load fewer on the march's
-// critical path.  The prep reads K_s through global memory after a barrier.
-__global__ __launch_bounds__(WW_NT) void k_base_rhs_prep(
-    const double* __restrict__ Gphi, double* __restrict__ aux_cur, double* __restrict__ Kcur,
-    unsigned long long* __restrict__ chk, double chk_tol, const double* __restrict__ sig, double g, double tau,
-    const double* __restrict__ y, const double* __restrict__ K, double* __restrict__ Ys,
-    const double* __restrict__ coef, int stage_next, size_t kstride, double* __restrict__ aux_next,
-    double* __restrict__ rhs0, int Np, double hsurf, int nmax, const cplx* __restrict__ tw, int N,
-    int* __restrict__ status) {
+template <int NF, int MAP>
+__global__ __launch_bounds__(STAGE_NT) void k_base_stage(StageArgs q) {
+  constexpr int PT = FftSz<NF>::PT;
   extern __shared__ cplx lds[];
-  cplx* Z = lds;
-  cplx* W = lds + N;
-  cplx* S = lds + 2 * N;
+  __shared__ double red[4];
+  const int N = q.N, nmax = q.nmax;
+  const int tid = threadIdx.x & 255, team = threadIdx.x >> 8;
+  cplx* B[3] = {lds, lds + N, lds + 2 * N};
   cplx* tws = lds + 3 * N;
+  cplx* buf = lds + team * N;
+  cplx* scr = q.inplace ? buf : lds + (4 + team) * N;
+  cplx* const Yb = B[2];   // the next state's spectrum: team 2's buffer
   const FftPlan P = make_plan(N);
-  lagged_check(chk, chk_tol, status, 32);
-  load_twiddles(tws, tw, N);
-  base_rhs_stage(Z, W, S, tws, P, Ys, Gphi, aux_cur, nmax, Kcur, sig, N, g, tau);
-  __syncthreads();   // K_s (global) and the LDS buffers are complete
-  base_prep_stage(Z, W, S, tws, P, y, K, Ys, coef, stage_next, kstride, aux_next, nmax, rhs0, Np, N, hsurf, status);
+  const int done = q.status[1];   // steps completed before this one
+  load_twiddles<(PT + 2) / 3>(tws, q.tw, N);
+  cplx acc[PT];   // team 2: y^ + sum over the earlier slopes
+  double Gv[PT];
+  if (team == 0) {
+    double exv[PT], psv[PT], etv[PT], iv[PT];
+    gload(exv, q.aux_cur + AUX_EX * nmax, N, tid);
+    gload(psv, q.aux_cur + AUX_PHS * nmax, N, tid);
+    gload(Gv, q.Gphi, N, tid);
+    gload(etv, q.Ys, N, tid);
+    if (MAP) gload(iv, q.mesh + mesh_einv(nmax), N, tid);
+    pin(exv);
+    pin(psv);
+    pin(Gv);
+    pin(etv);
+#pragma unroll
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      double ex = exv[m], ps = psv[m];
+      if (MAP) {
+        ex *= iv[m];
+        ps *= iv[m];
+        Gv[m] *= iv[m];
+      }
+      const double G = Gv[m];
+      const double den = 1.0 + ex * ex;
+      const double u = (ps - ex * G) / den;
+      const double v = (ex * ps + G) / den;
+      if (t < N) {
+        q.aux_cur[AUX_U * nmax + t] = u;
+        q.aux_cur[AUX_V * nmax + t] = v;
+        q.aux_cur[AUX_W3 * nmax + t] = den * sqrt(den);
+        B[0][t] = cmk(G, v * G - 0.5 * u * u - 0.5 * v * v - q.g * etv[m]);
+      }
+    }
+  } else if (team == 1) {
+    if (q.tau != 0.0) {
+      double exv[PT], iv[PT];
+      gload(exv, q.aux_cur + AUX_EX * nmax, N, tid);
+      if (MAP) gload(iv, q.mesh + mesh_einv(nmax), N, tid);
+#pragma unroll
+      for (int m = 0; m < PT; ++m) {
+        const int t = tid + WW_NT * m;
+        const double ex = MAP ? exv[m] * iv[m] : exv[m];
+        if (t < N) B[1][t] = cmk(q.tau * ex / sqrt(1.0 + ex * ex), 0.0);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      acc[m] = q.yhat[t < N ? t : N - 1];
+    }
+    for (int j = 0; j < q.s; ++j) {
+      const double w = q.w[j];
+      const cplx* Kj = reinterpret_cast<const cplx*>(q.K + (size_t)j * q.kstride);
+      cplx kv[PT];
+#pragma unroll
+      for (int m = 0; m < PT; ++m) {
+        const int t = tid + WW_NT * m;
+        kv[m] = Kj[t < N ? t : N - 1];
+      }
+#pragma unroll
+      for (int m = 0; m < PT; ++m) acc[m] = cmk(fma(w, kv[m].x, acc[m].x), fma(w, kv[m].y, acc[m].y));
+    }
+    if (tid < 64) lagged_check(q.chk, q.nchk, q.chk_tol, q.status, 32);
+  }
+  if constexpr (MAP) {
+    // the tension term's derivative and the E-weighted mean, in physical space
+    if (q.tau != 0.0) {
+      FftSz<NF>::run(buf, scr, tws, P, -1, tid, team == 1);
+      if (team == 1)
+        for (int t = tid; t < N; t += WW_NT) buf[t] = sym_deriv(buf[t], wavenum(t, N), N);
+      FftSz<NF>::run(buf, scr, tws, P, +1, tid, team == 1);
+    }
+    double sum = 0.0, pre[PT];
+    if (team == 0) {
+      double ew[PT], iv[PT];
+      gload(ew, q.mesh + mesh_e(nmax), N, tid);
+      gload(iv, q.mesh + mesh_einv(nmax), N, tid);
+#pragma unroll
+      for (int m = 0; m < PT; ++m) {
+        const int t = tid + WW_NT * m;
+        pre[m] = 0.0;
+        if (t < N) {
+          pre[m] = B[0][t].y;
+          if (q.tau != 0.0) pre[m] += B[1][t].x * iv[m];
+          sum += ew[m] * pre[m];
+        }
+      }
+      for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+      if ((tid & 63) == 0) red[tid >> 6] = sum;
+    }
+    __syncthreads();
+    if (team == 0) {
+      const double mean = (((red[0] + red[1]) + red[2]) + red[3]) / (double)N;
+#pragma unroll
+      for (int m = 0; m < PT; ++m) {
+        const int t = tid + WW_NT * m;
+        if (t < N) B[0][t].y = pre[m] - mean;
+      }
+    }
+    FftSz<NF>::run(buf, scr, tws, P, -1, tid, team == 0);
+  } else {
+    FftSz<NF>::run(buf, scr, tws, P, -1, tid, team == 0 || (team == 1 && q.tau != 0.0));
+  }
+  if (team == 2) {
+    const double w = q.w[q.s];
+    cplx* Ks = reinterpret_cast<cplx*>(q.K + (size_t)q.s * q.kstride);
+#pragma unroll
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      if (t < N) {
+        const double sg = q.sig[t];
+        const int k = wavenum(t, N);
+        cplx ks;
+        if (MAP) {
+          ks = cscale(B[0][t], sg);
+        } else {
+          cplx A, C, F = cmk(0.0, 0.0), dummy;
+          split_pair(B[0], t, N, A, C);
+          if (q.tau != 0.0) split_pair(B[1], t, N, F, dummy);
+          const cplx pt = (k == 0) ? cmk(0.0, 0.0) : cscale(cadd(C, sym_deriv(F, k, N)), sg);
+          ks = pack_pair(cscale(A, sg), pt);
+        }
+        Ks[t] = ks;
+        cplx Y = cmk(fma(w, ks.x, acc[m].x), fma(w, ks.y, acc[m].y));
+        if (q.end) {
+          Y = cscale(Y, sg);
+          q.yhat[t] = Y;
+        }
+        Yb[t] = Y;
+      }
+    }
+  }
+  __syncthreads();
+  // the three spectra: eta + i varphi, eta_x + i eta_xx, varphi' (team 2 replaces Yb by its
+  // own after everyone has read it)
+  {
+    cplx own[PT];
+#pragma unroll
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      if (t < N) {
+        if (team == 0) {
+          own[m] = Yb[t];
+        } else {
+          cplx E, F;
+          split_pair(Yb, t, N, E, F);
+          const int k = wavenum(t, N);
+          const cplx d = sym_deriv(team == 1 ? E : F, k, N);
+          own[m] = team == 1 ? pack_pair(d, sym_deriv(d, k, N)) : d;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      if (t < N) buf[t] = own[m];
+    }
+  }
+  FftSz<NF>::run(buf, scr, tws, P, +1, tid, true);
+  bool bad = false, bed = false;
+  for (int t = tid; t < N; t += WW_NT) {
+    const cplx z = buf[t];
+    if (team == 0) {
+      q.Ys[t] = z.x;
+      q.Ys[N + t] = z.y;
+      q.rhs0[t] = z.y;
+      if (q.end) {
+        q.y[t] = z.x;
+        q.y[N + t] = z.y;
+      }
+      const double sh = z.x + q.hsurf;
+      q.aux_next[AUX_EP * nmax + t] = exp(sh);
+      q.aux_next[AUX_EM * nmax + t] = exp(-sh);
+      bad |= !isfinite(z.x) || !isfinite(z.y);
+      bed |= q.hsurf > 0.0 && sh <= 0.0;
+    } else if (team == 1) {
+      q.aux_next[AUX_EX * nmax + t] = z.x;
+      q.aux_next[AUX_EXX * nmax + t] = z.y;
+    } else {
+      q.aux_next[AUX_PHS * nmax + t] = z.x;
+    }
+  }
+  for (int i = N + (int)threadIdx.x; i < q.Np; i += STAGE_NT) q.rhs0[i] = 0.0;
+  if (q.check && (bad || bed)) flag_state(q.status, bad, bed, q.end ? (done + 1) * 16 : done * 16 + q.s + 1);
+  if (q.end && threadIdx.x == 0) q.status[1] = done + 1;
 }
 
 // -------------------------------------------------------------------------------------
@@ -1016,67 +1267,66 @@ __global__ void k_col_pre(const double* __restrict__ y, const double* __restrict
 // transforms the four real signals G psidot, etadot u, (undifferentiated terms of
 // phidot_t) and (differentiated terms of phidot_t) and combines them spectrally.
 // -------------------------------------------------------------------------------------
-__global__ __launch_bounds__(WW_NT) void k_col_rhs(const double* __restrict__ Ys, const double* __restrict__ Gpsi,
-                                                   int Np, const double* __restrict__ aux, int nmax,
-                                                   double* __restrict__ Kout, const cplx* __restrict__ tw,
-                                                   const double* __restrict__ sig, int N, double g, double tau) {
+// Two teams: the two transforms of pass 2 run side by side.  Dynamic LDS: 5 N complex.
+template <int NF>
+__global__ __launch_bounds__(PREP_NT) void k_col_rhs(const double* __restrict__ Ys, const double* __restrict__ Gpsi,
+                                                     int Np, const double* __restrict__ aux, int nmax,
+                                                     double* __restrict__ Kout, const cplx* __restrict__ tw,
+                                                     const double* __restrict__ sig, int N, double g, double tau) {
+  constexpr int PT = FftSz<NF>::PT;
   extern __shared__ cplx lds[];
   cplx* Z = lds;
   cplx* W = lds + N;
   cplx* S = lds + 2 * N;
-  cplx* tws = lds + 3 * N;
+  cplx* X = lds + 3 * N;
+  cplx* tws = lds + 4 * N;
   const FftPlan P = make_plan(N);
-  load_twiddles(tws, tw, N);
+  const int tid = threadIdx.x & 255, team = threadIdx.x >> 8;
+  load_twiddles<(PT + 1) / 2>(tws, tw, N);
   const int c = blockIdx.x + 1;
-  const int tid = threadIdx.x;
   const double* ye = Ys + (size_t)c * 2 * N;
-  const double* yp = ye + N;
-  const double* gp = Gpsi + (size_t)(c - 1) * Np;
-  const double* au = aux + AUX_U * nmax;
-  const double* av = aux + AUX_V * nmax;
-  const double* aw = aux + AUX_W3 * nmax;
   // pass 1: d psidot, d etadot
-  double ev[NPT], pv[NPT], vv[NPT];
-  gload(ev, ye, N);
-  gload(pv, yp, N);
-  gload(vv, av, N);
-  pin(ev);
-  pin(pv);
-  pin(vv);
+  double ev[PT], vv[PT];
+  gload(ev, ye, N, tid);
+  gload(vv, aux + AUX_V * nmax, N, tid);
+  if (team == 0) {
+    double pv[PT];
+    gload(pv, ye + N, N, tid);
+    pin(ev);
+    pin(pv);
+    pin(vv);
 #pragma unroll
-  for (int m = 0; m < NPT; ++m) {
-    const int t = tidx(m);
-    if (t < N) Z[t] = cmk(pv[m] - vv[m] * ev[m], ev[m]);
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
+      if (t < N) Z[t] = cmk(pv[m] - vv[m] * ev[m], ev[m]);
+    }
   }
-  double uv[NPT], gv[NPT], wv[NPT];   // in flight during pass 1
-  gload(uv, au, N);
-  gload(gv, gp, N);
-  gload(wv, aw, N);
+  double uv[PT], gv[PT], wv[PT];   // in flight during pass 1
+  gload(uv, aux + AUX_U * nmax, N, tid);
+  gload(gv, Gpsi + (size_t)(c - 1) * Np, N, tid);
+  gload(wv, aux + AUX_W3 * nmax, N, tid);
   pin(uv);
   pin(gv);
   pin(wv);
-  fft_lds(Z, W, tws, P, -1);
-  for (int t = tid; t < N; t += WW_NT) {
-    cplx A, B;
-    split_pair(Z, t, N, A, B);
-    const int k = wavenum(t, N);
-    W[t] = pack_pair(sym_deriv(A, k, N), sym_deriv(B, k, N));
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, team == 0);
+  for (int t = threadIdx.x; t < N; t += PREP_NT) {
+    // i k times the spectrum of psidot + i etadot (both real, the multiplier odd)
+    W[t] = sym_deriv(Z[t], wavenum(t, N), N);
   }
-  fft_lds(W, Z, tws, P, +1);
+  FftSz<NF>::run(W, Z, tws, P, +1, tid, team == 0);
   // pass 2
 #pragma unroll
-  for (int m = 0; m < NPT; ++m) {
-    const int t = tidx(m);
+  for (int m = 0; m < PT; ++m) {
+    const int t = tid + WW_NT * m;
     if (t < N) {
       const double e = ev[m], u = uv[m], v = vv[m], G = gv[m];
       const double dpsi = W[t].x, deta = W[t].y;
-      Z[t] = cmk(G, e * u);
-      S[t] = cmk(-u * dpsi + v * G - g * e, -e * u * v + tau * deta / wv[m]);
+      if (team == 0) Z[t] = cmk(G, e * u);
+      else S[t] = cmk(-u * dpsi + v * G - g * e, -e * u * v + tau * deta / wv[m]);
     }
   }
-  fft_lds(Z, W, tws, P, -1);
-  fft_lds(S, W, tws, P, -1);
-  for (int t = tid; t < N; t += WW_NT) {
+  FftSz<NF>::run(team ? S : Z, team ? X : W, tws, P, -1, tid, true);
+  for (int t = threadIdx.x; t < N; t += PREP_NT) {
     cplx A, B, C, F;
     split_pair(Z, t, N, A, B);
     split_pair(S, t, N, C, F);
@@ -1086,9 +1336,9 @@ __global__ __launch_bounds__(WW_NT) void k_col_rhs(const double* __restrict__ Ys
     cplx pt = (k == 0) ? cmk(0.0, 0.0) : cscale(cadd(C, sym_deriv(F, k, N)), sg);
     W[t] = pack_pair(et, pt);
   }
-  fft_lds(W, Z, tws, P, +1);
+  FftSz<NF>::run(W, Z, tws, P, +1, tid, team == 0);
   double* ko = Kout + (size_t)c * 2 * N;
-  for (int t = tid; t < N; t += WW_NT) {
+  for (int t = threadIdx.x; t < N; t += PREP_NT) {
     ko[t] = W[t].x;
     ko[N + t] = W[t].y;
   }
@@ -1098,34 +1348,36 @@ __global__ __launch_bounds__(WW_NT) void k_col_rhs(const double* __restrict__ Ys
 // End of step, one workgroup per state column: y <- S_F[y + sum_s b_s dt k_s]
 // (the filter is applied to the solution after every step, Sec. 2.2).
 // -------------------------------------------------------------------------------------
+template <int NF>
 __global__ __launch_bounds__(WW_NT) void k_step_end(double* __restrict__ y, const double* __restrict__ K,
                                                     size_t kstride, int nst, const double* __restrict__ coef,
                                                     const cplx* __restrict__ tw, const double* __restrict__ sig,
                                                     int N, int c0, int* __restrict__ status) {
+  constexpr int PT = FftSz<NF>::PT;
   extern __shared__ cplx lds[];
   cplx* Z = lds;
   cplx* W = lds + N;
   cplx* tws = lds + 2 * N;
   const FftPlan P = make_plan(N);
-  load_twiddles(tws, tw, N);
+  load_twiddles<PT>(tws, tw, N);
   const int c = c0 + blockIdx.x;
   double* yc = y + (size_t)c * 2 * N;
   const int tid = threadIdx.x;
   {
-    double ev[NPT], pv[NPT];
+    double ev[PT], pv[PT];
     stage_combine_vec(ev, y + (size_t)c * 2 * N, K + (size_t)c * 2 * N, kstride, 0, coef + COEF_B, nst, N);
     stage_combine_vec(pv, y + (size_t)c * 2 * N, K + (size_t)c * 2 * N, kstride, N, coef + COEF_B, nst, N);
     pin(ev);
     pin(pv);
 #pragma unroll
-    for (int m = 0; m < NPT; ++m) {
+    for (int m = 0; m < PT; ++m) {
       const int t = tidx(m);
       if (t < N) Z[t] = cmk(ev[m], pv[m]);
     }
   }
-  fft_lds(Z, W, tws, P, -1);
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, true);
   for (int t = tid; t < N; t += WW_NT) Z[t] = cscale(Z[t], sig[t]);
-  fft_lds(Z, W, tws, P, +1);
+  FftSz<NF>::run(Z, W, tws, P, +1, tid, true);
   for (int t = tid; t < N; t += WW_NT) {
     yc[t] = Z[t].x;
     yc[N + t] = Z[t].y;
@@ -1139,7 +1391,7 @@ __global__ void k_status_reset(int* __restrict__ status) {
     status[0] = 0;
     status[1] = 0;
     status[2] = 0x7fffffff;
-    // status[4..7]: the two maxima of the lagged-solve test (k_base_dtn, k_base_rhs)
+    // status[4..7]: the two maxima of a double-double solve's residual test
     status[4] = status[5] = status[6] = status[7] = 0;
   }
 }
@@ -1455,32 +1707,39 @@ __global__ void k_save_aux(const double* __restrict__ aux, int nmax, int N, doub
 // (a relative residual, which bounds the normwise backward error); a column that
 // fails, or a NaN, sets status bit 4 (reported as WW_EREFINE).
 // -------------------------------------------------------------------------------------
+template <int NT>
 __device__ inline void refine_check_col(const double* __restrict__ rc, const double* __restrict__ bc, int N,
-                                        double tol, int* __restrict__ status, int flag) {
-  __shared__ double rr[WW_NT], rb[WW_NT];
+                                        double tol, int* __restrict__ status, int flag, double* red) {
+  double *rr = red, *rb = red + NT / 64;   // red: LDS of NT / 32 doubles, free again after the next barrier
   double mr = 0.0, mb = 0.0;
-  for (int i = threadIdx.x; i < N; i += WW_NT) {
+  for (int i = threadIdx.x; i < N; i += NT) {
     mr = fmax(mr, fabs(rc[i]));
     mb = fmax(mb, fabs(bc[i]));
     if (rc[i] != rc[i]) mr = INFINITY;
   }
-  rr[threadIdx.x] = mr;
-  rb[threadIdx.x] = mb;
-  __syncthreads();
-  for (int off = WW_NT / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      rr[threadIdx.x] = fmax(rr[threadIdx.x], rr[threadIdx.x + off]);
-      rb[threadIdx.x] = fmax(rb[threadIdx.x], rb[threadIdx.x + off]);
-    }
-    __syncthreads();
+  for (int off = 32; off > 0; off >>= 1) {
+    mr = fmax(mr, __shfl_xor(mr, off));
+    mb = fmax(mb, __shfl_xor(mb, off));
   }
-  if (threadIdx.x == 0 && !(rr[0] <= tol * rb[0])) atomicOr(status, flag);
+  if ((threadIdx.x & 63) == 0) {
+    rr[threadIdx.x >> 6] = mr;
+    rb[threadIdx.x >> 6] = mb;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NT / 64; ++w) {
+      mr = fmax(mr, rr[w]);
+      mb = fmax(mb, rb[w]);
+    }
+    if (!(mr <= tol * mb)) atomicOr(status, flag);
+  }
 }
 
 __global__ __launch_bounds__(WW_NT) void k_refine_check(const double* __restrict__ r, const double* __restrict__ B,
                                                         int Np, int N, double tol, int* __restrict__ status,
                                                         int flag) {
-  refine_check_col(r + (size_t)blockIdx.x * Np, B + (size_t)blockIdx.x * Np, N, tol, status, flag);
+  __shared__ double red[WW_NT / 32];
+  refine_check_col<WW_NT>(r + (size_t)blockIdx.x * Np, B + (size_t)blockIdx.x * Np, N, tol, status, flag, red);
 }
 
 // -------------------------------------------------------------------------------------

@@ -14,6 +14,7 @@ enum {
   MESH_EP,       // E' = xi''
   MESH_COUNT
 };
+static_assert(MESH_E == 1 && MESH_EINV == 2, "mesh_e, mesh_einv");
 
 // The change of variables of eq. (xi): E = 1 - A (s - 3/8) with s = sin^4(alpha/2)
 // (side 0: refined near x = pi) or cos^4(alpha/2) (side 1: refined near x = 0); 3/8 is
@@ -240,42 +241,16 @@ __device__ inline void base_rhs_map_stage(cplx* Z, cplx* W, const cplx* tws, con
   }
 }
 
-// chk (optional): the two maxima of a lagged-factor solve's test (see k_base_dtn)
 __global__ __launch_bounds__(WW_NT) void k_base_rhs_map(const double* __restrict__ Ys, const double* __restrict__ Gphi,
                                                         double* __restrict__ aux, const double* __restrict__ mesh,
                                                         int nmax, double* __restrict__ Kout,
-                                                        unsigned long long* __restrict__ chk, double chk_tol,
-                                                        int* __restrict__ status, const cplx* __restrict__ tw,
-                                                        const double* __restrict__ sig, int N, double g, double tau) {
+                                                        const cplx* __restrict__ tw, const double* __restrict__ sig,
+                                                        int N, double g, double tau) {
   extern __shared__ cplx lds[];
   __shared__ double red[WW_NT / 64];
   const FftPlan P = make_plan(N);
-  lagged_check(chk, chk_tol, status, 32);
   load_twiddles(lds + 3 * N, tw, N);
   base_rhs_map_stage(lds, lds + N, lds + 3 * N, P, red, Ys, Gphi, aux, mesh, nmax, Kout, sig, N, g, tau);
-}
-
-// The right-hand side of stage s and the prep of stage s + 1 in one launch (the mapped
-// counterpart of k_base_rhs_prep).
-__global__ __launch_bounds__(WW_NT) void k_base_rhs_prep_map(
-    const double* __restrict__ Gphi, double* __restrict__ aux_cur, double* __restrict__ Kcur,
-    unsigned long long* __restrict__ chk, double chk_tol, const double* __restrict__ sig, double g, double tau,
-    const double* __restrict__ y, const double* __restrict__ K, double* __restrict__ Ys,
-    const double* __restrict__ coef, int stage_next, size_t kstride, double* __restrict__ aux_next,
-    double* __restrict__ rhs0, int Np, double hsurf, int nmax, const cplx* __restrict__ tw, int N,
-    int* __restrict__ status, const double* __restrict__ mesh) {
-  extern __shared__ cplx lds[];
-  __shared__ double red[WW_NT / 64];
-  cplx* Z = lds;
-  cplx* W = lds + N;
-  cplx* S = lds + 2 * N;
-  cplx* tws = lds + 3 * N;
-  const FftPlan P = make_plan(N);
-  lagged_check(chk, chk_tol, status, 32);
-  load_twiddles(tws, tw, N);
-  base_rhs_map_stage(Z, W, tws, P, red, Ys, Gphi, aux_cur, mesh, nmax, Kcur, sig, N, g, tau);
-  __syncthreads();   // K_s (global) and the LDS buffers are complete
-  base_prep_stage(Z, W, S, tws, P, y, K, Ys, coef, stage_next, kstride, aux_next, nmax, rhs0, Np, N, hsurf, status);
 }
 
 // -------------------------------------------------------------------------------------
