@@ -525,9 +525,11 @@ unsigned ww_next_fallback(unsigned flags, unsigned fb, int status);
  *   blu_strip    64-tiles per task of a block elimination step, 1..16: a step takes the
  *                fewest that leave every task a compute unit, at most twice this number
  *   dtn_rows     rows per workgroup of the base DtN launch, 4..32, a multiple of 4
- *   gemm_split   wave groups splitting the inner dimension of a column product, 2 or 4
- *   gemm_rows    rows of a column product's output tile, 16 or 32 (16: twice the
- *                workgroups for the same columns)
+ *   gemm_split   2 or 4; kept for callers that set it, without effect (the eight waves of a
+ *                column product's workgroup always split the inner dimension)
+ *   gemm_rows    a column product's output tiles: 32 takes 16 x 32 ones, and 16 x 16 ones
+ *                where those would leave half the compute units without work; 16 always
+ *                takes 16 x 16 ones
  *   lag_fp32     FP64 form, lagged-factor march: 1 makes the lagged base solve (its
  *                first solve and the corrections of its refinement sweeps) read an FP32
  *                copy of the lagged inverse, written by the same launch as the FP64 one;

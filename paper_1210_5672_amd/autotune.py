@@ -41,7 +41,7 @@ SPACE = {
     "blu_strip": [4, 2, 3, 6, 8],
     "minv_wgs": [1 << 20],   # (without effect)
     "dtn_rows": [8, 4, 16],
-    "gemm_split": [4, 2],
+    "gemm_split": [4],       # (without effect)
     "asm_cw": [16, 32],
     "gemm_rows": [32, 16],
     "lag_fp32": [0, 1],

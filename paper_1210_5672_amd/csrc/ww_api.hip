@@ -257,8 +257,8 @@ struct ww_ctx {
   int graph_parts = 10;                    // parts of a march stage replayed from graphs (bit per part)
   int blu_strip = 4;                       // tiles per strip task of a block-LU step
   int dtn_rows = 8;                        // rows per workgroup of the base DtN launch
-  int gemm_split = 4;                      // wave groups splitting the inner dimension of a product
-  int gemm_rows = 32;                      // rows of a column product's output tile (16 or 32)
+  int gemm_split = 4;                      // kept in the interface, without effect
+  int gemm_rows = 32;                      // column products: tiles by size (32), 16 x 16 (16)
   int lag32 = 0;                           // FP64 form: lagged solves read an FP32 copy of the inverse
   int asm_cw = 16;                         // columns per assembly workgroup
   int tune_gen = 0;                        // bumped by ww_set_tuning (graphs are re-captured)
@@ -902,8 +902,8 @@ static int enqueue_assemble_lu(ww_ctx* c, const Fac& F) {
 
 // out = add + sgn * M B for R columns (ld Np) with the row-major M (element type T).
 // One column: one wave per row (mode: the 64-block range, 0 all, 1 strictly lower, 2
-// upper with the diagonal); several: 32 x 32 output tiles over the whole inner
-// dimension (the full matrix).
+// upper with the diagonal); several: output tiles over the whole inner dimension (the
+// full matrix).
 template <typename T>
 static int enqueue_gemm(ww_ctx* c, const T* Mr, int mode, const double* B, const double* add, double sgn,
                         double* out, int R) {
@@ -915,18 +915,15 @@ static int enqueue_gemm(ww_ctx* c, const T* Mr, int mode, const double* B, const
     return 0;
   }
   if (mode & 3) return fail(WW_EHIP, "internal: triangular product of several columns");
-  const dim3 g32(c->Np / GT, (R + GT - 1) / GT), g16(c->Np / 16, (R + GT - 1) / GT);
-  if (c->gemm_rows == 16) {
-    if (c->gemm_split == 2)
-      hipLaunchKernelGGL((k_gemm_rm<T, 2, 16>), g16, dim3(256), 0, c->stream, Mr, c->Np, B, R, add, sgn, out);
-    else
-      hipLaunchKernelGGL((k_gemm_rm<T, 4, 16>), g16, dim3(512), 0, c->stream, Mr, c->Np, B, R, add, sgn, out);
-  } else {
-    if (c->gemm_split == 2)
-      hipLaunchKernelGGL((k_gemm_rm<T, 2, 32>), g32, dim3(512), 0, c->stream, Mr, c->Np, B, R, add, sgn, out);
-    else
-      hipLaunchKernelGGL((k_gemm_rm<T, 4, 32>), g32, dim3(1024), 0, c->stream, Mr, c->Np, B, R, add, sgn, out);
-  }
+  // 16 x 32 tiles, or 16 x 16 (gemm_rows = 16: always) where those would leave half the CUs
+  // without one: N 256, R 64 2.7 against 3.5 us, N 2048, R 32 8.5 / 13.0; from one 16 x 32
+  // tile per CU on they read less: N 768, R 137 6.9 / 6.0, N 2048, R 257 54.6 / 51.9
+  const int w32 = c->Np / 16 * ((R + 31) / 32);
+  if (c->gemm_rows == 16 || w32 <= 128)
+    hipLaunchKernelGGL((k_gemm_rm<T, 1, 4>), dim3(c->Np / 16 * ((R + 15) / 16)), dim3(GEMM_NT), 0, c->stream, Mr,
+                       c->Np, B, R, add, sgn, out);
+  else
+    hipLaunchKernelGGL((k_gemm_rm<T, 2, 3>), dim3(w32), dim3(GEMM_NT), 0, c->stream, Mr, c->Np, B, R, add, sgn, out);
   LAUNCHCHK();
   return 0;
 }

@@ -585,118 +585,177 @@ __global__ __launch_bounds__(WW_NT) void k_gemv_row(const T* __restrict__ Mr, in
 // -------------------------------------------------------------------------------------
 // Product with a row-major matrix for R right-hand sides:  out = add + sgn * M B
 // (M: Np x Np row-major, element type T; B, add, out: Np x R column-major doubles,
-// ld Np; B is rounded to T on load).  One workgroup per TR x 32 output tile: the inner
-// dimension is split over GSPLIT wave groups (group g takes the 64-wide steps g,
-// g + GSPLIT, ...), in each group every wave computes one 16 x 16 block with
-// 16 x 16 x 4 MFMAs, the next step's operands in flight in
-// registers during the MFMAs; the partial tiles are summed in LDS in a fixed order,
-// ((g0 + g1) + g2) + g3, so each entry is one deterministic sum (no partials in
-// memory, no second launch).  The result is stored along the columns.
+// ld Np; B is rounded to T at the matrix instruction).  A workgroup's tile is 16 rows by 16 BC
+// columns, its eight waves split the inner index (chunks of 16: w, w + 8, ...); the partial
+// tiles are summed in LDS in a fixed order and stored once.
+//
+// Both operands have the inner index contiguous while a matrix instruction wants 16 rows (or
+// columns) in consecutive lanes: loaded in that order, each lane's 16 bytes are an address of
+// their own for the cache (60 cycles per load instruction; 23 us for N = 1024, R = 128).  So
+// eight consecutive lanes load the 128 bytes of one row's chunk, and the wave turns the chunk
+// round in its own piece of LDS (16-byte slots, slot s of row r at s ^ ((r >> 1) & 7): the 16
+// rows that a lane group reads fall into the 16 slots of LDS's 256-byte bank row).  No barrier
+// until the end, and D chunks per wave in flight in registers.
+// The inner indices of instruction (h, e) are 8 h + 2 rq + e, the same in both operands.
+//
+// Bound by the matrix units (2 Np^2 R operations, 73 TFLOP/s) and, where a CU has one tile,
+// by the latency of the first chunks and of the final sum.  Small tiles: larger ones read
+// less from L2 but fill the CUs unevenly (R = 257 in 32 x 32 tiles, N 1024: 22 us against
+// 18).  Workgroup b runs on XCD b mod 8: each XCD takes a band of row tiles with all their
+// column tiles, so that its L2 holds that band of M and all of B.
+// Measured, FP64, against 32 x 32 tiles whose operands the whole workgroup staged in LDS in
+// 128-deep chunks: N x R = 256 x 64 2.7 us (7.8), 768 x 137 6.0 (15.2), 1024 x 128 7.8 (19.2;
+// its operations 3.7), 2048 x 257 52 (94; 30).
 // -------------------------------------------------------------------------------------
-#define GT 32           // output tile edge
-#define GK 64           // inner step
-#define GA_LD (GK + 1)  // LDS pitch of the M tile (TR rows x 64) and of the B tile (32 columns x 64)
-// GSPLIT: wave groups splitting the inner dimension (2 or 4); TR: rows of the output
-// tile (32, or 16 for twice the workgroups at the same columns); a group has TR / 8
-// waves, each computing one 16 x 16 block of the TR x 32 tile.
-template <typename T, int GSPLIT, int TR>
-__global__ __launch_bounds__(8 * TR * GSPLIT) void k_gemm_rm(const T* __restrict__ M, int Np,
-                                                          const double* __restrict__ B, int R,
-                                                          const double* __restrict__ add, double sgn,
-                                                          double* __restrict__ out) {
-  constexpr int WPG = TR / 8;         // waves per group
-  constexpr int TPG = 64 * WPG;       // threads per group
-  constexpr int MA = TR * 64 / TPG;   // M-tile entries per thread and step (8)
-  constexpr int MB = 32 * 64 / TPG;   // B-tile entries per thread and step (8 or 16)
-  // operand tiles of the groups; after the inner loop the same memory holds the
-  // partial output tiles
-  constexpr int OPER = GSPLIT * (TR + GT) * GA_LD * (int)sizeof(T);
-  constexpr int PART = GSPLIT * GT * (TR + 1) * (int)sizeof(double);
-  __shared__ double smem[(OPER > PART ? OPER : PART) / 8];
-  T* const tiles = reinterpret_cast<T*>(smem);
-  double (*Cs)[GT * (TR + 1)] = reinterpret_cast<double (*)[GT * (TR + 1)]>(smem);
-  typedef typename Mfma<T>::V V;
-  const int r0 = blockIdx.x * TR, c0 = blockIdx.y * GT;
-  const int tid = threadIdx.x;
-  const int grp = tid / TPG, gt = tid % TPG;   // wave group and thread within it
-  const int lane = gt & 63, w = gt >> 6;
-  const int wr = (TR == 32 ? (w >> 1) : 0) * 16, wc = (w & 1) * 16;
-  const int li = lane & 15, lk = lane >> 4;
-  T* as = tiles + (size_t)grp * (TR + GT) * GA_LD;
-  T* bs = as + TR * GA_LD;
-  // loads of one inner step by the threads of a group: MA entries of the M tile (rows
-  // r0 + w + WPG m, columns k0..) and MB of the B tile (columns c0 + w + WPG m)
-  T ma[MA];
-  double bv[MB];
-  auto fetch = [&](int k0) {
-    const int kk = gt & 63;
+#define GEMM_NT 512
+typedef double dbl2v __attribute__((ext_vector_type(2)));
+typedef float flt2v __attribute__((ext_vector_type(2)));
+// The wave's own LDS accesses on either side stay in program order.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// One 16 x 16 operand block (rows r0 .. r0 + 15, 16 inner entries) of type T between global
+// memory, registers and LDS.  Double: 2 loads of 8 rows; float: 1 load of 16 rows.
+template <typename T> struct GemmOp;
+template <> struct GemmOp<double> {
+  static constexpr int L = 2, BYTES = 2048;   // loads, LDS bytes
+  typedef dbl2v V;
+  static __device__ int lrow(int lane) { return lane >> 3; }
+  static __device__ int lcol(int lane) { return 2 * (lane & 7); }
+  static __device__ int put_off(int lane, int l) {
+    const int r = 8 * l + (lane >> 3);
+    return r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+  }
+  static __device__ void get(const char* S, int cl, int rq, double (&v)[4]) {
 #pragma unroll
-    for (int m = 0; m < MA; ++m) ma[m] = M[(size_t)(r0 + (gt >> 6) + WPG * m) * Np + k0 + kk];
-#pragma unroll
-    for (int m = 0; m < MB; ++m) {
-      const int cc = c0 + (gt >> 6) + WPG * m;
-      bv[m] = cc < R ? B[(size_t)cc * Np + k0 + kk] : 0.0;
-    }
-  };
-  // two accumulators (even and odd 4-steps of the inner dimension): two independent
-  // MFMA chains per wave, summed once at the end
-  V acc = V{T(0), T(0), T(0), T(0)};
-  V acc1 = V{T(0), T(0), T(0), T(0)};
-  const int nsteps = Np / GK;
-  if (grp < nsteps) fetch(grp * GK);
-  // every group runs the same number of iterations (barriers are workgroup-wide); a
-  // group without a step in an iteration only waits
-  for (int it = 0; it * GSPLIT < nsteps; ++it) {
-    const int st = it * GSPLIT + grp;
-    const bool have = st < nsteps;
-    __syncthreads();
-    if (have) {
-      const int kk = gt & 63;
-#pragma unroll
-      for (int m = 0; m < MA; ++m) as[((gt >> 6) + WPG * m) * GA_LD + kk] = ma[m];
-#pragma unroll
-      for (int m = 0; m < MB; ++m) bs[((gt >> 6) + WPG * m) * GA_LD + kk] = (T)bv[m];
-    }
-    __syncthreads();
-    if (have && st + GSPLIT < nsteps) fetch((st + GSPLIT) * GK);
-    if (have) {
-#pragma unroll
-      for (int h = 0; h < GK; h += 32) {
-        T a[8], b[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          a[q] = as[(wr + li) * GA_LD + h + 4 * q + lk];
-          b[q] = bs[(wc + li) * GA_LD + h + 4 * q + lk];
-        }
-#pragma unroll
-        for (int q = 0; q < 8; q += 2) {
-          acc = Mfma<T>::step(a[q], b[q], acc);
-          acc1 = Mfma<T>::step(a[q + 1], b[q + 1], acc1);
-        }
-      }
+    for (int h = 0; h < 2; ++h) {
+      const dbl2v x = *reinterpret_cast<const dbl2v*>(S + cl * 128 + (((4 * h + rq) ^ (cl >> 1)) << 4));
+      v[2 * h] = x[0];
+      v[2 * h + 1] = x[1];
     }
   }
+};
+template <> struct GemmOp<float> {
+  static constexpr int L = 1, BYTES = 1024;
+  typedef flt4 V;
+  static __device__ int lrow(int lane) { return lane >> 2; }
+  static __device__ int lcol(int lane) { return 4 * (lane & 3); }
+  static __device__ int put_off(int lane, int) {
+    const int r = lane >> 2;
+    return r * 64 + (((lane & 3) ^ (r >> 2)) << 4);
+  }
+  static __device__ void get(const char* S, int cl, int rq, float (&v)[4]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] += acc1[i];
-  __syncthreads();   // every group is done with its operand tiles
+    for (int h = 0; h < 2; ++h) {
+      const flt2v x =
+          *reinterpret_cast<const flt2v*>(S + cl * 64 + (((2 * h + (rq >> 1)) ^ (cl >> 2)) << 4) + ((rq & 1) << 3));
+      v[2 * h] = x[0];
+      v[2 * h + 1] = x[1];
+    }
+  }
+};
+
+template <typename T, int BC, int D>
+__global__ __launch_bounds__(GEMM_NT) void k_gemm_rm(const T* __restrict__ M, int Np, const double* __restrict__ B, int R,
+                                                     const double* __restrict__ add, double sgn,
+                                                     double* __restrict__ out) {
+  constexpr int KS = GEMM_NT / 64, TR = 16, TC = 16 * BC, LD = TR + 1;
+  constexpr int WB = GemmOp<T>::BYTES + BC * GemmOp<double>::BYTES;   // LDS bytes of a wave
+  constexpr int SB = WB > TC * LD * 8 ? KS * WB : KS * TC * LD * 8;
+  constexpr int LA = GemmOp<T>::L, LB = BC * GemmOp<double>::L;
+  typedef typename Mfma<T>::V V;
+  typedef typename GemmOp<T>::V VA;
+  __shared__ __attribute__((aligned(256))) char sm[SB];
+  const int nrt = Np / TR, nct = (R + TC - 1) / TC;
+  int rt, ct;
+  if (nrt % 8 == 0) {
+    const int x = blockIdx.x % 8, l = blockIdx.x / 8;
+    rt = x * (nrt / 8) + l / nct;
+    ct = l % nct;
+  } else {
+    rt = blockIdx.x / nct;
+    ct = blockIdx.x % nct;
+  }
+  const int lane = threadIdx.x & 63, cl = lane & 15, rq = lane >> 4;
+  const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* const sa = sm + ks * WB;
+  char* const sb = sa + GemmOp<T>::BYTES;
+  const T* const ab = M + (size_t)(rt * TR) * Np + 16 * ks;
+  const unsigned ao = (unsigned)(GemmOp<T>::lrow(lane) * Np + GemmOp<T>::lcol(lane));
+  const double* bp[LB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) Cs[grp][(wc + li) * (TR + 1) + wr + Mfma<T>::row(i, lk)] = (double)acc[i];
-  __syncthreads();
-  if (grp == 0) {
-    // column c0 + gt / (TR / 4), rows r0 + 4 (gt % (TR / 4)) .. + 3
-    const int cc = c0 + gt / (TR / 4);
-    if (cc < R) {
+  for (int l = 0; l < LB; ++l)
+    bp[l] = B + (size_t)min(ct * TC + 8 * l + GemmOp<double>::lrow(lane), R - 1) * Np + 16 * ks +
+            GemmOp<double>::lcol(lane);
+  const int n = (Np / 16 - ks + KS - 1) / KS;   // chunks of this wave
+  VA a[D][LA];
+  dbl2v b[D][LB];
+  V acc[BC];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int rr = 4 * (gt % (TR / 4)) + q;
-        const int e = (gt / (TR / 4)) * (TR + 1) + rr;
-        double s = Cs[0][e];
+  for (int q = 0; q < BC; ++q) acc[q] = V{T(0), T(0), T(0), T(0)};
+  auto fetch = [&](int d, int i) {
 #pragma unroll
-        for (int g2 = 1; g2 < GSPLIT; ++g2) s += Cs[g2][e];
-        const size_t o = (size_t)cc * Np + r0 + rr;
-        out[o] = (add ? add[o] : 0.0) + sgn * s;
+    for (int l = 0; l < LA; ++l)
+      a[d][l] = *reinterpret_cast<const VA*>(ab + (size_t)(8 * l) * Np + (size_t)i * 16 * KS + ao);
+#pragma unroll
+    for (int l = 0; l < LB; ++l) b[d][l] = *reinterpret_cast<const dbl2v*>(bp[l] + (size_t)i * 16 * KS);
+  };
+  auto turn = [&](int d) {   // chunk of register set d into LDS
+    wave_lds_order();
+#pragma unroll
+    for (int l = 0; l < LA; ++l)
+      *reinterpret_cast<VA*>(sa + GemmOp<T>::put_off(lane, l)) = a[d][l];
+#pragma unroll
+    for (int l = 0; l < LB; ++l)
+      *reinterpret_cast<dbl2v*>(sb + l / 2 * 2048 + GemmOp<double>::put_off(lane, l % 2)) = b[d][l];
+    wave_lds_order();
+  };
+  auto product = [&](int dn) {   // chunk in LDS; the chunk of register set dn (>= 0) follows it
+    T av[4];
+    double bv[BC][4];
+    GemmOp<T>::get(sa, cl, rq, av);
+#pragma unroll
+    for (int q = 0; q < BC; ++q) GemmOp<double>::get(sb + q * 2048, cl, rq, bv[q]);
+    if (dn >= 0) turn(dn);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int q = 0; q < BC; ++q) acc[q] = Mfma<T>::step(av[j], (T)bv[q][j], acc[q]);
+  };
+  if (n > 0) {
+    // prefetches past the last chunk repeat it (in bounds, unused)
+#pragma unroll
+    for (int d = 0; d < D; ++d) fetch(d, min(d, n - 1));
+    turn(0);
+    int i = 0;
+    for (; i + D < n; i += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        fetch(d, min(i + d + D, n - 1));
+        product((d + 1) % D);
       }
     }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (i + d < n) product(d + 1 < D ? d + 1 : -1);
+  }
+  __syncthreads();
+  double* const Cs = reinterpret_cast<double*>(sm);
+#pragma unroll
+  for (int q = 0; q < BC; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Cs[(ks * TC + 16 * q + cl) * LD + Mfma<T>::row(i, rq)] = (double)acc[q][i];
+  __syncthreads();
+  for (int e = threadIdx.x; e < TR * TC; e += GEMM_NT) {
+    const int c = e / TR, r = e % TR, cc = ct * TC + c;
+    if (cc >= R) break;
+    double s = Cs[c * LD + r];
+#pragma unroll
+    for (int g = 1; g < KS; ++g) s += Cs[(g * TC + c) * LD + r];
+    const size_t o = (size_t)cc * Np + rt * TR + r;
+    out[o] = (add ? add[o] : 0.0) + sgn * s;
   }
 }
 
