@@ -167,7 +167,6 @@ struct ww_ctx {
   double *dd_pt_hi = nullptr, *dd_pt_lo = nullptr;
   double *dd_Ah = nullptr, *dd_Al = nullptr, *dd_Gh = nullptr, *dd_Gl = nullptr;
   double* dd_w = nullptr;
-  double* dd_part = nullptr;   // chunk partials of the one-column double-double product
   // SDC15 (shoot_eval_sdc), allocated at first use: the stage slopes of one step
   // (SDC_STAGES slots of 2 n_max r_max), the stage state, and the sparse stage rows
   // (SDC_STAGES + 1 rows of SDC_MAXNZ slot indices and weights; the last row is the
@@ -200,7 +199,7 @@ struct ww_ctx {
   int sdd_cnt[SDC_STAGES + 1] = {};
   double* sdd_lane = nullptr;   // the grouped sweeps' lanes (SDC_NODES of them)
   // the second group's solve workspace, partials and G phi (hi, lo) of the grouped sweeps
-  double *sdd_w2 = nullptr, *sdd_part2 = nullptr, *sdd_G2 = nullptr;
+  double *sdd_w2 = nullptr, *sdd_G2 = nullptr;
   int gmap = -1;   // `mapped` of the captured step graph
   int* status = nullptr;
   std::vector<void*> allocs;
@@ -1747,27 +1746,43 @@ static int ensure_dd(ww_ctx* c) {
   double** mats[] = {&c->dd_Ah, &c->dd_Al, &c->dd_Gh, &c->dd_Gl};
   for (double** q : mats)
     if ((rc = dalloc(c, (void**)q, np * np * 8))) return rc;
-  if (!c->dd_part && (rc = dalloc(c, (void**)&c->dd_part, (size_t)2 * DDGV_KS * np * 8))) return rc;
   return dalloc(c, (void**)&c->dd_w, (size_t)DD_WORK * np * c->r_max * 8);
 }
 
-// out = add + sgn A B in double-double for nrhs columns (ld Np): one column by the
-// inner-index split of k_dd_gemv_part / k_dd_gemv_sum, several by k_dd_gemm
-static int dd_gemm(ww_ctx* c, double* part, const double* Ah, const double* Al, const double* Bh, const double* Bl,
-                   const double* addh, const double* addl, double sgn, double* outh, double* outl, int nrhs) {
-  const int Np = c->Np;
+// out = add + sgn A B in double-double for nrhs columns (ld Np; Bl may be null: zero); mx
+// (optional): max |out| and max |add| over the rows < N join mx[0], mx[1]
+static int dd_gemm(ww_ctx* c, const double* Ah, const double* Al, const double* Bh, const double* Bl,
+                   const double* addh, const double* addl, double sgn, double* outh, double* outl, int nrhs,
+                   unsigned long long* mx = nullptr) {
+  const int Np = c->Np, N = c->N;
   if (nrhs == 1) {
-    double *Ph = part, *Pl = part + (size_t)DDGV_KS * c->np_max;
-    hipLaunchKernelGGL(k_dd_gemv_part, dim3(Np / 64, DDGV_KS), dim3(WW_NT), 0, c->stream, Ah, Al, Np, Bh, Bl, Ph, Pl);
-    LAUNCHCHK();
-    hipLaunchKernelGGL(k_dd_gemv_sum, dim3((Np + 255) / 256), dim3(256), 0, c->stream, Ph, Pl, DDGV_KS, Np, addh,
-                       addl, sgn, outh, outl);
+    hipLaunchKernelGGL(k_dd_gemv, dim3(Np / 16), dim3(DDV_NT), 0, c->stream, Ah, Al, Np, Bh, Bl, addh, addl, sgn,
+                       outh, outl, N, mx);
     LAUNCHCHK();
     return 0;
   }
-  hipLaunchKernelGGL(k_dd_gemm, dim3(Np / 64, (nrhs + 3) / 4), dim3(WW_NT), 0, c->stream, Ah, Al, Np, Bh, Bl, addh,
-                     addl, sgn, outh, outl, nrhs);
+  // columns per workgroup: the fewest rounds of the CUs, a round priced by its columns and
+  // half a column for its start and sum (N 1024, 129 columns: 2 columns 94 us, 3 89, 4 121)
+  int best = 0;
+  double cost = 0.0;
+  for (int nc = 2; nc <= 4; ++nc) {
+    const double t = ((Np / 64 * ((nrhs + nc - 1) / nc) + 255) / 256) * (nc + 0.5);
+    if (!best || t < cost) best = nc, cost = t;
+  }
+  const dim3 grid(Np / 64 * ((nrhs + best - 1) / best));
+#define DDG(NC)                                                                                                    \
+  hipLaunchKernelGGL(k_dd_gemm<NC>, grid, dim3(DDG_NT), 0, c->stream, Ah, Al, Np, Bh, Bl, addh, addl, sgn, outh,   \
+                     outl, nrhs)
+  if (best == 2) DDG(2);
+  else if (best == 3) DDG(3);
+  else DDG(4);
+#undef DDG
   LAUNCHCHK();
+  if (mx) {
+    const int blocks = (int)std::min<size_t>(((size_t)Np * nrhs + 255) / 256, 256);
+    hipLaunchKernelGGL(k_dd_maxabs, dim3(blocks), dim3(WW_NT), 0, c->stream, outh, addh, N, Np, nrhs, mx);
+    LAUNCHCHK();
+  }
   return 0;
 }
 
@@ -1810,7 +1825,7 @@ static size_t dd_lds_bytes(int N) { return (size_t)(3 * N + N / 2) * sizeof(cdd)
 struct DdLane {
   double *pt_hi, *pt_lo, *Ah, *Al, *Gh, *Gl;
   Fac F;
-  double *w, *part;   // the solve's workspace: DD_WORK planes, the one-column product's partials
+  double* w;   // the solve's workspace: DD_WORK planes
 };
 // the factors of the corrections: FP64, or FP32 on MFMA in a WW_MIXED context
 static Fac dd_fac(const ww_ctx* c, Fac F) {
@@ -1821,7 +1836,7 @@ static Fac dd_fac(const ww_ctx* c, Fac F) {
 }
 static DdLane dd_lane(ww_ctx* c) {
   return DdLane{c->dd_pt_hi, c->dd_pt_lo, c->dd_Ah, c->dd_Al, c->dd_Gh,
-                c->dd_Gl,    dd_fac(c, fac_default(c)), c->dd_w, c->dd_part};
+                c->dd_Gl,    dd_fac(c, fac_default(c)), c->dd_w};
 }
 
 // per-point quantities and the double-double assembly of the surface (sh, sl) into lane
@@ -1863,17 +1878,29 @@ static int dd_solve_enqueue(ww_ctx* c, const DdLane& L, const double* rhs_hi, co
   const int N = c->N, Np = c->Np;
   const size_t blk = (size_t)Np * nrhs, pl = (size_t)c->np_max * c->r_max;
   double* w = L.w;
-  double *psh = w, *psl = w + pl, *muh = w + 2 * pl, *mul = w + 3 * pl, *rh = w + 4 * pl, *rl = w + 5 * pl;
+  double *muh = w + 2 * pl, *mul = w + 3 * pl, *rh = w + 4 * pl, *rl = w + 5 * pl;
   double *del = w + 6 * pl, *gh = w + 7 * pl, *gl = w + 8 * pl, *hh = w + 9 * pl, *hl = w + 10 * pl;
-  double *oh = w + 11 * pl, *ol = w + 12 * pl;
+  const double *psh = rhs_hi, *psl = rhs_lo;
+  double *oh = out_hi, *ol = out_lo;
   const int blocks = (int)std::min<size_t>((blk + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_pad_copy, dim3(blocks), dim3(256), 0, c->stream, rhs_hi, N, psh, Np, N, Np, nrhs);
-  LAUNCHCHK();
-  if (rhs_lo)
-    hipLaunchKernelGGL(k_pad_copy, dim3(blocks), dim3(256), 0, c->stream, rhs_lo, N, psl, Np, N, Np, nrhs);
-  else
-    hipLaunchKernelGGL(k_pad_copy, dim3(blocks), dim3(256), 0, c->stream, psh, Np, psl, Np, 0, Np, nrhs);
-  LAUNCHCHK();
+  // the caller's planes serve as they are where they have the kernels' layout (no padding
+  // rows, the alignment of their 16-byte loads); out is written after the last use of rhs
+  const bool direct = N == Np && ((uintptr_t)rhs_hi & 15) == 0;
+  if (!direct) {
+    hipLaunchKernelGGL(k_pad_copy, dim3(blocks), dim3(256), 0, c->stream, rhs_hi, N, w, Np, N, Np, nrhs);
+    LAUNCHCHK();
+    psh = w;
+    oh = w + 11 * pl;
+    ol = w + 12 * pl;
+  }
+  if (!direct || !rhs_lo) {
+    if (rhs_lo)
+      hipLaunchKernelGGL(k_pad_copy, dim3(blocks), dim3(256), 0, c->stream, rhs_lo, N, w + pl, Np, N, Np, nrhs);
+    else
+      hipLaunchKernelGGL(k_pad_copy, dim3(blocks), dim3(256), 0, c->stream, psh, Np, w + pl, Np, 0, Np, nrhs);
+    LAUNCHCHK();
+    psl = w + pl;
+  }
   int rc;
   // corrections from the FP64 inverse, or from the FP32 one (a mixed context: more sweeps)
   auto corr = [&](const double* B, double* X) -> int {
@@ -1882,25 +1909,23 @@ static int dd_solve_enqueue(ww_ctx* c, const DdLane& L, const double* rhs_hi, co
   };
   const int sweeps = L.F.use32 ? DD_SWEEPS_32 : DD_SWEEPS;
   if ((rc = corr(psh, muh))) return rc;
-  hipLaunchKernelGGL(k_pad_copy, dim3(blocks), dim3(256), 0, c->stream, psh, Np, mul, Np, 0, Np, nrhs);
-  LAUNCHCHK();
-  for (int sweep = 0; sweep < sweeps; ++sweep) {
-    if ((rc = dd_gemm(c, L.part, L.Ah, L.Al, muh, mul, psh, psl, -1.0, rh, rl, nrhs))) return rc;
+  for (int sweep = 0; sweep < sweeps; ++sweep) {   // the first finds mu without a low part
+    if ((rc = dd_gemm(c, L.Ah, L.Al, muh, sweep ? mul : nullptr, psh, psl, -1.0, rh, rl, nrhs))) return rc;
     if ((rc = corr(rh, del))) return rc;
-    hipLaunchKernelGGL(k_dd_correct, dim3(blocks), dim3(256), 0, c->stream, muh, mul, del, blk);
+    hipLaunchKernelGGL(k_dd_correct, dim3(blocks), dim3(256), 0, c->stream, muh, mul, del, blk, sweep == 0);
     LAUNCHCHK();
   }
-  if ((rc = dd_gemm(c, L.part, L.Ah, L.Al, muh, mul, psh, psl, -1.0, rh, rl, nrhs))) return rc;
-  hipLaunchKernelGGL(k_dd_maxabs, dim3(std::min(blocks, 256)), dim3(256), 0, c->stream, rh, psh, N, Np, nrhs, mx);
-  LAUNCHCHK();
+  if ((rc = dd_gemm(c, L.Ah, L.Al, muh, mul, psh, psl, -1.0, rh, rl, nrhs, mx))) return rc;
   hipLaunchKernelGGL(k_dd_gamma, dim3(nrhs), dim3(WW_NT), dd_lds_bytes(N), c->stream, muh, mul, Np, c->dd_tw, N, gh,
                      gl, hh, hl);
   LAUNCHCHK();
-  if ((rc = dd_gemm(c, L.part, L.Gh, L.Gl, gh, gl, hh, hl, 1.0, oh, ol, nrhs))) return rc;
+  if ((rc = dd_gemm(c, L.Gh, L.Gl, gh, gl, hh, hl, 1.0, oh, ol, nrhs))) return rc;
   const size_t tot = (size_t)N * nrhs;
   const int ob = (int)std::min<size_t>((tot + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_pad_copy, dim3(ob), dim3(256), 0, c->stream, oh, Np, out_hi, N, Np, N, nrhs);
-  hipLaunchKernelGGL(k_pad_copy, dim3(ob), dim3(256), 0, c->stream, ol, Np, out_lo, N, Np, N, nrhs);
+  if (!direct) {
+    hipLaunchKernelGGL(k_pad_copy, dim3(ob), dim3(256), 0, c->stream, oh, Np, out_hi, N, Np, N, nrhs);
+    hipLaunchKernelGGL(k_pad_copy, dim3(ob), dim3(256), 0, c->stream, ol, Np, out_lo, N, Np, N, nrhs);
+  }
   if (mu_hi) {
     hipLaunchKernelGGL(k_pad_copy, dim3(ob), dim3(256), 0, c->stream, muh, Np, mu_hi, N, Np, N, nrhs);
     hipLaunchKernelGGL(k_pad_copy, dim3(ob), dim3(256), 0, c->stream, mul, Np, mu_lo, N, Np, N, nrhs);
@@ -3082,7 +3107,6 @@ static int ensure_sdd_lanes(ww_ctx* c) {
   const size_t per = 4 * np * np + 8 * nm + 4 * nm;   // A, Gm (hi, lo); 4 point planes (hi, lo); state (hi, lo)
   // the second group's solve workspace (its solves run on the LU stream) and G phi
   if (!c->sdd_w2 && (rc = dalloc(c, (void**)&c->sdd_w2, (size_t)DD_WORK * np * c->r_max * 8))) return rc;
-  if (!c->sdd_part2 && (rc = dalloc(c, (void**)&c->sdd_part2, (size_t)2 * DDGV_KS * np * 8))) return rc;
   if (!c->sdd_G2 && (rc = dalloc(c, (void**)&c->sdd_G2, 2 * nm * 8))) return rc;
   return dalloc(c, (void**)&c->sdd_lane, SDC_NODES * per * 8);
 }
@@ -3094,7 +3118,7 @@ static DdLane dd_sweep_lane(ww_ctx* c, int m, double** yh, double** yl) {
   const bool second = m >= GJ_GMAX;   // the second group's workspace
   return DdLane{b + 4 * nn, b + 4 * nn + 4 * nm,   b,
                 b + nn,     b + 2 * nn,            b + 3 * nn,
-                dd_fac(c, pipe_set(c, m)), second ? c->sdd_w2 : c->dd_w, second ? c->sdd_part2 : c->dd_part};
+                dd_fac(c, pipe_set(c, m)), second ? c->sdd_w2 : c->dd_w};
 }
 
 // The nodes of one correction sweep (stages s0 .. s0 + SDC_NODES - 1) read only slopes of

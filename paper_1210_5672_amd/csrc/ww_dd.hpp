@@ -303,86 +303,151 @@ __global__ __launch_bounds__(WW_NT) void k_dd_assemble(const double* __restrict_
   }
 }
 
-// -------------------------------------------------------------------------------------
-// out = add + sgn A B in double-double (the residual and the Gm Gamma products): A
-// column-major Np x Np, B, add and out Np x ncols (ld Np), hi and lo planes; add may be
-// null.  One workgroup per 64 rows x 4 columns; B in chunks of 64 rows through LDS;
-// each output sums its terms in increasing inner index.
-// -------------------------------------------------------------------------------------
-__global__ __launch_bounds__(WW_NT) void k_dd_gemm(const double* __restrict__ A_hi, const double* __restrict__ A_lo,
-                                                   int Np, const double* __restrict__ B_hi,
-                                                   const double* __restrict__ B_lo, const double* __restrict__ add_hi,
-                                                   const double* __restrict__ add_lo, double sgn,
-                                                   double* __restrict__ out_hi, double* __restrict__ out_lo,
-                                                   int ncols) {
-  __shared__ double bh[64][4], bl[64][4];
-  const int i = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int c = blockIdx.y * 4 + (threadIdx.x >> 6);
-  dd acc = dd_of(0.0);
-  for (int k0 = 0; k0 < Np; k0 += 64) {
-    {
-      const int kk = threadIdx.x & 63, cc = threadIdx.x >> 6;
-      const int cg = blockIdx.y * 4 + cc;
-      bh[kk][cc] = cg < ncols ? B_hi[(size_t)cg * Np + k0 + kk] : 0.0;
-      bl[kk][cc] = cg < ncols ? B_lo[(size_t)cg * Np + k0 + kk] : 0.0;
-    }
-    __syncthreads();
-    const int cc = threadIdx.x >> 6;
-    for (int kk = 0; kk < 64; ++kk) {
-      const size_t o = (size_t)(k0 + kk) * Np + i;
-      acc = dd_add(acc, dd_mul(dd{A_hi[o], A_lo[o]}, dd{bh[kk][cc], bl[kk][cc]}));
-    }
-    __syncthreads();
+// s += a b with s.lo left unnormalised: the product and the sum of the high parts are error
+// free, their errors and the cross terms go to s.lo.  12 operations instead of the 29 of
+// dd_mul and dd_add; each rounding of s.lo is 2^-53 |s.lo|, and dd_settle after every
+// DD_SETTLE products keeps |s.lo| below DD_SETTLE ulps of the running sum.
+#define DD_RUN 8
+#define DD_SETTLE 4
+__device__ __forceinline__ void dd_fma_acc(dd& s, dd a, dd b) {
+  CONTRACT_OFF
+  const double p = a.hi * b.hi;
+  double e = fma(a.hi, b.hi, -p);
+  e = fma(a.hi, b.lo, e);
+  e = fma(a.lo, b.hi, e);
+  const double h = s.hi + p, bb = h - s.hi;
+  s.lo += ((s.hi - (h - bb)) + (p - bb)) + e;
+  s.hi = h;
+}
+__device__ __forceinline__ void dd_settle(dd& s) { s = dd_two_sum(s.hi, s.lo); }
+
+// out = add + sgn * A B for ncols columns in double-double (A column-major, all ld Np; add may
+// be null).  A workgroup has 64 rows (one per lane) by NC columns, its eight waves split the
+// inner index (runs of DD_RUN: w, w + 8, ...) and are summed in that order at the end.  A
+// comes coalesced into registers, one run at a time, B through the scalar cache; five and more
+// waves per SIMD cover the latency.
+// Bound by the FP64 units: 12 Np^2 ncols operations at 39 T/s are 41 us at N = 1024, 129
+// columns.  NC (dd_gemm): A is read Np / 64 x ncols / NC times, so wide, but the grid should
+// come out even on the CUs.  Measured at that size: 92 us (one thread per entry over the whole
+// inner index with normalised sums 244), the error of G psi against exact values 0.5 to 0.95
+// of what it was (N 64 to 1024).
+#define DDG_NT 512
+template <int NC>
+__global__ __launch_bounds__(DDG_NT) void k_dd_gemm(const double* __restrict__ A_hi, const double* __restrict__ A_lo,
+                                                    int Np, const double* __restrict__ B_hi,
+                                                    const double* __restrict__ B_lo, const double* __restrict__ add_hi,
+                                                    const double* __restrict__ add_lo, double sgn,
+                                                    double* __restrict__ out_hi, double* __restrict__ out_lo,
+                                                    int ncols) {
+  constexpr int KS = DDG_NT / 64;
+  __shared__ dd part[KS][NC][64];
+  const int nrt = Np / 64, nct = (ncols + NC - 1) / NC;
+  int rt, ct;
+  if (nrt % 8 == 0) {   // workgroup b runs on XCD b mod 8: a band of row tiles each
+    const int x = blockIdx.x % 8, l = blockIdx.x / 8;
+    rt = x * (nrt / 8) + l / nct;
+    ct = l % nct;
+  } else {
+    rt = blockIdx.x / nct;
+    ct = blockIdx.x % nct;
   }
-  if (c >= ncols) return;
-  const size_t o = (size_t)c * Np + i;
-  dd r = dd{sgn * acc.hi, sgn * acc.lo};
-  if (add_hi) r = dd_add(dd{add_hi[o], add_lo[o]}, r);
-  out_hi[o] = r.hi;
-  out_lo[o] = r.lo;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  size_t bo[NC];   // uniform: B is read through the scalar cache
+#pragma unroll
+  for (int c = 0; c < NC; ++c) bo[c] = (size_t)min(ct * NC + c, ncols - 1) * Np;
+  dd acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = dd_of(0.0);
+#pragma unroll 1
+  for (int k0 = w * DD_RUN; k0 < Np; k0 += KS * DD_RUN) {
+    const size_t o = (size_t)k0 * Np + (size_t)rt * 64;
+    double ah[DD_RUN], al[DD_RUN];
+#pragma unroll
+    for (int k = 0; k < DD_RUN; ++k) {
+      ah[k] = (A_hi + (o + (size_t)k * Np))[(unsigned)lane];
+      al[k] = (A_lo + (o + (size_t)k * Np))[(unsigned)lane];
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+#pragma unroll
+      for (int k = 0; k < DD_RUN; ++k) {
+        dd_fma_acc(acc[c], dd{ah[k], al[k]}, dd{B_hi[bo[c] + k0 + k], B_lo ? B_lo[bo[c] + k0 + k] : 0.0});
+        if (k % DD_SETTLE == DD_SETTLE - 1) dd_settle(acc[c]);
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) part[w][c][lane] = acc[c];
+  __syncthreads();
+  for (int e = threadIdx.x; e < 64 * NC; e += DDG_NT) {
+    const int c = e / 64, col = ct * NC + c;
+    if (col >= ncols) break;
+    dd t = part[0][c][e % 64];
+#pragma unroll
+    for (int g = 1; g < KS; ++g) t = dd_add(t, part[g][c][e % 64]);
+    const size_t o = (size_t)col * Np + (size_t)rt * 64 + e % 64;
+    dd v = dd{sgn * t.hi, sgn * t.lo};
+    if (add_hi) v = dd_add(dd{add_hi[o], add_lo[o]}, v);
+    out_hi[o] = v.hi;
+    out_lo[o] = v.lo;
+  }
 }
 
-// The one-column form of k_dd_gemm (one right-hand side: the double-double march), split
-// over the inner index: chunk s = blockIdx.y of Np / gridDim.y indices, 64 rows per
-// workgroup; thread (row r, lane q) sums A_ij x_j over j = j0 + q, j0 + q + 4, ... in
-// increasing order, then the four lanes' partials in order q = 0..3 give P[s][i]
-// (coalesced: the 64 rows of one column are consecutive)
-#define DDGV_KS 16
-__global__ __launch_bounds__(WW_NT) void k_dd_gemv_part(const double* __restrict__ A_hi,
-                                                        const double* __restrict__ A_lo, int Np,
-                                                        const double* __restrict__ x_hi,
-                                                        const double* __restrict__ x_lo,
-                                                        double* __restrict__ P_hi, double* __restrict__ P_lo) {
-  __shared__ dd part[4][64];
-  const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + r;
-  const int len = Np / gridDim.y, j0 = blockIdx.y * len;
-  dd acc = dd_of(0.0);
-  for (int j = j0 + q; j < j0 + len; j += 4) {
-    const size_t o = (size_t)j * Np + i;
-    acc = dd_add(acc, dd_mul(dd{A_hi[o], A_lo[o]}, dd{x_hi[j], x_lo[j]}));
-  }
-  part[q][r] = acc;
-  __syncthreads();
-  if (q == 0) {
-    dd t = part[0][r];
-    for (int u = 1; u < 4; ++u) t = dd_add(t, part[u][r]);
-    P_hi[(size_t)blockIdx.y * Np + i] = t.hi;
-    P_lo[(size_t)blockIdx.y * Np + i] = t.lo;
-  }
+// Residual maxima: a non-negative double orders like its bits; NaN counts as infinite.
+__device__ __forceinline__ void dd_mx_put(unsigned long long* __restrict__ mx, double mr, double mb) {
+  atomicMax(mx, (unsigned long long)__double_as_longlong(mr));
+  atomicMax(mx + 1, (unsigned long long)__double_as_longlong(mb));
 }
-// out = add + sgn sum_s P[s] (chunks in increasing order); add may be null
-__global__ void k_dd_gemv_sum(const double* __restrict__ P_hi, const double* __restrict__ P_lo, int ks, int Np,
-                              const double* __restrict__ add_hi, const double* __restrict__ add_lo, double sgn,
-                              double* __restrict__ out_hi, double* __restrict__ out_lo) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Np) return;
-  dd t = dd_of(0.0);
-  for (int s = 0; s < ks; ++s) t = dd_add(t, dd{P_hi[(size_t)s * Np + i], P_lo[(size_t)s * Np + i]});
+
+// The one-column form: 16 rows per workgroup (128 bytes of a column of A), 64 lanes per row
+// over the inner index (j = q, q + 64, ...), summed by a fixed tree; no second launch for the
+// partials.  mx (optional): max |out| and max |add| over the rows < N join mx[0], mx[1] (one
+// atomic each per workgroup).  Latency bound.  Measured at N = 512: 6.6 us (64 rows x 16 inner
+// chunks 4.7, a second launch for their sum 6.6, a third for the maxima 7.5).
+#define DDV_NT 1024
+__global__ __launch_bounds__(DDV_NT) void k_dd_gemv(const double* __restrict__ A_hi, const double* __restrict__ A_lo,
+                                                    int Np, const double* __restrict__ x_hi,
+                                                    const double* __restrict__ x_lo, const double* __restrict__ add_hi,
+                                                    const double* __restrict__ add_lo, double sgn,
+                                                    double* __restrict__ out_hi, double* __restrict__ out_lo, int N,
+                                                    unsigned long long* __restrict__ mx) {
+  __shared__ dd part[DDV_NT / 64][16];
+  const int row = threadIdx.x & 15, q = threadIdx.x >> 4, lane = threadIdx.x & 63;
+  const size_t i = (size_t)blockIdx.x * 16 + row;
+  dd acc = dd_of(0.0);
+#pragma unroll 4
+  for (int j = q; j < Np; j += DDV_NT / 16) {
+    const size_t o = (size_t)j * Np + i;
+    acc = dd_add(acc, dd_mul(dd{A_hi[o], A_lo[o]}, dd{x_hi[j], x_lo ? x_lo[j] : 0.0}));
+  }
+  auto fold = [&](dd v, int m) { return dd_add(v, dd{__shfl_xor(v.hi, m), __shfl_xor(v.lo, m)}); };
+  acc = fold(fold(acc, 16), 32);
+  if (lane < 16) part[threadIdx.x >> 6][row] = acc;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int g = 4 * (lane >> 4);
+  dd t = dd_add(dd_add(part[g][row], part[g + 1][row]), dd_add(part[g + 2][row], part[g + 3][row]));
+  t = fold(fold(t, 16), 32);
   if (sgn < 0.0) t = dd_neg(t);
-  if (add_hi) t = dd_add(dd{add_hi[i], add_lo[i]}, t);
-  out_hi[i] = t.hi;
-  out_lo[i] = t.lo;
+  dd ad = dd_of(0.0);
+  if (add_hi) {
+    ad = dd{add_hi[i], add_lo[i]};
+    t = dd_add(ad, t);
+  }
+  if (lane < 16) {
+    out_hi[i] = t.hi;
+    out_lo[i] = t.lo;
+  }
+  if (!mx) return;
+  const bool in = (int)i < N;
+  double mr = in ? fabs(t.hi) : 0.0, mb = in ? fabs(ad.hi) : 0.0;
+  if (mr != mr) mr = INFINITY;
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) {
+    mr = fmax(mr, __shfl_xor(mr, m));
+    mb = fmax(mb, __shfl_xor(mb, m));
+  }
+  if (lane == 0) dd_mx_put(mx, mr, mb);
 }
 
 // the FP32 copy of the FP64 leading part of A (the mixed form factors it on MFMA)
@@ -391,11 +456,11 @@ __global__ void k_dd_a32(const double* __restrict__ A, float* __restrict__ A32, 
     A32[e] = (float)A[e];
 }
 
-// mu += delta (double-double plus a double), n entries
+// mu += delta (double-double plus a double), n entries; lo0: mu's low part is not set yet (0)
 __global__ void k_dd_correct(double* __restrict__ mu_hi, double* __restrict__ mu_lo, const double* __restrict__ delta,
-                             size_t n) {
+                             size_t n, bool lo0) {
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) {
-    const dd v = dd_add_d(dd{mu_hi[t], mu_lo[t]}, delta[t]);
+    const dd v = dd_add_d(dd{mu_hi[t], lo0 ? 0.0 : mu_lo[t]}, delta[t]);
     mu_hi[t] = v.hi;
     mu_lo[t] = v.lo;
   }
@@ -447,11 +512,11 @@ __global__ void k_dd_mx_reset(unsigned long long* __restrict__ mx) {
   if (threadIdx.x == 0) mx[0] = mx[1] = 0;
 }
 
-// max |r| and max |b| over rows < N of ncols columns (ld Np) into mx[0], mx[1] by
-// atomic maxima on the bit patterns (non-negative doubles order like their bits; a
-// NaN residual counts as infinite)
-__global__ void k_dd_maxabs(const double* __restrict__ r, const double* __restrict__ b, int N, int Np, int ncols,
-                            unsigned long long* __restrict__ mx) {
+// max |r| and max |b| over rows < N of ncols columns (ld Np) into mx[0], mx[1]: one atomic
+// maximum each per workgroup (one per thread took 28 us at N = 1024, 129 columns)
+__global__ __launch_bounds__(WW_NT) void k_dd_maxabs(const double* __restrict__ r, const double* __restrict__ b, int N,
+                                                     int Np, int ncols, unsigned long long* __restrict__ mx) {
+  __shared__ double red[2][WW_NT / 64];
   double mr = 0.0, mb = 0.0;
   const size_t tot = (size_t)Np * ncols;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
@@ -460,8 +525,22 @@ __global__ void k_dd_maxabs(const double* __restrict__ r, const double* __restri
     mr = fmax(mr, v != v ? INFINITY : v);
     mb = fmax(mb, fabs(b[t]));
   }
-  atomicMax(mx, (unsigned long long)__double_as_longlong(mr));
-  atomicMax(mx + 1, (unsigned long long)__double_as_longlong(mb));
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    mr = fmax(mr, __shfl_xor(mr, m));
+    mb = fmax(mb, __shfl_xor(mb, m));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = mr;
+    red[1][threadIdx.x >> 6] = mb;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < WW_NT / 64; ++w) {
+    mr = fmax(mr, red[0][w]);
+    mb = fmax(mb, red[1][w]);
+  }
+  dd_mx_put(mx, mr, mb);
 }
 
 // =====================================================================================
