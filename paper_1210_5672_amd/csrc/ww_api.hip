@@ -1815,7 +1815,10 @@ static int dd_tables(ww_ctx* c, int N) {
   return 0;
 }
 
-static size_t dd_lds_bytes(int N) { return (size_t)(3 * N + N / 2) * sizeof(cdd); }
+// LDS and threads of the double-double transforms (four buffers and half of one for the
+// twiddles; N threads: the butterflies of two transforms)
+static size_t dd_lds_bytes(int N) { return (size_t)(4 * N + N / 2) * sizeof(cdd); }
+static dim3 dd_threads(int N) { return dim3(std::min(DDF_NT, std::max(64, N))); }
 
 // The buffers of one double-double DtN: per-point quantities, A and Gm (hi and lo
 // planes), and the FP64 factor set whose Ar receives A's leading part and whose Mi the
@@ -1843,7 +1846,7 @@ static DdLane dd_lane(ww_ctx* c) {
 // L; domain (optional): status word for the finite-depth test h + eta > 0
 static int dd_prep_assemble(ww_ctx* c, const DdLane& L, const double* sh, const double* sl, int* domain) {
   const int N = c->N, Np = c->Np;
-  hipLaunchKernelGGL(k_dd_prep, dim3(1), dim3(WW_NT), dd_lds_bytes(N), c->stream, sh, sl, c->hsurf, c->dd_tw, N,
+  hipLaunchKernelGGL(k_dd_prep, dim3(1), dd_threads(N), dd_lds_bytes(N), c->stream, sh, sl, c->hsurf, c->dd_tw, N,
                      c->n_max, L.pt_hi, L.pt_lo, c->finite ? domain : nullptr);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_dd_assemble, dim3(Np / WW_TB, Np / 16), dim3(WW_NT), 0, c->stream, L.pt_hi, L.pt_lo, c->n_max,
@@ -1916,7 +1919,7 @@ static int dd_solve_enqueue(ww_ctx* c, const DdLane& L, const double* rhs_hi, co
     LAUNCHCHK();
   }
   if ((rc = dd_gemm(c, L.Ah, L.Al, muh, mul, psh, psl, -1.0, rh, rl, nrhs, mx))) return rc;
-  hipLaunchKernelGGL(k_dd_gamma, dim3(nrhs), dim3(WW_NT), dd_lds_bytes(N), c->stream, muh, mul, Np, c->dd_tw, N, gh,
+  hipLaunchKernelGGL(k_dd_gamma, dim3(nrhs), dd_threads(N), dd_lds_bytes(N), c->stream, muh, mul, Np, c->dd_tw, N, gh,
                      gl, hh, hl);
   LAUNCHCHK();
   if ((rc = dd_gemm(c, L.Gh, L.Gl, gh, gl, hh, hl, 1.0, oh, ol, nrhs))) return rc;
@@ -3082,10 +3085,8 @@ static int dd_rhs_tail(ww_ctx* c, const DdLane& L, const double* yh, const doubl
   int rc;
   const int N = c->N;
   if ((rc = dd_solve_enqueue(c, L, yh + N, yl + N, 1, gh, gl, nullptr, nullptr, mx))) return rc;
-  hipLaunchKernelGGL(k_dd_restest, dim3(1), dim3(64), 0, c->stream, mx, DD_TOL, c->status);
-  LAUNCHCHK();
-  hipLaunchKernelGGL(k_dd_base_rhs, dim3(1), dim3(WW_NT), dd_lds_bytes(N), c->stream, yh, yl, gh, gl, c->sdd_fh,
-                     c->sdd_fl, c->dd_tw, N, g, tau, kh, kl);
+  hipLaunchKernelGGL(k_dd_base_rhs, dim3(1), dd_threads(N), dd_lds_bytes(N), c->stream, yh, yl, gh, gl, c->sdd_fh,
+                     c->sdd_fl, c->dd_tw, N, g, tau, kh, kl, mx, DD_TOL, c->status);
   LAUNCHCHK();
   return 0;
 }
@@ -3275,7 +3276,7 @@ int shoot_eval_sdc_dd(ww_ctx* c, int N, double h, double tau, double g, const do
       if ((rc = dd_rhs(c, c->sdd_Yh, c->sdd_Yl, tau, g, c->sdd_Kh + s * n2, c->sdd_Kl + s * n2))) return rc;
     }
     if ((rc = combine(SDC_STAGES, c->sdd_yh, c->sdd_yl))) return rc;
-    hipLaunchKernelGGL(k_dd_filter_state, dim3(1), dim3(WW_NT), dd_lds_bytes(N), c->stream, c->sdd_yh, c->sdd_yl,
+    hipLaunchKernelGGL(k_dd_filter_state, dim3(1), dd_threads(N), dd_lds_bytes(N), c->stream, c->sdd_yh, c->sdd_yl,
                        c->sdd_fh, c->sdd_fl, c->dd_tw, N);
     LAUNCHCHK();
     if ((rc = dd_march_status(c, n))) return rc;

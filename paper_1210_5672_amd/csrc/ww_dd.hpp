@@ -18,7 +18,7 @@
 // the sum of a two-sum loses the low part).
 #define CONTRACT_OFF _Pragma("clang fp contract(off)")
 
-struct dd {
+struct alignas(16) dd {   // (one 16-byte LDS access)
   double hi, lo;
 };
 struct cdd {
@@ -100,20 +100,45 @@ __host__ __device__ inline cdd cdd_mul(cdd a, cdd b) {
 #define DD_LN2_HI 6.931471805599452862e-01
 #define DD_LN2_LO 2.319046813846299558e-17
 
-// exp in double-double: a = k ln2 + r, |r| <= ln2/2, exp(r) by its Taylor series to
-// the term r^27/27! (below 1e-37 for |r| <= 0.35), times 2^k.  No squarings: they would
-// multiply the rounding of the series.
-__device__ inline dd dd_exp(dd a) {
+// 1/n for n < 28 as double-doubles: hi the quotient, lo its remainder (1 - hi n) / n, formed
+// exactly from the upper 26 and the lower 27 bits of hi
+struct DdInv {
+  double hi[28], lo[28];
+  constexpr DdInv() : hi{}, lo{} {
+    for (int n = 1; n < 28; ++n) {
+      const double q = 1.0 / n, c = q * 134217729.0, h = c - (c - q), l = q - h;
+      hi[n] = q;
+      lo[n] = ((1.0 - h * n) - l * n) / n;
+    }
+  }
+};
+__device__ constexpr DdInv dd_inv{};
+
+// exp(a) and exp(-a) in double-double: a = k ln2 + r, |r| <= ln2/2, the even and the odd part
+// of exp(r)'s Taylor series to the term r^27/27! (below 1e-37 for |r| <= 0.35), their sum and
+// difference times 2^k and 2^-k.  No squarings: they would multiply the rounding of the
+// series; no divisions: 27 of them took half of k_dd_prep.
+__device__ inline void dd_exp_pm(dd a, dd* p, dd* m) {
   const double k = rint(a.hi / DD_LN2_HI);
   const dd ln2 = dd{DD_LN2_HI, DD_LN2_LO};
   const dd r = dd_sub(a, dd_mul_d(ln2, k));
-  dd term = r, sum = dd_add_d(r, 1.0);
-  for (int n = 2; n <= 27; ++n) {
-    term = dd_div_d(dd_mul(term, r), (double)n);
-    sum = dd_add(sum, term);
+  dd term = r, odd = r, even = dd_of(0.0);   // even: without the leading 1, which is added last
+#pragma unroll 1
+  for (int n = 2; n < 28; n += 2) {
+    term = dd_mul(dd_mul(term, r), dd{dd_inv.hi[n], dd_inv.lo[n]});
+    even = dd_add(even, term);
+    term = dd_mul(dd_mul(term, r), dd{dd_inv.hi[n + 1], dd_inv.lo[n + 1]});
+    odd = dd_add(odd, term);
   }
   const int ki = (int)k;
-  return dd{ldexp(sum.hi, ki), ldexp(sum.lo, ki)};
+  const dd u = dd_add(dd_of(1.0), dd_add(even, odd)), v = dd_add(dd_of(1.0), dd_sub(even, odd));
+  *p = dd{ldexp(u.hi, ki), ldexp(u.lo, ki)};
+  *m = dd{ldexp(v.hi, -ki), ldexp(v.lo, -ki)};
+}
+__device__ inline dd dd_exp(dd a) {
+  dd p, m;
+  dd_exp_pm(a, &p, &m);
+  return p;
 }
 
 // cot((x + i y)/2) from cos x, sin x, cosh y, sinh y by the two-branch formula of
@@ -132,38 +157,75 @@ __device__ inline void dd_cot_half(dd cx, dd sx, dd chy, dd shy, dd& re, dd& im)
 }
 
 // -------------------------------------------------------------------------------------
-// Radix-2 Stockham FFT of N = 2^a complex double-doubles in LDS (one workgroup);
-// a = data, b = scratch, tw[j] = exp(-2 pi i j / N) for j < N/2.  dir -1 forward, +1
-// inverse (with the 1/N).  Result in a.  Ends with a barrier.
+// Radix-2 Stockham FFTs of N = 2^lg complex double-doubles in LDS, NB of them side by side by
+// one workgroup; a = data, b = scratch, tw[j] = exp(-2 pi i j / N) for j < N/2.  dir -1
+// forward, +1 inverse (with the 1/N).  a and b are exchanged as needed: the results are in a.
+// Starts and ends with a barrier.
+//
+// Bound by the FP64 units of the one CU (156 operations a butterfly: 2.4 us of a transform at
+// N = 512) and each stage's chain of dependent operations: transforms that do not depend on each
+// other run together, indexing is shifts and masks, real and imaginary parts lie in planes
+// of their own (16-byte steps from lane to lane, no bank conflicts).  Two threads per butterfly
+// (one part each) took 1640 cycles a stage for their selects against 1500.  Measured at N = 512: 5.7 us a
+// transform, 8.7 us two (one at a time, divisions for the indices, a scaling pass: 11 us each).
 // -------------------------------------------------------------------------------------
-__device__ inline void dd_fft(cdd* a, cdd* b, const cdd* tw, int N, int dir) {
+#define DDF_NT 1024
+struct CddBuf {
+  dd *re, *im;
+  __device__ cdd get(int t) const { return cdd{re[t], im[t]}; }
+  __device__ void put(int t, cdd v) const {
+    re[t] = v.re;
+    im[t] = v.im;
+  }
+};
+// buffer q of N values in the dynamic LDS (dd_lds_bytes: four and the twiddles' half)
+__device__ inline CddBuf dd_buf(dd* lds, int q, int N) { return CddBuf{lds + (size_t)2 * q * N, lds + (size_t)(2 * q + 1) * N}; }
+__device__ inline CddBuf dd_twiddles(dd* lds, const cdd* __restrict__ twg, int N) {
+  const CddBuf tw{lds + (size_t)8 * N, lds + (size_t)8 * N + N / 2};
+  for (int t = threadIdx.x; t < N / 2; t += blockDim.x) tw.put(t, twg[t]);
+  return tw;
+}
+template <int NB>
+__device__ inline void dd_fft(CddBuf (&a)[NB], CddBuf (&b)[NB], CddBuf tw, int N, int dir) {
   __syncthreads();
-  cdd* src = a;
-  cdd* dst = b;
-  const int half = N / 2;
-  for (int Ns = 1; Ns < N; Ns *= 2) {
-    for (int j = threadIdx.x; j < half; j += blockDim.x) {
-      const int jm = j % Ns;
-      cdd w = tw[jm * (half / Ns)];
-      if (dir > 0) w.im = dd_neg(w.im);
-      const cdd u = src[j];
-      const cdd v = cdd_mul(src[j + half], w);
-      const int o = (j / Ns) * Ns * 2 + jm;
-      dst[o] = cdd_add(u, v);
-      dst[o + Ns] = cdd_sub(u, v);
+  const int lg = __builtin_ctz(N), half = N >> 1;
+  const double sc = dir > 0 ? 1.0 / (double)N : 1.0;   // exact: N is a power of two
+#pragma unroll 1
+  for (int s = 0; s < lg; ++s) {
+    const int Ns = 1 << s;
+    for (int it = threadIdx.x; it < NB * half; it += blockDim.x) {
+      const bool q = NB > 1 && it >= half;
+      const int j = it & (half - 1), jm = j & (Ns - 1), o = 2 * j - jm;
+      const CddBuf A = a[q ? NB - 1 : 0], B = b[q ? NB - 1 : 0];
+      const cdd u = A.get(j);
+      cdd v = A.get(j + half);
+      if (s > 0) {
+        cdd w = tw.get(jm << (lg - 1 - s));
+        if (dir > 0) w.im = dd_neg(w.im);
+        v = cdd_mul(v, w);
+      }
+      cdd x = cdd_add(u, v), y = cdd_sub(u, v);
+      if (s + 1 == lg && dir > 0) {
+        x = cdd{dd{x.re.hi * sc, x.re.lo * sc}, dd{x.im.hi * sc, x.im.lo * sc}};
+        y = cdd{dd{y.re.hi * sc, y.re.lo * sc}, dd{y.im.hi * sc, y.im.lo * sc}};
+      }
+      B.put(o, x);
+      B.put(o + Ns, y);
     }
     __syncthreads();
-    cdd* t = src;
-    src = dst;
-    dst = t;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const CddBuf t = a[q];
+      a[q] = b[q];
+      b[q] = t;
+    }
   }
-  const double sc = dir > 0 ? 1.0 / (double)N : 1.0;   // exact: N is a power of two
-  for (int t = threadIdx.x; t < N; t += blockDim.x) {
-    cdd v = src[t];
-    if (dir > 0) v = cdd{dd{v.re.hi * sc, v.re.lo * sc}, dd{v.im.hi * sc, v.im.lo * sc}};
-    a[t] = v;
-  }
-  __syncthreads();
+}
+__device__ inline void dd_fft1(CddBuf& a, CddBuf& b, CddBuf tw, int N, int dir) {
+  CddBuf x[1] = {a}, y[1] = {b};
+  dd_fft<1>(x, y, tw, N, dir);
+  a = x[0];
+  b = y[0];
 }
 
 // i k (with the Nyquist mode set to zero) times X
@@ -178,39 +240,35 @@ __device__ inline cdd dd_ik(cdd X, int k, int N) {
 // with the Nyquist mode set to zero, eta'' = d(eta')), exp(s) and exp(-s) of the
 // surface height s (h + eta at finite depth, eta otherwise); domain (optional, finite
 // depth): status bit 16 where s <= 0.  pt_hi / pt_lo: 4 planes
-// of nmax values each: eta', eta'', exp(s), exp(-s).  Dynamic LDS: 3.5 N complex
-// double-doubles (data, two scratch buffers, N/2 twiddles).
+// of nmax values each: eta', eta'', exp(s), exp(-s).  Measured at N = 512: 21.7 us (62).
 // -------------------------------------------------------------------------------------
-__global__ __launch_bounds__(WW_NT) void k_dd_prep(const double* __restrict__ eh, const double* __restrict__ el,
-                                                   double hsurf, const cdd* __restrict__ twg, int N, int nmax,
-                                                   double* __restrict__ pt_hi, double* __restrict__ pt_lo,
-                                                   int* __restrict__ domain) {
-  extern __shared__ cdd ldsd[];
-  cdd* Z = ldsd;
-  cdd* W = ldsd + N;
-  cdd* S = ldsd + 2 * N;
-  cdd* tw = ldsd + 3 * N;
-  for (int t = threadIdx.x; t < N / 2; t += WW_NT) tw[t] = twg[t];
-  for (int t = threadIdx.x; t < N; t += WW_NT) Z[t] = cdd{dd{eh[t], el ? el[t] : 0.0}, dd_of(0.0)};
-  dd_fft(Z, W, tw, N, -1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
+__global__ __launch_bounds__(DDF_NT) void k_dd_prep(const double* __restrict__ eh, const double* __restrict__ el,
+                                                    double hsurf, const cdd* __restrict__ twg, int N, int nmax,
+                                                    double* __restrict__ pt_hi, double* __restrict__ pt_lo,
+                                                    int* __restrict__ domain) {
+  extern __shared__ dd ldsd[];
+  CddBuf Z = dd_buf(ldsd, 0, N), W = dd_buf(ldsd, 1, N);
+  const CddBuf tw = dd_twiddles(ldsd, twg, N);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) Z.put(t, cdd{dd{eh[t], el ? el[t] : 0.0}, dd_of(0.0)});
+  dd_fft1(Z, W, tw, N, -1);
+  CddBuf D[2] = {W, dd_buf(ldsd, 2, N)}, X[2] = {Z, dd_buf(ldsd, 3, N)};   // eta', eta''
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
     const int k = t <= N / 2 ? t : t - N;
-    const cdd d1 = dd_ik(Z[t], k, N);
-    W[t] = d1;
-    S[t] = dd_ik(d1, k, N);
+    const cdd d1 = dd_ik(Z.get(t), k, N);
+    D[0].put(t, d1);
+    D[1].put(t, dd_ik(d1, k, N));
   }
-  dd_fft(W, Z, tw, N, +1);   // eta'
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
-    pt_hi[t] = W[t].re.hi;
-    pt_lo[t] = W[t].re.lo;
-  }
-  dd_fft(S, Z, tw, N, +1);   // eta''
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
-    pt_hi[nmax + t] = S[t].re.hi;
-    pt_lo[nmax + t] = S[t].re.lo;
+  dd_fft<2>(D, X, tw, N, +1);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
+    const dd d1 = D[0].re[t], d2 = D[1].re[t];
+    pt_hi[t] = d1.hi;
+    pt_lo[t] = d1.lo;
+    pt_hi[nmax + t] = d2.hi;
+    pt_lo[nmax + t] = d2.lo;
     const dd sh = dd_add_d(dd{eh[t], el ? el[t] : 0.0}, hsurf);
     if (domain && !(sh.hi > 0.0)) atomicOr(domain, 16);   // finite depth: h + eta > 0
-    const dd ep = dd_exp(sh), em = dd_exp(dd_neg(sh));
+    dd ep, em;
+    dd_exp_pm(sh, &ep, &em);
     pt_hi[2 * nmax + t] = ep.hi;
     pt_lo[2 * nmax + t] = ep.lo;
     pt_hi[3 * nmax + t] = em.hi;
@@ -467,47 +525,39 @@ __global__ void k_dd_correct(double* __restrict__ mu_hi, double* __restrict__ mu
 }
 
 // gamma = d mu/dalpha and H gamma / 2 (spectrum |k| mu_hat / 2, zero at k = 0 and at
-// Nyquist) of one column per workgroup, double-double; rows N..Np-1 zero.  Dynamic
-// LDS: 3.5 N complex double-doubles.
-__global__ __launch_bounds__(WW_NT) void k_dd_gamma(const double* __restrict__ mu_hi, const double* __restrict__ mu_lo,
-                                                    int Np, const cdd* __restrict__ twg, int N,
-                                                    double* __restrict__ g_hi, double* __restrict__ g_lo,
-                                                    double* __restrict__ h_hi, double* __restrict__ h_lo) {
-  extern __shared__ cdd ldsd[];
-  cdd* Z = ldsd;
-  cdd* W = ldsd + N;
-  cdd* S = ldsd + 2 * N;
-  cdd* tw = ldsd + 3 * N;
+// Nyquist) of one column per workgroup, double-double; rows N..Np-1 zero.
+// Measured: N = 512, one column 17 us (35); N = 1024, 129 columns 32 us (71).
+__global__ __launch_bounds__(DDF_NT) void k_dd_gamma(const double* __restrict__ mu_hi,
+                                                     const double* __restrict__ mu_lo, int Np,
+                                                     const cdd* __restrict__ twg, int N, double* __restrict__ g_hi,
+                                                     double* __restrict__ g_lo, double* __restrict__ h_hi,
+                                                     double* __restrict__ h_lo) {
+  extern __shared__ dd ldsd[];
+  CddBuf Z = dd_buf(ldsd, 0, N), W = dd_buf(ldsd, 1, N);
+  const CddBuf tw = dd_twiddles(ldsd, twg, N);
   const size_t off = (size_t)blockIdx.x * Np;
-  for (int t = threadIdx.x; t < N / 2; t += WW_NT) tw[t] = twg[t];
-  for (int t = threadIdx.x; t < N; t += WW_NT) Z[t] = cdd{dd{mu_hi[off + t], mu_lo[off + t]}, dd_of(0.0)};
-  dd_fft(Z, W, tw, N, -1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
+  for (int t = threadIdx.x; t < N; t += blockDim.x)
+    Z.put(t, cdd{dd{mu_hi[off + t], mu_lo[off + t]}, dd_of(0.0)});
+  dd_fft1(Z, W, tw, N, -1);
+  CddBuf D[2] = {W, dd_buf(ldsd, 2, N)}, X[2] = {Z, dd_buf(ldsd, 3, N)};
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
     const int k = t <= N / 2 ? t : t - N;
-    W[t] = dd_ik(Z[t], k, N);
+    const cdd z = Z.get(t);
+    D[0].put(t, dd_ik(z, k, N));
     const double hk = (k == 0 || 2 * k == N || 2 * k == -N) ? 0.0 : 0.5 * fabs((double)k);
-    S[t] = cdd{dd_mul_d(Z[t].re, hk), dd_mul_d(Z[t].im, hk)};
+    D[1].put(t, cdd{dd_mul_d(z.re, hk), dd_mul_d(z.im, hk)});
   }
-  dd_fft(W, Z, tw, N, +1);
-  dd_fft(S, Z, tw, N, +1);
-  for (int t = threadIdx.x; t < Np; t += WW_NT) {
+  dd_fft<2>(D, X, tw, N, +1);
+  for (int t = threadIdx.x; t < Np; t += blockDim.x) {
     const bool in = t < N;
-    g_hi[off + t] = in ? W[t].re.hi : 0.0;
-    g_lo[off + t] = in ? W[t].re.lo : 0.0;
-    h_hi[off + t] = in ? S[t].re.hi : 0.0;
-    h_lo[off + t] = in ? S[t].re.lo : 0.0;
+    const dd g = in ? D[0].re[t] : dd_of(0.0), h = in ? D[1].re[t] : dd_of(0.0);
+    g_hi[off + t] = g.hi;
+    g_lo[off + t] = g.lo;
+    h_hi[off + t] = h.hi;
+    h_lo[off + t] = h.lo;
   }
 }
 
-// the residual test of a double-double solve: status bit 4 unless max|r| <= tol max|b|
-// (mx from k_dd_maxabs); mx is cleared for the next solve
-__global__ void k_dd_restest(unsigned long long* __restrict__ mx, double tol, int* __restrict__ status) {
-  if (threadIdx.x != 0) return;
-  const double mr = __longlong_as_double((long long)mx[0]), mb = __longlong_as_double((long long)mx[1]);
-  if (!(mr <= tol * mb)) atomicOr(status, 4);
-  mx[0] = 0;
-  mx[1] = 0;
-}
 __global__ void k_dd_mx_reset(unsigned long long* __restrict__ mx) {
   if (threadIdx.x == 0) mx[0] = mx[1] = 0;
 }
@@ -600,73 +650,79 @@ __global__ void k_dd_sdc_combine(const double* __restrict__ y0h, const double* _
 //   u = (phi' - eta' G)/(1 + eta'^2),  v = (eta' phi' + G)/(1 + eta'^2),
 //   eta_t = G phi,  phi_t = P[v eta_t - u^2/2 - v^2/2 - g eta + tau d/dx(eta'/sqrt(1 + eta'^2))],
 // both filtered by one packed transform (the filter is even and real; P zeroes the mean
-// of phi_t only: the imaginary part of mode 0).  Dynamic LDS: 3.5 N complex
-// double-doubles.
-__global__ __launch_bounds__(WW_NT) void k_dd_base_rhs(const double* __restrict__ yh, const double* __restrict__ yl,
-                                                       const double* __restrict__ gh, const double* __restrict__ gl,
-                                                       const double* __restrict__ f_hi, const double* __restrict__ f_lo,
-                                                       const cdd* __restrict__ twg, int N, double g, double tau,
-                                                       double* __restrict__ kh, double* __restrict__ kl) {
-  extern __shared__ cdd ldsd[];
-  cdd* Z = ldsd;
-  cdd* W = ldsd + N;
-  cdd* S = ldsd + 2 * N;
-  cdd* tw = ldsd + 3 * N;
+// of phi_t only: the imaginary part of mode 0).  The capillary term's two transforms are left
+// out where tau = 0.  First the residual test of the solve behind G: status bit 4 unless
+// max|r| <= tol max|b| (mx, cleared for the next solve).  Measured at N = 512: 28 us (66).
+__global__ __launch_bounds__(DDF_NT) void k_dd_base_rhs(const double* __restrict__ yh, const double* __restrict__ yl,
+                                                        const double* __restrict__ gh, const double* __restrict__ gl,
+                                                        const double* __restrict__ f_hi,
+                                                        const double* __restrict__ f_lo, const cdd* __restrict__ twg,
+                                                        int N, double g, double tau, double* __restrict__ kh,
+                                                        double* __restrict__ kl, unsigned long long* __restrict__ mx,
+                                                        double tol, int* __restrict__ status) {
+  extern __shared__ dd ldsd[];
+  CddBuf Z = dd_buf(ldsd, 0, N), W = dd_buf(ldsd, 1, N), S = dd_buf(ldsd, 2, N);
+  dd* const w = ldsd + (size_t)6 * N;   // the nonlinear terms
+  const CddBuf tw = dd_twiddles(ldsd, twg, N);
   const dd zero = dd_of(0.0);
-  for (int t = threadIdx.x; t < N / 2; t += WW_NT) tw[t] = twg[t];
-  for (int t = threadIdx.x; t < N; t += WW_NT) Z[t] = cdd{dd_ld(yh, yl, t), dd_ld(yh, yl, N + t)};
-  dd_fft(Z, W, tw, N, -1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) Z[t] = dd_ik(Z[t], t <= N / 2 ? t : t - N, N);
-  dd_fft(Z, W, tw, N, +1);   // Z = eta' + i phi'
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
-    const dd ex = Z[t].re, ps = Z[t].im, G = dd_ld(gh, gl, t);
+  if (threadIdx.x == 0) {
+    const double mr = __longlong_as_double((long long)mx[0]), mb = __longlong_as_double((long long)mx[1]);
+    if (!(mr <= tol * mb)) atomicOr(status, 4);
+    mx[0] = 0;
+    mx[1] = 0;
+  }
+  for (int t = threadIdx.x; t < N; t += blockDim.x) Z.put(t, cdd{dd_ld(yh, yl, t), dd_ld(yh, yl, N + t)});
+  dd_fft1(Z, W, tw, N, -1);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) Z.put(t, dd_ik(Z.get(t), t <= N / 2 ? t : t - N, N));
+  dd_fft1(Z, W, tw, N, +1);   // Z = eta' + i phi'
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
+    const dd ex = Z.re[t], ps = Z.im[t], G = dd_ld(gh, gl, t);
     const dd den = dd_add_d(dd_mul(ex, ex), 1.0);
     const dd u = dd_div(dd_sub(ps, dd_mul(ex, G)), den);
     const dd v = dd_div(dd_add(dd_mul(ex, ps), G), den);
     dd s = dd_sub(dd_mul(v, G), dd_mul_d(dd_add(dd_mul(u, u), dd_mul(v, v)), 0.5));
-    s = dd_sub(s, dd_mul_d(dd_ld(yh, yl, t), g));
-    W[t] = cdd{s, zero};
-    S[t] = cdd{dd_div(ex, dd_sqrt(den)), zero};
+    w[t] = dd_sub(s, dd_mul_d(dd_ld(yh, yl, t), g));
+    if (tau != 0.0) S.put(t, cdd{dd_div(ex, dd_sqrt(den)), zero});
   }
-  dd_fft(S, Z, tw, N, -1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) S[t] = dd_ik(S[t], t <= N / 2 ? t : t - N, N);
-  dd_fft(S, Z, tw, N, +1);   // S.re = d/dx(eta'/sqrt(1 + eta'^2))
-  for (int t = threadIdx.x; t < N; t += WW_NT)
-    Z[t] = cdd{dd_ld(gh, gl, t), dd_add(W[t].re, dd_mul_d(S[t].re, tau))};
-  dd_fft(Z, W, tw, N, -1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
+  if (tau != 0.0) {
+    dd_fft1(S, W, tw, N, -1);
+    for (int t = threadIdx.x; t < N; t += blockDim.x) S.put(t, dd_ik(S.get(t), t <= N / 2 ? t : t - N, N));
+    dd_fft1(S, W, tw, N, +1);   // S.re = d/dx(eta'/sqrt(1 + eta'^2))
+  }
+  for (int t = threadIdx.x; t < N; t += blockDim.x)
+    Z.put(t, cdd{dd_ld(gh, gl, t), tau != 0.0 ? dd_add(w[t], dd_mul_d(S.re[t], tau)) : w[t]});
+  dd_fft1(Z, W, tw, N, -1);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
     const dd f = dd_filt_at(f_hi, f_lo, t, N);
-    cdd v = cdd{dd_mul(Z[t].re, f), dd_mul(Z[t].im, f)};
+    cdd v = cdd{dd_mul(Z.re[t], f), dd_mul(Z.im[t], f)};
     if (t == 0) v.im = zero;   // P: the mean of phi_t
-    Z[t] = v;
+    Z.put(t, v);
   }
-  dd_fft(Z, W, tw, N, +1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
-    dd_st(kh, kl, t, Z[t].re);
-    dd_st(kh, kl, N + t, Z[t].im);
+  dd_fft1(Z, W, tw, N, +1);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
+    dd_st(kh, kl, t, Z.re[t]);
+    dd_st(kh, kl, N + t, Z.im[t]);
   }
 }
 
 // the filter on the state after a step (eta and phi packed), in place
-__global__ __launch_bounds__(WW_NT) void k_dd_filter_state(double* __restrict__ yh, double* __restrict__ yl,
-                                                           const double* __restrict__ f_hi,
-                                                           const double* __restrict__ f_lo, const cdd* __restrict__ twg,
-                                                           int N) {
-  extern __shared__ cdd ldsd[];
-  cdd* Z = ldsd;
-  cdd* W = ldsd + N;
-  cdd* tw = ldsd + 3 * N;
-  for (int t = threadIdx.x; t < N / 2; t += WW_NT) tw[t] = twg[t];
-  for (int t = threadIdx.x; t < N; t += WW_NT) Z[t] = cdd{dd_ld(yh, yl, t), dd_ld(yh, yl, N + t)};
-  dd_fft(Z, W, tw, N, -1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
+__global__ __launch_bounds__(DDF_NT) void k_dd_filter_state(double* __restrict__ yh, double* __restrict__ yl,
+                                                            const double* __restrict__ f_hi,
+                                                            const double* __restrict__ f_lo,
+                                                            const cdd* __restrict__ twg, int N) {
+  extern __shared__ dd ldsd[];
+  CddBuf Z = dd_buf(ldsd, 0, N), W = dd_buf(ldsd, 1, N);
+  const CddBuf tw = dd_twiddles(ldsd, twg, N);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) Z.put(t, cdd{dd_ld(yh, yl, t), dd_ld(yh, yl, N + t)});
+  dd_fft1(Z, W, tw, N, -1);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
     const dd f = dd_filt_at(f_hi, f_lo, t, N);
-    Z[t] = cdd{dd_mul(Z[t].re, f), dd_mul(Z[t].im, f)};
+    Z.put(t, cdd{dd_mul(Z.re[t], f), dd_mul(Z.im[t], f)});
   }
-  dd_fft(Z, W, tw, N, +1);
-  for (int t = threadIdx.x; t < N; t += WW_NT) {
-    dd_st(yh, yl, t, Z[t].re);
-    dd_st(yh, yl, N + t, Z[t].im);
+  dd_fft1(Z, W, tw, N, +1);
+  for (int t = threadIdx.x; t < N; t += blockDim.x) {
+    dd_st(yh, yl, t, Z.re[t]);
+    dd_st(yh, yl, N + t, Z.im[t]);
   }
 }
 

@@ -19,7 +19,7 @@ def _ww():
     return ww, torch
 
 
-@pytest.mark.parametrize("N,R", [(64, 1), (64, 2), (256, 7), (512, 1), (512, 33), (1024, 2), (1024, 64), (1024, 129)])
+@pytest.mark.parametrize("N,R", [(16, 3), (32, 1), (64, 1), (64, 2), (256, 7), (512, 1), (512, 33), (1024, 2), (1024, 64), (1024, 129)])
 def test_flat_symbol_over_the_launch_shapes(N, R):
     """G cos(k x) = k tanh(k h) cos(k x).  Tolerance: a sum of N terms rounds to N 2^-104 at
     worst, the derivative multiplies that by up to N/2: N^2 2^-105 of the symbol."""
