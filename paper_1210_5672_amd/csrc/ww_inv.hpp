@@ -125,6 +125,71 @@ __device__ __forceinline__ void band_mfma(T (&acc)[16], const T (&l)[16], const 
     for (int i = 0; i < 4; ++i) acc[4 * J + i] = v[J][i];
 }
 
+// A tile of a matrix behind a buffer descriptor: with on = false its loads give zero and its
+// stores are dropped, without memory traffic and without a branch
+typedef unsigned gj_u2 __attribute__((ext_vector_type(2)));
+template <typename T>
+struct TileBuf {
+  __amdgpu_buffer_rsrc_t r;
+  int ld;
+  __device__ TileBuf(const T* p, int ld_, bool on)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, on ? 64 * ld_ * (int)sizeof(T) : 0, 0x00027000)),
+        ld(ld_) {}
+  // entry e of this lane's band (band_load), of its share of the columns (rf_fetch)
+  __device__ int band_at(int e) const { return (16 * (e >> 2) + Mfma<T>::rowc(e & 3)) * ld * (int)sizeof(T); }
+  __device__ int rf_at(int m) const { return 4 * m * ld * (int)sizeof(T); }
+  __device__ T get(int voff, int soff) const {
+    if constexpr (sizeof(T) == 8) {
+      const gj_u2 u = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+      return __builtin_bit_cast(T, u);
+    } else {
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+    }
+  }
+  __device__ void put(T v, int voff, int soff) const {
+    if constexpr (sizeof(T) == 8)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(gj_u2, v), r, voff, soff, 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
+  }
+};
+
+// band_mfma with memory operations in between: bg(s), s = 0 .. 31, after every second matrix
+// instruction.  A load holds the wave's issue for about 72 cycles when the four waves send
+// theirs together, a matrix instruction occupies its unit for 64: 32 loads in front of the
+// product cost 2300 cycles and 16 stores behind it 800 beside its own 4300.  The empty
+// asm statements keep that order (matrix instructions have no order of their own).
+template <typename T, typename Bg>
+__device__ __forceinline__ void band_mfma_bg(T (&acc)[16], const T (&l)[16], const T* S, Bg bg) {
+  typedef typename Mfma<T>::V V;
+  const int lane = threadIdx.x & 63, cl = lane & 15, rq = lane >> 4;
+  V v[4];
+#pragma unroll
+  for (int J = 0; J < 4; ++J) v[J] = V{acc[4 * J], acc[4 * J + 1], acc[4 * J + 2], acc[4 * J + 3]};
+  T a[2][4];
+  auto rd = [&](int g) {   // operands of group g = 4 Q + i
+#pragma unroll
+    for (int J = 0; J < 4; ++J) a[g & 1][J] = S[(16 * J + cl) * GJ_LD + 16 * (g >> 2) + Mfma<T>::row(g & 3, rq)];
+  };
+  rd(0);
+#pragma unroll
+  for (int g = 0; g < 16; ++g) {
+    if (g < 15) rd(g + 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      v[2 * h] = Mfma<T>::step(a[g & 1][2 * h], l[g], v[2 * h]);
+      v[2 * h + 1] = Mfma<T>::step(a[g & 1][2 * h + 1], l[g], v[2 * h + 1]);
+      asm volatile("" : "+v"(v[2 * h]), "+v"(v[2 * h + 1]));
+      bg(2 * g + h);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int J = 0; J < 4; ++J)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[4 * J + i] = v[J][i];
+}
+
 // -------------------------------------------------------------------------------------
 // Gauss-Jordan inverse of a 16 x 16 block by one wave, without pivoting, in the MFMA
 // result layout (lane: column cl = lane & 15, rows Mfma<T>::row(i, lane >> 4)).  For pivot
@@ -336,6 +401,11 @@ __host__ __device__ inline int gj_step_tasks(int nb, int k, int strip) {
   return nb * ((nb + strip - 1) / strip) + (k + 1 < nb ? 1 : 0);
 }
 
+// Measured per step (FP64, alone on the device), with the memory operations of a tile between
+// its matrix instructions against in front of and behind them: N 1024, one matrix 15.0 us
+// (15.6), two 16.2 (18.0), four 21.4 (26.1); N 2048 20.8 (25.6); a strip's tile 2.2 us (3.4;
+// its matrix instructions 1.7).  Below that the critical task is the step: 13.8 us at N = 512
+// (14.3), 8 of them gj64 and 3.5 its two products.
 template <typename T>
 __global__ __launch_bounds__(WW_NT, 2) void k_gj_step(GjGroup<T> g, int k) {
   extern __shared__ __attribute__((aligned(16))) double sm_raw[];
@@ -349,20 +419,26 @@ __global__ __launch_bounds__(WW_NT, 2) void k_gj_step(GjGroup<T> g, int k) {
   T* dst = last ? GJ_SEL(g, Mr, m) : (k & 1) ? GJ_SEL(g, W1, m) : GJ_SEL(g, W0, m);
   T* Dinv = GJ_SEL(g, Dinv, m);
   const T* Dk = Dinv + (size_t)k * 4096;
+  // this lane's byte offsets in a tile: its band, its share of the columns
+  const int bdo = (int)(band_off<T>(Np) * sizeof(T));
+  const int rfo = (int)(((threadIdx.x >> 6) * Np + (threadIdx.x & 63)) * sizeof(T));
   if (!last) {
     if (q == 0) {
       T l[16], c[16], vd[16], vr[16];
-      band_load<T>(l, src + gj_tile<T>(Np, k + 1, k), Np);
       rf_fetch<T>(vd, Dk, 64);
-      rf_fetch<T>(vr, src + gj_tile<T>(Np, k, k + 1), Np);
+      band_load<T>(l, src + gj_tile<T>(Np, k + 1, k), Np);
+      const TileBuf<T> tr(src + gj_tile<T>(Np, k, k + 1), Np, true), tc(src + gj_tile<T>(Np, k + 1, k + 1), Np, true);
       rf_put<T>(sm, vd);
-      rf_put<T>(sm + GJ_TILE, vr);
       __syncthreads();
-      band_load<T>(c, src + gj_tile<T>(Np, k + 1, k + 1), Np);   // in flight during the first product
       T a[16] = {};
-      band_mfma<T>(a, l, sm);   // L = B_{k+1,k} D_k
+      band_mfma_bg<T>(a, l, sm, [&](int s) {   // L = B_{k+1,k} D_k
+        if (s < 16) vr[s] = tr.get(rfo, tr.rf_at(s));
+        else c[s - 16] = tc.get(bdo, tc.band_at(s - 16));
+      });
 #pragma unroll
       for (int e = 0; e < 16; ++e) a[e] = -a[e];
+      rf_put<T>(sm + GJ_TILE, vr);
+      __syncthreads();
       band_mfma<T>(c, a, sm + GJ_TILE);
       __syncthreads();   // every wave is done with the first tile: the inverse's scratch
       const T mp = gj64<T>(c, sm);
@@ -380,49 +456,59 @@ __global__ __launch_bounds__(WW_NT, 2) void k_gj_step(GjGroup<T> g, int k) {
     while (j < p1 && (j == k || (j == k + 1 && i == k + 1))) ++j;
     return j;
   };
+  // the tiles j of row k and of row i (which row k's own strips do not take: zero)
   T l[16], vr[16], cn[16];
-  auto fetch = [&](int j) {
-    rf_fetch<T>(vr, src + gj_tile<T>(Np, k, j), Np);
-    if (i != k) {
-      band_load<T>(cn, src + gj_tile<T>(Np, i, j), Np);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) cn[e] = T(0);
-    }
-  };
+  auto rowk = [&](int j) { return TileBuf<T>(src + gj_tile<T>(Np, k, min(j, nb - 1)), Np, j < p1); };
+  auto rowi = [&](int j) { return TileBuf<T>(src + gj_tile<T>(Np, i, min(j, nb - 1)), Np, j < p1 && i != k); };
   int j = next(p0);
-  if (i == k) {
-    band_load<T>(l, Dk, 64);
-    if (j < p1) fetch(j);
-  } else {
-    T b[16], vd[16];
-    band_load<T>(b, src + gj_tile<T>(Np, i, k), Np);
-    rf_fetch<T>(vd, Dk, 64);
-    if (j < p1) fetch(j);
-    rf_put<T>(sm, vd);
-    __syncthreads();
+  {
+    const TileBuf<T> tr = rowk(j), tc = rowi(j);
+    auto fetch = [&](int s) {
+      if (s < 16) vr[s] = tr.get(rfo, tr.rf_at(s));
+      else cn[s - 16] = tc.get(bdo, tc.band_at(s - 16));
+    };
+    if (i == k) {
+      band_load<T>(l, Dk, 64);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) l[e] = T(0);
-    band_mfma<T>(l, b, sm);
+      for (int s = 0; s < 32; ++s) fetch(s);
+    } else {
+      T b[16], vd[16];
+      rf_fetch<T>(vd, Dk, 64);
+      band_load<T>(b, src + gj_tile<T>(Np, i, k), Np);
+      rf_put<T>(sm, vd);
+      __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 16; ++e) l[e] = -l[e];
+      for (int e = 0; e < 16; ++e) l[e] = T(0);
+      band_mfma_bg<T>(l, b, sm, fetch);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) l[e] = -l[e];
+    }
   }
   if (p0 <= k && k < p1) {   // column k: -B_ik D_k, and D_k itself
     band_store<T, T>(l, dst + gj_tile<T>(Np, i, k), Np);
     if (m32) band_store<T, float>(l, m32 + gj_tile<T>(Np, i, k), Np);
   }
+  // per tile: the next tile's loads and the stores of the tile before ride in its product
+  T c[16], cs[16];
+  int js = p1;   // tile of cs (p1: none)
   for (int buf = 1; j < p1; buf ^= 1) {
     T* S = sm + buf * GJ_TILE;
     rf_put<T>(S, vr);
-    T c[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) c[e] = cn[e];
     __syncthreads();   // the tile is complete; every wave is done with the product before
     const int jn = next(j + 1);
-    if (jn < p1) fetch(jn);
-    band_mfma<T>(c, l, S);
-    band_store<T, T>(c, dst + gj_tile<T>(Np, i, j), Np);
+    const TileBuf<T> tr = rowk(jn), tc = rowi(jn), ts(dst + gj_tile<T>(Np, i, min(js, nb - 1)), Np, js < p1);
+    band_mfma_bg<T>(c, l, S, [&](int s) {
+      if (s < 16) vr[s] = tr.get(rfo, tr.rf_at(s));
+      else cn[s - 16] = tc.get(bdo, tc.band_at(s - 16));
+      if (s % 2 == 0) ts.put(cs[s / 2], bdo, ts.band_at(s / 2));
+    });
     if (m32) band_store<T, float>(c, m32 + gj_tile<T>(Np, i, j), Np);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) cs[e] = c[e];
+    js = j;
     j = jn;
   }
+  if (js < p1) band_store<T, T>(cs, dst + gj_tile<T>(Np, i, js), Np);
 }
