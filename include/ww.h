@@ -515,7 +515,8 @@ unsigned ww_next_fallback(unsigned flags, unsigned fb, int status);
  * the fastest per (N, M, precision, GPU architecture) in a JSON cache.
  *   lag          lagged-factor march: the base solve of stage s uses the explicit
  *                inverse of stage s - lag (0: each stage's own factors), 0..11
- *   lu_group     consecutive stages factored by one launch sequence, 1..4 (<= lag)
+ *   lu_group     consecutive stages factored by one launch sequence, 1..4 (<= lag); the
+ *                default, 2, takes four of them where lag >= 8
  *   lu_streams   streams the LU groups rotate over, 1..6
  *   graph_parts  march parts replayed from HIP graphs, one bit each: 1 prep and
  *                assembly, 2 LU, 4 base chain, 8 column chain (the rest launched

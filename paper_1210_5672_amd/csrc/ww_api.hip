@@ -250,7 +250,7 @@ struct ww_ctx {
   // stage s runs on one of `lag` streams; the column chain of stage s waits for it
   int lag = 8;   // environment WW_PIPE_LAG, 0..PIPE_MAXLAG (0: every solve uses its own factors)
   // stages factored together by one LU launch sequence (environment WW_LU_GROUP,
-  // 1..GJ_GMAX; at most the lag)
+  // 1..GJ_GMAX; at most the lag; 2: up to four, see lu_group())
   int lu_group = 2;
   int minv_wgs = 1 << 20;                  // workgroup cap of the explicit-inverse launch
   int graph_parts = 10;                    // parts of a march stage replayed from graphs (bit per part)
@@ -1123,9 +1123,6 @@ static bool pipelined(const ww_ctx* c, bool cols, bool two_streams) {
   return c->lag > 0 && two_streams && c->fb == 0 && c->nst > c->lag && !c->gm_active;
 }
 
-// a march without columns keeps to two LU streams: they carry its LUs, and a third
-// concurrent LU only slows its base chain
-static int lu_count(const ww_ctx* c) { return std::min(c->pcols ? c->nlus : std::min(c->nlus, 2), c->lag); }
 // LU groups: consecutive stages g G .. g G + G - 1 (the last group of a step may be
 // shorter) are factored by one launch sequence, on LU stream g mod (LU streams); the
 // group is at most the lag, so that a base solve never waits for its own group.  The
@@ -1133,7 +1130,23 @@ static int lu_count(const ww_ctx* c) { return std::min(c->pcols ? c->nlus : std:
 // group anyway); without columns nothing reads the others, and only that stage is
 // factored (N = 1024, two streams: the LUs of every stage took 141 us a stage, the base
 // chain 100).
-static int lu_group(const ww_ctx* c) { return std::max(1, std::min(c->lu_group, c->lag)); }
+// The default of 2 becomes 4 where the lag leaves four stages of base chain to hide the
+// longer group behind: a step of the elimination is bound by its critical task, which four
+// matrices share, the lagged factors are no older (a stage reads those of s - lag's group,
+// its last), and a group's launches cost the host as much as one stage's.  Groups of 2
+// against 4: march N 256, M 64 21.5 / 15.2 ms (host bound), N 1024, M 128 34.6 / 33.8, mixed
+// N 768, M 137 26.0 / 24.6, f only N 1024 25.8 / 22.3.
+static int lu_group(const ww_ctx* c) {
+  const int g = c->lu_group == 2 && c->lag >= 8 ? GJ_GMAX : c->lu_group;
+  return std::max(1, std::min(g, c->lag));
+}
+// a march without columns (one LU per group) keeps to one LU stream where that LU is shorter
+// than the base chain of a full group's stages (N = 1024: 254 us against 4 x 70; a second
+// one beside it only slows the chain, 22.3 against 21.0 ms), to two otherwise
+static int lu_count(const ww_ctx* c) {
+  const int most = c->pcols ? c->nlus : c->Np <= 1024 && lu_group(c) == GJ_GMAX ? 1 : 2;
+  return std::min(std::min(c->nlus, most), c->lag);
+}
 static int grp_first(const ww_ctx* c, int s) { return s / lu_group(c) * lu_group(c); }
 static int grp_last(const ww_ctx* c, int s) { return std::min(c->nst, grp_first(c, s) + lu_group(c)) - 1; }
 static hipStream_t lu_stream(const ww_ctx* c, int s) { return c->lus[(s / lu_group(c)) % lu_count(c)]; }
