@@ -359,10 +359,13 @@ int shoot_eval_batch(int n_inst, ww_ctx *const *ctx, const double *const *params
  * shoot_adjoint (Sec. 3.2, App. B; discrete form): gradient of f = r.r/2 with respect
  * to the parameters, grad = J^T r, by the exact transpose of the discretised
  * variational march (reverse Runge-Kutta stages, transposed LU solves, transposed
- * Gm, -d/dx, -H), with the base state recomputed from checkpoints taken every
- * `ckpt_every` steps.  The factors are FP64 also in a WW_MIXED context.  Device
- * workspace for the checkpoints and for the factors of one segment (ckpt_every x stages
- * x 2 Np^2 doubles) is allocated on the first call and kept until ww_destroy.
+ * Gm, -d/dx, -H).  The factors of every stage (steps x stages x 2 Np^2 doubles) stay from
+ * the march where they fit into 1/8 of the free device memory and 16 GiB (environment
+ * WW_ADJOINT_KEEP at ww_create: another bound in MiB, 0 for never); otherwise the base
+ * state is recomputed from checkpoints taken every `ckpt_every` steps and the workspace
+ * holds the factors of one such segment.  Same results either way.  The factors are FP64
+ * also in a WW_MIXED context.  The workspace is allocated on the first call that needs it
+ * and kept until ww_destroy.
  * grad: device M.  dfdT (host or NULL): df/dT = r . drdT.  f (host or NULL).
  * Synchronises.  A pivot below the guard redoes the call with partial pivoting.
  * Errors: WW_ENOSETUP, WW_EINVAL, WW_EPIVOT, WW_ENONFINITE, WW_EHIP.

@@ -208,6 +208,7 @@ struct ww_ctx {
   size_t ckpt_cap = 0;
   double* seg = nullptr;
   size_t seg_cap = 0;
+  size_t adj_keep = (size_t)16 << 30;   // most bytes of a whole march's factors (environment WW_ADJOINT_KEEP, MiB)
   double* adj = nullptr;   // lam, mu, ups[16], gt, hd, e1, q, g2, zeta, y2, rv, dv
   // optional HIP events around phases of every stage of the captured step
   // (0: block LU, 1: whole base chain, 2: column chain); the values of the last
@@ -502,6 +503,7 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
     const char* ns = std::getenv("WW_LU_STREAMS");
     if (ns) c->nlus = std::max(1, std::min(PIPE_MAXLUS, std::atoi(ns)));
     const char* lg = std::getenv("WW_LU_GROUP");
+    if (const char* ak = std::getenv("WW_ADJOINT_KEEP")) c->adj_keep = (size_t)std::max(0L, std::atol(ak)) << 20;
     if (lg) c->lu_group = std::max(1, std::min(GJ_GMAX, std::atoi(lg)));
     const char* gp = std::getenv("WW_GRAPH_PARTS");
     if (gp) c->graph_parts = std::atoi(gp) & 15;
@@ -3423,11 +3425,34 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
   c->dtn_ready = false;
   c->gm_active = false;   // the transposed solves need the factors
   const int N = c->N, Np = c->Np, M = c->M, nst = c->nst;
-  const int C = std::min(ckpt_every, nsteps);
-  const int nseg = (nsteps + C - 1) / C;
   // buffers: checkpoints, per-stage factor sets of one segment, adjoint work vectors
   const size_t n2 = (size_t)2 * N;
   const size_t slot = (size_t)2 * Np * Np + (size_t)3 * N;   // inverse, Gm, saux
+  // One segment of all steps, whose factors the forward march leaves behind, where they are
+  // at most adj_keep bytes and 1/8 of the memory now free (what this context holds for them
+  // already counts as free): the march is then run once, not twice (N = 512, 13 steps:
+  // 0.66 GB, 53.4 against 30.4 ms).  Otherwise segments of ckpt_every steps, recomputed, but for the last
+  // one, which the march leaves behind.
+  int C = std::min(ckpt_every, nsteps);
+  const size_t all = (size_t)nsteps * nst * slot;
+  if (C < nsteps && all * 8 <= c->adj_keep) {
+    size_t free_b = 0, total_b = 0;
+    if (c->seg_cap >= all) {
+      C = nsteps;
+    } else if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && all * 8 <= (free_b + c->seg_cap * 8) / 8) {
+      if (c->seg) HIPCHK(hipFree(c->seg));
+      c->seg = nullptr;
+      c->seg_cap = 0;
+      if (hipMalloc(&c->seg, all * 8) == hipSuccess) {
+        c->seg_cap = all;
+        C = nsteps;
+      } else {
+        (void)hipGetLastError();
+        c->seg = nullptr;
+      }
+    }
+  }
+  const int nseg = (nsteps + C - 1) / C;
   const size_t nslot = (size_t)C * nst;
   if (c->ckpt_cap < (size_t)(nseg + 1) * n2) {
     if (c->ckpt) HIPCHK(hipFree(c->ckpt));
@@ -3496,15 +3521,16 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
     hipLaunchKernelGGL(k_init_state, dim3(blocks), dim3(256), 0, c->stream, c->y, c->basis, c->qfix, params, N, M);
     LAUNCHCHK();
   }
-  // 1. forward base march with checkpoints (FP64 factors)
+  // 1. forward base march with checkpoints (FP64 factors; those of the last segment, which
+  // the reverse sweep needs first, stay in the slots)
   Fac F0 = fac_set(c, 0);
   F0.use32 = false;
-  auto base_step = [&](const Fac* per_stage_base, size_t slot0) -> int {
+  auto base_step = [&](bool keep, size_t slot0) -> int {
     for (int s = 0; s < nst; ++s) {
-      const Fac F = per_stage_base ? slot_fac(slot0 + s) : F0;
+      const Fac F = keep ? slot_fac(slot0 + s) : F0;
       int r2 = enqueue_base_chain(c, c->y, s, c->K + (size_t)s * kstride(c), F);
       if (r2) return r2;
-      if (per_stage_base) {
+      if (keep) {
         hipLaunchKernelGGL(k_save_aux, dim3((N + 255) / 256), dim3(256), 0, c->stream, F.aux, c->n_max, N,
                            slot_aux(slot0 + s));
         LAUNCHCHK();
@@ -3517,7 +3543,8 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
   };
   for (int n = 0; n < nsteps; ++n) {
     if (n % C == 0) HIPCHK(hipMemcpyAsync(c->ckpt + (size_t)(n / C) * n2, c->y, n2 * 8, hipMemcpyDeviceToDevice, c->stream));
-    if ((rc = base_step(nullptr, 0))) return rc;
+    const int last0 = (nseg - 1) * C;
+    if ((rc = base_step(n >= last0, (size_t)std::max(0, n - last0) * nst))) return rc;
   }
   hipLaunchKernelGGL(k_check_finite, dim3(64), dim3(256), 0, c->stream, c->y, n2, c->status);
   LAUNCHCHK();
@@ -3534,9 +3561,11 @@ static int adjoint_run(ww_ctx* c, const double* params, double T, int nsteps, in
   bool first = true;
   for (int sg = nseg - 1; sg >= 0; --sg) {
     const int n0 = sg * C, n1 = std::min(n0 + C, nsteps);
-    HIPCHK(hipMemcpyAsync(c->y, c->ckpt + (size_t)sg * n2, n2 * 8, hipMemcpyDeviceToDevice, c->stream));
-    for (int n = n0; n < n1; ++n)
-      if ((rc = base_step(&F0, (size_t)(n - n0) * nst))) return rc;
+    if (sg < nseg - 1) {
+      HIPCHK(hipMemcpyAsync(c->y, c->ckpt + (size_t)sg * n2, n2 * 8, hipMemcpyDeviceToDevice, c->stream));
+      for (int n = n0; n < n1; ++n)
+        if ((rc = base_step(true, (size_t)(n - n0) * nst))) return rc;
+    }
     for (int n = n1 - 1; n >= n0; --n) {
       // lambda_{n+1} (seed, or mu + sum ups of the step after) and mu = S_F lambda_{n+1}
       hipLaunchKernelGGL(k_adj_step, dim3(1), dim3(WW_NT), fft_lds_bytes(N, 3), c->stream, lam, mu, ups, ustride, nst,
