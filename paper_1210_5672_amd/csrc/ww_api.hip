@@ -37,6 +37,11 @@ static double* g_scratch_dev[SCRATCH_MAX_DEV] = {};
 
 static thread_local std::string g_err;
 
+// the size classes of the spectral kernels (FftSz), X(size, ...) for each
+#define NF_CLASSES(X, ...)                                                                                         \
+  X(64, __VA_ARGS__) X(128, __VA_ARGS__) X(256, __VA_ARGS__) X(384, __VA_ARGS__) X(512, __VA_ARGS__)               \
+  X(768, __VA_ARGS__) X(1024, __VA_ARGS__) X(1536, __VA_ARGS__) X(2048, __VA_ARGS__)
+
 // The library's working streams of a device (LU streams; one of them doubles as the column
 // stream where there is one), shared by its contexts: HIP spreads a process's streams over
 // four hardware queues, in the order of their creation, and a second context with streams
@@ -526,11 +531,10 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
   const int big = 160 * 1024;
   CCHK(hipFuncSetAttribute((const void*)k_gj_step<double>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   CCHK(hipFuncSetAttribute((const void*)k_gj_step<float>, hipFuncAttributeMaxDynamicSharedMemorySize, big));
-#define NF_ALL(K) \
-  (const void*)K<256>, (const void*)K<512>, (const void*)K<1024>, (const void*)K<2048>, (const void*)K<-1>, (const void*)K<0>
-#define NF_ALL2(K, M)                                                                                        \
-  (const void*)K<256, M>, (const void*)K<512, M>, (const void*)K<1024, M>, (const void*)K<2048, M>, (const void*)K<-1, M>, \
-      (const void*)K<0, M>
+#define NF_PTR(F, K) (const void*)K<F>,
+#define NF_PTR2(F, K, M) (const void*)K<F, M>,
+#define NF_ALL(K) NF_CLASSES(NF_PTR, K) (const void*)K<-1>, (const void*)K<0>
+#define NF_ALL2(K, M) NF_CLASSES(NF_PTR2, K, M) (const void*)K<-1, M>, (const void*)K<0, M>
   // Dynamic LDS of a launch beside the kernel's static LDS must stay within a compute
   // unit's 160 KB: five work buffers of the largest transform take all of it.
   static_assert(5 * WW_NMAX * sizeof(cplx) <= 160 * 1024, "five transform buffers must fit");
@@ -676,11 +680,10 @@ int ww_set_tableau(ww_ctx* c, int s, const double* a, const double* b, const dou
 // kernel sequences
 // ------------------------------------------------------------------------------------
 // the instance of a spectral kernel for the size class of N (FftSz)
-#define NF_SEL(N, K) \
-  ((N) == 256 ? K<256> : (N) == 512 ? K<512> : (N) == 1024 ? K<1024> : (N) == 2048 ? K<2048> : (N) <= 1024 ? K<-1> : K<0>)
-#define NF_SEL2(N, K, M)                                                                              \
-  ((N) == 256 ? K<256, M> : (N) == 512 ? K<512, M> : (N) == 1024 ? K<1024, M> : (N) == 2048 ? K<2048, M> \
-                                                                   : (N) <= 1024 ? K<-1, M> : K<0, M>)
+#define NF_CASE(F, N, K) (N) == F ? K<F> :
+#define NF_CASE2(F, N, K, M) (N) == F ? K<F, M> :
+#define NF_SEL(N, K) (NF_CLASSES(NF_CASE, N, K) (N) <= 1024 ? K<-1> : K<0>)
+#define NF_SEL2(N, K, M) (NF_CLASSES(NF_CASE2, N, K, M) (N) <= 1024 ? K<-1, M> : K<0, M>)
 static size_t fft_lds_bytes(int N, int nbuf) { return (size_t)nbuf * N * sizeof(cplx); }
 // measurement hook: a pair of HIP events attached to one kernel dispatch on the current
 // stream (hipExtLaunchKernel: the events take the dispatch's own start and end times),

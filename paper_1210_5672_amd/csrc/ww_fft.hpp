@@ -159,7 +159,7 @@ __device__ __forceinline__ void fft_pass(const cplx* src, cplx* dst, const cplx*
   }
 }
 
-// The same transform with N a compile-time power of two (256 .. WW_NMAX): the passes are
+// The same transform with N a compile-time constant (2^a or 3 2^a): the passes are
 // unrolled with their span, radix and layout flags as constants, so that the index
 // arithmetic folds away; the last pass works in place (all of its inputs read before a
 // barrier, then written), which saves the copy of an odd pass count, and carries the 1/N of
@@ -174,7 +174,7 @@ __device__ __forceinline__ void fft_pass_fixed(const cplx* src, cplx* dst, const
 #pragma unroll
   for (int u = 0; u < per; ++u) {
     const int j = tid + FFT_NT * u;
-    if (on && j < nb) fft_load<R>(src, twp, nb, j, j & (Ns - 1), Ns, dir, rsw, v[u]);
+    if (on && j < nb) fft_load<R>(src, twp, nb, j, j % Ns, Ns, dir, rsw, v[u]);   // (Ns a constant)
   }
   if (inplace) __syncthreads();   // every input of the pass has been read
 #pragma unroll
@@ -182,7 +182,7 @@ __device__ __forceinline__ void fft_pass_fixed(const cplx* src, cplx* dst, const
     const int j = tid + FFT_NT * u;
     if (on && j < nb) {
       fft_bfly<R>(v[u], dir);
-      const int jm = j & (Ns - 1);
+      const int jm = j % Ns;
       const int idxD = (j - jm) * R + jm;
 #pragma unroll
       for (int q = 0; q < R; ++q) dst[fft_swz(idxD + q * Ns, wsw)] = sc == 1.0 ? v[u][q] : cscale(v[u][q], sc);
@@ -190,16 +190,23 @@ __device__ __forceinline__ void fft_pass_fixed(const cplx* src, cplx* dst, const
   }
 }
 
+// passes before span Ns (radix 4 first, then 3, then 2, as in the general form)
+constexpr int fft_radix(int n) { return n % 4 == 0 ? 4 : n % 3 == 0 ? 3 : 2; }
+constexpr int fft_passes(int N, int Ns) {
+  int p = 0;
+  for (int s = 1; s < Ns; s *= fft_radix(N / s)) ++p;
+  return p;
+}
 template <int N, int Ns>
 __device__ __forceinline__ void fft_fixed_from(cplx* a, cplx* b, const cplx* tw, int dir, bool first, int tid,
                                                bool on) {
   if constexpr (Ns < N) {
-    constexpr int R = (N / Ns) % 4 == 0 ? 4 : 2;
+    constexpr int R = fft_radix(N / Ns);
     constexpr bool last = Ns * R == N;
     constexpr bool sw = (N & 7) == 0;
     const cplx* twp = tw + (Ns - 1);
     // ping-pong a -> b -> a ...; the last pass lands in a (in place when it reads a)
-    constexpr int p = __builtin_ctz(Ns) / 2;   // passes before this one (radix 4 first)
+    constexpr int p = fft_passes(N, Ns);
     constexpr bool from_a = (p & 1) == 0;
     cplx* src = from_a ? a : b;
     cplx* dst = last ? a : (from_a ? b : a);
@@ -251,12 +258,15 @@ __device__ inline void fft_team_general(cplx* a, cplx* b, const cplx* tw, const 
 
 // Size classes of the spectral kernels (a template argument, so that a kernel holds the code
 // of one transform and loops of the right length: with every size in every kernel the code of
-// one launch no longer fits the instruction cache of the unit it lands on): N itself for the
-// powers of two from 256, -1 for other sizes up to 1024, 0 for the rest.
+// one launch no longer fits the instruction cache of the unit it lands on): N itself for 2^a
+// from 64 and 3 2^a from 384, the grids that halving and refining by one half give; -1 for
+// other sizes up to 1024, 0 for the rest.  A class of its own against the general passes:
+// mixed march N 768, M 137 22.7 ms against 24.5, five batched instances of several sizes 72.9
+// against 74.5.
 // PT: entries per thread of a team.
 template <int NF>
 struct FftSz {
-  static constexpr int PT = NF > 0 ? NF / FFT_NT : NF < 0 ? 4 : WW_NMAX / FFT_NT;
+  static constexpr int PT = NF > 0 ? (NF + FFT_NT - 1) / FFT_NT : NF < 0 ? 4 : WW_NMAX / FFT_NT;
   static __device__ __forceinline__ void run(cplx* a, cplx* b, const cplx* tw, const FftPlan& P, int dir, int tid,
                                              bool on) {
     if constexpr (NF > 0) {

@@ -32,8 +32,8 @@ def _rel(a, b):
 
 
 @pytest.mark.parametrize("rows", [4, 8])
-@pytest.mark.parametrize("N,tau", [(16, 0.0), (48, 0.01), (256, 0.0), (256, 0.01), (512, 0.0), (972, 0.005),
-                                   (1024, 0.0), (1458, 0.002), (2048, 0.0)])
+@pytest.mark.parametrize("N,tau", [(16, 0.0), (48, 0.01), (64, 0.01), (128, 0.0), (256, 0.0), (256, 0.01),
+                                   (384, 0.005), (512, 0.0), (768, 0.002), (972, 0.005), (1024, 0.0), (1458, 0.002), (1536, 0.0), (2048, 0.0)])
 def test_spectral_base_chain(N, tau, rows):
     ww = _ww()
     print(f"N={N} tau={tau} rows={rows}", flush=True)
@@ -51,7 +51,7 @@ def test_spectral_base_chain(N, tau, rows):
     ctx.close()
 
 
-@pytest.mark.parametrize("N,tau", [(72, 0.01), (256, 0.0), (512, 0.005), (1296, 0.0)])
+@pytest.mark.parametrize("N,tau", [(64, 0.0), (72, 0.01), (256, 0.0), (512, 0.005), (768, 0.0), (1296, 0.0)])
 def test_spectral_base_chain_on_a_mapped_grid(N, tau):
     ww = _ww()
     print(f"mapped N={N} tau={tau}", flush=True)
