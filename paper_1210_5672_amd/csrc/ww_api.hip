@@ -548,7 +548,7 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
     CCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, big));
   }
   for (const void* fn : {NF_ALL(k_base_dtn), NF_ALL(k_step_end), NF_ALL2(k_base_stage, 0), NF_ALL2(k_base_stage, 1),
-                         (const void*)k_base_rhs_map, (const void*)k_col_rhs_map}) {
+                         NF_ALL(k_col_rhs_map), (const void*)k_base_rhs_map}) {
     hipFuncAttributes fa;
     CCHK(hipFuncGetAttributes(&fa, fn));
     CCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, big - (int)fa.sharedSizeBytes));
@@ -1106,8 +1106,8 @@ static int enqueue_col_chain(ww_ctx* c, int s, const Fac& F) {
   LAUNCHCHK();
   if ((rc = enqueue_dtn_cols(c, F, c->Psi, c->Ytmp, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr, M))) return rc;
   if (c->mapped)
-    hipLaunchKernelGGL(k_col_rhs_map, dim3(M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys, c->Gpsi,
-                       c->Np, F.aux, c->mesh, c->n_max, c->K + (size_t)s * kstride(c), c->tw, c->sig, c->N, c->g,
+    hipLaunchKernelGGL(NF_SEL(c->N, k_col_rhs_map), dim3(M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys,
+                       c->Gpsi, c->Np, F.aux, c->mesh, c->n_max, c->K + (size_t)s * kstride(c), c->tw, c->sig, c->N, c->g,
                        c->tau);
   else
     hipLaunchKernelGGL(NF_SEL(c->N, k_col_rhs), dim3(M), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->Ys, c->Gpsi, c->Np,
@@ -2582,8 +2582,8 @@ static int sdc_base_rhs(ww_ctx* c, const double* Ys, const double* gphi, double*
 }
 static int sdc_col_rhs(ww_ctx* c, const double* Ys, const double* aux, double* kout) {
   if (c->mapped)
-    hipLaunchKernelGGL(k_col_rhs_map, dim3(c->M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, Ys, c->Gpsi, c->Np,
-                       aux, c->mesh, c->n_max, kout, c->tw, c->sig, c->N, c->g, c->tau);
+    hipLaunchKernelGGL(NF_SEL(c->N, k_col_rhs_map), dim3(c->M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, Ys,
+                       c->Gpsi, c->Np, aux, c->mesh, c->n_max, kout, c->tw, c->sig, c->N, c->g, c->tau);
   else
     hipLaunchKernelGGL(NF_SEL(c->N, k_col_rhs), dim3(c->M), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, Ys, c->Gpsi, c->Np, aux,
                        c->n_max, kout, c->tw, c->sig, c->N, c->g, c->tau);

@@ -260,46 +260,51 @@ __global__ __launch_bounds__(WW_NT) void k_base_rhs_map(const double* __restrict
 //   phidot_t = P[(1/E) d(-etadot u v + tau d_x etadot / (1 + eta_x^2)^{3/2})
 //               - u d_x psidot + v G psidot - g etadot]
 // P the E-weighted zero-mean projection, then both filtered in alpha.
+// Six transforms in sequence (1/E stands between each derivative and its use), bound by
+// their latency.  Compiled per size class (FftSz): two segments N 768 and 1024, M 200 35.4 ms
+// against 35.7 with every size in one kernel.
 // -------------------------------------------------------------------------------------
+template <int NF>
 __global__ __launch_bounds__(WW_NT) void k_col_rhs_map(const double* __restrict__ Ys, const double* __restrict__ Gpsi,
                                                        int Np, const double* __restrict__ aux,
                                                        const double* __restrict__ mesh, int nmax,
                                                        double* __restrict__ Kout, const cplx* __restrict__ tw,
                                                        const double* __restrict__ sig, int N, double g, double tau) {
+  constexpr int PT = FftSz<NF>::PT;
   extern __shared__ cplx lds[];
   __shared__ double red[WW_NT / 64];
   cplx* Z = lds;
   cplx* W = lds + N;
   cplx* tws = lds + 3 * N;
   const FftPlan P = make_plan(N);
-  load_twiddles(tws, tw, N);
+  load_twiddles<PT>(tws, tw, N);
   const int c = blockIdx.x + 1;
   const int tid = threadIdx.x;
   const double* ye = Ys + (size_t)c * 2 * N;
   const double* yp = ye + N;
-  double ev[NPT], vv[NPT], uv[NPT], gv[NPT], wv[NPT], iv[NPT];
+  double ev[PT], vv[PT], uv[PT], gv[PT], wv[PT], iv[PT];
   {
-    double pv[NPT];
-    gload(ev, ye, N);
-    gload(pv, yp, N);
-    gload(vv, aux + AUX_V * nmax, N);
+    double pv[PT];
+    gload(ev, ye, N, tid);
+    gload(pv, yp, N, tid);
+    gload(vv, aux + AUX_V * nmax, N, tid);
 #pragma unroll
-    for (int m = 0; m < NPT; ++m) {
-      const int t = tidx(m);
+    for (int m = 0; m < PT; ++m) {
+      const int t = tid + WW_NT * m;
       if (t < N) Z[t] = cmk(pv[m] - vv[m] * ev[m], ev[m]);   // (psidot, etadot)
     }
   }
-  gload(uv, aux + AUX_U * nmax, N);
-  gload(gv, Gpsi + (size_t)(c - 1) * Np, N);
-  gload(wv, aux + AUX_W3 * nmax, N);
-  gload(iv, mesh + MESH_EINV * nmax, N);
-  fft_lds(Z, W, tws, P, -1);
+  gload(uv, aux + AUX_U * nmax, N, tid);
+  gload(gv, Gpsi + (size_t)(c - 1) * Np, N, tid);
+  gload(wv, aux + AUX_W3 * nmax, N, tid);
+  gload(iv, mesh + MESH_EINV * nmax, N, tid);
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, true);
   for (int t = tid; t < N; t += WW_NT) W[t] = sym_deriv(Z[t], wavenum(t, N), N);
-  fft_lds(W, Z, tws, P, +1);
-  double dps[NPT];
+  FftSz<NF>::run(W, Z, tws, P, +1, tid, true);
+  double dps[PT];
 #pragma unroll
-  for (int m = 0; m < NPT; ++m) {
-    const int t = tidx(m);
+  for (int m = 0; m < PT; ++m) {
+    const int t = tid + WW_NT * m;
     gv[m] *= iv[m];   // G psidot
     if (t < N) {
       dps[m] = W[t].x * iv[m];
@@ -310,15 +315,15 @@ __global__ __launch_bounds__(WW_NT) void k_col_rhs_map(const double* __restrict_
       dps[m] = 0.0;
     }
   }
-  fft_lds(Z, W, tws, P, -1);
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, true);
   for (int t = tid; t < N; t += WW_NT) W[t] = sym_deriv(Z[t], wavenum(t, N), N);
-  fft_lds(W, Z, tws, P, +1);
-  double ew[NPT], et[NPT], pre[NPT];
-  gload(ew, mesh + MESH_E * nmax, N);
+  FftSz<NF>::run(W, Z, tws, P, +1, tid, true);
+  double ew[PT], et[PT], pre[PT];
+  gload(ew, mesh + MESH_E * nmax, N, tid);
   double s = 0.0;
 #pragma unroll
-  for (int m = 0; m < NPT; ++m) {
-    const int t = tidx(m);
+  for (int m = 0; m < PT; ++m) {
+    const int t = tid + WW_NT * m;
     et[m] = pre[m] = 0.0;
     if (t < N) {
       const double e = ev[m], u = uv[m], G = gv[m];
@@ -329,13 +334,13 @@ __global__ __launch_bounds__(WW_NT) void k_col_rhs_map(const double* __restrict_
   }
   const double mean = block_sum_fixed(s, red) / (double)N;
 #pragma unroll
-  for (int m = 0; m < NPT; ++m) {
-    const int t = tidx(m);
+  for (int m = 0; m < PT; ++m) {
+    const int t = tid + WW_NT * m;
     if (t < N) Z[t] = cmk(et[m], pre[m] - mean);
   }
-  fft_lds(Z, W, tws, P, -1);
+  FftSz<NF>::run(Z, W, tws, P, -1, tid, true);
   for (int t = tid; t < N; t += WW_NT) Z[t] = cscale(Z[t], sig[t]);
-  fft_lds(Z, W, tws, P, +1);
+  FftSz<NF>::run(Z, W, tws, P, +1, tid, true);
   double* ko = Kout + (size_t)c * 2 * N;
   for (int t = tid; t < N; t += WW_NT) {
     ko[t] = Z[t].x;
