@@ -262,7 +262,7 @@ int shoot_eval_sdc_dd(ww_ctx *ctx, int N, double h, double tau, double g, const 
  * may be NULL for zero) at depth h (as dtn_setup; h is a double): eta', eta'' by
  * double-double FFTs, exp(+-height) in double-double, A = I/2 + K/N and Gm = G/N of
  * eq. (fred), (G), (K1K2) assembled in double-double from double-double circulant
- * tables, and the FP64 factors (block LU and explicit inverse) of the leading part of A
+ * tables, and the FP64 factors (explicit inverse) of the leading part of A
  * (in a WW_MIXED context: of its FP32 copy, on MFMA).
  * N must be a power of two, 16 <= N <= min(n_max, 1024).  The FP64 factors of an earlier
  * dtn_setup are replaced (dtn_solve_multi then needs a new dtn_setup).  Synchronises.
@@ -376,14 +376,14 @@ int shoot_adjoint(ww_ctx *ctx, const double *params, double T, int nsteps, int c
 /*
  * Measurement hooks (not part of the method): ww_profile(ctx, 1) adds timestamp nodes
  * (a one-thread kernel reading the GPU's constant-rate wall clock) around three phases
- * of every stage of the step graph -- 0: the block LU of A (a launch sequence, which in
- * a lagged-factor march inverts the matrices of a group of stages), 1: the whole base chain (spectral prep, assembly, base
- * solve, base DtN, base right-hand side), 2: the column chain (the M variational
+ * of every stage of the step graph -- 0: the elimination of A (a launch sequence, which in
+ * a lagged-factor march inverts the matrices of a group of stages), 1: the whole base
+ * chain (spectral prep, assembly, base solve, base DtN, base right-hand side), 2: the column chain (the M variational
  * columns) -- and clears the accumulated sums (stream-ordered); phase 3 is the host
  * time spent enqueueing one step (graph launches and event operations).  With 2 added
  * to `enable` (enable = 3), every elimination step kernel (k_gj_step) that carries a
- * diagonal inverse and that a march step launches directly (not from a graph) also carries a pair of HIP events attached to its
- * dispatch on its stream (hipExtLaunchKernel), which take the kernel's own start and end
+ * diagonal inverse and that a march step launches directly (not from a graph) also carries
+ * a pair of HIP events attached to its dispatch on its stream (hipExtLaunchKernel), which take the kernel's own start and end
  * times; phase 4 reads their mean elapsed time (the kernel's average launch duration,
  * over at most the first 16384 launches of the interval).
  * ww_profile_read returns in *avg_ms the mean duration of `phase` over every interval
@@ -517,7 +517,8 @@ unsigned ww_next_fallback(unsigned flags, unsigned fb, int status);
  * (paper_1210_5672_amd/autotune.py) times short marches over these choices and keeps
  * the fastest per (N, M, precision, GPU architecture) in a JSON cache.
  *   lag          lagged-factor march: the base solve of stage s uses the explicit
- *                inverse of stage s - lag (0: each stage's own factors), 0..11
+ *                inverse of the newest stage of stage s - lag's group (0: each stage's own
+ *                factors), 0..11
  *   lu_group     consecutive stages factored by one launch sequence, 1..4 (<= lag); the
  *                default, 2, takes four of them where lag >= 8
  *   lu_streams   streams the LU groups rotate over, 1..6

@@ -2,7 +2,7 @@
 
 None of the choices changes what is computed: they decide how the work of a march is
 cut into launches and streams (LU group size and streams, the lag of the base solve,
-which parts replay from graphs, the strip length of a block-LU step, rows per
+which parts replay from graphs, the strip length of a elimination step, rows per
 workgroup of the base DtN launch, the inner-dimension split and the output-tile rows
 of the column products, the assembly strip width, the workgroup cap of the explicit
 inverse, an FP32 copy of the lagged inverse for the base solve's products, the

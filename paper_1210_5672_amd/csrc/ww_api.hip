@@ -220,7 +220,7 @@ struct ww_ctx {
   // replayed step are read back by ww_profile_read
   bool prof = false;
   int prof_stage = -1;   // stage being enqueued (marks are taken only inside a step)
-  bool prof_kev = false;   // time every directly launched block-LU step with HIP events
+  bool prof_kev = false;   // time every directly launched elimination step with HIP events
   std::vector<hipEvent_t> kev_a, kev_b;
   size_t kev_n = 0;
   unsigned long long* stamps = nullptr;   // [phase][stage] x {start, sum, count}
@@ -252,15 +252,15 @@ struct ww_ctx {
   int* seg_perm = nullptr;
   size_t seg_perm_cap = 0;
   // lagged-factor pipeline of single-instance marches: the base solve of stage s uses
-  // the factors of stage s - lag (refined against its own matrix) while the LU of
-  // stage s runs on one of `lag` streams; the column chain of stage s waits for it
+  // the factors of stage s - lag's group (refined against its own matrix) while the LU of
+  // stage s runs on an LU stream; the column chain of stage s waits for it
   int lag = 8;   // environment WW_PIPE_LAG, 0..PIPE_MAXLAG (0: every solve uses its own factors)
   // stages factored together by one LU launch sequence (environment WW_LU_GROUP,
   // 1..GJ_GMAX; at most the lag; 2: up to four, see lu_group())
   int lu_group = 2;
-  int minv_wgs = 1 << 20;                  // workgroup cap of the explicit-inverse launch
+  int minv_wgs = 1 << 20;                  // kept in the interface, without effect
   int graph_parts = 10;                    // parts of a march stage replayed from graphs (bit per part)
-  int blu_strip = 4;                       // tiles per strip task of a block-LU step
+  int blu_strip = 4;                       // tiles per strip task of an elimination step
   int dtn_rows = 8;                        // rows per workgroup of the base DtN launch
   int gemm_split = 4;                      // kept in the interface, without effect
   int gemm_rows = 32;                      // column products: tiles by size (32), 16 x 16 (16)
@@ -905,20 +905,18 @@ static int enqueue_assemble_lu(ww_ctx* c, const Fac& F) {
 }
 
 // out = add + sgn * M B for R columns (ld Np) with the row-major M (element type T).
-// One column: one wave per row (mode: the 64-block range, 0 all, 1 strictly lower, 2
-// upper with the diagonal); several: output tiles over the whole inner dimension (the
-// full matrix).
+// One column: one wave per row; several: output tiles over the whole inner dimension.
+// B 16-byte aligned.
 template <typename T>
-static int enqueue_gemm(ww_ctx* c, const T* Mr, int mode, const double* B, const double* add, double sgn,
+static int enqueue_gemm(ww_ctx* c, const T* Mr, const double* B, const double* add, double sgn,
                         double* out, int R) {
   if (!Mr) return fail(WW_EHIP, "internal: product without its matrix");
   if (R == 1) {
-    hipLaunchKernelGGL(k_gemv_row<T>, dim3(c->Np * 64 / WW_NT), dim3(WW_NT), 0, c->stream, Mr, c->Np, mode, B, add,
-                       sgn, out);
+    hipLaunchKernelGGL(k_gemv_row<T>, dim3(c->Np * 64 / WW_NT), dim3(WW_NT), 0, c->stream, Mr, c->Np, B, add, sgn,
+                       out);
     LAUNCHCHK();
     return 0;
   }
-  if (mode & 3) return fail(WW_EHIP, "internal: triangular product of several columns");
   // 16 x 32 tiles, or 16 x 16 (gemm_rows = 16: always) where those would leave half the CUs
   // without one: N 256, R 64 2.7 against 3.5 us, N 2048, R 32 8.5 / 13.0; from one 16 x 32
   // tile per CU on they read less: N 768, R 137 6.9 / 6.0, N 2048, R 257 54.6 / 51.9
@@ -938,7 +936,7 @@ static int enqueue_gemm(ww_ctx* c, const T* Mr, int mode, const double* B, const
 static const double REFINE_TOL = 1.1368683772161603e-13;
 
 // X = A^{-1} B for R columns (ld Np); Rs is scratch; B is kept.  Mi is the explicit
-// inverse Z (I + X) of the block LU (row-major).
+// inverse (row-major).
 // FP64:  X = Mi B.
 // mixed: X = Mi32 B, then nref sweeps of  r = B - A X (FP64 residual with the FP64
 //        matrix),  X += Mi32 r  (FP32 inverse, FP64 accumulation).
@@ -952,15 +950,15 @@ static int enqueue_solve(ww_ctx* c, const Fac& F, double* B, double* Y, double* 
     LAUNCHCHK();
     B = c->pb;
   }
-  if (!F.use32) return enqueue_gemm<double>(c, F.Mi, 0, B, nullptr, 1.0, X, R);
-  if ((rc = enqueue_gemm<float>(c, F.Mi32, 0, B, nullptr, 1.0, X, R))) return rc;
+  if (!F.use32) return enqueue_gemm<double>(c, F.Mi, B, nullptr, 1.0, X, R);
+  if ((rc = enqueue_gemm<float>(c, F.Mi32, B, nullptr, 1.0, X, R))) return rc;
   for (int it = 0; it < c->nref; ++it) {
-    if ((rc = enqueue_gemm<double>(c, F.Ar, 0, X, B, -1.0, Rs, R))) return rc;
-    if ((rc = enqueue_gemm<float>(c, F.Mi32, 0, Rs, X, 1.0, X, R))) return rc;
+    if ((rc = enqueue_gemm<double>(c, F.Ar, X, B, -1.0, Rs, R))) return rc;
+    if ((rc = enqueue_gemm<float>(c, F.Mi32, Rs, X, 1.0, X, R))) return rc;
   }
   {
     // convergence test on the FP64 residual of the final solution (also with no sweep)
-    if ((rc = enqueue_gemm<double>(c, F.Ar, 0, X, B, -1.0, Rs, R))) return rc;
+    if ((rc = enqueue_gemm<double>(c, F.Ar, X, B, -1.0, Rs, R))) return rc;
     hipLaunchKernelGGL(k_refine_check, dim3(R), dim3(WW_NT), 0, c->stream, Rs, B, c->Np, c->N, REFINE_TOL,
                        c->status, 4);
     LAUNCHCHK();
@@ -976,7 +974,7 @@ static int enqueue_dtn_cols(ww_ctx* c, const Fac& F, double* B, double* Yt, doub
   hipLaunchKernelGGL(NF_SEL(c->N, k_gamma), dim3((R + 1) / 2), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, Mu, c->Np, R, Gam,
                      HGm, c->tw, c->N, nullptr, nullptr, 0.0, nullptr, 0);
   LAUNCHCHK();
-  return enqueue_gemm<double>(c, F.Gmr, 0, Gam, HGm, 1.0, out, R);
+  return enqueue_gemm<double>(c, F.Gmr, Gam, HGm, 1.0, out, R);
 }
 
 static size_t kstride(const ww_ctx* c) { return (size_t)2 * c->N * (c->M + 1); }
@@ -1029,7 +1027,7 @@ static int enqueue_gmres(ww_ctx* c, const Fac& F, double* psi, double* mu, doubl
   hipLaunchKernelGGL(k_gm_finish, dim3(1), dim3(GM_NT), 0, c->stream, b, mu);
   LAUNCHCHK();
   int rc;
-  if ((rc = enqueue_gemm<double>(c, F.Ar, 0, mu, psi, -1.0, rs, 1))) return rc;
+  if ((rc = enqueue_gemm<double>(c, F.Ar, mu, psi, -1.0, rs, 1))) return rc;
   hipLaunchKernelGGL(k_refine_check, dim3(1), dim3(WW_NT), 0, c->stream, rs, psi, c->Np, c->N, REFINE_TOL, c->status,
                      64);
   LAUNCHCHK();
@@ -1078,7 +1076,7 @@ static int enqueue_base_chain(ww_ctx* c, const double* ysrc, int s, double* kout
     hipLaunchKernelGGL(NF_SEL(c->N, k_gamma), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, c->mu0, c->Np, 1, c->gam0,
                        c->hg0, c->tw, c->N, nullptr, nullptr, 0.0, nullptr, 0);
     LAUNCHCHK();
-    if ((rc = enqueue_gemm<double>(c, F.Gmr, 0, c->gam0, c->hg0, 1.0, c->gphi0, 1))) return rc;
+    if ((rc = enqueue_gemm<double>(c, F.Gmr, c->gam0, c->hg0, 1.0, c->gphi0, 1))) return rc;
   } else {
     if ((rc = enqueue_assemble_lu(c, F))) return rc;
     if ((rc = enqueue_dtn_cols(c, F, c->rhs0, c->y0t, c->mu0, c->gam0, c->hg0, c->gphi0, c->rr0, 1))) return rc;
@@ -1118,7 +1116,7 @@ static int enqueue_col_chain(ww_ctx* c, int s, const Fac& F) {
 
 // ----- lagged-factor pipeline -----
 // A changes little between nearby stages (a second-kind operator of a surface that
-// moves by O(dt)): with the factors of stage s - lag, one refinement sweep with the
+// moves by O(dt)): with the factors of stage s - lag's group, one refinement sweep with the
 // FP64 residual of stage s's own matrix already reaches the rounding level.  The base
 // chain (the march's critical path) therefore solves with lagged factors while the
 // LU of its own matrix runs concurrently; the column chain, which lags behind anyway,
@@ -1254,9 +1252,9 @@ static int enqueue_pipe_part(ww_ctx* c, int s, int part) {
     // refinement sweeps against this stage's matrix: r = psi - A x, x += Mi_old r
     const int nref = c->nref_lag >= 0 ? c->nref_lag : c->nref;
     for (int it = 0; it < nref; ++it) {
-      if ((rc = enqueue_gemm<double>(c, F.Ar, 0, c->mu0, c->rhs0, -1.0, c->rr0, 1))) return rc;
-      rc = (Fo.use32 || Fo.lag32) ? enqueue_gemm<float>(c, Fo.Mi32, 0, c->rr0, c->mu0, 1.0, c->mu0, 1)
-                    : enqueue_gemm<double>(c, Fo.Mi, 0, c->rr0, c->mu0, 1.0, c->mu0, 1);
+      if ((rc = enqueue_gemm<double>(c, F.Ar, c->mu0, c->rhs0, -1.0, c->rr0, 1))) return rc;
+      rc = (Fo.use32 || Fo.lag32) ? enqueue_gemm<float>(c, Fo.Mi32, c->rr0, c->mu0, 1.0, c->mu0, 1)
+                    : enqueue_gemm<double>(c, Fo.Mi, c->rr0, c->mu0, 1.0, c->mu0, 1);
       if (rc) return rc;
     }
     // gamma, (1/2) H gamma, G phi and the residual of the convergence test in one
@@ -1881,7 +1879,7 @@ static int dd_prep_assemble(ww_ctx* c, const DdLane& L, const double* sh, const 
 }
 
 // The double-double set-up of the grid's surface in the context's lane: per-point
-// quantities, the double-double assembly, the FP64 factors (block LU and explicit
+// quantities, the double-double assembly, the FP64 factors (explicit
 // inverse) of A's leading part
 static int dd_setup_enqueue(ww_ctx* c, const double* sh, const double* sl, int* domain) {
   const DdLane L = dd_lane(c);
@@ -1925,8 +1923,8 @@ static int dd_solve_enqueue(ww_ctx* c, const DdLane& L, const double* rhs_hi, co
   int rc;
   // corrections from the FP64 inverse, or from the FP32 one (a mixed context: more sweeps)
   auto corr = [&](const double* B, double* X) -> int {
-    return L.F.use32 ? enqueue_gemm<float>(c, L.F.Mi32, 0, B, nullptr, 1.0, X, nrhs)
-                     : enqueue_gemm<double>(c, L.F.Mi, 0, B, nullptr, 1.0, X, nrhs);
+    return L.F.use32 ? enqueue_gemm<float>(c, L.F.Mi32, B, nullptr, 1.0, X, nrhs)
+                     : enqueue_gemm<double>(c, L.F.Mi, B, nullptr, 1.0, X, nrhs);
   };
   const int sweeps = L.F.use32 ? DD_SWEEPS_32 : DD_SWEEPS;
   if ((rc = corr(psh, muh))) return rc;
@@ -2713,19 +2711,19 @@ struct SdcStep {
     double* psi = rhsn(q);
     // x (+)= Mi_b B with the lagged inverse: FP64, or its FP32 copy in the mixed form
     auto lag_mul = [&](const double* B, const double* add, double* out) {
-      return F[qb].use32 ? enqueue_gemm<float>(c, F[qb].Mi32, 0, B, add, 1.0, out, 1)
-                         : enqueue_gemm<double>(c, F[qb].Mi, 0, B, add, 1.0, out, 1);
+      return F[qb].use32 ? enqueue_gemm<float>(c, F[qb].Mi32, B, add, 1.0, out, 1)
+                         : enqueue_gemm<double>(c, F[qb].Mi, B, add, 1.0, out, 1);
     };
     if ((rc = lag_mul(psi, nullptr, b.mu0))) return rc;
     for (int it = 0; it < c->sdc_lag_sweeps; ++it) {
-      if ((rc = enqueue_gemm<double>(c, F[q].Ar, 0, b.mu0, psi, -1.0, b.rr0, 1))) return rc;
+      if ((rc = enqueue_gemm<double>(c, F[q].Ar, b.mu0, psi, -1.0, b.rr0, 1))) return rc;
       if ((rc = lag_mul(b.rr0, b.mu0, b.mu0))) return rc;
     }
-    if ((rc = enqueue_gemm<double>(c, F[q].Ar, 0, b.mu0, psi, -1.0, b.rr0, 1))) return rc;
+    if ((rc = enqueue_gemm<double>(c, F[q].Ar, b.mu0, psi, -1.0, b.rr0, 1))) return rc;
     hipLaunchKernelGGL(NF_SEL(c->N, k_gamma), dim3(1), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, b.mu0, c->Np, 1, b.gam0,
                        b.hg0, c->tw, c->N, b.rr0, psi, REFINE_TOL, c->status, 32);
     LAUNCHCHK();
-    if ((rc = enqueue_gemm<double>(c, F[q].Gmr, 0, b.gam0, b.hg0, 1.0, b.gphi0, 1))) return rc;
+    if ((rc = enqueue_gemm<double>(c, F[q].Gmr, b.gam0, b.hg0, 1.0, b.gphi0, 1))) return rc;
     return sdc_base_rhs(c, ysn(q), b.gphi0, F[q].aux, c->sdc_K + (size_t)s * ks);
   }
   // the base solve and right-hand side (slot s) on the current stream with scratch b,

@@ -215,38 +215,47 @@ __global__ __launch_bounds__(PREP_NT) void k_base_prep(
   if (status && (bad || bed)) flag_state(status, bad, bed, status[1] * 16 + stage);
 }
 
+typedef double dbl2v __attribute__((ext_vector_type(2)));
+typedef float flt2v __attribute__((ext_vector_type(2)));
+
 // -------------------------------------------------------------------------------------
-// One row of y = add + sgn * M x over the 64-block range of `mode` (0 all, 1 strictly
-// lower, 2 upper incl. diagonal) from the row-major M (element type T, accumulation in
-// double), by one wave: contiguous row reads, sixteen loads in flight per lane, a
-// fixed-order shuffle reduction.
+// One row of y = add + sgn * M x from the row-major M (element type T, accumulation in
+// double), by one wave: contiguous row reads, two entries a lane (x and M 2-entry aligned),
+// eight pairs in flight, a fixed-order shuffle reduction.  Bound by memory latency.  With one
+// entry a lane and load, sixteen in flight: f only N 1024 21.1 ms against 20.7, adjoint N 512
+// 30.4 / 29.8.
 // -------------------------------------------------------------------------------------
 template <typename T>
-__device__ __forceinline__ void gemv_row_wave(const T* __restrict__ Mr, int Np, int mode, const double* __restrict__ x,
+__device__ __forceinline__ void gemv_row_wave(const T* __restrict__ Mr, int Np, const double* __restrict__ x,
                                               const double* __restrict__ add, double sgn, double* __restrict__ y,
                                               int row, int lane) {
-  const int rb = row / WW_TB;
-  const int tri = mode & 3;
-  const int lo = (tri == 2) ? rb * WW_TB : 0;
-  const int hi = (tri == 1) ? rb * WW_TB : Np;
-  const T* mr = Mr + (size_t)row * Np;
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  const T2* mr = reinterpret_cast<const T2*>(Mr + (size_t)row * Np);
+  const dbl2v* xr = reinterpret_cast<const dbl2v*>(x);
+  const int n = Np / 2;
   double s0 = 0.0, s1 = 0.0;
-  int j = lo + lane;
-  for (; j + 15 * 64 < hi; j += 16 * 64) {   // sixteen loads of the row in flight per lane
-    T m[16];
-    double xv[16];
+  int j = lane;
+  for (; j + 7 * 64 < n; j += 8 * 64) {
+    T2 m[8];
+    dbl2v xv[8];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < 8; ++q) {
       m[q] = mr[j + 64 * q];
-      xv[q] = x[j + 64 * q];
+      xv[q] = xr[j + 64 * q];
     }
 #pragma unroll
-    for (int q = 0; q < 16; q += 2) {
-      s0 = fma((double)m[q], xv[q], s0);
-      s1 = fma((double)m[q + 1], xv[q + 1], s1);
+    for (int q = 0; q < 8; ++q) {
+      s0 = fma((double)m[q][0], xv[q][0], s0);
+      s1 = fma((double)m[q][1], xv[q][1], s1);
     }
   }
-  for (; j < hi; j += 64) s0 = fma((double)mr[j], x[j], s0);
+#pragma unroll 4
+  for (; j < n; j += 64) {
+    const T2 m = mr[j];
+    const dbl2v v = xr[j];
+    s0 = fma((double)m[0], v[0], s0);
+    s1 = fma((double)m[1], v[1], s1);
+  }
   double s = s0 + s1;
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if (lane == 0) y[row] = (add ? add[row] : 0.0) + sgn * s;
@@ -301,9 +310,9 @@ __global__ __launch_bounds__(WW_NT) void k_assemble(
     const int row = g * (WW_NT / 64) + (threadIdx.x >> 6);
     if (row >= Np) return;
     if (Mx32)
-      gemv_row_wave<float>(Mx32, Np, 0, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
+      gemv_row_wave<float>(Mx32, Np, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
     else if (Mx64)
-      gemv_row_wave<double>(Mx64, Np, 0, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
+      gemv_row_wave<double>(Mx64, Np, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
     return;
   }
   // stage the per-point quantities of the strip's rows and 64 columns and the circulant
@@ -567,18 +576,15 @@ __global__ void k_permute_rows(const double* __restrict__ src, double* __restric
 }
 
 // -------------------------------------------------------------------------------------
-// One right-hand side: y = add + sgn * M x over the 64-block range of `mode` (0 all,
-// 1 strictly lower, 2 upper incl. diagonal), from the row-major copy Mr (element type
-// T, accumulation in double).  One wave per row: contiguous row reads, eight loads in
-// flight per lane, a fixed-order shuffle reduction (no cross-workgroup reduction).
+// One right-hand side: y = add + sgn * M x, one wave per row (no cross-workgroup reduction).
 // -------------------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(WW_NT) void k_gemv_row(const T* __restrict__ Mr, int Np, int mode,
+__global__ __launch_bounds__(WW_NT) void k_gemv_row(const T* __restrict__ Mr, int Np,
                                                     const double* __restrict__ x, const double* __restrict__ add,
                                                     double sgn, double* __restrict__ y) {
   const int row = (blockIdx.x * WW_NT + threadIdx.x) >> 6;
   if (row >= Np) return;
-  gemv_row_wave<T>(Mr, Np, mode, x, add, sgn, y, row, threadIdx.x & 63);
+  gemv_row_wave<T>(Mr, Np, x, add, sgn, y, row, threadIdx.x & 63);
 }
 
 
@@ -608,8 +614,6 @@ __global__ __launch_bounds__(WW_NT) void k_gemv_row(const T* __restrict__ Mr, in
 // its operations 3.7), 2048 x 257 52 (94; 30).
 // -------------------------------------------------------------------------------------
 #define GEMM_NT 512
-typedef double dbl2v __attribute__((ext_vector_type(2)));
-typedef float flt2v __attribute__((ext_vector_type(2)));
 // The wave's own LDS accesses on either side stay in program order.
 __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

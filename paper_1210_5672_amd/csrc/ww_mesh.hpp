@@ -75,9 +75,9 @@ __global__ __launch_bounds__(WW_NT) void k_assemble_map(const double* __restrict
     const int row = g * (WW_NT / 64) + (threadIdx.x >> 6);
     if (row >= Np) return;
     if (Mx32)
-      gemv_row_wave<float>(Mx32, Np, 0, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
+      gemv_row_wave<float>(Mx32, Np, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
     else if (Mx64)
-      gemv_row_wave<double>(Mx64, Np, 0, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
+      gemv_row_wave<double>(Mx64, Np, psi, nullptr, 1.0, x0, row, threadIdx.x & 63);
     return;
   }
   __shared__ double rq[7][CW];      // eta', eta'', exp(s), exp(-s), xi, E, E' of the rows

@@ -417,12 +417,12 @@ class Context:
 
     def profile(self, enable: bool = True, kernel_events: bool = False):
         """Timestamps around the phases of every stage; with kernel_events, also HIP
-        events around every block-LU step launched outside a graph (phase 4)."""
+        events around every elimination step launched outside a graph (phase 4)."""
         _check(self.lib.ww_profile(self.ptr, (1 if enable else 0) | (2 if enable and kernel_events else 0)))
 
     def profile_read(self, phase: int) -> float:
         """Mean duration (ms) of a phase over every stage of every step replayed since
-        the last profile(True): 0 block LU, 1 base chain, 2 column chain."""
+        the last profile(True): 0 elimination, 1 base chain, 2 column chain."""
         return self.profile_stats(phase)[0]
 
     def profile_stats(self, phase: int):
