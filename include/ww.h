@@ -48,8 +48,8 @@ typedef struct ww_ctx ww_ctx;
 #define WW_ENOCONV (-8)    /* an iteration did not converge (thin SVD) */
 
 /* context flags */
-#define WW_FP64 0u         /* LU, triangular solves, everything in FP64 */
-#define WW_MIXED 1u        /* LU and triangular solves in FP32 on MFMA, FP64 iterative
+#define WW_FP64 0u         /* elimination, solves, everything in FP64 */
+#define WW_MIXED 1u        /* elimination and solves in FP32 on MFMA, FP64 iterative
                               refinement of every solve (residuals in FP64): a fixed number
                               of sweeps (2; environment WW_NREF, 0..8; 0 leaves the FP32
                               solve, which then fails the test), then the FP64

@@ -14,7 +14,7 @@
 
 #include "ww_fft.hpp"
 
-#define WW_TB 64          // tile edge of the blocked LU / triangular solves / GEMM
+#define WW_TB 64          // tile edge of the elimination
 #define WW_NT 256         // threads per workgroup
 
 // offsets of the mesh tables that the shared kernels read (see ww_mesh.hpp)
