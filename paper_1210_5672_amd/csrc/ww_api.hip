@@ -1352,6 +1352,7 @@ static int capture_part(ww_ctx* c, int s, int part, hipGraphExec_t* out) {
   if (eb != hipSuccess) return fail(WW_EHIP, std::string("hipStreamBeginCapture: ") + hipGetErrorString(eb));
   c->stream = c->cap_stream;
   c->prof_stage = part < 0 ? -1 : s;
+  c->plast = false;   // (still set from the march before) replays are never a march's last base chain
   const int rc = part < 0 ? enqueue_pipe_end(c) : enqueue_pipe_part(c, s, part);
   c->prof_stage = -1;
   hipGraph_t g = nullptr;
