@@ -519,8 +519,9 @@ unsigned ww_next_fallback(unsigned flags, unsigned fb, int status);
  *   lag          lagged-factor march: the base solve of stage s uses the explicit
  *                inverse of the newest stage of stage s - lag's group (0: each stage's own
  *                factors), 0..11
- *   lu_group     consecutive stages factored by one launch sequence, 1..4 (<= lag); the
- *                default, 2, takes four of them where lag >= 8
+ *   lu_group     consecutive stages factored by one launch sequence, 1..4 (<= lag).  A
+ *                context that was given none reads 2 and takes four where lag >= 8; a value
+ *                that was set is taken as it is
  *   lu_streams   streams the LU groups rotate over, 1..6
  *   graph_parts  march parts replayed from HIP graphs, one bit each: 1 prep and
  *                assembly, 2 LU, 4 base chain, 8 column chain (the rest launched
@@ -555,6 +556,12 @@ typedef struct ww_tuning {
 } ww_tuning;
 int ww_get_tuning(ww_ctx *ctx, ww_tuning *t);
 int ww_set_tuning(ww_ctx *ctx, const ww_tuning *t);
+/* Only the named fields of t (bit i: the i-th field of ww_tuning); the others keep their
+ * values, and lu_group, unless named, stays by its rule.  Errors: as ww_set_tuning, and
+ * WW_EINVAL for an unknown bit. */
+#define WW_TUNE_ALL 0xfffu
+#define WW_TUNE_LU_GROUP 0x2u
+int ww_set_tuning_fields(ww_ctx *ctx, const ww_tuning *t, unsigned fields);
 
 /* thread-local message of the last failure on this thread ("" if none) */
 const char *ww_last_error(void);

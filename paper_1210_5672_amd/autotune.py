@@ -31,7 +31,8 @@ import time
 CACHE_ENV = "WW_TUNING_CACHE"
 DEFAULT_CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning_cache.json")
 
-# candidate values of every choice (the defaults of ww_create are among them)
+# candidate values of every choice (ww_create's defaults first; a context that was given no
+# lu_group reads 2 and runs 4 where lag >= 8, which is a candidate of its own)
 SPACE = {
     "graph_parts": [10, 0, 15, 2],
     "lu_group": [2, 1, 3, 4],

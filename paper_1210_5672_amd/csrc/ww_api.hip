@@ -256,8 +256,9 @@ struct ww_ctx {
   // stage s runs on an LU stream; the column chain of stage s waits for it
   int lag = 8;   // environment WW_PIPE_LAG, 0..PIPE_MAXLAG (0: every solve uses its own factors)
   // stages factored together by one LU launch sequence (environment WW_LU_GROUP,
-  // 1..GJ_GMAX; at most the lag; 2: up to four, see lu_group())
+  // 1..GJ_GMAX; at most the lag); lu_rule: never chosen, taken by rule (see lu_group())
   int lu_group = 2;
+  bool lu_rule = true;
   int minv_wgs = 1 << 20;                  // kept in the interface, without effect
   int graph_parts = 10;                    // parts of a march stage replayed from graphs (bit per part)
   int blu_strip = 4;                       // tiles per strip task of an elimination step
@@ -509,7 +510,10 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
     if (ns) c->nlus = std::max(1, std::min(PIPE_MAXLUS, std::atoi(ns)));
     const char* lg = std::getenv("WW_LU_GROUP");
     if (const char* ak = std::getenv("WW_ADJOINT_KEEP")) c->adj_keep = (size_t)std::max(0L, std::atol(ak)) << 20;
-    if (lg) c->lu_group = std::max(1, std::min(GJ_GMAX, std::atoi(lg)));
+    if (lg) {
+      c->lu_group = std::max(1, std::min(GJ_GMAX, std::atoi(lg)));
+      c->lu_rule = false;
+    }
     const char* gp = std::getenv("WW_GRAPH_PARTS");
     if (gp) c->graph_parts = std::atoi(gp) & 15;
     const char* mw = std::getenv("WW_MINV_WGS");
@@ -620,8 +624,18 @@ int ww_get_tuning(ww_ctx* c, ww_tuning* t) {
   return 0;
 }
 
-int ww_set_tuning(ww_ctx* c, const ww_tuning* t) {
-  if (!c || !t) return fail(WW_EINVAL, "null argument");
+int ww_set_tuning(ww_ctx* c, const ww_tuning* t) { return ww_set_tuning_fields(c, t, WW_TUNE_ALL); }
+
+int ww_set_tuning_fields(ww_ctx* c, const ww_tuning* from, unsigned fields) {
+  if (!c || !from) return fail(WW_EINVAL, "null argument");
+  if (fields & ~WW_TUNE_ALL) return fail(WW_EINVAL, "tuning: unknown field");
+  ww_tuning cur;
+  ww_get_tuning(c, &cur);
+  const int n = sizeof(ww_tuning) / sizeof(int);   // (a struct of ints)
+  static_assert(WW_TUNE_ALL == (1u << (sizeof(ww_tuning) / sizeof(int))) - 1, "one bit per field");
+  for (int i = 0; i < n; ++i)
+    if (fields >> i & 1) std::memcpy((int*)&cur + i, (const int*)from + i, sizeof(int));
+  const ww_tuning* t = &cur;
   if (t->lag < 0 || t->lag > PIPE_MAXLAG) return fail(WW_EINVAL, "tuning: lag out of range");
   if (t->lu_group < 1 || t->lu_group > GJ_GMAX) return fail(WW_EINVAL, "tuning: lu_group out of range");
   if (t->lu_streams < 1 || t->lu_streams > PIPE_MAXLUS) return fail(WW_EINVAL, "tuning: lu_streams out of range");
@@ -636,6 +650,7 @@ int ww_set_tuning(ww_ctx* c, const ww_tuning* t) {
   if (t->lag_sweeps < 1 || t->lag_sweeps > 8) return fail(WW_EINVAL, "tuning: lag_sweeps out of range");
   c->lag = t->lag;
   c->lu_group = t->lu_group;
+  if (fields & WW_TUNE_LU_GROUP) c->lu_rule = false;
   c->nlus = t->lu_streams;
   c->graph_parts = t->graph_parts;
   c->minv_wgs = t->minv_wgs;
@@ -1133,14 +1148,14 @@ static bool pipelined(const ww_ctx* c, bool cols, bool two_streams) {
 // group anyway); without columns nothing reads the others, and only that stage is
 // factored (N = 1024, two streams: the LUs of every stage took 141 us a stage, the base
 // chain 100).
-// The default of 2 becomes 4 where the lag leaves four stages of base chain to hide the
-// longer group behind: a step of the elimination is bound by its critical task, which four
+// A context that was given no group (lu_rule) takes 2, or 4 where the lag leaves four
+// stages of base chain to hide the longer group behind: a step of the elimination is bound by its critical task, which four
 // matrices share, the lagged factors are no older (a stage reads those of s - lag's group,
 // its last), and a group's launches cost the host as much as one stage's.  Groups of 2
 // against 4: march N 256, M 64 21.5 / 15.2 ms (host bound), N 1024, M 128 34.6 / 33.8, mixed
 // N 768, M 137 26.0 / 24.6, f only N 1024 25.8 / 22.3.
 static int lu_group(const ww_ctx* c) {
-  const int g = c->lu_group == 2 && c->lag >= 8 ? GJ_GMAX : c->lu_group;
+  const int g = c->lu_rule && c->lag >= 8 ? GJ_GMAX : c->lu_group;
   return std::max(1, std::min(g, c->lag));
 }
 // a march without columns (one LU per group) keeps to one LU stream where that LU is shorter

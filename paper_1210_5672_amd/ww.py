@@ -79,7 +79,7 @@ EXPORTS = ["ww_create", "ww_destroy", "ww_set_stream", "ww_set_tableau", "dtn_se
            "dtn_solve_multi", "shoot_setup", "shoot_eval", "shoot_adjoint", "ww_last_error",
            "ww_version", "ww_profile", "ww_profile_read", "shoot_eval_batch", "ww_fallbacks",
            "ww_thin_svd", "ww_levmar", "ww_lm_default_opts", "ww_bfgs", "ww_bfgs_default_opts",
-           "dtn_solve_multi_noalloc", "ww_next_fallback", "ww_get_tuning", "ww_set_tuning",
+           "dtn_solve_multi_noalloc", "ww_next_fallback", "ww_get_tuning", "ww_set_tuning", "ww_set_tuning_fields",
            "shoot_eval_segments", "dtn_setup_dd", "dtn_solve_multi_dd", "shoot_eval_sdc",
            "shoot_eval_sdc_dd", "shoot_eval_segments_sdc"]
 
@@ -115,6 +115,7 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.ww_next_fallback.argtypes = [U, U, I]
     lib.ww_get_tuning.argtypes = [P, ctypes.POINTER(Tuning)]
     lib.ww_set_tuning.argtypes = [P, ctypes.POINTER(Tuning)]
+    lib.ww_set_tuning_fields.argtypes = [P, ctypes.POINTER(Tuning), U]
     lib.ww_next_fallback.restype = U
     lib.shoot_setup.argtypes = [P, I, D, D, D, P, P, I]
     lib.shoot_eval.argtypes = [P, P, D, I, P, P, P, DP]
@@ -405,15 +406,15 @@ class Context:
         return t.as_dict()
 
     def set_tuning(self, **choices):
-        """Change some of the launch and scheduling choices (ww_set_tuning; the others
-        keep their current values)."""
-        cur = self.tuning()
-        unknown = set(choices) - set(cur)
+        """Change some of the launch and scheduling choices (ww_set_tuning_fields; the
+        others keep their current values)."""
+        names = [n for n, _ in Tuning._fields_]
+        unknown = set(choices) - set(names)
         if unknown:
             raise ValueError(f"unknown tuning fields {sorted(unknown)}")
-        cur.update(choices)
-        t = Tuning(**{k: int(v) for k, v in cur.items()})
-        _check(self.lib.ww_set_tuning(self.ptr, ctypes.byref(t)))
+        t = Tuning(**{k: int(v) for k, v in choices.items()})
+        fields = sum(1 << i for i, n in enumerate(names) if n in choices)
+        _check(self.lib.ww_set_tuning_fields(self.ptr, ctypes.byref(t), fields))
 
     def profile(self, enable: bool = True, kernel_events: bool = False):
         """Timestamps around the phases of every stage; with kernel_events, also HIP
