@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <functional>
 #include <string>
 #include <vector>
@@ -42,20 +43,30 @@ static thread_local std::string g_err;
   X(64, __VA_ARGS__) X(128, __VA_ARGS__) X(256, __VA_ARGS__) X(384, __VA_ARGS__) X(512, __VA_ARGS__)               \
   X(768, __VA_ARGS__) X(1024, __VA_ARGS__) X(1536, __VA_ARGS__) X(2048, __VA_ARGS__)
 
-// The library's working streams of a device (LU streams; one of them doubles as the column
-// stream where there is one), shared by its contexts: HIP spreads a process's streams over
-// four hardware queues, in the order of their creation, and a second context with streams
-// of its own would have its LUs queue in front of base chains (measured, N = 1024, 24 steps,
-// one context marching beside two idle ones: 58.8 ms with streams of their own, 47 ms alone).
+// The library's working streams of a device: sets of LU streams and a column stream.  A
+// call that marches on more than its caller's stream takes a set for its duration
+// (StreamLease), the first that no other call holds.  So contexts that march one at a time
+// share one set -- HIP spreads a process's streams over a few hardware queues (four by
+// default), in the order of their creation, and a second context with streams of its own
+// would have its LUs queue in front of base chains (N = 1024, 24 steps, one context marching
+// beside two idle ones: 58.8 ms with streams of their own, 47 ms alone) -- and calls made at
+// the same time, from several threads, never wait for each other's streams: a march whose
+// caller's stream is held up holds up no other (beside one that waits 380 ms, 16 hardware
+// queues, the other march's 35 ms took 380 on shared streams).
 // A context holds the pool from ww_create to ww_destroy; the last one to go destroys the
-// streams.  Work of several contexts on one stream is only put in sequence: every
-// dependency is an event recorded before its wait, so no order of enqueues can deadlock.
+// streams.  A call ends with its work joined into the caller's stream and waited for; after
+// an error that leaves work behind, the next march on the set is only put behind it.
 // Nothing is ever captured from these streams (captures take streams of their own).
-#define POOL_STREAMS 6
-#define POOL_SIDE 2   // the column stream: not LU stream 0 or 1, which it runs beside
+#define POOL_STREAMS 6             // LU streams
+#define POOL_SIDE 2                // the column stream: not LU stream 0 or 1, which it runs beside
+#define POOL_SIDE_OWN POOL_STREAMS // ... of a context whose columns never run on the LU streams
+struct StreamSet {
+  hipStream_t s[POOL_STREAMS + 1] = {};
+  bool busy = false;
+};
 struct StreamPool {
   int refs = 0;
-  hipStream_t s[POOL_STREAMS] = {};
+  std::deque<StreamSet> sets;   // (at most one per call in progress)
 };
 static std::mutex g_pool_mu;
 static StreamPool g_pool[SCRATCH_MAX_DEV];
@@ -68,22 +79,36 @@ static void pool_release(int dev) {
   std::lock_guard<std::mutex> lk(g_pool_mu);
   StreamPool& p = g_pool[dev];
   if (--p.refs > 0) return;
-  for (hipStream_t& s : p.s)
-    if (s) {
-      (void)hipStreamDestroy(s);
-      s = nullptr;
-    }
+  for (StreamSet& q : p.sets)
+    for (hipStream_t s : q.s)
+      if (s) (void)hipStreamDestroy(s);
+  p.sets.clear();
 }
-// streams 0..i of the pool (created in order on first need, with the device current)
-static hipError_t pool_get(int dev, int i, hipStream_t* out) {
+// the first set that is not in use
+static int pool_take(int dev) {
   std::lock_guard<std::mutex> lk(g_pool_mu);
-  StreamPool& p = g_pool[dev];
-  for (int q = 0; q <= i; ++q)
-    if (!p.s[q]) {
-      const hipError_t e = hipStreamCreateWithFlags(&p.s[q], hipStreamNonBlocking);
-      if (e != hipSuccess) return e;
-    }
-  *out = p.s[i];
+  std::deque<StreamSet>& v = g_pool[dev].sets;
+  size_t i = 0;
+  while (i < v.size() && v[i].busy) ++i;
+  if (i == v.size()) v.emplace_back();
+  v[i].busy = true;
+  return (int)i;
+}
+static void pool_give(int dev, int set) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  g_pool[dev].sets[set].busy = false;
+}
+// stream i of a set (created on first need, with the device current)
+static hipError_t pool_get(int dev, int set, int i, hipStream_t* out) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  std::deque<StreamSet>& v = g_pool[dev].sets;
+  if (v.empty()) v.emplace_back();
+  hipStream_t& s = v[set].s[i];
+  if (!s) {
+    const hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e != hipSuccess) return e;
+  }
+  *out = s;
   return hipSuccess;
 }
 
@@ -142,8 +167,9 @@ struct ww_ctx {
   // device buffers: two factor sets; stages alternate between them so that the column
   // chain of stage s overlaps the base chain of stage s + 1
   FacSet set[2];
-  hipStream_t side = nullptr;  // column-chain stream (of the device's pool)
+  hipStream_t side = nullptr;  // column-chain stream (of the call's stream set)
   bool pool = false;           // the context holds the device's stream pool
+  int sset = -1;               // the stream set of the call in progress (StreamLease)
   hipEvent_t evB[16] = {}, evC[16] = {};
   double *Rr = nullptr, *rr0 = nullptr;   // residuals of the refinement sweeps
   int nref = 2;                            // refinement sweeps per solve (mixed mode)
@@ -315,6 +341,28 @@ static bool valid_n(int N) {
   while (m % 2 == 0) m /= 2;
   while (m % 3 == 0) m /= 3;
   return m == 1;
+}
+
+// The stream set of a call that marches on several streams, for the duration of the call (of
+// the outermost one, where such calls nest)
+struct StreamLease {
+  ww_ctx* c;
+  bool own;
+  explicit StreamLease(ww_ctx* cc, bool on = true) : c(cc), own(on && cc->sset < 0) {
+    if (own) c->sset = pool_take(c->dev);
+  }
+  ~StreamLease() {
+    if (!own) return;
+    for (hipStream_t& s : c->lus) s = nullptr;
+    c->side = nullptr;
+    pool_give(c->dev, c->sset);
+    c->sset = -1;
+  }
+  StreamLease(const StreamLease&) = delete;
+  StreamLease& operator=(const StreamLease&) = delete;
+};
+static hipError_t side_get(ww_ctx* c) {
+  return pool_get(c->dev, c->sset, c->cols_on_lu ? POOL_SIDE : POOL_SIDE_OWN, &c->side);
 }
 
 static int dalloc(ww_ctx* c, void** p, size_t bytes) {
@@ -523,8 +571,9 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
     pool_acquire(c->dev);
     c->pool = true;
     const int nls = c->lag > 0 ? std::min(c->nlus, c->lag) : 0;
-    for (int i = 0; i < nls; ++i) CCHK(pool_get(c->dev, i, &c->lus[i]));
-    if (!c->cols_on_lu) CCHK(pool_get(c->dev, POOL_SIDE, &c->side));
+    hipStream_t st;
+    for (int i = 0; i < nls; ++i) CCHK(pool_get(c->dev, 0, i, &st));
+    if (!c->cols_on_lu) CCHK(pool_get(c->dev, 0, POOL_SIDE_OWN, &st));
     const char* pg = std::getenv("WW_PIVOT_GUARD");
     if (pg) {
       const double v = std::atof(pg);
@@ -1184,7 +1233,7 @@ static int ensure_ring(ww_ctx* c, int n) {
 
 static int ensure_pipe(ww_ctx* c) {
   for (int i = 0; i < lu_count(c); ++i)
-    if (!c->lus[i]) HIPCHK(pool_get(c->dev, i, &c->lus[i]));
+    if (!c->lus[i]) HIPCHK(pool_get(c->dev, c->sset, i, &c->lus[i]));
   for (int i = 0; i < 16; ++i) {
     if (!c->evA[i]) HIPCHK(hipEventCreateWithFlags(&c->evA[i], hipEventDisableTiming));
     if (!c->evL[i]) HIPCHK(hipEventCreateWithFlags(&c->evL[i], hipEventDisableTiming));
@@ -2149,7 +2198,7 @@ static int shoot_prepare(ww_ctx* c, const double* params, double T, int nsteps, 
     // do not run on the LU streams
     const bool pipe = pipelined(c, cols, two_streams);
     if (cols && c->M > 0 && two_streams && !(pipe && graphed(c) && c->cols_on_lu) && !c->side)
-      HIPCHK(pool_get(c->dev, POOL_SIDE, &c->side));
+      HIPCHK(side_get(c));
   }
   if (pipelined(c, cols, two_streams)) {
     c->pcols = cols && c->M > 0;
@@ -2245,6 +2294,7 @@ static int shoot_run(ww_ctx* c, const double* params, double T, int nsteps, doub
                      double* f, int* st, int* where) {
   const bool cols = (J != nullptr) && c->M > 0;
   const bool two = c->overlap && !pivoted(c);
+  const StreamLease lease(c);
   int rc;
   if (pivoted(c) && (rc = ensure_pivot_buffers(c))) return rc;
   if ((rc = shoot_prepare(c, params, T, nsteps, cols, two))) return rc;
@@ -2337,6 +2387,7 @@ static int seg_run(ww_ctx* c, const double* params, double T, int nseg, const ww
   const bool cols = (J != nullptr) && c->M > 0;
   const bool two = c->overlap && !pivoted(c);
   const bool sdc_two = sdc && two && !c->gm_active;
+  const StreamLease lease(c);
   int rc;
   if (pivoted(c) && (rc = ensure_pivot_buffers(c))) return rc;
   if (sdc && (rc = ensure_sdc(c))) return rc;
@@ -2608,8 +2659,8 @@ static int sdc_col_rhs(ww_ctx* c, const double* Ys, const double* aux, double* k
 // the factor sets, the LU and column streams and the lane events of the two-stream form
 // (first use)
 static int ensure_sdc_groups(ww_ctx* c) {
-  if (!c->lus[0]) HIPCHK(pool_get(c->dev, 0, &c->lus[0]));
-  if (!c->side) HIPCHK(pool_get(c->dev, POOL_SIDE, &c->side));
+  if (!c->lus[0]) HIPCHK(pool_get(c->dev, c->sset, 0, &c->lus[0]));
+  if (!c->side) HIPCHK(side_get(c));
   if (!c->sdc_ev) HIPCHK(hipEventCreateWithFlags(&c->sdc_ev, hipEventDisableTiming));
   for (int i = 0; i < SDC_NODES; ++i) {
     if (!c->sdc_evB[i]) HIPCHK(hipEventCreateWithFlags(&c->sdc_evB[i], hipEventDisableTiming));
@@ -2922,6 +2973,7 @@ static int sdc_steps(ww_ctx* c, bool cols, double dt, int nsteps, bool two) {
 static int sdc_run(ww_ctx* c, const double* params, double T, int nsteps, double* r, double* J, double* drdT,
                    double* f, int* st, int* where) {
   const bool cols = (J != nullptr) && c->M > 0;
+  const StreamLease lease(c);
   int rc;
   if (pivoted(c) && (rc = ensure_pivot_buffers(c))) return rc;
   if ((rc = ensure_sdc(c))) return rc;
@@ -3245,6 +3297,7 @@ int shoot_eval_sdc_dd(ww_ctx* c, int N, double h, double tau, double g, const do
       !std::isfinite(tau) || !(h > 0.0))
     return fail(WW_EINVAL, "nsteps >= 1, finite T and g, finite tau >= 0 and h > 0 required");
   if (int rj = pipe_join(c)) return rj;
+  const StreamLease lease(c);
   int rc;
   if ((rc = set_grid(c, N, h))) return rc;
   if ((rc = ensure_dd(c))) return rc;
@@ -3397,6 +3450,7 @@ int shoot_eval_batch(int n_inst, ww_ctx* const* ctx, const double* const* params
   // which the hardware overlaps across instances (two-stream graphs of several
   // instances run one after the other)
   const bool two = n_inst == 1 && ctx[0]->overlap;
+  const StreamLease lease(ctx[0], two);
   for (int i = 0; i < n_inst; ++i) {
     const bool cols = J && J[i] && ctx[i]->M > 0;
     ctx[i]->fb = ctx[i]->lag_off ? WW_FB_DIRECT : 0;
