@@ -39,7 +39,7 @@ typedef struct ww_ctx ww_ctx;
 #define WW_ENOSETUP (-2)   /* dtn_solve_multi before dtn_setup, shoot_* before shoot_setup */
 #define WW_EHIP (-3)       /* HIP runtime failure; the message carries the HIP error string */
 #define WW_EDOMAIN (-4)    /* finite depth with surface height h + eta <= 0 somewhere */
-#define WW_ENONFINITE (-5) /* NaN or Inf in the marched state */
+#define WW_ENONFINITE (-5) /* NaN or Inf in the marched state, a surface or its matrix */
 #define WW_EPIVOT (-6)     /* a pivot fell below the guard: of the unpivoted LU in a
                               WW_STRICT context, else of the partially pivoted fallback
                               (A numerically singular) */

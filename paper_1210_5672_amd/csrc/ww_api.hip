@@ -1657,7 +1657,7 @@ static int dtn_factor(ww_ctx* c) {
     if ((rc = enqueue_assemble_lu(c, fac_default(c)))) return rc;
     int st = 0;
     if ((rc = read_status(c, &st))) return rc;
-    if (st & 2) return fail(WW_ENONFINITE, "non-finite surface");
+    if (st & 2) return fail(WW_ENONFINITE, "non-finite surface or matrix");
     if (!(st & (1 | 8))) return 0;
     if (pivoted(c)) return fail(WW_EPIVOT, MSG_PIVOT2);
     if (strict(c)) return fail(WW_EPIVOT, MSG_PIVOT);
@@ -2036,7 +2036,7 @@ int dtn_setup_dd(ww_ctx* c, const double* surface_hi, const double* surface_lo, 
   if ((rc = dd_setup_enqueue(c, surface_hi, surface_lo, nullptr))) return rc;
   int st = 0;
   if ((rc = read_status(c, &st))) return rc;
-  if (st & 2) return fail(WW_ENONFINITE, "non-finite surface");
+  if (st & 2) return fail(WW_ENONFINITE, "non-finite surface or matrix");
   if (st & (1 | 8)) return fail(WW_EPIVOT, "double-double DtN: pivot below the guard (no pivoted form)");
   c->dd_ready = true;
   return 0;
@@ -3153,7 +3153,7 @@ static int dd_march_status(ww_ctx* c, int n) {
   if ((rc = read_status(c, &st))) return rc;
   const std::string at = n >= 0 ? " (double-double march, step " + std::to_string(n) + ")" : " (double-double march)";
   if (st & 16) return fail(WW_EDOMAIN, "finite depth: surface height h + eta <= 0" + at);
-  if (st & 2) return fail(WW_ENONFINITE, "non-finite surface" + at);
+  if (st & 2) return fail(WW_ENONFINITE, "non-finite surface or matrix" + at);
   if (st & (1 | 8)) return fail(WW_EPIVOT, "double-double DtN: pivot below the guard" + at);
   if (st & 4) return fail(WW_EREFINE, "double-double DtN: residual above 2^-96 of the right-hand side" + at);
   return 0;
