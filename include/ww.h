@@ -530,6 +530,8 @@ unsigned ww_next_fallback(unsigned flags, unsigned fb, int status);
  *                the explicit inverse in place, which once took a launch of its own)
  *   blu_strip    64-tiles per task of a block elimination step, 1..16: a step takes the
  *                fewest that leave every task a compute unit, at most twice this number
+ *                (environment WW_GJ_STRIP, read by ww_create: exactly so many tiles of a row,
+ *                a test hook)
  *   dtn_rows     rows per workgroup of the base DtN launch, 4..32, a multiple of 4
  *   gemm_split   2 or 4; kept for callers that set it, without effect (the eight waves of a
  *                column product's workgroup always split the inner dimension)

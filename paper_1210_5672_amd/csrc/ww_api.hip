@@ -287,7 +287,8 @@ struct ww_ctx {
   bool lu_rule = true;
   int minv_wgs = 1 << 20;                  // kept in the interface, without effect
   int graph_parts = 10;                    // parts of a march stage replayed from graphs (bit per part)
-  int blu_strip = 4;                       // tiles per strip task of an elimination step
+  int blu_strip = 4;                       // half the most tiles per strip task of an elimination step
+  int strip_set = 0;                       // tiles per strip task whatever the rule (WW_GJ_STRIP, a test hook)
   int dtn_rows = 8;                        // rows per workgroup of the base DtN launch
   int gemm_split = 4;                      // kept in the interface, without effect
   int gemm_rows = 32;                      // column products: tiles by size (32), 16 x 16 (16)
@@ -564,6 +565,7 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
     }
     const char* gp = std::getenv("WW_GRAPH_PARTS");
     if (gp) c->graph_parts = std::atoi(gp) & 15;
+    if (const char* gs = std::getenv("WW_GJ_STRIP")) c->strip_set = std::max(0, std::atoi(gs));
     const char* mw = std::getenv("WW_MINV_WGS");
     if (mw) c->minv_wgs = std::max(1, std::atoi(mw));
     // the working streams: created in order, so that the caller's stream and three LU
@@ -905,11 +907,12 @@ static int enqueue_assemble(ww_ctx* c, const Fac& F, const Fac* Fo = nullptr, co
 
 // Tiles per strip task: the fewest with which a step's tasks still find a CU each (256, the
 // critical task of every matrix among them: with one more workgroup than CUs the critical
-// one shares its matrix units and the step gets longer), at most blu_strip.  One tile a
+// one shares its matrix units and the step gets longer), at most twice blu_strip.  One tile a
 // task repeats the row's left factor for every tile; four leave most CUs idle below
 // N = 1024.
 static int gj_strip(const ww_ctx* c, int count) {
   const int nb = c->Np / WW_TB;
+  if (c->strip_set) return std::min(c->strip_set, nb);
   int s = 1;
   while (s < 2 * c->blu_strip && gj_step_tasks(nb, 0, s) * count > 256) ++s;
   return s;

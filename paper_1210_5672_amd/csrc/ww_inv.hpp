@@ -34,7 +34,7 @@
 // only the right factors pass through LDS (one barrier per tile, double-buffered).
 // -------------------------------------------------------------------------------------
 #define GJ_GMAX 4           // matrices of a group
-#define GJ_STRIP_MAX 16     // tiles of a strip task
+#define GJ_STRIP_MAX 16     // largest blu_strip (a strip task takes at most twice as many tiles)
 #define GJ_LD 66            // pitch of a right factor in LDS, stored by columns: conflict-free reads and writes
 #define GJ_TILE (64 * GJ_LD)
 #define GJ_BLD 18           // pitch of the 16-row bands of the diagonal inverse (16-byte aligned in FP64)
