@@ -1642,7 +1642,8 @@ static int read_status(ww_ctx* c, int* st, int* where) {
   HIPCHK(hipStreamSynchronize(c->stream));
   HIPCHK(hipMemcpy(h, c->status, sizeof(h), hipMemcpyDeviceToHost));
   HIPCHK(hipMemset(c->status, 0, sizeof(int)));
-  *st = h[0];
+  // NaN from an elimination without a small pivot (1, 8): its matrix was not finite (2)
+  *st = (h[0] & ~128) | ((h[0] & 128) && !(h[0] & (1 | 8)) ? 2 : 0);
   if (where) *where = h[2];
   return 0;
 }
@@ -2254,7 +2255,7 @@ static int shoot_finish(ww_ctx* c, bool cols, double* r, double* J, double* drdT
 }
 
 // Status bits of a march: 1 pivot below the guard (unpivoted LU), 8 pivot below the
-// guard (pivoted LU), 2 non-finite state, 4 failed refinement test (mixed form), 16
+// guard (pivoted LU), 2 non-finite state or matrix, 4 failed refinement test (mixed form), 16
 // surface through the bottom, 32 failed refinement test of a lagged-factor solve, 64
 // failed residual test of a GMRES solve.  The fallback that a redo of the call takes,
 // or 0.  A small pivot redoes the march with pivoted factors first (which also ends

@@ -375,33 +375,26 @@ __device__ __forceinline__ T gj64(T (&x)[16], T* scr) {
 }
 
 // The pivot guard of an inverted diagonal block (status bit 1), x: an entry of the inverse.
-// A NaN pivot passes the minimum unseen, but leaves no finite entry in its block's inverse:
-// with no small pivot found so far (one of zero leaves NaN behind too, for the redo with row
-// interchanges to mend) the matrix itself is not finite (bit 2).  FP64 only: entries beyond
-// FP32's range fail the refinement test of the mixed form, which is redone in FP64.
-// flag: four ints of LDS that no wave uses any more.
+// A NaN pivot passes the minimum unseen, but leaves no finite entry in its block's inverse
+// (bit 128): the matrix is not finite, unless a small pivot did that, which read_status
+// decides (a pivot of zero leaves NaN behind too, for the redo with row interchanges to
+// mend).  FP64 only: entries beyond FP32's range fail the refinement test of the mixed
+// form, which is redone in FP64.
 template <typename T>
-__device__ __forceinline__ void gj_guard(T minpiv, T x, double guard, int* __restrict__ status, int* flag) {
-  const bool small = !((double)minpiv >= guard), lead = (threadIdx.x & 63) == 0;
-  if (lead && small) atomicOr(status, 1);
-  if constexpr (sizeof(T) == 8) {
-    if (lead) flag[threadIdx.x >> 6] = small;
-    __syncthreads();
-    if (!isfinite(x) && !(flag[0] | flag[1] | flag[2] | flag[3]) && !(atomicOr(status, 0) & (1 | 8)))
-      atomicOr(status, 2);
-  }
+__device__ __forceinline__ void gj_guard(T minpiv, T x, double guard, int* __restrict__ status) {
+  if ((threadIdx.x & 63) == 0 && !((double)minpiv >= guard)) atomicOr(status, 1);
+  if (sizeof(T) == 8 && !isfinite(x)) atomicOr(status, 128);
 }
 
 // D_0 (and, for a single block, the inverse itself)
 template <typename T>
 __global__ __launch_bounds__(WW_NT) void k_gj_init(GjGroup<T> g) {
   __shared__ __attribute__((aligned(16))) T scr[GJ_SCR];
-  __shared__ int flag[4];
   const int m = blockIdx.x;
   T x[16];
   band_load<T>(x, GJ_SEL(g, S0, m), g.Np);
   const T mp = gj64<T>(x, scr);
-  gj_guard<T>(mp, x[0], g.pivguard, g.status, flag);
+  gj_guard<T>(mp, x[0], g.pivguard, g.status);
   band_store<T, T>(x, GJ_SEL(g, Dinv, m), 64);
   if (g.Np == WW_TB) {
     band_store<T, T>(x, GJ_SEL(g, Mr, m), g.Np);
@@ -454,10 +447,9 @@ __global__ __launch_bounds__(WW_NT, 2) void k_gj_step(GjGroup<T> g, int k) {
       rf_put<T>(sm + GJ_TILE, vr);
       __syncthreads();
       band_mfma<T>(c, a, sm + GJ_TILE);
-      // (the inverse's scratch is the first tile, which every wave has left before the barrier
-      // above; the second is free after the barriers of the inverse)
+      // (the inverse's scratch is the first tile, which every wave has left before the barrier above)
       const T mp = gj64<T>(c, sm);
-      gj_guard<T>(mp, c[0], g.pivguard, g.status, reinterpret_cast<int*>(sm + GJ_TILE));
+      gj_guard<T>(mp, c[0], g.pivguard, g.status);
       band_store<T, T>(c, Dinv + (size_t)(k + 1) * 4096, 64);
       return;
     }
