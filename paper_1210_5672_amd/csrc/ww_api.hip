@@ -177,7 +177,7 @@ struct ww_ctx {
   double *cosT = nullptr, *sinT = nullptr, *c0T = nullptr, *sig = nullptr;
   cplx* tw = nullptr;
   double *rhs0 = nullptr, *y0t = nullptr, *mu0 = nullptr, *gam0 = nullptr, *hg0 = nullptr, *gphi0 = nullptr;
-  double *Psi = nullptr, *Ytmp = nullptr, *Mu = nullptr, *Gam = nullptr, *HG = nullptr, *Gpsi = nullptr;
+  double *Psi = nullptr, *Mu = nullptr, *Gam = nullptr, *HG = nullptr, *Gpsi = nullptr;
   double *y = nullptr, *Ys = nullptr, *K = nullptr, *Kx = nullptr, *ydtn = nullptr;
   double *basis = nullptr, *qfix = nullptr;
   double* coef = nullptr;
@@ -509,7 +509,6 @@ int ww_create(ww_ctx** out, int n_max, int r_max, unsigned flags, void* hip_stre
   AL(c->hg0, np * 8);
   AL(c->gphi0, np * 8);
   AL(c->Psi, np * R * 8);
-  AL(c->Ytmp, np * R * 8);
   AL(c->Mu, np * R * 8);
   AL(c->Gam, np * R * 8);
   AL(c->HG, np * R * 8);
@@ -1007,8 +1006,7 @@ static const double REFINE_TOL = 1.1368683772161603e-13;
 // FP64:  X = Mi B.
 // mixed: X = Mi32 B, then nref sweeps of  r = B - A X (FP64 residual with the FP64
 //        matrix),  X += Mi32 r  (FP32 inverse, FP64 accumulation).
-static int enqueue_solve(ww_ctx* c, const Fac& F, double* B, double* Y, double* X, double* Rs, int R) {
-  (void)Y;
+static int enqueue_solve(ww_ctx* c, const Fac& F, double* B, double* X, double* Rs, int R) {
   int rc;
   if (F.perm) {   // the inverse is that of P A: solve with P B
     const size_t n = (size_t)c->Np * R;
@@ -1034,10 +1032,10 @@ static int enqueue_solve(ww_ctx* c, const Fac& F, double* B, double* Y, double* 
 }
 
 // DtN of R columns in B (ld Np): out = G psi (ld Np); mu in Mu; Rs residual scratch
-static int enqueue_dtn_cols(ww_ctx* c, const Fac& F, double* B, double* Yt, double* Mu, double* Gam, double* HGm,
+static int enqueue_dtn_cols(ww_ctx* c, const Fac& F, double* B, double* Mu, double* Gam, double* HGm,
                             double* out, double* Rs, int R) {
   int rc;
-  if ((rc = enqueue_solve(c, F, B, Yt, Mu, Rs, R))) return rc;
+  if ((rc = enqueue_solve(c, F, B, Mu, Rs, R))) return rc;
   hipLaunchKernelGGL(NF_SEL(c->N, k_gamma), dim3((R + 1) / 2), dim3(PREP_NT), fft_lds_bytes(c->N, 5), c->stream, Mu, c->Np, R, Gam,
                      HGm, c->tw, c->N, nullptr, nullptr, 0.0, nullptr, 0);
   LAUNCHCHK();
@@ -1146,7 +1144,7 @@ static int enqueue_base_chain(ww_ctx* c, const double* ysrc, int s, double* kout
     if ((rc = enqueue_gemm<double>(c, F.Gmr, c->gam0, c->hg0, 1.0, c->gphi0, 1))) return rc;
   } else {
     if ((rc = enqueue_assemble_lu(c, F))) return rc;
-    if ((rc = enqueue_dtn_cols(c, F, c->rhs0, c->y0t, c->mu0, c->gam0, c->hg0, c->gphi0, c->rr0, 1))) return rc;
+    if ((rc = enqueue_dtn_cols(c, F, c->rhs0, c->mu0, c->gam0, c->hg0, c->gphi0, c->rr0, 1))) return rc;
   }
   if (c->mapped)
     hipLaunchKernelGGL(k_base_rhs_map, dim3(1), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys, c->gphi0,
@@ -1169,7 +1167,7 @@ static int enqueue_col_chain(ww_ctx* c, int s, const Fac& F) {
   hipLaunchKernelGGL(k_col_pre, dim3(blocks), dim3(256), 0, c->stream, c->y, c->K, c->Ys, c->coef, s, kstride(c),
                      F.aux, c->n_max, c->Psi, c->Np, c->N, M);
   LAUNCHCHK();
-  if ((rc = enqueue_dtn_cols(c, F, c->Psi, c->Ytmp, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr, M))) return rc;
+  if ((rc = enqueue_dtn_cols(c, F, c->Psi, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr, M))) return rc;
   if (c->mapped)
     hipLaunchKernelGGL(NF_SEL(c->N, k_col_rhs_map), dim3(M), dim3(WW_NT), fft_lds_bytes(c->N, 4), c->stream, c->Ys,
                        c->Gpsi, c->Np, F.aux, c->mesh, c->n_max, c->K + (size_t)s * kstride(c), c->tw, c->sig, c->N, c->g,
@@ -1211,8 +1209,10 @@ static int lu_group(const ww_ctx* c) {
   return std::max(1, std::min(g, c->lag));
 }
 // a march without columns (one LU per group) keeps to one LU stream where that LU is shorter
-// than the base chain of a full group's stages (N = 1024: 254 us against 4 x 70; a second
-// one beside it only slows the chain, 22.3 against 21.0 ms), to two otherwise
+// than the base chain of a full group's stages (N = 1024: 254 us against 4 x 70), since a
+// second one beside it only slows the chain, to two otherwise.  us a stage with one and with
+// two, FP64: N 256 39.5 / 39.2, 512 48.4 / 53.9, 768 62.9 / 67.2, 1024 75.3 / 79.4, 1296 120 /
+// 124, 1536 136 / 132, 2048 229 / 215 (mixed: 1024 65.6 / 69.9, 1536 106 / 110, 2048 167 / 161)
 static int lu_count(const ww_ctx* c) {
   const int most = c->pcols ? c->nlus : c->Np <= 1024 && lu_group(c) == GJ_GMAX ? 1 : 2;
   return std::min(std::min(c->nlus, most), c->lag);
@@ -1705,10 +1705,9 @@ int dtn_setup(ww_ctx* c, const double* surface, double h, double tau, int N) {
 
 }  // extern "C"
 
-// work arrays of one dtn_solve_multi call (each Np x nrhs, ld Np; Rr only in the mixed
-// form) and the split-K partials of its products
+// work arrays of one dtn_solve_multi call (each Np x nrhs, ld Np; Rr only in the mixed form)
 struct SolveWork {
-  double *Psi, *Ytmp, *Mu, *Gam, *HG, *Gpsi, *Rr;
+  double *Psi, *Mu, *Gam, *HG, *Gpsi, *Rr;
 };
 
 static int dtn_solve_impl(ww_ctx* c, const double* rhs, int nrhs, double* dtn_out, double* mu_out,
@@ -1721,7 +1720,7 @@ static int dtn_solve_impl(ww_ctx* c, const double* rhs, int nrhs, double* dtn_ou
   int rc;
   for (;;) {
     const Fac F = fac_default(c);
-    if ((rc = enqueue_dtn_cols(c, F, w.Psi, w.Ytmp, w.Mu, w.Gam, w.HG, w.Gpsi, w.Rr, nrhs))) return rc;
+    if ((rc = enqueue_dtn_cols(c, F, w.Psi, w.Mu, w.Gam, w.HG, w.Gpsi, w.Rr, nrhs))) return rc;
     if (!use32(c)) break;
     int st = 0;   // the refinement test of the mixed path
     if ((rc = read_status(c, &st))) return rc;
@@ -1754,7 +1753,7 @@ extern "C" {
 int dtn_solve_multi(ww_ctx* c, const double* rhs, int nrhs, double* dtn_out, double* mu_out) {
   int rc;
   if ((rc = dtn_solve_check(c, rhs, nrhs, dtn_out))) return rc;
-  const SolveWork w{c->Psi, c->Ytmp, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr};
+  const SolveWork w{c->Psi, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr};
   return dtn_solve_impl(c, rhs, nrhs, dtn_out, mu_out, w);
 }
 
@@ -1762,14 +1761,14 @@ int dtn_solve_multi_noalloc(ww_ctx* c, const double* rhs, int nrhs, double* dtn_
   int rc;
   if ((rc = dtn_solve_check(c, rhs, nrhs, dtn_out))) return rc;
   if (!c->scratch) return fail(WW_EHIP, "internal: fixed workspace address not resolved");
-  // layout: Psi, Ytmp, Mu, Gam, HG, Gpsi, Rr, Np x nrhs each
+  // layout: Psi, Mu, Gam, HG, Gpsi, Rr, Np x nrhs each (the limit of seven is the interface's)
   const size_t blk = (size_t)c->Np * nrhs;
   const size_t nbuf = 7;
   if (nbuf * blk > WW_SCRATCH_DOUBLES)
     return fail(WW_EINVAL, "dtn_solve_multi_noalloc: 7 Np nrhs doubles exceed the fixed workspace (" +
                                std::to_string(WW_SCRATCH_BYTES >> 20) + " MiB); use dtn_solve_multi");
   double* s = c->scratch;
-  const SolveWork w{s, s + blk, s + 2 * blk, s + 3 * blk, s + 4 * blk, s + 5 * blk, s + 6 * blk};
+  const SolveWork w{s, s + blk, s + 2 * blk, s + 3 * blk, s + 4 * blk, s + 5 * blk};
   return dtn_solve_impl(c, rhs, nrhs, dtn_out, mu_out, w);
 }
 
@@ -2672,7 +2671,7 @@ static int ensure_sdc_groups(ww_ctx* c) {
     if (!c->sdc_evL[i]) HIPCHK(hipEventCreateWithFlags(&c->sdc_evL[i], hipEventDisableTiming));
   }
   int rc;
-  if (!c->sdc_b2 && (rc = dalloc(c, (void**)&c->sdc_b2, (size_t)6 * c->np_max * 8))) return rc;
+  if (!c->sdc_b2 && (rc = dalloc(c, (void**)&c->sdc_b2, (size_t)5 * c->np_max * 8))) return rc;
   return ensure_ring(c, SDC_NODES);
 }
 
@@ -2699,7 +2698,7 @@ struct SdcStep {
   // base-chain scratch: the context's (main stream), and a second set for the chains
   // that run on the LU stream
   struct Bs {
-    double *y0t, *mu0, *gam0, *hg0, *gphi0, *rr0;
+    double *mu0, *gam0, *hg0, *gphi0, *rr0;
   } bm, b2;
 
   bool lag;   // lagged factors for the predictor's base solves
@@ -2710,10 +2709,10 @@ struct SdcStep {
       F[m].lag32 = false;
     }
     lag = c->sdc_lag && !(c->fb & WW_FB_DIRECT);
-    bm = Bs{c->y0t, c->mu0, c->gam0, c->hg0, c->gphi0, c->rr0};
+    bm = Bs{c->mu0, c->gam0, c->hg0, c->gphi0, c->rr0};
     const size_t np = c->np_max;
     double* w = c->sdc_b2;
-    b2 = Bs{w, w + np, w + 2 * np, w + 3 * np, w + 4 * np, w + 5 * np};
+    b2 = Bs{w, w + np, w + 2 * np, w + 3 * np, w + 4 * np};
   }
   double* yn(int q) const { return c->sdc_yn + q * ks; }
   double* ysn(int q) const { return c->sdc_ysn + q * ks; }
@@ -2802,7 +2801,7 @@ struct SdcStep {
   int chains(int s, int q, const Bs& b) {
     int rc;
     double* kout = c->sdc_K + (size_t)s * ks;
-    if ((rc = enqueue_dtn_cols(c, F[q], rhsn(q), b.y0t, b.mu0, b.gam0, b.hg0, b.gphi0, b.rr0, 1))) return rc;
+    if ((rc = enqueue_dtn_cols(c, F[q], rhsn(q), b.mu0, b.gam0, b.hg0, b.gphi0, b.rr0, 1))) return rc;
     if ((rc = sdc_base_rhs(c, ysn(q), b.gphi0, F[q].aux, kout))) return rc;
     if (!cols) return 0;
     HIPCHK(hipEventRecord(c->sdc_evB[q], c->stream));
@@ -2825,7 +2824,7 @@ struct SdcStep {
     hipLaunchKernelGGL(k_col_pre, dim3(cb), dim3(256), 0, c->stream, yn(q), c->K, ysn(q), c->coef, 0, ks, F[q].aux,
                        c->n_max, c->Psi, c->Np, c->N, M);
     LAUNCHCHK();
-    if ((rc = enqueue_dtn_cols(c, F[q], c->Psi, c->Ytmp, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr, M))) return rc;
+    if ((rc = enqueue_dtn_cols(c, F[q], c->Psi, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr, M))) return rc;
     return sdc_col_rhs(c, ysn(q), F[q].aux, kout);
   }
   int sweep(int s0) {
@@ -2920,7 +2919,7 @@ static int enqueue_col_chain_at(ww_ctx* c, const double* ysrc, double* kout, con
   hipLaunchKernelGGL(k_col_pre, dim3(blocks), dim3(256), 0, c->stream, ysrc, c->K, c->Ys, c->coef, 0, kstride(c),
                      F.aux, c->n_max, c->Psi, c->Np, c->N, M);
   LAUNCHCHK();
-  if ((rc = enqueue_dtn_cols(c, F, c->Psi, c->Ytmp, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr, M))) return rc;
+  if ((rc = enqueue_dtn_cols(c, F, c->Psi, c->Mu, c->Gam, c->HG, c->Gpsi, c->Rr, M))) return rc;
   return sdc_col_rhs(c, c->Ys, F.aux, kout);
 }
 
