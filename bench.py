@@ -24,24 +24,23 @@ FP64_PEAK_TFLOPS = 78.6    # MI355X dense FP64 (vector and MFMA)
 FP32_PEAK_TFLOPS = 157.3   # MI355X dense FP32 MFMA
 HBM_PEAK_GBS = 8000.0      # MI355X HBM3E
 
-# HBM bytes of the block LU at N = 1024, FP64, LU groups of two stages, from the
-# FETCH_SIZE and WRITE_SIZE counter passes in profiles/block_lu_c3_hbm_counters.md,
-# calibrated with a plain 256 MiB copy: per k_blu_step launch (averaged over the 15
-# steps of a sequence) and per launch sequence (init, 15 steps, final, explicit
-# inverse).  Valid only for the kernel source they were measured on: reported as null
-# once the kernels header changes.
-BLU_STEP_TRAFFIC_BYTES = 26.57e6
-LU_SEQ_TRAFFIC_BYTES = 483.3e6
-LU_TRAFFIC_SOURCE_SHA256 = "020bbe7fa62336249d1675eb422202b8b7a861eb98a99b27e83be4f92382c65f"
-LU_TRAFFIC_GROUP = 2
+# HBM bytes of the elimination at N = 1024, FP64, groups of four stages, from the
+# FETCH_SIZE and WRITE_SIZE counter passes in profiles/elimination_c3_hbm_counters.md,
+# calibrated with a plain 256 MiB copy: per k_gj_step launch with a diagonal inverse
+# (averaged over the 15 of a sequence) and per launch sequence (init, 16 steps).  Valid only
+# for the kernel source they were measured on: reported as null once that header changes.
+GJ_STEP_TRAFFIC_BYTES = 71.43e6
+GJ_SEQ_TRAFFIC_BYTES = 1143.0e6
+GJ_TRAFFIC_SOURCE_SHA256 = "f4c48e4c7b33e236bb79ebfc9de20972434dceb0e4c67ddab826ed6f6b3235d6"
+GJ_TRAFFIC_GROUP = 4
 
 
 def lu_traffic_valid():
     import hashlib
-    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1210_5672_amd", "csrc", "ww_kernels.hpp")
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1210_5672_amd", "csrc", "ww_inv.hpp")
     try:
         with open(path, "rb") as fh:
-            return hashlib.sha256(fh.read()).hexdigest() == LU_TRAFFIC_SOURCE_SHA256
+            return hashlib.sha256(fh.read()).hexdigest() == GJ_TRAFFIC_SOURCE_SHA256
     except OSError:
         return False
 
@@ -50,8 +49,9 @@ def blu_step_flops(N: int, b: int = 64) -> float:
     """Algorithmic LU flops of the k_gj_step launches of one factorisation: step k
     forms the m = nb - k - 1 left factors L_ik = A_ik D_k (2 b^3 each) and updates the
     m^2 trailing tiles (2 b^3 each), i.e. 2 b^3 (m^2 + m); summed over the steps this is
-    2/3 N^3 up to the diagonal-block inversions.  The elimination of the blocks above and left of the pivot, by which the
-    same launches leave the explicit inverse, is not counted."""
+    2/3 N^3 up to the diagonal-block inversions.  The elimination of the blocks above and
+    left of the pivot, by which the same launches leave the explicit inverse, is not
+    counted."""
     nb = N // b
     return sum(2.0 * b ** 3 * (m * m + m) for m in range(1, nb))
 
@@ -113,7 +113,10 @@ def run(w, nsteps, T, mixed, steps, warmup, profile, tuned=True):
     torch.cuda.synchronize()
     t = time.perf_counter() - t0
     phases = None
+    tuning = ctx.tuning()
     if profile:
+        # the elimination outside graphs, where its launches can carry events
+        ctx.set_tuning(graph_parts=tuning["graph_parts"] & ~2)
         ctx.profile(True, kernel_events=True)
         ctx.shoot_eval(params, T, nsteps)   # captures the graphs with the stamp nodes
         ctx.profile(True, kernel_events=True)   # clear the sums
@@ -135,7 +138,7 @@ def run(w, nsteps, T, mixed, steps, warmup, profile, tuned=True):
                   "profiled_eval_ms": prof_ms}
         print(f"# {tag} profiled evaluation done", file=sys.stderr, flush=True)
     timing = {"median_ms": statistics.median(each), "min_ms": min(each), "max_ms": max(each),
-              "first_call_ms": first_ms, "tuning": ctx.tuning(), "tuning_from_cache": from_cache}
+              "first_call_ms": first_ms, "tuning": tuning, "tuning_from_cache": from_cache}
     return t, res, phases, timing
 
 
@@ -607,16 +610,16 @@ def main():
         G = phases["lu_stages_per_sequence"]
         nb = w.N // 64
         seq_flops = G * blu_step_flops(w.N)
-        valid = lu_traffic_valid() and w.N == 1024 and timing["tuning"]["lu_group"] == LU_TRAFFIC_GROUP
+        valid = lu_traffic_valid() and w.N == 1024 and G == GJ_TRAFFIC_GROUP
         seq = {"kernels": "k_gj_init, 16 x k_gj_step",
                "stages": G, "ms": phases["block_lu_ms"],
                "achieved": G * (2.0 / 3.0) * n3 / (phases["block_lu_ms"] * 1e-3) / 1e12,
-               "traffic": LU_SEQ_TRAFFIC_BYTES if valid else None}
+               "traffic": GJ_SEQ_TRAFFIC_BYTES if valid else None}
         if phases.get("blu_step_launches"):
             step_s = phases["blu_step_ms"] * 1e-3
             ach = seq_flops / (nb - 1) / step_s / 1e12
             roofline = {"bound": "mfma", "achieved": ach, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                        "frac": ach / FP64_PEAK_TFLOPS, "traffic": BLU_STEP_TRAFFIC_BYTES if valid else None,
+                        "frac": ach / FP64_PEAK_TFLOPS, "traffic": GJ_STEP_TRAFFIC_BYTES if valid else None,
                         "kernel": f"k_gj_step<double>, one launch per block step of a group of {G:g} stages",
                         "flops_per_launch": seq_flops / (nb - 1),
                         "launch_us": phases["blu_step_ms"] * 1e3,
