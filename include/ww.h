@@ -118,7 +118,8 @@ int ww_set_tableau(ww_ctx *ctx, int s, const double *a, const double *b, const d
  * does not enter A or Gm).  Synchronises to check the pivot guard; a pivot below it
  * refactors with partial pivoting (WW_FB_PIVOTED).  The factors serve dtn_solve_multi
  * until the next dtn_setup, shoot_setup, shoot_eval or shoot_adjoint on the context.
- * Errors: WW_EINVAL, WW_EDOMAIN (finite depth, h + eta <= 0), WW_EPIVOT, WW_EHIP.
+ * Errors: WW_EINVAL, WW_EDOMAIN (finite depth, h + eta <= 0), WW_ENONFINITE (the surface,
+ * or its matrix: heights out of range), WW_EPIVOT, WW_EHIP.
  */
 int dtn_setup(ww_ctx *ctx, const double *surface, double h, double tau, int N);
 
@@ -130,7 +131,7 @@ int dtn_setup(ww_ctx *ctx, const double *surface, double h, double tau, int N);
  * (device, N x nrhs, or NULL) receives mu.  nrhs <= r_max.  Stream-ordered, except in a
  * WW_MIXED context, where it synchronises to check the refinement test; a failed test
  * refactors A in FP64 (kept for later calls) and solves again (WW_FB_FP64).
- * Errors: WW_ENOSETUP, WW_EINVAL, WW_EPIVOT, WW_EREFINE (WW_STRICT), WW_EHIP.
+ * Errors: WW_ENOSETUP, WW_EINVAL, WW_ENONFINITE, WW_EPIVOT, WW_EREFINE (WW_STRICT), WW_EHIP.
  */
 int dtn_solve_multi(ww_ctx *ctx, const double *rhs, int nrhs, double *dtn_out, double *mu_out);
 
@@ -173,27 +174,29 @@ int shoot_setup(ww_ctx *ctx, int N, double h, double tau, double g, const double
  *   f    (host)   f = r.r / 2, or NULL
  * Lagged factors (L = 8; environment WW_PIPE_LAG, 0..11, read by ww_create; 0 turns
  * them off): in a march of one instance, the base chain of stage s (the march's
- * critical path) solves with the explicit inverse of stage s - L (the first product in
- * the same launch as the assembly of its own matrix) and refines the solution with
- * the FP64 residual of its own matrix (the same number of sweeps and the same
+ * critical path) solves with the explicit inverse of the newest stage of stage s - L's
+ * group (the first product in the same launch as the assembly of its own matrix) and
+ * refines the solution with the FP64 residual of its own matrix (the same number of sweeps and the same
  * convergence test as WW_MIXED; environment WW_NREF_LAG, 1..8, sets the sweeps of
  * these solves alone), while its own matrix is factored concurrently: the LUs of G
- * consecutive stages (G = 2, at most L; environment WW_LU_GROUP, 1..4) share one
- * launch sequence, on one of the context's LU streams (group g on stream g mod K,
- * K = 3; environment WW_LU_STREAMS, 1..L).  The column chain of stage s uses that
+ * consecutive stages (G = 4, 2 where L < 8, at most L; environment WW_LU_GROUP, 1..4)
+ * share one launch sequence, on one of the LU streams that the call holds (group g on
+ * stream g mod K, K = 3; environment WW_LU_STREAMS, 1..L; calls made at the same time on
+ * several contexts hold streams of their own).  The column chain of stage s uses that
  * stage's own factors and runs on the LU stream of its group after the group's LU,
  * the column chains in stage order (WW_COLS_ON_LU=0: on a column stream of their own,
  * with K = 2).  Each branch of a stage (spectral prep and assembly; the LU of a group;
- * the lagged base solve to the base right-hand side; the column chain) is a graph of
- * its own, replayed on its stream with the dependencies as events; the step end of the
+ * the lagged base solve to the base right-hand side; the column chain) is launched
+ * on its stream, directly or from a graph of its own (graph_parts, below), with the
+ * dependencies as events; the step end of the
  * base column runs on the caller's stream, that of the Jacobian columns after the last
  * column chain, and the caller's stream joins the others before the outputs.  The
  * results do not depend on K or on where the column chains run.  A
  * failed test (checked after the first step, and at the end) redoes the march with
  * every stage's own factors (WW_FB_DIRECT); the context's later marches then start that
  * way, until the next shoot_setup (not with WW_STRICT, which reports every failure).
- * Marches with and without J (M > 0 or J NULL) both use lagged factors; without J, on
- * at most two of the LU streams.
+ * Marches with and without J (M > 0 or J NULL) both use lagged factors; without J only
+ * the newest stage of a group is factored, on one LU stream (two above N = 1024).
  * Synchronises to check the status flags.  A pivot below the guard anywhere in the
  * march redoes it with partial pivoting; a failed refinement test (WW_MIXED) redoes it
  * with FP64 factors (see ww_fallbacks).

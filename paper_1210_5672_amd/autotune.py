@@ -2,12 +2,10 @@
 
 None of the choices changes what is computed: they decide how the work of a march is
 cut into launches and streams (LU group size and streams, the lag of the base solve,
-which parts replay from graphs, the strip length of a elimination step, rows per
-workgroup of the base DtN launch, the inner-dimension split and the output-tile rows
-of the column products, the assembly strip width, the workgroup cap of the explicit
-inverse, an FP32 copy of the lagged inverse for the base solve's products, the
-refinement sweeps of a lagged solve).  The tuner times
-short marches of a workload, one fresh context per candidate, and improves one choice
+which parts replay from graphs, the strip length of an elimination step, rows per
+workgroup of the base DtN launch, the output tiles of the column products, the assembly
+strip width, an FP32 copy of the lagged inverse for the base solve's products, the
+refinement sweeps of a lagged solve).  The tuner times short marches of a workload, one fresh context per candidate, and improves one choice
 at a time (coordinate descent, a few passes); the winner is stored in a JSON cache
 keyed by GPU architecture, N, M and precision form, and `apply` hands it to a context.
 

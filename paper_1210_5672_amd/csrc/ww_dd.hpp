@@ -387,8 +387,8 @@ __device__ __forceinline__ void dd_settle(dd& s) { s = dd_two_sum(s.hi, s.lo); }
 // Bound by the FP64 units: 12 Np^2 ncols operations at 39 T/s are 41 us at N = 1024, 129
 // columns.  NC (dd_gemm): A is read Np / 64 x ncols / NC times, so wide, but the grid should
 // come out even on the CUs.  Measured at that size: 92 us (one thread per entry over the whole
-// inner index with normalised sums 244), the error of G psi against exact values 0.5 to 0.95
-// of what it was (N 64 to 1024).
+// inner index with normalised sums 244), the error of G psi against exact values (geometric
+// mean over eight wavenumbers) 0.79 of what it was at N = 64, 0.49 at N = 1024.
 #define DDG_NT 512
 template <int NC>
 __global__ __launch_bounds__(DDG_NT) void k_dd_gemm(const double* __restrict__ A_hi, const double* __restrict__ A_lo,
