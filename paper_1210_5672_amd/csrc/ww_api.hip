@@ -54,8 +54,8 @@ static thread_local std::string g_err;
 // caller's stream is held up holds up no other (beside one that waits 380 ms, 16 hardware
 // queues, the other march's 35 ms took 380 on shared streams).
 // A context holds the pool from ww_create to ww_destroy; the last one to go destroys the
-// streams.  A call ends with its work joined into the caller's stream and waited for; after
-// an error that leaves work behind, the next march on the set is only put behind it.
+// streams.  A call ends with its work joined into the caller's stream and waited for, also
+// after an error part-way.
 // Nothing is ever captured from these streams (captures take streams of their own).
 #define POOL_STREAMS 6             // LU streams
 #define POOL_SIDE 2                // the column stream: not LU stream 0 or 1, which it runs beside
@@ -348,12 +348,24 @@ static bool valid_n(int N) {
 // the outermost one, where such calls nest)
 struct StreamLease {
   ww_ctx* c;
-  bool own;
+  bool own, joined = false;
   explicit StreamLease(ww_ctx* cc, bool on = true) : c(cc), own(on && cc->sset < 0) {
     if (own) c->sset = pool_take(c->dev);
   }
+  // the call's result; a call that succeeds has waited for all of its work
+  int end(int rc) {
+    joined = rc == 0;
+    return rc;
+  }
   ~StreamLease() {
     if (!own) return;
+    // after an error part-way nothing of this call may run beside the context's next one,
+    // which may take another set
+    if (!joined) {
+      for (hipStream_t s : c->lus)
+        if (s) (void)hipStreamSynchronize(s);
+      if (c->side) (void)hipStreamSynchronize(c->side);
+    }
     for (hipStream_t& s : c->lus) s = nullptr;
     c->side = nullptr;
     pool_give(c->dev, c->sset);
@@ -2297,7 +2309,7 @@ static int shoot_run(ww_ctx* c, const double* params, double T, int nsteps, doub
                      double* f, int* st, int* where) {
   const bool cols = (J != nullptr) && c->M > 0;
   const bool two = c->overlap && !pivoted(c);
-  const StreamLease lease(c);
+  StreamLease lease(c);
   int rc;
   if (pivoted(c) && (rc = ensure_pivot_buffers(c))) return rc;
   if ((rc = shoot_prepare(c, params, T, nsteps, cols, two))) return rc;
@@ -2316,7 +2328,7 @@ static int shoot_run(ww_ctx* c, const double* params, double T, int nsteps, doub
       if ((rc = pipe_join(c))) return rc;
       HIPCHK(hipStreamSynchronize(c->stream));
       HIPCHK(hipMemcpy(&peek, c->status, sizeof(int), hipMemcpyDeviceToHost));
-      if (peek) return read_status(c, st, where);
+      if (peek) return lease.end(read_status(c, st, where));
     }
   }
   if ((rc = shoot_finish(c, cols, r, J, drdT, f))) {
@@ -2327,7 +2339,7 @@ static int shoot_run(ww_ctx* c, const double* params, double T, int nsteps, doub
     g_err = msg;
     return rc;
   }
-  return read_status(c, st, where);
+  return lease.end(read_status(c, st, where));
 }
 
 // marches from fallback mode fb0 until the status needs no further fallback
@@ -2390,7 +2402,7 @@ static int seg_run(ww_ctx* c, const double* params, double T, int nseg, const ww
   const bool cols = (J != nullptr) && c->M > 0;
   const bool two = c->overlap && !pivoted(c);
   const bool sdc_two = sdc && two && !c->gm_active;
-  const StreamLease lease(c);
+  StreamLease lease(c);
   int rc;
   if (pivoted(c) && (rc = ensure_pivot_buffers(c))) return rc;
   if (sdc && (rc = ensure_sdc(c))) return rc;
@@ -2466,7 +2478,7 @@ static int seg_run(ww_ctx* c, const double* params, double T, int nseg, const ww
     g_err = msg;
     return rc;
   }
-  return read_status(c, st, where);
+  return lease.end(read_status(c, st, where));
 }
 
 // ----- SDC15 time stepping (Sec. 2.2) -----
@@ -2976,7 +2988,7 @@ static int sdc_steps(ww_ctx* c, bool cols, double dt, int nsteps, bool two) {
 static int sdc_run(ww_ctx* c, const double* params, double T, int nsteps, double* r, double* J, double* drdT,
                    double* f, int* st, int* where) {
   const bool cols = (J != nullptr) && c->M > 0;
-  const StreamLease lease(c);
+  StreamLease lease(c);
   int rc;
   if (pivoted(c) && (rc = ensure_pivot_buffers(c))) return rc;
   if ((rc = ensure_sdc(c))) return rc;
@@ -2996,7 +3008,7 @@ static int sdc_run(ww_ctx* c, const double* params, double T, int nsteps, double
     g_err = msg;
     return rc;
   }
-  return read_status(c, st, where);
+  return lease.end(read_status(c, st, where));
 }
 
 // ----- the base march in double-double (SDC15 of the quadruple-precision workflow) -----
@@ -3300,7 +3312,7 @@ int shoot_eval_sdc_dd(ww_ctx* c, int N, double h, double tau, double g, const do
       !std::isfinite(tau) || !(h > 0.0))
     return fail(WW_EINVAL, "nsteps >= 1, finite T and g, finite tau >= 0 and h > 0 required");
   if (int rj = pipe_join(c)) return rj;
-  const StreamLease lease(c);
+  StreamLease lease(c);
   int rc;
   if ((rc = set_grid(c, N, h))) return rc;
   if ((rc = ensure_dd(c))) return rc;
@@ -3379,7 +3391,7 @@ int shoot_eval_sdc_dd(ww_ctx* c, int N, double h, double tau, double g, const do
   LAUNCHCHK();
   HIPCHK(hipMemcpyAsync(f, c->sdd_fo, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
-  return 0;
+  return lease.end(0);
 }
 
 }   // extern "C"
@@ -3453,7 +3465,7 @@ int shoot_eval_batch(int n_inst, ww_ctx* const* ctx, const double* const* params
   // which the hardware overlaps across instances (two-stream graphs of several
   // instances run one after the other)
   const bool two = n_inst == 1 && ctx[0]->overlap;
-  const StreamLease lease(ctx[0], two);
+  StreamLease lease(ctx[0], two);
   for (int i = 0; i < n_inst; ++i) {
     const bool cols = J && J[i] && ctx[i]->M > 0;
     ctx[i]->fb = ctx[i]->lag_off ? WW_FB_DIRECT : 0;
@@ -3486,7 +3498,7 @@ int shoot_eval_batch(int n_inst, ww_ctx* const* ctx, const double* const* params
     }
     if (e && !first_err) first_err = e;
   }
-  return first_err;
+  return lease.end(first_err);
 }
 
 }  // extern "C"
